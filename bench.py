@@ -428,27 +428,29 @@ def run_config(args, config_id):
     ver_stream_gbps = verify_bytes / (stream["verify"] * 1e-6) / 1e9 if "verify" in stream else ver_gbps
     blk_stream_gbps = block_bytes / (stream["block"] * 1e-6) / 1e9 if "block" in stream else blk_gbps
 
-    def attn_kernel_name(c):
-        """The kernel the library's size rule picks for this call (the rule itself lives in the library)."""
+    def attn_kernel_name(c, stored_v=0):
+        """The kernel the library's size rule picks for this call (the rule itself lives in the library).  stored_v:
+        the kernels' code for V's storage, 1 = e4m3, 2 = block-scaled e2m1."""
         group = c.H // c.Hkv
         wide_tiles = c.B * c.Hkv * -(-group * c.N // 256)
         fp8 = c.qk_dtype == wl.FP8_E4M3
         if wide_tiles >= 192 and c.N >= 512 and (not fp8 or c.d == 128):
             fold = not fp8 and c.N >= 1024          # bf16 without per-head scales: the folded-scale form
-            return f"attn_wide_kernel<{c.d}, {'true' if fp8 else 'false'}, false, {'true' if fold else 'false'}, 2>"
+            return f"attn_wide_kernel<{c.d}, {'true' if fp8 else 'false'}, false, {'true' if fold else 'false'}, 2, {stored_v}>"
         if not fp8 and c.B * c.Hkv * -(-group * c.N // 128) < 256:
             return f"attn_stream_kernel<{c.d}>"
-        return f"attn_mfma_kernel<{c.d}, {'true' if fp8 else 'false'}, false, false, false>"
+        return (f"attn_mfma_kernel<{c.d}, {'true' if fp8 else 'false'}, false, {'true' if stored_v == 1 else 'false'}, "
+                f"{'true' if stored_v == 2 else 'false'}>")
 
     # the peak the attention call is priced against: each contraction at the peak of its own operand type
     if mx:
-        attn_kernel, attn_bound = f"attn_mfma_kernel<{cfg.d}, true, false, false, true>", "mfma"
+        attn_kernel, attn_bound = attn_kernel_name(dataclasses.replace(cfg, qk_dtype=wl.FP8_E4M3), 2), "mfma"
         attn_peak = 2.0 / (1.0 / PEAK_FP8_TFLOPS + 1.0 / PEAK_BF16_TFLOPS)
         attn_peak_note = ("half of the FLOPs (S = Q K^T) run on the block-scaled fp8 matrix instruction (5.0 PFLOP/s), half "
                           "(O = P V, V decoded to bf16 on its way into LDS) as bf16 MFMA (2.5 PFLOP/s): time-weighted peak "
                           "3.33 PFLOP/s")
     elif fp8v:
-        attn_kernel, attn_bound = f"attn_mfma_kernel<{cfg.d}, true, false, true, false>", "mfma"
+        attn_kernel, attn_bound = attn_kernel_name(cfg, 1), "mfma"
         attn_peak = 2.0 / (1.0 / PEAK_FP8_TFLOPS + 1.0 / PEAK_BF16_TFLOPS)
         attn_peak_note = ("half of the FLOPs (S = Q K^T) run as fp8 MFMA on the e4m3 operands as stored (5.0 PFLOP/s), half "
                           "(O = P V, V decoded to bf16 on its way into LDS) as bf16 MFMA (2.5 PFLOP/s): time-weighted peak "

@@ -757,20 +757,6 @@ hipError_t launch_attention_mfma(const AttnArgs &a, hipStream_t stream)
     const dim3 grid((unsigned)blocks), block(kAttnThreads);
     if (a.Kblk == nullptr) k.block_len = 0;                                // no row is taken from block tensors
     hipError_t e;
-    if (a.q_mx != nullptr) {
-        // block-scaled inputs, verifier form
-        if (blk || a.k_mx == nullptr || a.v_mx == nullptr) return hipErrorInvalidValue;
-        return a.d == 128 ? launch(attn_mfma_kernel<128, true, false, false, true>, grid, block, stream, k)
-                          : launch(attn_mfma_kernel<64, true, false, false, true>, grid, block, stream, k);
-    }
-    if (a.v_dtype == 2) {
-        // fp8 V (with fp8 Q/K): this file's kernel serves every shape of the workload
-        if (!blk) return a.d == 128 ? launch(attn_mfma_kernel<128, true, false, true>, grid, block, stream, k)
-                                    : launch(attn_mfma_kernel<64, true, false, true>, grid, block, stream, k);
-        e = a.d == 128 ? launch(attn_mfma_kernel<128, true, true, true>, grid, block, stream, k)
-                       : launch(attn_mfma_kernel<64, true, true, true>, grid, block, stream, k);
-        return e != hipSuccess ? e : finish_attention(a, k.splits, stream);
-    }
     if (!blk && (!fp8 || a.d == 128)) {
         // The wide-wave kernel (256 query rows per workgroup, one wave per SIMD; bf16, or fp8 Q/K with
         // d = 128) wins once there are enough row tiles to occupy the chip; below that smaller workgroups
@@ -778,6 +764,22 @@ hipError_t launch_attention_mfma(const AttnArgs &a, hipStream_t stream)
         const long tiles = (long)a.B * a.Hkv * (((long)(a.H / a.Hkv) * a.Nq + 255) / 256);
         const bool wide = tune("DD_TUNE_ATTN_WIDE", tiles >= 192 && a.N >= 512) != 0;
         if (wide && a.N >= 64) return launch_attention_wide(a, stream);   // its K/V tiles are 64 whole rows
+    }
+    if (a.q_mx != nullptr) {
+        // block-scaled inputs, verifier form
+        if (blk || a.k_mx == nullptr || a.v_mx == nullptr) return hipErrorInvalidValue;
+        return a.d == 128 ? launch(attn_mfma_kernel<128, true, false, false, true>, grid, block, stream, k)
+                          : launch(attn_mfma_kernel<64, true, false, false, true>, grid, block, stream, k);
+    }
+    if (a.v_dtype == 2) {
+        // fp8 V (with fp8 Q/K)
+        if (!blk) return a.d == 128 ? launch(attn_mfma_kernel<128, true, false, true>, grid, block, stream, k)
+                                    : launch(attn_mfma_kernel<64, true, false, true>, grid, block, stream, k);
+        e = a.d == 128 ? launch(attn_mfma_kernel<128, true, true, true>, grid, block, stream, k)
+                       : launch(attn_mfma_kernel<64, true, true, true>, grid, block, stream, k);
+        return e != hipSuccess ? e : finish_attention(a, k.splits, stream);
+    }
+    if (!blk && (!fp8 || a.d == 128)) {
         // A small bf16 call leaves most compute units idle with 128-row workgroups: the streaming kernel's
         // 64-row workgroups (two row blocks x two key phases) spread it over more of them.
         const bool small = tune("DD_TUNE_BIDIR_STREAM", blocks < 256) != 0;

@@ -123,6 +123,38 @@ __device__ __forceinline__ void qk_next(floatx16 &s, const KT kf, const QT qfrag
     else asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(s) : "v"(kf), "a"(qfrag));
 }
 
+// The block-scaled forms (MX): the same instruction with the E8M0 scales of both operands applied by the hardware.  J
+// selects the scale byte of each scale register: byte 0 for the first instruction of a row, byte 2 for the second (a
+// lane's register holds its row's four scale bytes shifted right by 8 hh, see mx_scales in the kernel).
+template <int J, typename KT, typename QT>
+__device__ __forceinline__ void qk_scaled(floatx16 &s, const KT kf, const QT qfrag, unsigned ksc, unsigned qsc)
+{
+    if constexpr (J == 0)
+        asm volatile("v_mfma_scale_f32_32x32x64_f8f6f4 %0, %1, %2, 0, %3, %4 op_sel_hi:[0,0,0]"
+                     : "=&v"(s) : "v"(kf), "a"(qfrag), "v"(ksc), "v"(qsc));
+    else
+        asm volatile("v_mfma_scale_f32_32x32x64_f8f6f4 %0, %1, %2, %0, %3, %4 op_sel_hi:[1,1,0]"
+                     : "+v"(s) : "v"(kf), "a"(qfrag), "v"(ksc), "v"(qsc));
+}
+
+// Sixteen bytes of stored V -> bf16 (exact): e4m3 codes (16 elements) or packed e2m1 codes (32 elements) times the
+// power of two `scale`, two elements per instruction.
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ uint4 decode_e4m3x8(unsigned w0, unsigned w1)
+{
+    return make_uint4(__builtin_bit_cast(unsigned, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(w0, 1.0f, false)),
+                      __builtin_bit_cast(unsigned, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(w0, 1.0f, true)),
+                      __builtin_bit_cast(unsigned, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(w1, 1.0f, false)),
+                      __builtin_bit_cast(unsigned, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(w1, 1.0f, true)));
+}
+__device__ __forceinline__ uint4 decode_e2m1x8(unsigned w, float scale)
+{
+    return make_uint4(__builtin_bit_cast(unsigned, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp4(w, scale, 0)),
+                      __builtin_bit_cast(unsigned, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp4(w, scale, 1)),
+                      __builtin_bit_cast(unsigned, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp4(w, scale, 2)),
+                      __builtin_bit_cast(unsigned, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp4(w, scale, 3)));
+}
+
 // A wave-uniform pointer that the compiler happens to hold in vector registers, as a scalar register pair
 // (a no-op when it already is one).
 __device__ __forceinline__ const uint8_t *scalar_ptr(const uint8_t *p)
@@ -131,6 +163,9 @@ __device__ __forceinline__ const uint8_t *scalar_ptr(const uint8_t *p)
     const unsigned lo = __builtin_amdgcn_readfirstlane((unsigned)v), hi = __builtin_amdgcn_readfirstlane((unsigned)(v >> 32));
     return reinterpret_cast<const uint8_t *>(((unsigned long long)hi << 32) | lo);
 }
+
+// How V is stored (see the kernel)
+constexpr int kVBf16 = 0, kVE4m3 = 1, kVMx = 2;
 
 // s_waitcnt immediate: wait until at most n vector-memory operations are outstanding, nothing else
 constexpr int waitcnt_vm(int n) { return (n & 15) | ((n >> 4) << 14) | (7 << 4) | (15 << 8); }
@@ -170,7 +205,15 @@ using F_ = std::false_type;
 // QB: 32-row query blocks per wave.  2 is the form described above; 1 (the drafter's call only) halves the row
 // tile to 128 rows - every K and V fragment then feeds one matrix instruction instead of two, but twice as many
 // workgroups share the call, which can spare it the key splits, their partial states and the merge launch.
-template <int D, bool FP8, bool BLOCK, bool FOLD = false, int QB = 2>
+// VS: how V is stored.  kVBf16: as multiplied.  kVE4m3 (fp8 Q/K only): e4m3 codes, v_scale multiplies the output once.
+// kVMx (fp8 Q/K, verifier form): block-scaled inputs, Q/K e4m3 and V e2m1 with E8M0 scales per 32 head dims.  Stored
+// tiles of the last two go to LDS as they are, one stage earlier than a bf16 tile would, and are decoded to the bf16
+// tile the pipeline reads during the stage in between, each wave a quarter of the tile: per stage and wave 16
+// conversions and 5-7 LDS accesses beside 48 matrix instructions, where decoding behind the fragment reads would make
+// every wave convert the whole tile.  MX scales: a tile's K and V scale words (one per row) travel by one 4-byte-per-lane
+// load each.  Measured (16 x 32 / 8 heads x 2048 keys): e4m3 V 992 -> 720 us, block-scaled 1188 -> 743 us against the
+// 128-row kernel of attention_mfma.hip, where every workgroup transposes and decodes V for half the rows; bf16 V 702 us.
+template <int D, bool FP8, bool BLOCK, bool FOLD = false, int QB = 2, int VS = kVBf16>
 __global__ __launch_bounds__(kAttnThreads) __attribute__((amdgpu_waves_per_eu(1, 1)))
 void attn_wide_kernel(const AttnKernelArgs a)
 {
@@ -180,6 +223,9 @@ void attn_wide_kernel(const AttnKernelArgs a)
 #if defined(__HIP_DEVICE_COMPILE__)
     static_assert(!(FOLD && FP8), "the scale cannot be folded into fp8 operands");
     static_assert(QB == 2 || (QB == 1 && BLOCK), "one or two row blocks per wave");
+    constexpr bool MX = VS == kVMx, VDEC = VS != kVBf16;
+    static_assert(!VDEC || (FP8 && D == 128), "stored V other than bf16 comes with fp8 Q/K, whole 128-wide rows");
+    static_assert(!MX || !BLOCK, "block-scaled inputs: verifier form");
     constexpr int kRowsWave = 32 * QB, kRowsWG = 4 * kRowsWave;
     constexpr int NE = 16 * QB;                      // scores per lane and unit
     constexpr int CH = D / 8;                        // 16-byte chunks (8 bf16) per V / O row
@@ -194,9 +240,11 @@ void attn_wide_kernel(const AttnKernelArgs a)
     static_assert(FPM == (FP8 ? 2 : 1), "operand widths");
     constexpr int DMA_ROWS = 1024 / ROWB;            // rows moved by one wave-wide 16-byte-per-lane load (V)
     constexpr int KDMA_ROWS = 1024 / KROWB;          // ... (Q, K)
-    constexpr int NDMA = TKW / DMA_ROWS / 4;         // such loads per wave per V tile
     constexpr int NDMA_K = TKW / KDMA_ROWS / 4;      // ... per K tile
     constexpr int NQDMA = kRowsWave / KDMA_ROWS;     // ... per wave for its Q rows
+    constexpr int VSROWB = VS == kVMx ? D / 2 : VS == kVE4m3 ? D : ROWB;     // bytes per V row as stored
+    constexpr int VSCH = VSROWB / 16;                // its 16-byte chunks
+    constexpr int VSDMA_ROWS = 1024 / VSROWB, NDMA_V = TKW / VSDMA_ROWS / 4; // rows per load, loads per wave and stored V tile
     constexpr int NQK = KS * QB;                     // pieces of a step: S(u+1) ...
     constexpr int NPV = 2 * DC * QB;                 // ... O += V P ...
     constexpr int NP = NQK + NPV + 2 * QB;           // ... and the row sums
@@ -204,7 +252,7 @@ void attn_wide_kernel(const AttnKernelArgs a)
     constexpr int CHK = NP - 6;                      // FOLD: the piece that tests the unit's weights, after the last pack ...
     constexpr int EXC = FOLD ? CHK - kPackLag : NP - MAXC;   // pieces that carry the 32 exponentials
     constexpr int RD = 3;                            // fragment rings: fetched RD uses (2 RD MFMAs) ahead
-    static_assert(NDMA_K + NDMA + 1 <= NP, "one tile load per piece");
+    static_assert(NDMA_K + NDMA_V + 2 <= NP, "one tile load per piece");
     static_assert(FOLD || 16 % (2 * MAXC) == 0, "whole pairs of scores per maximum piece");
     static_assert(KF >= RD && 2 * DC >= RD, "fragment rings are three deep");
     static_assert((4 * DMA_ROWS) % 8 == 0 && DMA_ROWS <= 8, "swizzle phase must not depend on the load index");
@@ -218,6 +266,8 @@ void attn_wide_kernel(const AttnKernelArgs a)
     constexpr int QOW = kRowsWave * OPITCH;          // bytes per wave
     static_assert(QOW % 16 == 0, "wave regions stay 16-byte aligned");
     __shared__ uint4 QO[4 * QOW / 16];
+    __shared__ uint4 R0[VDEC ? TKW * VSCH : 1], R1[VDEC ? TKW * VSCH : 1];          // stored V tiles [key][chunk]
+    __shared__ unsigned KX0[MX ? TKW : 1], KX1[MX ? TKW : 1], VX0[MX ? TKW : 1], VX1[MX ? TKW : 1];   // a tile's scale words
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -267,11 +317,11 @@ void attn_wide_kernel(const AttnKernelArgs a)
         const int rt = t % a.row_tiles, bk = t / a.row_tiles, kvh = bk % a.Hkv, b = bk / a.Hkv;
         Tile r;
         r.k = static_cast<const uint8_t *>(a.K) + (size_t)bk * a.kv_stride * (size_t)KROWB;
-        r.v = static_cast<const uint8_t *>(a.V) + (size_t)bk * a.kv_stride * (size_t)ROWB;
+        r.v = static_cast<const uint8_t *>(a.V) + (size_t)bk * a.kv_stride * (size_t)VSROWB;
         r.kb = r.vb = nullptr;
         if (BLOCK && a.block_len) {
             r.kb = static_cast<const uint8_t *>(a.Kblk) + (size_t)bk * a.block_len * (size_t)KROWB;
-            r.vb = static_cast<const uint8_t *>(a.Vblk) + (size_t)bk * a.block_len * (size_t)ROWB;
+            r.vb = static_cast<const uint8_t *>(a.Vblk) + (size_t)bk * a.block_len * (size_t)VSROWB;
         }
         r.bh0 = b * a.H + kvh * a.group;             // first query head of the group
         r.row_base = (size_t)r.bh0 * a.Nq;           // row of virtual row 0 in Q and O
@@ -296,14 +346,15 @@ void attn_wide_kernel(const AttnKernelArgs a)
     const int dma_row0 = wave * DMA_ROWS + lane / CH;                      // row of load 0; load i: + 4 i DMA_ROWS
     const int dma_krow0 = wave * KDMA_ROWS + lane / KCH;
     const unsigned dma_koff = dma_krow0 * KROWB + ((lane % KCH) ^ (dma_krow0 & 7)) * 16;
-    const unsigned dma_voff = dma_row0 * ROWB + ((lane % CH) ^ ((dma_row0 & (CH / 4 - 1)) << 2)) * 16;
+    // (a stored V tile that is decoded later is copied as it is)
+    const unsigned dma_voff = VDEC ? wave * 1024 + lane * 16 : dma_row0 * ROWB + ((lane % CH) ^ ((dma_row0 & (CH / 4 - 1)) << 2)) * 16;
     // Tile `tile` of this workgroup's pass: where its 64 rows start in memory (K and V side), and which of them
     // count: rows [vlo, vhi) of the tile.  A tile is always 64 whole rows of its source (the cache, or the block
     // tensors): the window is pushed back into the source where the nominal rows 64 T .. of the part would hang
     // over its end, so a last tile repeats rows of its predecessor, and the tile of a part shorter than 64 rows
     // holds rows of the neighbouring part as well - all of those are masked in the scores, as is every row of a
     // stand-in tile past the end of the pass.  All of it is scalar arithmetic.
-    struct TileAt { const uint8_t *k, *v; int vlo, vhi; };
+    struct TileAt { const uint8_t *k, *v; int vlo, vhi, row; };              // row: the first one of the source (MX)
     auto tile_at = [&](const Tile &t, int tile) __attribute__((always_inline)) {
         // (every captured value is copied before any choice is made between them: the compiler otherwise
         // turns "choose one of several loaded values" into a load through a chosen address, which pins the
@@ -323,7 +374,8 @@ void attn_wide_kernel(const AttnKernelArgs a)
         const int win = min(first, src_rows - TKW);                          // first row actually loaded
         TileAt r;
         r.k = kp + (size_t)win * KROWB;
-        r.v = vp + (size_t)win * ROWB;
+        r.v = vp + (size_t)win * VSROWB;
+        r.row = win;
         r.vlo = standin ? TKW : first - win;
         r.vhi = standin ? TKW : off + min(T * TKW + TKW, len) - win;
         return r;
@@ -342,12 +394,23 @@ void attn_wide_kernel(const AttnKernelArgs a)
         else
             asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2 offset:-4096" : : "s"(d), "v"(lane_off), "s"(sbase) : "memory", "m0");
     };
+    // MX: the scale words of the tile whose first row is source row `row` of kv head `bk`: wave 0 loads K's, wave 1 V's
+    auto dma_scales = [&](unsigned *dk, unsigned *dv, int bk, int row) __attribute__((always_inline)) {
+        if constexpr (MX) {
+            if (wave < 2) {                          // uniform
+                const uint8_t *src = scalar_ptr((wave == 0 ? a.k_mx : a.v_mx) + ((size_t)bk * a.kv_stride + row) * 4);
+                const unsigned d = wave == 0 ? lds_addr(dk) : lds_addr(dv), o = lane * 4;
+                asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dword %1, %2" : : "s"(d), "v"(o), "s"(src) : "memory", "m0");
+            }
+        }
+    };
     // Wait until at most `pending` of this wave's memory operations are outstanding, then meet the other
     // waves.  (The barrier by itself is no fence for the compiler: the empty statements keep it from
     // moving LDS accesses across.)
     auto wait_loads_and_sync = [&](auto pending) __attribute__((always_inline)) {
         asm volatile("" ::: "memory");
-        __builtin_amdgcn_s_waitcnt(waitcnt_vm(decltype(pending)::value));
+        // (with decoded V tiles also until this wave's LDS writes are done)
+        __builtin_amdgcn_s_waitcnt(VDEC ? waitcnt_vm(decltype(pending)::value) & ~(15 << 8) : waitcnt_vm(decltype(pending)::value));
         __builtin_amdgcn_s_barrier();
         asm volatile("" ::: "memory");
     };
@@ -393,8 +456,42 @@ void attn_wide_kernel(const AttnKernelArgs a)
     };
     auto kbuf = [&](auto p) __attribute__((always_inline)) -> uint4 * { if constexpr (decltype(p)::value == 0) return K0; else return K1; };
     auto vbuf = [&](auto p) __attribute__((always_inline)) -> uint4 * { if constexpr (decltype(p)::value == 0) return V0; else return V1; };
+    auto rbuf = [&](auto p) __attribute__((always_inline)) -> uint4 * { if constexpr (decltype(p)::value == 0) return R0; else return R1; };
+    auto kxbuf = [&](auto p) __attribute__((always_inline)) -> unsigned * { if constexpr (decltype(p)::value == 0) return KX0; else return KX1; };
+    auto vxbuf = [&](auto p) __attribute__((always_inline)) -> unsigned * { if constexpr (decltype(p)::value == 0) return VX0; else return VX1; };
+
+    // ---- decoding a stored V tile into a bf16 tile, in parts that a step deals out over its pieces.  Lane l of wave w
+    // takes 16-byte chunks of the stored tile in order: load i is chunk 64 (4 i + w) + l.
+    constexpr int DEC_E = VSROWB < ROWB ? 8 * ROWB / VSROWB : 8;             // elements per stored chunk (16 or 32)
+    constexpr int DEC_W = DEC_E / 8;                                         // bf16 chunks it becomes
+    constexpr int DEC_R = VDEC ? TKW * VSCH / 256 : 1;                       // stored chunks per lane
+    const int dec_row = lane / VSCH, dec_ch = lane % VSCH;                   // of load 0: + 4 i 64 / VSCH rows
+    const int dec_row0 = wave * (64 / VSCH) + dec_row;
+    int dec_off[DEC_W];                                                      // where the bf16 chunks go (load 0)
+    static_assert(!VDEC || (256 / VSCH) % 8 == 0, "swizzle phase must not depend on the load index");
+#pragma unroll
+    for (int k = 0; k < DEC_W; ++k)
+        dec_off[k] = dec_row0 * ROWB + ((DEC_W * dec_ch + k) ^ ((dec_row0 & (CH / 4 - 1)) << 2)) * 16;
+    uint4 dec_raw[DEC_R];
+    float dec_scale[DEC_R];
+    auto dec_load = [&](const uint4 *src, const unsigned *scales, int i) __attribute__((always_inline)) {
+        dec_raw[i] = src[(4 * i + wave) * 64 + lane];
+        if constexpr (MX)                                                    // E8M0: the byte is the exponent field
+            dec_scale[i] = __uint_as_float((unsigned)reinterpret_cast<const uint8_t *>(scales)[(dec_row0 + i * (256 / VSCH)) * 4 + dec_ch] << 23);
+        else dec_scale[i] = 1.0f;
+    };
+    auto dec_store = [&](uint4 *dst, int i, int k) __attribute__((always_inline)) {
+        const unsigned w[4] = {dec_raw[i].x, dec_raw[i].y, dec_raw[i].z, dec_raw[i].w};
+        uint4 r;
+        if constexpr (MX) r = decode_e2m1x8(w[k], dec_scale[i]);
+        else r = decode_e4m3x8(w[(2 * k) & 3], w[(2 * k + 1) & 3]);
+        *reinterpret_cast<uint4 *>(reinterpret_cast<char *>(dst) + i * (256 / VSCH) * ROWB + dec_off[k]) = r;
+    };
 
     // ---- per-lane state of the two query blocks
+    unsigned qsw[QB];                                // MX: the scale bytes of this lane's query rows, shifted by 8 hh
+#pragma unroll
+    for (int q = 0; q < QB; ++q) qsw[q] = 0u;
     float c[QB], c_next[QB];                         // scores are exponentiated as 2^(s*c); the next row tile's factor
     using qfrag_t = std::conditional_t<FP8, intx8, intx4>;
     qfrag_t qf[QB][KS];                              // B operands of S^T = K Q^T (one per instruction), kept in accumulation VGPRs
@@ -532,10 +629,13 @@ void attn_wide_kernel(const AttnKernelArgs a)
             c_next[q] = a.scale_log2;                        // takes effect with the tile's first score block
             if (a.q_scale) c_next[q] *= a.q_scale[t.bh0 + v / a.Nq];
             if (a.k_scale) c_next[q] *= a.k_scale[t.kvs];
+            if constexpr (MX)
+                qsw[q] = *reinterpret_cast<const unsigned *>(a.q_mx + (t.row_base + v) * 4) >> (8 * (ln >> 5));
         }
         // the matrix instructions written as assembly are invisible to the compiler's hazard padding:
         // keep them clear of the register writes above
         asm volatile("s_nop 15" : "+a"(qf[0][0]), "+a"(qf[QB - 1][KS - 1]));
+        if constexpr (MX) asm volatile("s_nop 7" : "+v"(qsw[0]), "+v"(qsw[QB - 1]));
     };
     // Finished tile: normalise, transpose through this wave's region of QO, write whole rows.
     // O^T register r of chunk i holds dim 32 i + 8 (r / 4) + 4 hh + (r % 4) of query row l32 of its block:
@@ -556,12 +656,14 @@ void attn_wide_kernel(const AttnKernelArgs a)
                     if (v >= rows_total) continue;
                     const size_t slot = (t.row_base + v) * (size_t)a.splits + split;
                     float *po = a.part_o + slot * D + (ln >> 5) * 4;
+                    const float vs = VS == kVE4m3 ? a.v_scale[t.kvs] : 1.0f;   // the decoded V values times this are the real ones
 #pragma unroll
                     for (int i = 0; i < DC; ++i)
 #pragma unroll
                         for (int q4 = 0; q4 < 4; ++q4)
                             *reinterpret_cast<float4 *>(po + i * 32 + q4 * 8) =
-                                make_float4(acc[q][i][4 * q4], acc[q][i][4 * q4 + 1], acc[q][i][4 * q4 + 2], acc[q][i][4 * q4 + 3]);
+                                VS == kVE4m3 ? make_float4(acc[q][i][4 * q4] * vs, acc[q][i][4 * q4 + 1] * vs, acc[q][i][4 * q4 + 2] * vs, acc[q][i][4 * q4 + 3] * vs)
+                                             : make_float4(acc[q][i][4 * q4], acc[q][i][4 * q4 + 1], acc[q][i][4 * q4 + 2], acc[q][i][4 * q4 + 3]);
                     if ((ln >> 5) == 0) {
                         a.part_ml[slot * 2] = mc_done[q];
                         a.part_ml[slot * 2 + 1] = l_row;
@@ -573,7 +675,8 @@ void attn_wide_kernel(const AttnKernelArgs a)
         char *wbase = region + (ln & 31) * OPITCH + (ln >> 5) * 8;
 #pragma unroll
         for (int q = 0; q < QB; ++q) {
-            const float inv = __builtin_amdgcn_rcpf(row_sum(q));          // 1 ulp; the result is rounded to bf16
+            float inv = __builtin_amdgcn_rcpf(row_sum(q));                // 1 ulp; the result is rounded to bf16
+            if constexpr (VS == kVE4m3) inv *= a.v_scale[t.kvs];          // (one per kv head)
 #pragma unroll
             for (int i = 0; i < DC; ++i)
 #pragma unroll
@@ -631,8 +734,12 @@ void attn_wide_kernel(const AttnKernelArgs a)
     auto step = [&](int u, floatx16 (&s_cur)[QB], floatx16 (&s_nxt)[QB], unsigned (&pk_prev)[QB][2][4],
                     unsigned (&pk_cur)[QB][2][4], const uint4 *kb, int ksub, const uint4 *vb, int vsub,
                     auto primed, auto chain, auto dma, uint4 *dk, const uint8_t *kg,
-                    uint4 *dv, const uint8_t *vg, auto can_finish, bool fin, const Tile &cur, auto maskable, auto first)
+                    uint4 *dv, const uint8_t *vg, auto can_finish, bool fin, const Tile &cur, auto maskable, auto first,
+                    auto dec, const unsigned *kx)
                     __attribute__((always_inline)) {
+        // `dec` (decoded V): the parity of the stored V tile that a `dma` step decodes, into V[dec]; kx: K(u+1)'s scale words (MX)
+        constexpr int DEC = decltype(dec)::value;
+        unsigned ksw = 0u;
         // `first` (FOLD): S(u) is the first score block of a row tile - the softmax reference is set from it
         constexpr bool FIRST = decltype(first)::value;
         constexpr bool PRIMED = decltype(primed)::value, CHAIN = decltype(chain)::value;
@@ -643,6 +750,10 @@ void attn_wide_kernel(const AttnKernelArgs a)
         if (!PRIMED) {
 #pragma unroll
             for (int j = 0; j < RDK; ++j) kfr[j] = k_frag(kb, ksub, j);
+        }
+        if constexpr (MX) {
+            ksw = kx[ksub * 32 + l32] >> (8 * hh);
+            asm volatile("s_nop 1" : "+v"(ksw));             // (written by a vector instruction, read by one the compiler does not pad)
         }
         // keys of unit u's tile outside the rows that count (see tile_at) score -inf
         const TileAt cur_at = tile_at(cur, u >> 1);
@@ -725,9 +836,17 @@ void attn_wide_kernel(const AttnKernelArgs a)
         };
         // everything of the step that is not an MFMA, dealt out over the NP pieces
         auto piece = [&](int t) __attribute__((always_inline)) {
-            if (DMA && t >= 1 && t <= NDMA_K + NDMA) {
+            if (DMA && t >= 1 && t <= NDMA_K + NDMA_V) {
                 if (t <= NDMA_K) dma_one(dk, kg, dma_koff, t - 1);
                 else dma_one(dv, vg, dma_voff, t - 1 - NDMA_K);
+            }
+            // a stored chunk is read some pieces before its first conversion, then one bf16 chunk per QB pieces
+            if constexpr (VDEC && DMA) {
+                constexpr int first_load = NDMA_K, first_store = first_load + 2 + 2 * QB;
+                static_assert(first_store + QB * DEC_R * DEC_W <= NP, "the tile is decoded within one step");
+                if (t >= first_load && t < first_load + DEC_R) dec_load(rbuf(dec), vxbuf(dec), t - first_load);
+                if (t >= first_store && t < first_store + QB * DEC_R * DEC_W && (t - first_store) % QB == 0)
+                    dec_store(vbuf(I_<DEC>{}), (t - first_store) / QB / DEC_W, (t - first_store) / QB % DEC_W);
             }
             if constexpr (MAXC > 0) if (t < MAXC) {
                 // row maxima of S(u) decide, without a divergent branch, whether the maxima in use are raised
@@ -778,8 +897,13 @@ void attn_wide_kernel(const AttnKernelArgs a)
                 if constexpr (FP8) {
                     // the unit's four fragments are all in registers; the first V fragments: two with the first
                     // instruction, one with the second
-                    if (j == 0) qk_first<true>(s_nxt[q], k_pair(kfr[0], kfr[1]), qf[q][0]);
-                    else qk_next<true>(s_nxt[q], k_pair(kfr[2 * j], kfr[2 * j + 1]), qf[q][j]);
+                    if constexpr (MX) {
+                        if (j == 0) qk_scaled<0>(s_nxt[q], k_pair(kfr[0], kfr[1]), qf[q][0], ksw, qsw[q]);
+                        else qk_scaled<1>(s_nxt[q], k_pair(kfr[2 * j], kfr[2 * j + 1]), qf[q][j], ksw, qsw[q]);
+                    } else {
+                        if (j == 0) qk_first<true>(s_nxt[q], k_pair(kfr[0], kfr[1]), qf[q][0]);
+                        else qk_next<true>(s_nxt[q], k_pair(kfr[2 * j], kfr[2 * j + 1]), qf[q][j]);
+                    }
                     static_assert(!FP8 || (KS == 2 && RD == 3), "V fragment schedule of the fp8 form");
                     if (q == 0 && j == 0) { vfr[0] = v_frag(vb, vsub, 0); vfr[1] = v_frag(vb, vsub, 1); }
                     if (q == 0 && j == 1) vfr[2] = v_frag(vb, vsub, 2);
@@ -887,10 +1011,15 @@ void attn_wide_kernel(const AttnKernelArgs a)
             __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));
             install_q(nxt);
         }
-        const int ktile = KIND == 0 ? sp + 2 : KIND - 1, vtile = last ? 0 : sp + 1;
+        // decoded V: the stored tile travels a stage ahead (tile sp+2, beside the K tile, into R[PAR]) while tile sp+1
+        // is decoded from R[1-PAR] into V[1-PAR]
+        const int ktile = KIND == 0 ? sp + 2 : KIND - 1, vtile = VDEC ? ktile : last ? 0 : sp + 1;
+        const Tile &ktile_of = KIND == 0 || BLOCK ? cur : nxt, &vtile_of = VDEC ? ktile_of : last && !BLOCK ? nxt : cur;
+        uint4 *const vdst = VDEC ? rbuf(I_<PAR>{}) : vbuf(I_<1 - PAR>{});
+        if constexpr (MX) dma_scales(kxbuf(I_<PAR>{}), vxbuf(I_<PAR>{}), ktile_of.kvs, tile_at(ktile_of, ktile).row);
         step(2 * sp + 1, s1, s0, pk0, pk1, kbuf(I_<1 - PAR>{}), 0, vbuf(I_<PAR>{}), 0, F_{}, T_{}, T_{},
-             kbuf(I_<PAR>{}), tile_at(KIND == 0 || BLOCK ? cur : nxt, ktile).k,
-             vbuf(I_<1 - PAR>{}), tile_at(last && !BLOCK ? nxt : cur, vtile).v, F_{}, false, cur, maskable, F_{});
+             kbuf(I_<PAR>{}), tile_at(ktile_of, ktile).k,
+             vdst, tile_at(vtile_of, vtile).v, F_{}, false, cur, maskable, F_{}, I_<1 - PAR>{}, kxbuf(I_<1 - PAR>{}));
         if (!BLOCK && KIND == 1 && has_next) dma_q(nxt);               // after this stage's tile loads: see the barrier below
         if (last) {
 #pragma unroll
@@ -904,7 +1033,7 @@ void attn_wide_kernel(const AttnKernelArgs a)
         }
         step(last ? 0 : 2 * sp + 2, s0, s1, pk1, pk0, kbuf(I_<1 - PAR>{}), 1, vbuf(I_<PAR>{}), 1, T_{}, F_{}, F_{},
              kbuf(I_<PAR>{}), cur.k, vbuf(I_<1 - PAR>{}), cur.v, std::integral_constant<bool, last>{}, last, cur, maskable,
-             std::integral_constant<bool, last>{});
+             std::integral_constant<bool, last>{}, I_<0>{}, kxbuf(I_<1 - PAR>{}));
         // The barrier that ends a stage waits for the stage's tile loads.  Memory operations complete in
         // order, so the requests issued after those loads - the next tile's Q rows, the finished tile's
         // output rows - can stay in flight: wait until only that many are outstanding.
@@ -936,24 +1065,48 @@ void attn_wide_kernel(const AttnKernelArgs a)
     // ---- prologue of the first row tile: Q rows and K tiles 0, 1 and V tile 0 go straight to LDS
     dma_q(cur);
     dma_tile(K0, tile_at(cur, 0).k, dma_koff, I_<NDMA_K>{});
-    dma_tile(V0, tile_at(cur, 0).v, dma_voff, I_<NDMA>{});
+    dma_tile(VDEC ? R0 : V0, tile_at(cur, 0).v, dma_voff, I_<NDMA_V>{});
     dma_tile(K1, tile_at(cur, 1).k, dma_koff, I_<NDMA_K>{});
+    if constexpr (VDEC) dma_tile(R1, tile_at(cur, 1).v, dma_voff, I_<NDMA_V>{});
+    if constexpr (MX) {
+        dma_scales(KX0, VX0, cur.kvs, tile_at(cur, 0).row);
+        dma_scales(KX1, VX1, cur.kvs, tile_at(cur, 1).row);
+    }
     // the Q rows (first in line, and this wave's own) are turned into fragments while the tiles still arrive
     asm volatile("" ::: "memory");
-    __builtin_amdgcn_s_waitcnt(waitcnt_vm(2 * NDMA_K + NDMA));
+    __builtin_amdgcn_s_waitcnt(waitcnt_vm(2 * NDMA_K + (VDEC ? 2 : 1) * NDMA_V));
     asm volatile("" ::: "memory");
     install_q(cur);
     wait_loads_and_sync(I_<0>{});
 #pragma unroll
     for (int q = 0; q < QB; ++q) c[q] = c_next[q];
+    if constexpr (VDEC) {                            // the first V tile (the others: a stage ahead of their use)
+#pragma unroll
+        for (int i = 0; i < DEC_R; ++i) dec_load(R0, VX0, i);
+#pragma unroll
+        for (int i = 0; i < DEC_R; ++i)
+#pragma unroll
+            for (int k = 0; k < DEC_W; ++k) dec_store(V0, i, k);
+        wait_loads_and_sync(I_<0>{});
+    }
+    unsigned ksw0 = 0u;                              // MX: K scales of the first unit
+    if constexpr (MX) {
+        ksw0 = KX0[l32] >> (8 * hh);
+        asm volatile("s_nop 7" : "+v"(ksw0));
+    }
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks)
 #pragma unroll
         for (int q = 0; q < QB; ++q) {
             if constexpr (FP8) {
                 const intx8 kx = k_pair(k_frag(K0, 0, 2 * ks), k_frag(K0, 0, 2 * ks + 1));
-                if (ks == 0) qk_first<true>(s0[q], kx, qf[q][0]);
-                else qk_next<true>(s0[q], kx, qf[q][ks]);
+                if constexpr (MX) {
+                    if (ks == 0) qk_scaled<0>(s0[q], kx, qf[q][0], ksw0, qsw[q]);
+                    else qk_scaled<1>(s0[q], kx, qf[q][ks], ksw0, qsw[q]);
+                } else {
+                    if (ks == 0) qk_first<true>(s0[q], kx, qf[q][0]);
+                    else qk_next<true>(s0[q], kx, qf[q][ks]);
+                }
             } else {
                 if (ks == 0) qk_first<false>(s0[q], k_frag(K0, 0, 0), qf[q][0]);       // (FOLD: from zero, the reference is 0)
                 else qk_next<false>(s0[q], k_frag(K0, 0, ks), qf[q][ks]);
@@ -968,7 +1121,7 @@ void attn_wide_kernel(const AttnKernelArgs a)
     if constexpr (QB == 2) asm volatile("s_nop 15\n\ts_nop 15" : "+v"(s0[0]), "+v"(s0[QB - 1]));
     else asm volatile("s_nop 15\n\ts_nop 15" : "+v"(s0[0]));
     if constexpr (FP8) asm volatile("s_nop 15\n\ts_nop 15" : "+v"(s0[0]));                     // (an instruction of twice the passes)
-    step(0, s0, s1, pk1, pk0, K0, 1, V0, 0, F_{}, F_{}, F_{}, K0, cur.k, V0, cur.v, F_{}, false, cur, T_{}, T_{});
+    step(0, s0, s1, pk1, pk0, K0, 1, V0, 0, F_{}, F_{}, F_{}, K0, cur.k, V0, cur.v, F_{}, false, cur, T_{}, T_{}, I_<0>{}, KX0);
     __syncthreads();   // K tile 0 is overwritten during stage 0: every wave must be done with it
 
     // ---- passes: stages 0 .. nt_even-1 = steps 1 .. 2 nt_even; the product with P(u) happens in step u+1,
@@ -1017,6 +1170,8 @@ hipError_t launch_attention_wide(const AttnArgs &a, hipStream_t stream)
     const dim3 grid((unsigned)wgs), block(kAttnThreads);
     if (a.qk_dtype == 2) {
         if (a.d != 128) return hipErrorInvalidValue;      // 64-byte fp8 rows are not worth a variant
+        if (a.q_mx != nullptr) return launch(attn_wide_kernel<128, true, false, false, 2, kVMx>, grid, block, stream, k);
+        if (a.v_dtype == 2) return launch(attn_wide_kernel<128, true, false, false, 2, kVE4m3>, grid, block, stream, k);
         return launch(attn_wide_kernel<128, true, false>, grid, block, stream, k);
     }
     // bf16 without per-head scales, long key ranges: the form with the softmax scale folded into Q
@@ -1032,7 +1187,7 @@ hipError_t launch_attention_wide(const AttnArgs &a, hipStream_t stream)
 // be empty or at least one tile long.
 bool attn_wide_block_fits(const AttnArgs &a)
 {
-    if (a.qk_dtype == 0 || a.v_dtype != 1 || (a.qk_dtype == 2 && a.d != 128)) return false;
+    if (a.qk_dtype == 0 || a.q_mx != nullptr || (a.qk_dtype == 2 && a.d != 128)) return false;
     if ((long)(a.H / a.Hkv) * a.Nq < tune("DD_TUNE_BLOCK_WIDE_MIN_ROWS", 65)) return false;
     // a tile is 64 whole rows of its source: the cache, and the block tensors when rows are spliced in from them
     return a.N >= TKW && (a.Kblk == nullptr || a.block_len >= TKW);
@@ -1097,7 +1252,10 @@ hipError_t launch_attention_wide_block(const AttnArgs &a, hipStream_t stream)
     const dim3 grid((unsigned)((long)a.B * a.Hkv * k.row_tiles * splits)), block(kAttnThreads);
     const bool fold = a.q_scale == nullptr && a.k_scale == nullptr && a.N >= kFoldMinKeys;
     hipError_t e;
-    if (narrow)
+    if (a.v_dtype == 2)
+        e = narrow ? launch(attn_wide_kernel<128, true, true, false, 1, kVE4m3>, grid, block, stream, k)
+                   : launch(attn_wide_kernel<128, true, true, false, 2, kVE4m3>, grid, block, stream, k);
+    else if (narrow)
         e = a.qk_dtype == 2 ? launch(attn_wide_kernel<128, true, true, false, 1>, grid, block, stream, k)
           : a.d == 128 ? (fold ? launch(attn_wide_kernel<128, false, true, true, 1>, grid, block, stream, k)
                                : launch(attn_wide_kernel<128, false, true, false, 1>, grid, block, stream, k))

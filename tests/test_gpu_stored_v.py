@@ -1,0 +1,63 @@
+"""Wide kernel with V tiles decoded on their way to the matrix cores (e4m3, and block-scaled e2m1), against the CPU
+oracle at the tolerance of the fp8 path: one row tile and several per workgroup, key ranges at the edges of the 64-key
+tiles, an even and an odd tile count, GQA groups that end inside a row tile; the drafter's form on both row tiles, with
+and without key splits."""
+import numpy as np
+import pytest
+
+import oracle
+import paper_2604_05250_amd as dd
+from paper_2604_05250_amd import workloads as wl
+from _util import assert_attention_close, out_to_f64, to_dev
+
+pytestmark = pytest.mark.gpu
+FP8 = wl.FP8_E4M3
+
+# (B, H, Hkv, N, cap on the persistent workgroups)
+SHAPES = [(1, 2, 2, 64, None), (1, 2, 1, 65, None), (2, 3, 1, 127, None), (1, 4, 4, 128, "1"), (1, 4, 2, 129, "2"),
+          (2, 4, 1, 255, "3"), (1, 5, 5, 320, "2"), (1, 3, 1, 641, "1"), (2, 7, 1, 1000, "5")]
+
+
+@pytest.mark.parametrize("B,H,Hkv,N,grid", SHAPES)
+@pytest.mark.parametrize("store", ["fp8v", "mx"])
+def test_bidir_decoded_v(monkeypatch, store, B, H, Hkv, N, grid):
+    import torch
+    monkeypatch.setenv("DD_TUNE_ATTN_WIDE", "1")
+    if grid:
+        monkeypatch.setenv("DD_TUNE_ATTN_WIDE_GRID", grid)
+    cfg = wl.custom_config(B=B, H=H, Hkv=Hkv, N=N, d=128, qk_dtype=FP8, v_dtype=FP8, prompt=0, G=N, bl=min(16, N))
+    if store == "mx":
+        inp = wl.mx_attention_inputs(cfg, seed=N)
+        # scales that differ from block to block: a misplaced one is a gross error
+        inp["Vs"] = (inp["Vs"].astype(np.int32) + np.random.default_rng(N).integers(-3, 2, inp["Vs"].shape)).astype(np.uint8)
+        O = dd.dd_bidir_attention_mx(*(to_dev(inp[k]) for k in ("Q", "Qs", "K", "Ks", "V", "Vs")))
+        ref = oracle.bidir_attention_mx(inp["Q"], inp["Qs"], inp["K"], inp["Ks"], inp["V"], inp["Vs"])
+    else:
+        inp = wl.attention_inputs(cfg, seed=N)
+        O = dd.dd_bidir_attention_fp8v(*(to_dev(inp[k]) for k in ("Q", "K", "V", "q_scale", "k_scale", "v_scale")))
+        ref = oracle.bidir_attention(inp["Q"], inp["K"], inp["V"], FP8, FP8, inp["q_scale"], inp["k_scale"], v_scale=inp["v_scale"])
+    torch.cuda.synchronize()
+    assert_attention_close(out_to_f64(O, wl.BF16), ref, FP8, f"{store} bidir {B}x{H}/{Hkv}x{N} grid {grid}")
+
+
+# (B, H, Hkv, N, block_len, block_start, rows per workgroup): key-stream parts that are empty, whole tiles, ragged
+BLOCKS = [(1, 8, 2, 64, 64, 0, "128"), (2, 4, 2, 333, 64, 101, "128"), (1, 8, 2, 1000, 64, 936, "256"), (1, 6, 1, 517, 80, 0, "256"),
+          (1, 4, 2, 4097, 64, 2000, "128"), (2, 12, 3, 2048, 96, 1536, "256")]
+
+
+@pytest.mark.parametrize("B,H,Hkv,N,bl,bs,rows", BLOCKS)
+def test_block_decoded_v(monkeypatch, B, H, Hkv, N, bl, bs, rows):
+    import torch
+    monkeypatch.setenv("DD_TUNE_BLOCK_WIDE_ROWS", rows)
+    cfg = wl.custom_config(B=B, H=H, Hkv=Hkv, N=N, d=128, qk_dtype=FP8, v_dtype=FP8, bl=bl, prompt=0, G=N)
+    cache = wl.cache_inputs(cfg, seed=bs + N)
+    blk = wl.block_inputs(cfg, bs, 0, k_scale=cache["k_scale"], v_scale=cache["v_scale"])
+    for fresh in (True, False):
+        Kb, Vb = (blk["Kblk"], blk["Vblk"]) if fresh else (None, None)
+        O = dd.dd_block_attention_cached_fp8v(to_dev(blk["Qblk"]), to_dev(cache["Kc"]), to_dev(cache["Vc"]), bs,
+                                              to_dev(blk["q_scale"]), to_dev(cache["k_scale"]), to_dev(cache["v_scale"]),
+                                              Kblk=to_dev(Kb), Vblk=to_dev(Vb))
+        torch.cuda.synchronize()
+        ref = oracle.block_attention_cached(blk["Qblk"], cache["Kc"], cache["Vc"], bs, FP8, FP8, Kb, Vb, blk["q_scale"],
+                                            cache["k_scale"], v_scale=cache["v_scale"])
+        assert_attention_close(out_to_f64(O, wl.BF16), ref, FP8, f"fp8-V block {B}x{H}/{Hkv} N{N} bl{bl}@{bs} fresh={fresh}")

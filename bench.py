@@ -438,7 +438,7 @@ def run_config(args, config_id):
             fold = not fp8 and c.N >= 1024          # bf16 without per-head scales: the folded-scale form
             return f"attn_wide_kernel<{c.d}, {'true' if fp8 else 'false'}, false, {'true' if fold else 'false'}, 2, {stored_v}>"
         if not fp8 and c.B * c.Hkv * -(-group * c.N // 128) < 256:
-            return f"attn_stream_kernel<{c.d}>"
+            return f"attn_stream_kernel<{c.d}, false>"
         return (f"attn_mfma_kernel<{c.d}, {'true' if fp8 else 'false'}, false, {'true' if stored_v == 1 else 'false'}, "
                 f"{'true' if stored_v == 2 else 'false'}>")
 

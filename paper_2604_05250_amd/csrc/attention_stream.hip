@@ -59,7 +59,11 @@ __device__ __forceinline__ float swap_sum(float x)
     return __uint_as_float(r.x) + __uint_as_float(r.y);
 }
 
-template <int D>
+// s_waitcnt immediate: wait until at most n vector-memory operations are outstanding, nothing else
+constexpr int waitcnt_vm(int n) { return (n & 15) | ((n >> 4) << 14) | (7 << 4) | (15 << 8); }
+
+// NT: the K/V tiles are loaded with the non-temporal hint (see the launcher).
+template <int D, bool NT>
 __global__ __launch_bounds__(kAttnThreads) __attribute__((amdgpu_waves_per_eu(1, 1)))
 void attn_stream_kernel(const AttnKernelArgs a)
 {
@@ -125,9 +129,9 @@ void attn_stream_kernel(const AttnKernelArgs a)
             const uint8_t *ks = (in_blk ? kb_ : kc) + roff + dma_koff;
             const uint8_t *vs = (in_blk ? vb_ : vc) + roff + dma_voff;
             __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)ks,
-                                             (__attribute__((address_space(3))) void *)(kd + r0 * CH), 16, 0, 0);
+                                             (__attribute__((address_space(3))) void *)(kd + r0 * CH), 16, 0, NT ? 2 : 0);
             __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)vs,
-                                             (__attribute__((address_space(3))) void *)(vd + r0 * CH), 16, 0, 0);
+                                             (__attribute__((address_space(3))) void *)(vd + r0 * CH), 16, 0, NT ? 2 : 0);
         }
     };
 
@@ -144,15 +148,20 @@ void attn_stream_kernel(const AttnKernelArgs a)
         for (int ks = 0; ks < KS; ++ks)
             qf[q][ks] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4 *>(
                             static_cast<const uint16_t *>(a.Q) + (row_base + vv) * D + ks * 16 + hh * 8));
-        c[q] = a.scale_log2;
-        if (a.q_scale) c[q] *= a.q_scale[b * a.H + kvh * a.group + vv / a.Nq];
-        if (a.k_scale) c[q] *= a.k_scale[b * a.Hkv + kvh];
+        c[q] = 1.0f;
+        if (a.q_scale) c[q] = a.q_scale[b * a.H + kvh * a.group + vv / a.Nq];
     }
-
-    // the first three tiles; the Q loads above are older, so the first partial wait below covers them too
+    float k_scale = 1.0f;
+    if (a.k_scale) k_scale = a.k_scale[b * a.Hkv + kvh];
+    __builtin_amdgcn_sched_barrier(0);               // these loads are requested before the first three tiles ...
+    // (a tile past the range repeats its last row)
 #pragma unroll
-    for (int t0 = 0; t0 < kRing - 1; ++t0)
-        if (t0 < ntiles) dma_tile(t0);
+    for (int t0 = 0; t0 < kRing - 1; ++t0) dma_tile(t0);
+    // ... and waited for here while the tiles are still on their way: the compiler, left to place this wait, waits for
+    // the tiles as well, and the memory pipeline runs empty before the first tile is even looked at
+    __builtin_amdgcn_s_waitcnt(waitcnt_vm((kRing - 1) * 2 * NDMA));
+#pragma unroll
+    for (int q = 0; q < QBS; ++q) c[q] = a.scale_log2 * c[q] * k_scale;
 
     floatx16 acc[QBS][DC];                           // O^T, unnormalised
 #pragma unroll
@@ -292,7 +301,7 @@ void attn_stream_kernel(const AttnKernelArgs a)
     // done with tile t-1, whose slot then receives tile t+3.  A wave takes the unit of its key phase.
     for (int t = 0; t < ntiles; ++t) {
         const int newer = ntiles - 1 - t;                    // tiles after t (all requested up to t + 2)
-        if (newer >= 2) asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(2 * 2 * NDMA) : "memory");
+        if (newer >= 2 || t == 0) asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(2 * 2 * NDMA) : "memory");
         else if (newer == 1) asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(2 * NDMA) : "memory");
         else asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");
         if (t + kRing - 1 < ntiles) dma_tile(t + kRing - 1);
@@ -383,14 +392,21 @@ void attn_stream_kernel(const AttnKernelArgs a)
 // The streaming kernel serves calls with at most this many query rows per (batch, kv head).
 bool attn_stream_fits(const AttnArgs &a) { return (long)(a.H / a.Hkv) * a.Nq <= 2 * kRowsWaveS; }
 
+constexpr double kStreamPastCacheBytes = 100.0e6;
+
 hipError_t launch_attention_stream(const AttnArgs &a, hipStream_t stream)
 {
     AttnKernelArgs k;
     fill_kernel_args(a, k, 2 * kRowsWaveS, TKS);
     if (a.Kblk == nullptr) k.block_len = 0;                 // no row is taken from the block tensors
     const dim3 grid((unsigned)((long)a.B * a.Hkv * k.row_tiles * k.splits)), block(kAttnThreads);
-    const hipError_t e = a.d == 128 ? launch(attn_stream_kernel<128>, grid, block, stream, k)
-                                    : launch(attn_stream_kernel<64>, grid, block, stream, k);
+    // A cache too large to survive in the 256 MB last-level cache until it is read again is streamed past it: 8 x 32
+    // heads x 1024 keys (134 MB) 30.5 -> 27.0 us per call (4.7 -> 5.3 TB/s), 16 x 32 x 2048 (537 MB) 98.8 -> 88.3 us.  A
+    // smaller one may still be there from the call before: 67 MB, in calls on four copies of it in turn, 20.9 us with plain
+    // loads against 22.8 with the hint.  The verifier's rows share K/V between workgroups: never for them.
+    const bool nt = a.Nq != a.N && 2.0 * a.B * a.Hkv * a.N * a.d * 2 > kStreamPastCacheBytes;
+    const hipError_t e = a.d == 128 ? (nt ? launch(attn_stream_kernel<128, true>, grid, block, stream, k) : launch(attn_stream_kernel<128, false>, grid, block, stream, k))
+                                    : (nt ? launch(attn_stream_kernel<64, true>, grid, block, stream, k) : launch(attn_stream_kernel<64, false>, grid, block, stream, k));
     return e != hipSuccess ? e : finish_attention(a, k.splits, stream);
 }
 

@@ -431,13 +431,16 @@ def run_config(args, config_id):
     def attn_kernel_name(c, stored_v=0):
         """The kernel the library's size rule picks for this call (the rule itself lives in the library).  stored_v:
         the kernels' code for V's storage, 1 = e4m3, 2 = block-scaled e2m1."""
-        group = c.H // c.Hkv
-        wide_tiles = c.B * c.Hkv * -(-group * c.N // 256)
+        heads, rows = c.B * c.Hkv, (c.H // c.Hkv) * c.N
         fp8 = c.qk_dtype == wl.FP8_E4M3
-        if wide_tiles >= 192 and c.N >= 512 and (not fp8 or c.d == 128):
-            fold = not fp8 and c.N >= 1024          # bf16 without per-head scales: the folded-scale form
-            return f"attn_wide_kernel<{c.d}, {'true' if fp8 else 'false'}, false, {'true' if fold else 'false'}, 2, {stored_v}>"
-        if not fp8 and c.B * c.Hkv * -(-group * c.N // 128) < 256:
+        one_round = {r: heads * -(-rows // r) <= 256 for r in (64, 128)}
+        fold = not fp8 and c.N >= 1024              # bf16 without per-head scales: the folded-scale form
+        if not fp8 or c.d == 128:
+            if one_round[128] and (c.N >= 448 or (c.N >= 192 and (fp8 or not one_round[64]))):
+                return f"attn_wide_kernel<{c.d}, {'true' if fp8 else 'false'}, true, {'true' if fold else 'false'}, 1, {stored_v}>"
+            if not one_round[128] and c.N >= 448:
+                return f"attn_wide_kernel<{c.d}, {'true' if fp8 else 'false'}, false, {'true' if fold else 'false'}, 2, {stored_v}>"
+        if not fp8 and one_round[64]:
             return f"attn_stream_kernel<{c.d}, false>"
         return (f"attn_mfma_kernel<{c.d}, {'true' if fp8 else 'false'}, false, {'true' if stored_v == 1 else 'false'}, "
                 f"{'true' if stored_v == 2 else 'false'}>")

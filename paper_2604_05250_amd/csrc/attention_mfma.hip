@@ -757,13 +757,23 @@ hipError_t launch_attention_mfma(const AttnArgs &a, hipStream_t stream)
     const dim3 grid((unsigned)blocks), block(kAttnThreads);
     if (a.Kblk == nullptr) k.block_len = 0;                                // no row is taken from block tensors
     hipError_t e;
-    if (!blk && (!fp8 || a.d == 128)) {
-        // The wide-wave kernel (256 query rows per workgroup, one wave per SIMD; bf16, or fp8 Q/K with
-        // d = 128) wins once there are enough row tiles to occupy the chip; below that smaller workgroups
-        // spread better.
-        const long tiles = (long)a.B * a.Hkv * (((long)(a.H / a.Hkv) * a.Nq + 255) / 256);
-        const bool wide = tune("DD_TUNE_ATTN_WIDE", tiles >= 192 && a.N >= 512) != 0;
-        if (wide && a.N >= 64) return launch_attention_wide(a, stream);   // its K/V tiles are 64 whole rows
+    // Verifier calls: do workgroups of 64 / 128 query rows fit the chip's 256 compute units in one round?
+    const long heads = (long)a.B * a.Hkv, rows = (long)(a.H / a.Hkv) * a.Nq;
+    const bool one_round64 = heads * ((rows + 63) / 64) <= 256, one_round128 = heads * ((rows + 127) / 128) <= 256;
+    if (!blk && (!fp8 || a.d == 128) && a.N >= 64) {           // (the wide kernel's K/V tiles are 64 whole rows)
+        // One round of 128-row workgroups: the wide kernel on 128-row tiles, which has twice the workgroups of its
+        // 256-row tiles, each 0.7 of one's time per key.  More: its 256-row tiles (persistent).  Measured against the
+        // kernel such calls ran on before (us, bf16 / fp8 Q and K): 1 x 32 heads, N 512 14.1 -> 12.7 / 15.5 -> 11.6, N 900
+        // 27.4 -> 24.3 / 24.3 -> 20.5; 1 x 28 (4 kv), N 1100 30.5 -> 23.6 / 27.8 -> 21.2; 1 x 16, N 2048 50.5 -> 38.7 /
+        // 45.4 -> 33.0; past the round 256-row tiles win at once: 1 x 32, N 1100 42.8 -> 31.2 / 38.7 -> 27.2 (128-row
+        // tiles 43.4 / 38.4).  Below about 450 keys the fill and drain of either weigh more than the shorter loop saves:
+        // one round of 64-row bf16 workgroups streams (N 300 10.6 against 11.7), a call with more than one round of
+        // 128-row workgroups (8 x 32, N 200: 17.6 against 17.7; N 300, where 256-row tiles pad most: 28.2 against 31.8)
+        // or under 192 keys (N 150: 9.4 against 10.5) stays on the kernel of this file.
+        const int by_size = one_round128 ? (a.N >= 448 || (a.N >= 192 && (fp8 || !one_round64)) ? 2 : 0) : (a.N >= 448 ? 1 : 0);
+        const int pick = tune("DD_TUNE_ATTN_WIDE", by_size);
+        if (pick == 1) return launch_attention_wide(a, stream);
+        if (pick == 2) return launch_attention_wide_narrow(a, stream);
     }
     if (a.q_mx != nullptr) {
         // block-scaled inputs, verifier form
@@ -781,8 +791,9 @@ hipError_t launch_attention_mfma(const AttnArgs &a, hipStream_t stream)
     }
     if (!blk && (!fp8 || a.d == 128)) {
         // A small bf16 call leaves most compute units idle with 128-row workgroups: the streaming kernel's
-        // 64-row workgroups (two row blocks x two key phases) spread it over more of them.
-        const bool small = tune("DD_TUNE_BIDIR_STREAM", blocks < 256) != 0;
+        // 64-row workgroups (two row blocks x two key phases) spread it over more of them, one round of them at most (a
+        // second one doubles the call: 1 x 32 heads, N 700, 33 us).
+        const bool small = tune("DD_TUNE_BIDIR_STREAM", one_round64) != 0;
         if (small && !fp8) return launch_attention_stream(a, stream);
     }
     if (blk && !fp8 && a.Nq != a.N && attn_stream_fits(a)) {

@@ -202,9 +202,10 @@ using F_ = std::false_type;
 // registers by LDS reads instead of kept in registers - half the gain; the same mechanism without the folded
 // scale, one multiplication per score - slower than the row-maximum form, which therefore stays for fp8 and
 // per-head scales.)
-// QB: 32-row query blocks per wave.  2 is the form described above; 1 (the drafter's call only) halves the row
+// QB: 32-row query blocks per wave.  2 is the form described above; 1 (compiled for the drafter's form only) halves the row
 // tile to 128 rows - every K and V fragment then feeds one matrix instruction instead of two, but twice as many
-// workgroups share the call, which can spare it the key splits, their partial states and the merge launch.
+// workgroups share the call, which can spare it the key splits, their partial states and the merge launch.  Verifier
+// calls of few rows run on it too (a key stream of one part, no splits).
 // VS: how V is stored.  kVBf16: as multiplied.  kVE4m3 (fp8 Q/K only): e4m3 codes, v_scale multiplies the output once.
 // kVMx (fp8 Q/K, verifier form): block-scaled inputs, Q/K e4m3 and V e2m1 with E8M0 scales per 32 head dims.  Stored
 // tiles of the last two go to LDS as they are, one stage earlier than a bf16 tile would, and are decoded to the bf16
@@ -225,7 +226,7 @@ void attn_wide_kernel(const AttnKernelArgs a)
     static_assert(QB == 2 || (QB == 1 && BLOCK), "one or two row blocks per wave");
     constexpr bool MX = VS == kVMx, VDEC = VS != kVBf16;
     static_assert(!VDEC || (FP8 && D == 128), "stored V other than bf16 comes with fp8 Q/K, whole 128-wide rows");
-    static_assert(!MX || !BLOCK, "block-scaled inputs: verifier form");
+    static_assert(!MX || !BLOCK || QB == 1, "block-scaled inputs: verifier calls only (on 128-row tiles through the drafter's form)");
     constexpr int kRowsWave = 32 * QB, kRowsWG = 4 * kRowsWave;
     constexpr int NE = 16 * QB;                      // scores per lane and unit
     constexpr int CH = D / 8;                        // 16-byte chunks (8 bf16) per V / O row
@@ -1180,6 +1181,26 @@ hipError_t launch_attention_wide(const AttnArgs &a, hipStream_t stream)
                                 : launch(attn_wide_kernel<128, false, false>, grid, block, stream, k);
     return fold ? launch(attn_wide_kernel<64, false, false, true>, grid, block, stream, k)
                 : launch(attn_wide_kernel<64, false, false>, grid, block, stream, k);
+}
+
+// The verifier's call on 128-row tiles: the drafter's form with a key stream of one part and no splits.
+hipError_t launch_attention_wide_narrow(const AttnArgs &a, hipStream_t stream)
+{
+    if (a.N < TKW) return hipErrorInvalidValue;            // a K/V tile is 64 whole rows
+    AttnKernelArgs k;
+    fill_kernel_args(a, k, kRowsWGNarrow, TKW);
+    const dim3 grid((unsigned)((long)a.B * a.Hkv * k.row_tiles)), block(kAttnThreads);
+    if (a.qk_dtype == 2) {
+        if (a.d != 128) return hipErrorInvalidValue;
+        if (a.q_mx != nullptr) return launch(attn_wide_kernel<128, true, true, false, 1, kVMx>, grid, block, stream, k);
+        if (a.v_dtype == 2) return launch(attn_wide_kernel<128, true, true, false, 1, kVE4m3>, grid, block, stream, k);
+        return launch(attn_wide_kernel<128, true, true, false, 1>, grid, block, stream, k);
+    }
+    const bool fold = a.q_scale == nullptr && a.k_scale == nullptr && a.N >= kFoldMinKeys;
+    if (a.d == 128) return fold ? launch(attn_wide_kernel<128, false, true, true, 1>, grid, block, stream, k)
+                                : launch(attn_wide_kernel<128, false, true, false, 1>, grid, block, stream, k);
+    return fold ? launch(attn_wide_kernel<64, false, true, true, 1>, grid, block, stream, k)
+                : launch(attn_wide_kernel<64, false, true, false, 1>, grid, block, stream, k);
 }
 
 // The drafter's call on the wide kernel: worth it from 65 query rows per kv head (GQA groups times the block

@@ -1,7 +1,7 @@
-"""Wide kernel with V tiles decoded on their way to the matrix cores (e4m3, and block-scaled e2m1), against the CPU
-oracle at the tolerance of the fp8 path: one row tile and several per workgroup, key ranges at the edges of the 64-key
-tiles, an even and an odd tile count, GQA groups that end inside a row tile; the drafter's form on both row tiles, with
-and without key splits."""
+"""The wide kernel's forms beside the 256-row bf16 / fp8 one: V tiles decoded on their way to the matrix cores (e4m3, and
+block-scaled e2m1), and verifier calls on 128-row tiles, against the CPU oracle at the contract's tolerances.  Shapes: one row
+tile and several per workgroup, key ranges at the edges of the 64-key tiles, an even and an odd tile count, GQA groups that
+end inside a row tile; the drafter's form on both row tiles, with and without key splits."""
 import numpy as np
 import pytest
 
@@ -20,9 +20,10 @@ SHAPES = [(1, 2, 2, 64, None), (1, 2, 1, 65, None), (2, 3, 1, 127, None), (1, 4,
 
 @pytest.mark.parametrize("B,H,Hkv,N,grid", SHAPES)
 @pytest.mark.parametrize("store", ["fp8v", "mx"])
-def test_bidir_decoded_v(monkeypatch, store, B, H, Hkv, N, grid):
+@pytest.mark.parametrize("tile", ["256", "128"])
+def test_bidir_decoded_v(monkeypatch, store, tile, B, H, Hkv, N, grid):
     import torch
-    monkeypatch.setenv("DD_TUNE_ATTN_WIDE", "1")
+    monkeypatch.setenv("DD_TUNE_ATTN_WIDE", "1" if tile == "256" else "2")
     if grid:
         monkeypatch.setenv("DD_TUNE_ATTN_WIDE_GRID", grid)
     cfg = wl.custom_config(B=B, H=H, Hkv=Hkv, N=N, d=128, qk_dtype=FP8, v_dtype=FP8, prompt=0, G=N, bl=min(16, N))
@@ -61,3 +62,25 @@ def test_block_decoded_v(monkeypatch, B, H, Hkv, N, bl, bs, rows):
         ref = oracle.block_attention_cached(blk["Qblk"], cache["Kc"], cache["Vc"], bs, FP8, FP8, Kb, Vb, blk["q_scale"],
                                             cache["k_scale"], v_scale=cache["v_scale"])
         assert_attention_close(out_to_f64(O, wl.BF16), ref, FP8, f"fp8-V block {B}x{H}/{Hkv} N{N} bl{bl}@{bs} fresh={fresh}")
+
+
+# verifier calls on 128-row tiles (one per workgroup): (B, H, Hkv, N, d) - one key tile, overlapping last tiles, rows of
+# a kv head that end inside a wave / inside a workgroup, and (1025 keys) the folded-scale form
+NARROW = [(1, 2, 2, 64, 128), (1, 2, 1, 65, 64), (2, 3, 1, 127, 128), (1, 4, 4, 129, 64), (1, 5, 1, 191, 128), (2, 2, 2, 320, 128),
+          (1, 2, 1, 1025, 128), (1, 2, 1, 1025, 64)]
+
+
+@pytest.mark.parametrize("B,H,Hkv,N,d", NARROW)
+@pytest.mark.parametrize("qk", [wl.BF16, FP8])
+def test_bidir_128_row_tiles(monkeypatch, qk, B, H, Hkv, N, d):
+    import torch
+    if qk == FP8 and d == 64:
+        pytest.skip("fp8 with 64 head dims has no wide form")
+    monkeypatch.setenv("DD_TUNE_ATTN_WIDE", "2")
+    cfg = wl.custom_config(B=B, H=H, Hkv=Hkv, N=N, d=d, qk_dtype=qk, v_dtype=wl.BF16, prompt=0, G=N, bl=min(16, N))
+    inp = wl.attention_inputs(cfg, seed=N + d)
+    O = dd.dd_bidir_attention(to_dev(inp["Q"]), to_dev(inp["K"]), to_dev(inp["V"]), q_scale=to_dev(inp["q_scale"]),
+                              k_scale=to_dev(inp["k_scale"]), qk_dtype=qk, v_dtype=wl.BF16)
+    torch.cuda.synchronize()
+    ref = oracle.bidir_attention(inp["Q"], inp["K"], inp["V"], qk, wl.BF16, inp["q_scale"], inp["k_scale"])
+    assert_attention_close(out_to_f64(O, wl.BF16), ref, qk, f"128-row tiles {B}x{H}/{Hkv}x{N}x{d}")

@@ -1,4 +1,4 @@
-"""Build the HIP library (libdd.so) in-tree for gfx950 with hipcc."""
+"""Build the HIP library (libdd.so, hipcc for gfx950) and the native part of the Python binding (_binding.so, g++) in-tree."""
 from __future__ import annotations
 
 import os
@@ -40,5 +40,33 @@ def build_library(force: bool = True, verbose: bool = False, extra_flags=()) -> 
     return LIB
 
 
+BINDING = os.path.join(_HERE, "_binding.so")
+BINDING_SOURCE = os.path.join(CSRC, "binding.cpp")
+
+
+def build_binding(verbose: bool = False) -> str:
+    """Compile the binding's native part against torch's headers; it loads libdd.so from its own directory."""
+    import sysconfig
+
+    import torch
+    t = os.path.dirname(os.path.abspath(torch.__file__))
+    inc = [os.path.join(t, "include"), os.path.join(t, "include", "torch", "csrc", "api", "include"),
+           os.path.join(os.environ.get("ROCM_PATH", "/opt/rocm"), "include"), sysconfig.get_paths()["include"]]
+    lib = os.path.join(t, "lib")
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}"]
+    cmd += [x for d in inc for x in ("-isystem", d)] + ["-o", BINDING, BINDING_SOURCE, "-L" + _HERE, "-l:" + os.path.basename(LIB)]
+    cmd += ["-L" + lib, "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python", "-lamdhip64", "-Wl,-rpath,$ORIGIN"]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    res = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+    if res.returncode != 0:
+        raise RuntimeError("g++ failed:\n" + res.stdout)
+    if verbose and res.stdout.strip():
+        print(res.stdout)
+    return BINDING
+
+
 if __name__ == "__main__":
     print(build_library(force=True, verbose=True, extra_flags=sys.argv[1:]))
+    print(build_binding(verbose=True))

@@ -459,8 +459,8 @@ def run_config(args, config_id):
                           "(O = P V, V decoded to bf16 on its way into LDS) as bf16 MFMA (2.5 PFLOP/s): time-weighted peak "
                           "3.33 PFLOP/s")
     elif cfg.qk_dtype == wl.F32:
-        attn_kernel, attn_bound, attn_peak = "attn_f32_kernel", "alu", PEAK_FP32_VALU_TFLOPS
-        attn_peak_note = "fp32 inputs: vector ALUs (no fp32 MFMA path is used), 157.3 TFLOP/s"
+        attn_kernel, attn_bound, attn_peak = "attn_f32_kernel", "mfma", PEAK_FP32_VALU_TFLOPS
+        attn_peak_note = "fp32 inputs: fp32 matrix instruction, 157.3 TFLOP/s"
     elif cfg.qk_dtype == wl.FP8_E4M3:
         attn_kernel, attn_bound = attn_kernel_name(cfg), "mfma"
         attn_peak = 2.0 / (1.0 / PEAK_FP8_TFLOPS + 1.0 / PEAK_BF16_TFLOPS)

@@ -1,143 +1,200 @@
-// fp32 attention, softmax(Q K^T / sqrt(d_k)) V (Eq. 3) over all key positions (Sec. 2.2),
-// computed in fp32 throughout on the vector ALUs.  It serves fp32 inputs (the small
+// fp32 attention, softmax(Q K^T / sqrt(d_k)) V (Eq. 3) over all key positions (Sec. 2.2), in fp32 throughout, on the
+// fp32 matrix instruction (v_mfma_f32_16x16x4_f32: fp32 products and sums).  It serves fp32 inputs (the small
 // CPU-checkable configuration) for both the verifier's full attention and the drafter's
-// block attention over the cached K/V (Sec. 2.3); the bf16 / fp8 workloads run on the
-// matrix cores in attention_mfma.hip.
+// block attention over the cached K/V (Sec. 2.3); the bf16 / fp8 workloads run on the kernels of the other files.
 //
-// d/32 adjacent lanes share one query row, each owning 32 of its dims.  A tile of 32 keys
-// (K and V rows, fp32) is staged in LDS; K rows are read as wave-wide broadcasts.
+// Such calls are small (a few heads, a few hundred keys), so what counts is the length of the dependent chain, not a
+// rate: one workgroup takes 16 (or 32) query rows of one (batch, kv head), its eight waves take 16-key units in turn,
+// and nothing passes through LDS before the waves' states are merged at the end.  K and V go from memory straight into
+// the instruction's operand registers in 16-byte loads; which head dim or key an operand element stands for is free as
+// long as both operands agree:
+//   S^T = K Q^T   k index g of step (j, e) is head dim 16 j + 4 g + e: lane (key l % 16, g = l / 16) loads
+//                 K[key][16 j + 4 g ..+3], the Q fragment likewise.  The result holds, per lane, query l % 16 and keys
+//                 4 g + r: the softmax row reductions are in-register plus two lane exchanges;
+//   O^T += V^T P^T  k index g of step r is key 4 g + r, so the weights are the B operand as they stand; row m of chunk
+//                 (h, e) is head dim 64 h + 4 m + e: lane (m, g) loads V[key][64 h + 4 m ..+3] and its four elements
+//                 are the operands of four instructions.
+// The next unit's K and V are requested before the current one is worked on.  Measured against the vector-ALU kernel before
+// it (one lane per 32 dims of a query row, keys in turn, K/V broadcast from LDS), us per call: the smallest workload (4
+// heads, 128 keys, d = 64) 43.2 -> 5.2 (drafter) and 43.8 -> 5.3 (verifier), of which some 4 are any launch; 1 x 32 heads x 512
+// keys, d = 128 194 -> 72; 2 x 32 x 1024, d = 64 360 -> 198 (87 TFLOP/s of the instruction's 157).
 #include "attention_common.h"
 #include "dd_internal.h"
 
 namespace dd {
 namespace {
 
-constexpr int TKF = 32;   // keys per LDS tile
+typedef float floatx4 __attribute__((ext_vector_type(4)));
+
+constexpr int kThreadsF = 512;
+constexpr int kWavesF = kThreadsF / 64;
+constexpr int kUnitF = 16;                          // keys per unit
+constexpr int kSplitKeys = 256;                     // keys per key split, at least
 
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 
-template <int D>
-__global__ __launch_bounds__(kAttnThreads) void attn_f32_kernel(const AttnKernelArgs a)
+// RB: 16-row query blocks per workgroup
+template <int D, int RB>
+__global__ __launch_bounds__(kThreadsF) void attn_f32_kernel(const AttnKernelArgs a)
 {
-    constexpr int LPQ = D / 32;                 // lanes per query row
-    constexpr int ROWS = kAttnThreads / LPQ;    // query rows per workgroup
-    constexpr int CH = D / 4;                   // float4 chunks per row
-    __shared__ float4 Ks[TKF * CH];
-    __shared__ float4 Vs[TKF * CH];
+    constexpr int NJ = D / 16;                      // 16-byte fragments of a Q / K row per lane
+    constexpr int NH = D / 64;                      // ... of a V row
+    constexpr int NO = NH * 4;                      // 16-byte pieces of an O row per lane
+    __shared__ floatx4 states[kWavesF * RB * NO * 64];
+    __shared__ float ml[kWavesF][RB][2][16];        // per wave: (max in use, sum) of its query rows
 
-    const int tid = threadIdx.x;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int l16 = lane & 15, g = lane >> 4;
     int bid = blockIdx.x;
     const int sp = bid % a.splits; bid /= a.splits;
     const int rt = bid % a.row_tiles; bid /= a.row_tiles;
     const int kvh = bid % a.Hkv;
     const int b = bid / a.Hkv;
-    const int rows_total = a.group * a.Nq;
-    const int v = rt * ROWS + tid / LPQ;
-    const int sub = tid % LPQ;
-    const bool row_ok = v < rows_total;
-    const int vv = row_ok ? v : rows_total - 1;
-    const int head = kvh * a.group + vv / a.Nq;
-    const int qi = vv % a.Nq;
-    const size_t orow = ((size_t)b * a.H + head) * (size_t)a.Nq + qi;
-
-    float q[32], o[32];
-    {
-        const float4 *qp = reinterpret_cast<const float4 *>(static_cast<const float *>(a.Q) + orow * D + sub * 32);
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            const float4 w = qp[i];
-            q[4 * i] = w.x; q[4 * i + 1] = w.y; q[4 * i + 2] = w.z; q[4 * i + 3] = w.w;
-        }
-#pragma unroll
-        for (int i = 0; i < 32; ++i) o[i] = 0.f;
-    }
-    float c = a.scale_log2;
-    if (a.q_scale) c *= a.q_scale[b * a.H + head];
-    if (a.k_scale) c *= a.k_scale[b * a.Hkv + kvh];
+    const int rows_total = a.group * a.Nq;          // query rows of this (batch, kv head): contiguous in memory
+    const size_t row_base = ((size_t)b * a.H + (size_t)kvh * a.group) * a.Nq;
 
     const int k_begin = sp * a.keys_per_split;
     const int k_end = min(a.N, k_begin + a.keys_per_split);
     const size_t kv_head = (size_t)b * a.Hkv + kvh;
     const int bstart = a.block_starts ? a.block_starts[b] : a.block_start;   // any value is safe: rows are chosen by range test
-    float m_run = -INFINITY, l_run = 0.f;
+    const float *const kc = static_cast<const float *>(a.K) + kv_head * a.kv_stride * D;
+    const float *const vc = static_cast<const float *>(a.V) + kv_head * a.kv_stride * D;
+    const float *const kb = a.Kblk ? static_cast<const float *>(a.Kblk) + kv_head * a.block_len * D : nullptr;
+    const float *const vb = a.Kblk ? static_cast<const float *>(a.Vblk) + kv_head * a.block_len * D : nullptr;
 
-    for (int k0 = k_begin; k0 < k_end; k0 += TKF) {
-        __syncthreads();
-        for (int id = tid; id < TKF * CH; id += kAttnThreads) {
-            const int row = id / CH, ch = id % CH;
-            const int j = k0 + row;
-            float4 kw = make_float4(0.f, 0.f, 0.f, 0.f), vw = kw;
-            if (j < k_end) {
-                const bool in_blk = a.Kblk != nullptr && (unsigned)j - (unsigned)bstart < (unsigned)a.block_len;
-                const size_t off = in_blk ? (kv_head * a.block_len + (size_t)(j - bstart)) * D
-                                          : (kv_head * a.kv_stride + (size_t)j) * D;
-                const float *kp = static_cast<const float *>(in_blk ? a.Kblk : a.K) + off;
-                const float *vp = static_cast<const float *>(in_blk ? a.Vblk : a.V) + off;
-                kw = reinterpret_cast<const float4 *>(kp)[ch];
-                vw = reinterpret_cast<const float4 *>(vp)[ch];
-            }
-            Ks[id] = kw;
-            Vs[id] = vw;
+    floatx4 qf[RB][NJ], acc[RB][NO], kf[2][NJ], vf[2][4][NH];
+    float c[RB], m_run[RB], l_run[RB];
+    // rows past the end of the range repeat its last one (their scores are masked)
+    auto load_unit = [&](int u, floatx4 (&k)[NJ], floatx4 (&v)[4][NH]) __attribute__((always_inline)) {
+        const int j0 = k_begin + u * kUnitF;
+        {
+            const int j = min(j0 + l16, k_end - 1);
+            const bool in_blk = kb != nullptr && (unsigned)j - (unsigned)bstart < (unsigned)a.block_len;
+            const float *p = (in_blk ? kb + (size_t)(j - bstart) * D : kc + (size_t)j * D) + 4 * g;
+#pragma unroll
+            for (int i = 0; i < NJ; ++i) k[i] = *reinterpret_cast<const floatx4 *>(p + 16 * i);
         }
-        __syncthreads();
-
-        float s[TKF];
-        float tmax = -INFINITY;
 #pragma unroll
-        for (int j = 0; j < TKF; ++j) {
-            float dot = 0.f;
+        for (int r = 0; r < 4; ++r) {
+            const int j = min(j0 + 4 * g + r, k_end - 1);
+            const bool in_blk = kb != nullptr && (unsigned)j - (unsigned)bstart < (unsigned)a.block_len;
+            const float *p = (in_blk ? vb + (size_t)(j - bstart) * D : vc + (size_t)j * D) + 4 * l16;
 #pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                const float4 kw = Ks[j * CH + sub * 8 + i];
-                dot = fmaf(q[4 * i], kw.x, dot);
-                dot = fmaf(q[4 * i + 1], kw.y, dot);
-                dot = fmaf(q[4 * i + 2], kw.z, dot);
-                dot = fmaf(q[4 * i + 3], kw.w, dot);
-            }
-#pragma unroll
-            for (int w = 1; w < LPQ; w <<= 1) dot += __shfl_xor(dot, w);
-            if (k0 + j >= k_end) dot = -INFINITY;
-            s[j] = dot;
-            tmax = fmaxf(tmax, dot);
+            for (int h = 0; h < NH; ++h) v[r][h] = *reinterpret_cast<const floatx4 *>(p + 64 * h);
         }
-        const float m_new = fmaxf(m_run, tmax);
-        const float corr = fast_exp2((m_run - m_new) * c);
-        m_run = m_new;
-        const float mc = m_new * c;
+    };
+    const int units = (k_end - k_begin + kUnitF - 1) / kUnitF;
+    if (wave < units) load_unit(wave, kf[0], vf[0]);
 #pragma unroll
-        for (int i = 0; i < 32; ++i) o[i] *= corr;
-        float psum = 0.f;
+    for (int q = 0; q < RB; ++q) {
+        const int v = min((rt * RB + q) * 16 + l16, rows_total - 1);
+        const float *p = static_cast<const float *>(a.Q) + (row_base + v) * D + 4 * g;
 #pragma unroll
-        for (int j = 0; j < TKF; ++j) {
-            const float p = fast_exp2(fmaf(s[j], c, -mc));
-            psum += p;
+        for (int i = 0; i < NJ; ++i) qf[q][i] = *reinterpret_cast<const floatx4 *>(p + 16 * i);
+        c[q] = a.scale_log2;
+        if (a.q_scale) c[q] *= a.q_scale[b * a.H + kvh * a.group + v / a.Nq];
+        if (a.k_scale) c[q] *= a.k_scale[kv_head];
+        m_run[q] = -INFINITY;
+        l_run[q] = 0.f;
 #pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                const float4 vw = Vs[j * CH + sub * 8 + i];
-                o[4 * i] = fmaf(p, vw.x, o[4 * i]);
-                o[4 * i + 1] = fmaf(p, vw.y, o[4 * i + 1]);
-                o[4 * i + 2] = fmaf(p, vw.z, o[4 * i + 2]);
-                o[4 * i + 3] = fmaf(p, vw.w, o[4 * i + 3]);
-            }
-        }
-        l_run = l_run * corr + psum;
+        for (int i = 0; i < NO; ++i) acc[q][i] = floatx4{0.f, 0.f, 0.f, 0.f};
     }
 
-    if (!row_ok) return;
-    if (a.splits == 1) {
-        const float inv = 1.0f / l_run;
-        float4 *op = reinterpret_cast<float4 *>(static_cast<float *>(a.O) + orow * D + sub * 32);
+    auto unit = [&](int u, const floatx4 (&k)[NJ], const floatx4 (&v)[4][NH]) __attribute__((always_inline)) {
+        const int j0 = k_begin + u * kUnitF;
 #pragma unroll
-        for (int i = 0; i < 8; ++i)
-            op[i] = make_float4(o[4 * i] * inv, o[4 * i + 1] * inv, o[4 * i + 2] * inv, o[4 * i + 3] * inv);
-    } else {
-        float4 *op = reinterpret_cast<float4 *>(a.part_o + (orow * a.splits + sp) * D + sub * 32);
+        for (int q = 0; q < RB; ++q) {
+            floatx4 s = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int i = 0; i < 8; ++i) op[i] = make_float4(o[4 * i], o[4 * i + 1], o[4 * i + 2], o[4 * i + 3]);
-        if (sub == 0) {
-            float *ml = a.part_ml + (orow * a.splits + sp) * 2;
-            ml[0] = m_run * c;
-            ml[1] = l_run;
+            for (int i = 0; i < NJ; ++i)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) s = __builtin_amdgcn_mfma_f32_16x16x4f32(k[i][e], qf[q][i][e], s, 0, 0, 0);
+            if (j0 + kUnitF > k_end) {
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                    if (j0 + 4 * g + r >= k_end) s[r] = -INFINITY;
+            }
+            float t = fmaxf(fmaxf(s[0], s[1]), fmaxf(s[2], s[3]));
+            t = fmaxf(t, __shfl_xor(t, 16));
+            t = fmaxf(t, __shfl_xor(t, 32));
+            const float m_new = fmaxf(m_run[q], t);
+            const float corr = fast_exp2((m_run[q] - m_new) * c[q]), mc = m_new * c[q];
+            m_run[q] = m_new;
+            float p[4];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) p[r] = fast_exp2(fmaf(s[r], c[q], -mc));
+            l_run[q] = l_run[q] * corr + ((p[0] + p[1]) + (p[2] + p[3]));
+#pragma unroll
+            for (int i = 0; i < NO; ++i)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) acc[q][i][r] *= corr;
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+#pragma unroll
+                for (int h = 0; h < NH; ++h)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        acc[q][h * 4 + e] = __builtin_amdgcn_mfma_f32_16x16x4f32(v[r][h][e], p[r], acc[q][h * 4 + e], 0, 0, 0);
+        }
+    };
+    for (int u = wave; u < units; u += 2 * kWavesF) {        // wave-uniform
+        if (u + kWavesF < units) load_unit(u + kWavesF, kf[1], vf[1]);
+        unit(u, kf[0], vf[0]);
+        if (u + kWavesF < units) {
+            if (u + 2 * kWavesF < units) load_unit(u + 2 * kWavesF, kf[0], vf[0]);
+            unit(u + kWavesF, kf[1], vf[1]);
+        }
+    }
+
+    // ---- merge the waves' states.  Register r of chunk (h, e) is head dim 64 h + 4 (4 g + r) + e of query row l16: piece
+    // (h, r) is four consecutive dims.
+#pragma unroll
+    for (int q = 0; q < RB; ++q) {
+        float l = l_run[q];
+        l += __shfl_xor(l, 16);
+        l += __shfl_xor(l, 32);
+        if (g == 0) {
+            ml[wave][q][0][l16] = m_run[q] * c[q];           // log2 units (a wave without keys: -inf)
+            ml[wave][q][1][l16] = l;
+        }
+#pragma unroll
+        for (int h = 0; h < NH; ++h)
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+                states[((wave * RB + q) * NO + h * 4 + r) * 64 + lane] =
+                    floatx4{acc[q][h * 4][r], acc[q][h * 4 + 1][r], acc[q][h * 4 + 2][r], acc[q][h * 4 + 3][r]};
+    }
+    __syncthreads();
+    for (int i = tid; i < RB * NO * 64; i += kThreadsF) {
+        const int q = i / (NO * 64), piece = (i / 64) % NO, ln = i & 63;
+        const int row = (rt * RB + q) * 16 + (ln & 15);
+        if (row >= rows_total) continue;
+        float m = -INFINITY, l = 0.f;
+#pragma unroll
+        for (int w = 0; w < kWavesF; ++w) m = fmaxf(m, ml[w][q][0][ln & 15]);
+        floatx4 o = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int w = 0; w < kWavesF; ++w) {
+            const float x = fast_exp2(ml[w][q][0][ln & 15] - m);
+            const floatx4 s = states[((w * RB + q) * NO + piece) * 64 + ln];
+            l += x * ml[w][q][1][ln & 15];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) o[r] += x * s[r];
+        }
+        const size_t orow = row_base + row;
+        const int dim = (piece / 4) * 64 + (ln >> 4) * 16 + (piece & 3) * 4;
+        if (a.splits == 1) {
+            const float inv = 1.0f / l;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) o[r] *= inv;
+            *reinterpret_cast<floatx4 *>(static_cast<float *>(a.O) + orow * D + dim) = o;
+        } else {
+            *reinterpret_cast<floatx4 *>(a.part_o + (orow * a.splits + sp) * D + dim) = o;
+            if (dim == 0) {
+                a.part_ml[(orow * a.splits + sp) * 2] = m;
+                a.part_ml[(orow * a.splits + sp) * 2 + 1] = l;
+            }
         }
     }
 }
@@ -147,13 +204,22 @@ __global__ __launch_bounds__(kAttnThreads) void attn_f32_kernel(const AttnKernel
 hipError_t launch_attention_f32(const AttnArgs &a, hipStream_t stream)
 {
     AttnKernelArgs k;
-    const int rows_per_wg = kAttnThreads / (a.d / 32);
-    fill_kernel_args(a, k, rows_per_wg, TKF);
-    const long blocks = (long)a.B * a.Hkv * k.row_tiles * k.splits;
-    const dim3 grid((unsigned)blocks), block(kAttnThreads);
-    const hipError_t e = a.d == 128 ? launch(attn_f32_kernel<128>, grid, block, stream, k)
-                                    : launch(attn_f32_kernel<64>, grid, block, stream, k);
-    return e != hipSuccess ? e : finish_attention(a, k.splits, stream);
+    // 32 rows per workgroup (d = 64; at d = 128 they do not fit the registers) halve the K/V reads per row; taken once
+    // such workgroups alone fill the chip
+    const long heads = (long)a.B * a.Hkv, rows = (long)(a.H / a.Hkv) * a.Nq;
+    const bool two = a.d == 64 && heads * ((rows + 31) / 32) >= 512;
+    AttnArgs s = a;
+    // A workgroup's eight waves split the keys already: splitting them over workgroups as well (a merge launch) is for
+    // key ranges that leave every wave several units, and only until there is a workgroup per compute unit.
+    const int rows_per_wg = two ? 32 : 16;
+    const long wgs = heads * ((rows + rows_per_wg - 1) / rows_per_wg);
+    const long most = a.N / kSplitKeys < 256 / wgs ? a.N / kSplitKeys : 256 / wgs;
+    if (s.splits > most) s.splits = most > 1 ? (int)most : 1;
+    fill_kernel_args(s, k, rows_per_wg, kUnitF);
+    const dim3 grid((unsigned)(heads * k.row_tiles * k.splits)), block(kThreadsF);
+    const hipError_t e = a.d == 128 ? launch(attn_f32_kernel<128, 1>, grid, block, stream, k)
+                       : two ? launch(attn_f32_kernel<64, 2>, grid, block, stream, k) : launch(attn_f32_kernel<64, 1>, grid, block, stream, k);
+    return e != hipSuccess ? e : finish_attention(s, k.splits, stream);
 }
 
 }  // namespace dd

@@ -1,0 +1,39 @@
+"""fp32 attention against the CPU oracle at the edges of its 16-row blocks and 16-key units, with one and several units per
+wave, key splits, both row tiles of d = 64, GQA groups that end inside a row block, and block rows spliced in."""
+import pytest
+
+import oracle
+import paper_2604_05250_amd as dd
+from paper_2604_05250_amd import workloads as wl
+from _util import assert_attention_close, out_to_f64, to_dev
+
+pytestmark = pytest.mark.gpu
+F32 = wl.F32
+
+
+# (32 x 17 heads x 17 rows: enough workgroups for the 32-row tile)
+@pytest.mark.parametrize("B,H,Hkv,N,d", [(1, 1, 1, 1, 64), (1, 2, 1, 15, 128), (1, 2, 2, 16, 64), (2, 3, 1, 17, 128), (1, 2, 2, 129, 64),
+                                         (1, 4, 2, 255, 128), (1, 5, 1, 257, 64), (32, 17, 17, 17, 64), (16, 32, 32, 33, 64)])
+def test_bidir_f32(B, H, Hkv, N, d):
+    import torch
+    cfg = wl.custom_config(B=B, H=H, Hkv=Hkv, N=N, d=d, qk_dtype=F32, v_dtype=F32, prompt=0, G=N, bl=min(16, N))
+    inp = wl.attention_inputs(cfg, seed=N)
+    O = dd.dd_bidir_attention(to_dev(inp["Q"]), to_dev(inp["K"]), to_dev(inp["V"]))
+    torch.cuda.synchronize()
+    assert_attention_close(out_to_f64(O, F32), oracle.bidir_attention(inp["Q"], inp["K"], inp["V"], F32, F32), F32,
+                           f"fp32 {B}x{H}/{Hkv}x{N}x{d}")
+
+
+@pytest.mark.parametrize("B,H,Hkv,N,d,bl,bs", [(1, 4, 4, 128, 64, 16, 64), (1, 4, 1, 511, 128, 5, 506), (1, 2, 2, 512, 64, 17, 0),
+                                               (1, 2, 1, 1037, 128, 16, 77), (2, 2, 2, 2050, 64, 1, 2049)])
+def test_block_f32(B, H, Hkv, N, d, bl, bs):
+    import torch
+    cfg = wl.custom_config(B=B, H=H, Hkv=Hkv, N=N, d=d, qk_dtype=F32, v_dtype=F32, bl=bl, prompt=0, G=N)
+    cache = wl.cache_inputs(cfg, seed=bs + N)
+    blk = wl.block_inputs(cfg, bs, 0)
+    for fresh in (True, False):
+        Kb, Vb = (blk["Kblk"], blk["Vblk"]) if fresh else (None, None)
+        O = dd.dd_block_attention_cached(to_dev(blk["Qblk"]), to_dev(cache["Kc"]), to_dev(cache["Vc"]), bs, Kblk=to_dev(Kb), Vblk=to_dev(Vb))
+        torch.cuda.synchronize()
+        ref = oracle.block_attention_cached(blk["Qblk"], cache["Kc"], cache["Vc"], bs, F32, F32, Kb, Vb)
+        assert_attention_close(out_to_f64(O, F32), ref, F32, f"fp32 block {B}x{H}/{Hkv} N{N} d{d} bl{bl}@{bs} fresh={fresh}")

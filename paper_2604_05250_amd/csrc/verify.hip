@@ -47,23 +47,38 @@ __device__ __forceinline__ uint4 stream_load16(const uint4 *p)
     return make_uint4(w.x, w.y, w.z, w.w);
 }
 
+// Reductions over the 64 lanes of a wave, every lane with the result (the same bits: a + b == b + a): neighbours, pairs of
+// two, halves of eight and of sixteen lanes by DPP, the rest by the two lane-half exchanges.  Shuffles through the LDS
+// crossbar cost their latency six times per reduction, and a short call is a chain of such reductions.
+template <int CTRL> __device__ __forceinline__ unsigned dpp(unsigned v)
+{
+    return (unsigned)__builtin_amdgcn_update_dpp((int)v, (int)v, CTRL, 0xF, 0xF, false);
+}
+template <typename F> __device__ __forceinline__ unsigned wave_reduce(unsigned v, F &&f)
+{
+    typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+    v = f(v, dpp<0xB1>(v));                                  // quad_perm [1,0,3,2]
+    v = f(v, dpp<0x4E>(v));                                  // quad_perm [2,3,0,1]
+    v = f(v, dpp<0x141>(v));                                 // row_half_mirror
+    v = f(v, dpp<0x140>(v));                                 // row_mirror
+    const u32x2 h = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+    v = f(h.x, h.y);
+    const u32x2 w = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+    return f(w.x, w.y);
+}
 __device__ __forceinline__ float wave_max(float v)
 {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o));
-    return v;
+    return __uint_as_float(wave_reduce(__float_as_uint(v), [](unsigned x, unsigned y) {
+        return __float_as_uint(fmaxf(__uint_as_float(x), __uint_as_float(y))); }));
 }
 __device__ __forceinline__ int wave_min(int v)
 {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v = min(v, __shfl_xor(v, o));
-    return v;
+    return (int)wave_reduce((unsigned)v, [](unsigned x, unsigned y) { return (unsigned)min((int)x, (int)y); });
 }
 __device__ __forceinline__ float wave_sum(float v)
 {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
-    return v;
+    return __uint_as_float(wave_reduce(__float_as_uint(v), [](unsigned x, unsigned y) {
+        return __float_as_uint(__uint_as_float(x) + __uint_as_float(y)); }));
 }
 
 // e^{ref - m} with the convention that an empty state (ref = -inf) weighs nothing
@@ -243,8 +258,8 @@ __device__ __forceinline__ bool reduce_range(const uint4 *__restrict__ pv, const
     __shared__ WaveState ws[NW];
     WaveState w;
     w.ref_d = st.ref_d;
-    w.s_d = wave_sum(st.s_d);
-    w.a = wave_sum(st.a);
+    w.s_d = KL ? wave_sum(st.s_d) : 0.f;
+    w.a = KL ? wave_sum(st.a) : 0.f;
     w.best_v = st.best_v;
     w.s_v = wave_sum(st.s_v);
     w.idx = st.idx_v;

@@ -324,12 +324,18 @@ __device__ __forceinline__ void finish_row(int row, double md, double sd, double
                                            const uint8_t *__restrict__ mask, int mode, float threshold, uint64_t seed,
                                            int kl_mode, uint8_t *__restrict__ out_mask,
                                            int32_t *__restrict__ out_tokens, float *__restrict__ out_scores,
-                                           int idx_d = 0, const VerifyExtra ex = VerifyExtra{})
+                                           int idx_d = 0, const VerifyExtra ex = VerifyExtra{}, float *keep_score = nullptr,
+                                           int *keep_token = nullptr)
 {
     const double score = kl_mode ? a / sd - (md + log(sd)) + (mv + log(sv)) : 1.0 / sv;
     const float s32 = (float)score;
     out_scores[row] = s32;
     out_tokens[row] = idx;
+    if (keep_score != nullptr) {                 // a per-sequence rule follows in this workgroup (it decides out_mask)
+        *keep_score = s32;
+        *keep_token = idx;
+        return;
+    }
     if (mode == kModeScores) {                   // every per-position quantity, no rule: c = e^{max - lse} = 1 / sum
         ex.conf_v[row] = (float)(1.0 / sv);
         if (ex.conf_d) ex.conf_d[row] = (float)(1.0 / sd);
@@ -357,7 +363,8 @@ __device__ __forceinline__ void merge_splits_and_finish(const VerifyPartial *__r
                                                         int mode, float threshold, uint64_t seed, int kl_mode,
                                                         uint8_t *__restrict__ out_mask,
                                                         int32_t *__restrict__ out_tokens,
-                                                        float *__restrict__ out_scores, const VerifyExtra &ex)
+                                                        float *__restrict__ out_scores, const VerifyExtra &ex,
+                                                        float *keep_score = nullptr, int *keep_token = nullptr)
 {
     const bool have = row_ok && sp < S;                    // no early exit: the shuffles below need every lane
     VerifyPartial p;
@@ -387,7 +394,7 @@ __device__ __forceinline__ void merge_splits_and_finish(const VerifyPartial *__r
     }
     if (sp == 0 && row_ok)
         finish_row((int)row, md, sd, a, mv, sv, idx, mask, mode, threshold, seed, kl_mode, out_mask, out_tokens,
-                   out_scores, idx_d, ex);
+                   out_scores, idx_d, ex, keep_score, keep_token);
 }
 
 __global__ __launch_bounds__(256) void verify_finalize_kernel(const VerifyPartial *__restrict__ part, int S, int P,
@@ -554,9 +561,9 @@ __global__ __launch_bounds__(256) void unmask_select_kernel(const float *__restr
 
 // Split path with a per-sequence rule (Eq. 6, the budgeted rules, the unmasking step): one workgroup per
 // sequence first finishes the rows of its sequence from their partial states, then applies the rule to them
-// - the second and third launch of such a call in one.  The scores and tokens the rule reads were written by
-// this workgroup; the barrier between the two phases makes them visible to all of its lanes.
-constexpr int kSeqThreads = 1024;
+// - the second and third launch of such a call in one.  The split path has fewer than 192 rows, so a sequence's scores,
+// tokens and mask bytes stay in LDS between the two: reading them back from memory was a third of this kernel's time.
+constexpr int kSeqThreads = 1024, kSeqMaxRows = 192;
 __global__ __launch_bounds__(kSeqThreads) void verify_finalize_seq_kernel(const VerifyPartial *__restrict__ part, int S, int G,
                                                                   const uint8_t *__restrict__ mask, int mode,
                                                                   float threshold, uint64_t seed, int kl_mode,
@@ -565,28 +572,72 @@ __global__ __launch_bounds__(kSeqThreads) void verify_finalize_seq_kernel(const 
                                                                   float *__restrict__ out_scores,
                                                                   int32_t *__restrict__ x_tokens)
 {
-    __shared__ __attribute__((aligned(16))) float bad_sh[kTopkChunk];
-    __shared__ double red[kSeqThreads];
+    __shared__ __attribute__((aligned(16))) float score_sh[kSeqMaxRows], bad_sh[kSeqMaxRows];
+    __shared__ int token_sh[kSeqMaxRows];
+    __shared__ uint8_t mask_sh[kSeqMaxRows];
+    __shared__ double red[kSeqThreads / 64];
     const int tid = threadIdx.x;
     const size_t base = (size_t)blockIdx.x * G;
+    const uint8_t mbyte = tid < G ? mask[base + tid] : 0;    // lane g holds row g's mask byte (requested with the states)
     constexpr int kRowsPerPass = kSeqThreads / kFinalizeLanes;
     for (int g0 = 0; g0 < G; g0 += kRowsPerPass) {           // uniform trip count
         const int g = g0 + tid / kFinalizeLanes;
         merge_splits_and_finish(part, S, (long)base + g, g < G, tid % kFinalizeLanes, mask, mode, threshold, seed, kl_mode,
-                                out_mask, out_tokens, out_scores, VerifyExtra{});
+                                out_mask, out_tokens, out_scores, VerifyExtra{}, &score_sh[min(g, G - 1)], &token_sh[min(g, G - 1)]);
     }
-    __threadfence_block();
+    if (tid < G) mask_sh[tid] = mbyte;
     __syncthreads();
-    const int slabs = (G + kSeqThreads / 4 - 1) / (kSeqThreads / 4);
-    if (mode == 3) {
-        klprob_sequence<kSeqThreads>(out_scores, mask, base, G, seed, out_mask, red);
-    } else if (mode == 5 || mode == 6) {
-        for (int slab = 0; slab < slabs; ++slab)
-            topk_slab<kSeqThreads>(out_scores, mask, base, G, slab, kl_mode, floorf(threshold), out_mask, bad_sh);
-    } else {
-        for (int slab = 0; slab < slabs; ++slab)
-            unmask_slab<kSeqThreads>(out_scores, mask, out_tokens, base, G, slab, mode - kModeUnmaskThresh,
-                                     mode == kModeUnmaskTopk ? floorf(threshold) : threshold, out_mask, x_tokens, bad_sh);
+    if (mode == 3) {                                         // Eq. 6: sum of the eligible rows' divergences, then the draws
+        const float s = tid < G ? score_sh[tid] : 0.f;
+        const double k = s > 0.0f ? (double)s : 0.0;
+        double local = mbyte == 0 ? k : 0.0;
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) local += __shfl_xor(local, o);
+        if ((tid & 63) == 0) red[tid >> 6] = local;
+        __syncthreads();
+        double total = 0.0;
+        for (int w = 0; w < kSeqMaxRows / 64; ++w) total += red[w];          // (later waves hold no row)
+        if (tid < G) {
+            const double p = total > 0.0 ? k / total : 0.0;
+            const bool remask = mbyte == 0 && row_uniform(seed, (uint64_t)(base + tid)) < p;
+            out_mask[base + tid] = (uint8_t)(mbyte != 0 || remask);
+        }
+        return;
+    }
+    // the other rules rank the candidates of the sequence (see sequence_rank): rows still masked (unmasking) or decoded
+    const bool unmasking = mode == kModeUnmaskThresh || mode == kModeUnmaskTopk;
+    const bool candidate = tid < G && (mbyte != 0) == unmasking && (!unmasking || mbyte == 1);
+    const float sign = unmasking || kl_mode ? 1.0f : -1.0f;
+    const int n16 = (G + 15) & ~15;
+    if (tid < n16) bad_sh[tid] = candidate ? sign * score_sh[tid] : kNegInf;
+    __syncthreads();
+    // eight lanes per row, each a part of the comparisons (G <= 192: two passes of 128 rows at most)
+    const float budget = mode == kModeUnmaskThresh ? 0.f : floorf(threshold);
+    for (int g0 = 0; g0 < G; g0 += kSeqThreads / 8) {
+        const int g = g0 + tid / 8, sub = tid % 8;
+        const float bad = g < G ? bad_sh[g] : kNegInf;
+        int rank = 0;
+        for (int j = 4 * sub; j < n16; j += 32) {
+            const float4 o = *reinterpret_cast<const float4 *>(&bad_sh[j]);
+            rank += (o.x > bad || (o.x == bad && j < g)) ? 1 : 0;
+            rank += (o.y > bad || (o.y == bad && j + 1 < g)) ? 1 : 0;
+            rank += (o.z > bad || (o.z == bad && j + 2 < g)) ? 1 : 0;
+            rank += (o.w > bad || (o.w == bad && j + 3 < g)) ? 1 : 0;
+        }
+        rank += __shfl_xor(rank, 1);
+        rank += __shfl_xor(rank, 2);
+        rank += __shfl_xor(rank, 4);
+        if (g < G && sub == 0) {
+            const uint8_t m = mask_sh[g];
+            const bool is = unmasking ? m == 1 : m == 0;
+            if (unmasking) {
+                const bool take = is && (mode == kModeUnmaskThresh ? (rank == 0 || score_sh[g] > threshold) : (float)rank < budget);
+                out_mask[base + g] = (uint8_t)(m != 0 && !take);
+                if (take && x_tokens) x_tokens[base + g] = token_sh[g];
+            } else {
+                out_mask[base + g] = (uint8_t)(m != 0 || (is && (float)rank < budget));
+            }
+        }
     }
 }
 

@@ -441,7 +441,7 @@ def run_config(args, config_id):
             if not one_round[128] and c.N >= 448:
                 return f"attn_wide_kernel<{c.d}, {'true' if fp8 else 'false'}, false, {'true' if fold else 'false'}, 2, {stored_v}>"
         if not fp8 and one_round[64]:
-            return f"attn_stream_kernel<{c.d}, false>"
+            return f"attn_stream_kernel<{c.d}, false, false>"
         return (f"attn_mfma_kernel<{c.d}, {'true' if fp8 else 'false'}, false, {'true' if stored_v == 1 else 'false'}, "
                 f"{'true' if stored_v == 2 else 'false'}>")
 

@@ -1,11 +1,11 @@
-// Drafter attention over the cached K/V (Sec. 2.3), streaming form (bf16):
+// Drafter attention over the cached K/V (Sec. 2.3), streaming form (bf16, or fp8 Q/K with 128 head dims):
 //     O = softmax(Q_blk K^T / sqrt(d_k)) V     for the block_len queries of the active block (Eq. 3),
 // key/value row j coming from the block tensors inside the block and from the cache elsewhere.
 //
 // With a few dozen query rows per head this call is bound by reading K and V once, so the kernel is
 // built around the memory pipeline, not the matrix cores:
 //   - K/V tiles of 64 keys go from global memory straight into LDS (global_load_lds_dwordx4, no
-//     staging registers) through a ring of four tile buffers: three tiles (96 KB per compute unit) are
+//     staging registers) through a ring of four tile buffers (fp8: three): three tiles (96 KB per compute unit) are
 //     always in flight while a fourth is consumed.  The barrier that opens a tile only waits until the
 //     two newest tiles are the only loads outstanding (memory operations complete in order).  The
 //     compiler would wait for every outstanding LDS load before any read of such a buffer, so the
@@ -30,11 +30,11 @@ namespace {
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float floatx16 __attribute__((ext_vector_type(16)));
 typedef float floatx2 __attribute__((ext_vector_type(2)));
+typedef int intx8 __attribute__((ext_vector_type(8)));
 typedef short short4v __attribute__((ext_vector_type(4)));
 typedef short short8v __attribute__((ext_vector_type(8)));
 
 constexpr int TKS = 64;                 // keys per tile
-constexpr int kRing = 4;                // tile buffers
 constexpr int QBS = 1;                  // 32-row query blocks per wave
 constexpr int kRowsWaveS = 32 * QBS;
 constexpr float kSlackS = 8.0f;         // the maximum in use is raised when exceeded by 2^8
@@ -63,8 +63,16 @@ __device__ __forceinline__ float swap_sum(float x)
 constexpr int waitcnt_vm(int n) { return (n & 15) | ((n >> 4) << 14) | (7 << 4) | (15 << 8); }
 
 // NT: the K/V tiles are loaded with the non-temporal hint (see the launcher).
-template <int D, bool NT>
-__global__ __launch_bounds__(kAttnThreads) __attribute__((amdgpu_waves_per_eu(1, 1)))
+// FP8: Q and K are e4m3 codes with per-head scales (in the exponent's factor), V bf16.  K tiles stay as stored, 128-byte
+// rows; S = K Q^T is two 64-deep fp8 matrix instructions per unit (the block-scaled one with the neutral scale code 127:
+// of a lane's 32 operand bytes the first 16 are dims 16 hh .. of the 64, the last 16 dims 32 + 16 hh ..).  A tile is 24 KB
+// instead of 32 and what bounds a workgroup is its chain of dependent steps per tile, some 1.3 us however many bytes: three
+// tile buffers and half the registers let two workgroups share a compute unit and work in each other's gaps (with four
+// buffers, alone on it: 24.0 us for the first call below).  us per call against the MFMA kernel, which transposes V through
+// registers: 11 x 32 / 8 heads, 16 rows, 1237 keys 21.2 -> 18.6; 1 x 32, 512 keys 12.8 -> 9.2; 8 x 32, 64 rows, 1024 keys 29.5
+// -> 21.6 (4.9 TB/s); 16 x 32, 64 rows, 4096 keys 164.9 -> 149.7 (5.4 TB/s).
+template <int D, bool NT, bool FP8>
+__global__ __launch_bounds__(kAttnThreads) __attribute__((amdgpu_waves_per_eu(FP8 ? 2 : 1, FP8 ? 2 : 1)))
 void attn_stream_kernel(const AttnKernelArgs a)
 {
     constexpr int CH = D / 8;                        // 16-byte chunks (8 bf16) per row
@@ -74,10 +82,17 @@ void attn_stream_kernel(const AttnKernelArgs a)
     constexpr int DMA_ROWS = 1024 / ROWB;            // rows moved by one wave-wide 16-byte-per-lane load
     constexpr int NDMA = TKS / DMA_ROWS / 4;         // such loads per wave per K or V tile
     static_assert((4 * DMA_ROWS) % 8 == 0, "swizzle phase must not depend on the load index");
+    static_assert(!FP8 || D == 128, "fp8 K rows are 128 bytes");
+    constexpr int KROWB = FP8 ? D : ROWB, KCH = KROWB / 16;   // K as stored: bytes and chunks per row, ...
+    constexpr int KDMA_ROWS = 1024 / KROWB, KDMA = TKS / KDMA_ROWS / 4;      // ... rows per load, loads per wave and tile
+    constexpr int NLOADS = KDMA + NDMA;              // loads per wave and tile
+    constexpr int KF = KROWB / 32;                   // 16-byte K fragments per lane and unit
 
-    constexpr int TILEB = TKS * ROWB;                // bytes of one K or V tile
-    static_assert(QBS * DC * 16 * 64 * 4 <= 2 * TILEB, "a wave's O state must fit a quarter of the ring");
-    __shared__ __attribute__((aligned(1024))) uint4 KV[2 * kRing * TKS * CH];   // K ring [key][chunk ^ (key & 7)], then
+    constexpr int kRing = FP8 ? 3 : 4;               // tile buffers
+    constexpr int TILEB = TKS * ROWB, KTILEB = TKS * KROWB;   // bytes of one V / K tile
+    constexpr int STATE = QBS * DC * 16 * 64;        // floats of a wave's O state
+    static_assert(4 * STATE * 4 <= kRing * (TILEB + KTILEB), "the waves' O states must fit the ring");
+    __shared__ __attribute__((aligned(1024))) uint4 KV[kRing * TKS * (KCH + CH)];   // K ring [key][chunk ^ (key & 7)], then
                                                      // V ring [key][chunk ^ ((key % (CH/4)) << 2)]
     __shared__ float ml_sh[4][2][64];                // per wave: (max, sum) of its query block, for the phase merge
 
@@ -110,56 +125,69 @@ void attn_stream_kernel(const AttnKernelArgs a)
     // lands at chunk position l % CH of row l / CH and therefore fetches the chunk the swizzle maps there.
     const int dma_row = lane / CH, dma_pos = lane % CH;
     const int dma_row0 = wave * DMA_ROWS + dma_row;
-    const unsigned dma_koff = (dma_pos ^ (dma_row0 & 7)) * 16;
+    const int kdma_row0 = wave * KDMA_ROWS + lane / KCH;
+    const unsigned dma_koff = (lane % KCH ^ (kdma_row0 & 7)) * 16;
     const unsigned dma_voff = (dma_pos ^ ((dma_row0 & (CH / 4 - 1)) << 2)) * 16;
     const size_t kv_head = (size_t)b * a.Hkv + kvh;
-    const uint8_t *const kc = static_cast<const uint8_t *>(a.K) + kv_head * a.kv_stride * (size_t)ROWB;
+    const uint8_t *const kc = static_cast<const uint8_t *>(a.K) + kv_head * a.kv_stride * (size_t)KROWB;
     const uint8_t *const vc = static_cast<const uint8_t *>(a.V) + kv_head * a.kv_stride * (size_t)ROWB;
-    const uint8_t *const kb_ = a.block_len ? static_cast<const uint8_t *>(a.Kblk) + kv_head * a.block_len * (size_t)ROWB : nullptr;
+    const uint8_t *const kb_ = a.block_len ? static_cast<const uint8_t *>(a.Kblk) + kv_head * a.block_len * (size_t)KROWB : nullptr;
     const uint8_t *const vb_ = a.block_len ? static_cast<const uint8_t *>(a.Vblk) + kv_head * a.block_len * (size_t)ROWB : nullptr;
     // rows of the last tile at or past the end of the key range repeat its last row (finite stand-ins, masked later)
     auto dma_tile = [&](int tile) __attribute__((always_inline)) {
-        uint4 *kd = KV + (tile % kRing) * (TKS * CH), *vd = KV + (kRing + tile % kRing) * (TKS * CH);
+        uint4 *kd = KV + (tile % kRing) * (TKS * KCH), *vd = KV + kRing * TKS * KCH + (tile % kRing) * (TKS * CH);
 #pragma unroll
         for (int i = 0; i < NDMA; ++i) {
-            const int r0 = (i * 4 + wave) * DMA_ROWS;
+            if (i < KDMA) {
+                const int j = min(kbeg + tile * TKS + i * 4 * KDMA_ROWS + kdma_row0, kend - 1);
+                const bool in_blk = (unsigned)j - (unsigned)bstart < (unsigned)a.block_len;
+                const uint8_t *ks = (in_blk ? kb_ : kc) + (size_t)(in_blk ? j - bstart : j) * KROWB + dma_koff;
+                __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)ks,
+                                                 (__attribute__((address_space(3))) void *)(kd + (i * 4 + wave) * 64), 16, 0, NT ? 2 : 0);
+            }
             const int j = min(kbeg + tile * TKS + i * 4 * DMA_ROWS + dma_row0, kend - 1);
             const bool in_blk = (unsigned)j - (unsigned)bstart < (unsigned)a.block_len;
-            const size_t roff = (size_t)(in_blk ? j - bstart : j) * ROWB;
-            const uint8_t *ks = (in_blk ? kb_ : kc) + roff + dma_koff;
-            const uint8_t *vs = (in_blk ? vb_ : vc) + roff + dma_voff;
-            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)ks,
-                                             (__attribute__((address_space(3))) void *)(kd + r0 * CH), 16, 0, NT ? 2 : 0);
+            const uint8_t *vs = (in_blk ? vb_ : vc) + (size_t)(in_blk ? j - bstart : j) * ROWB + dma_voff;
             __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)vs,
-                                             (__attribute__((address_space(3))) void *)(vd + r0 * CH), 16, 0, NT ? 2 : 0);
+                                             (__attribute__((address_space(3))) void *)(vd + (i * 4 + wave) * 64), 16, 0, NT ? 2 : 0);
         }
     };
 
     // ---- Q fragments (B operand of S^T = K Q^T): lane (query l32, half hh) holds dims 16 ks + 8 hh .. +7
     bool row_ok[QBS];
     float c[QBS];                                    // scores are exponentiated as 2^(s*c)
-    bf16x8 qf[QBS][KS];
+    bf16x8 qf[QBS][FP8 ? 1 : KS];
+    intx8 qx[QBS][FP8 ? D / 64 : 1];
 #pragma unroll
     for (int q = 0; q < QBS; ++q) {
         const int v = v_first + q * 32 + l32;
         row_ok[q] = v < rows_total;
         const int vv = row_ok[q] ? v : rows_total - 1;
+        if constexpr (FP8) {
+            const uint8_t *qrow = static_cast<const uint8_t *>(a.Q) + (row_base + vv) * D + 16 * hh;
 #pragma unroll
-        for (int ks = 0; ks < KS; ++ks)
-            qf[q][ks] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4 *>(
-                            static_cast<const uint16_t *>(a.Q) + (row_base + vv) * D + ks * 16 + hh * 8));
+            for (int j = 0; j < D / 64; ++j) {
+                const uint4 lo = *reinterpret_cast<const uint4 *>(qrow + 64 * j), hi = *reinterpret_cast<const uint4 *>(qrow + 64 * j + 32);
+                qx[q][j] = intx8{(int)lo.x, (int)lo.y, (int)lo.z, (int)lo.w, (int)hi.x, (int)hi.y, (int)hi.z, (int)hi.w};
+            }
+        } else {
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks)
+                qf[q][ks] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4 *>(
+                                static_cast<const uint16_t *>(a.Q) + (row_base + vv) * D + ks * 16 + hh * 8));
+        }
         c[q] = 1.0f;
         if (a.q_scale) c[q] = a.q_scale[b * a.H + kvh * a.group + vv / a.Nq];
     }
     float k_scale = 1.0f;
     if (a.k_scale) k_scale = a.k_scale[b * a.Hkv + kvh];
-    __builtin_amdgcn_sched_barrier(0);               // these loads are requested before the first three tiles ...
+    __builtin_amdgcn_sched_barrier(0);               // these loads are requested before the first tiles ...
     // (a tile past the range repeats its last row)
 #pragma unroll
     for (int t0 = 0; t0 < kRing - 1; ++t0) dma_tile(t0);
     // ... and waited for here while the tiles are still on their way: the compiler, left to place this wait, waits for
     // the tiles as well, and the memory pipeline runs empty before the first tile is even looked at
-    __builtin_amdgcn_s_waitcnt(waitcnt_vm((kRing - 1) * 2 * NDMA));
+    __builtin_amdgcn_s_waitcnt(waitcnt_vm((kRing - 1) * NLOADS));
 #pragma unroll
     for (int q = 0; q < QBS; ++q) c[q] = a.scale_log2 * c[q] * k_scale;
 
@@ -174,9 +202,9 @@ void attn_stream_kernel(const AttnKernelArgs a)
     float l_run[QBS] = {0.f};                        // this lane half's share of the running sums
 
     // operand addresses inside a tile buffer (bytes), without the unit offset
-    int k_off[KS], v_off[DC];
+    int k_off[KF], v_off[DC];
 #pragma unroll
-    for (int ks = 0; ks < KS; ++ks) k_off[ks] = (l32 * CH + ((2 * ks + hh) ^ (l32 & 7))) * 16;
+    for (int ks = 0; ks < KF; ++ks) k_off[ks] = (l32 * KCH + ((2 * ks + hh) ^ (l32 & 7))) * 16;
     {
         const int t = lane & 15, gq = l32 >> 4, row = 4 * hh + (t >> 2);
 #pragma unroll
@@ -190,9 +218,9 @@ void attn_stream_kernel(const AttnKernelArgs a)
     // One 32-key unit: S = K Q^T, online softmax, O += V P.  kaddr / vaddr = LDS byte addresses of the
     // unit's first K / V row, key0 = global index of its first key.
     auto unit = [&](unsigned kaddr, unsigned vaddr, int key0) __attribute__((always_inline)) {
-        // ---- all K fragments of the unit (keys l32, dims 16 ks + 8 hh .. +7) in one go, with their wait
-        uint4 kf[KS];
-        if constexpr (KS == 8) {
+        // ---- all K fragments of the unit (keys l32, 16-byte chunks 2 ks + hh of the stored row) in one go, with their wait
+        uint4 kf[KF];
+        if constexpr (KF == 8) {
             asm volatile("ds_read_b128 %0, %8\n\tds_read_b128 %1, %9\n\tds_read_b128 %2, %10\n\tds_read_b128 %3, %11\n\t"
                          "ds_read_b128 %4, %12\n\tds_read_b128 %5, %13\n\tds_read_b128 %6, %14\n\tds_read_b128 %7, %15\n\t"
                          "s_waitcnt lgkmcnt(0)"
@@ -213,10 +241,20 @@ void attn_stream_kernel(const AttnKernelArgs a)
 #pragma unroll
             for (int r = 0; r < 16; ++r) s[q][r] = 0.f;
 #pragma unroll
-        for (int ks = 0; ks < KS; ++ks)
+        for (int ks = 0; ks < (FP8 ? 0 : KF); ++ks)
 #pragma unroll
             for (int q = 0; q < QBS; ++q)
                 s[q] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, kf[ks]), qf[q][ks], s[q], 0, 0, 0);
+        if constexpr (FP8) {
+#pragma unroll
+            for (int j = 0; j < D / 64; ++j) {
+                const uint4 lo = kf[2 * j], hi = kf[2 * j + 1];
+                const intx8 kx = {(int)lo.x, (int)lo.y, (int)lo.z, (int)lo.w, (int)hi.x, (int)hi.y, (int)hi.z, (int)hi.w};
+#pragma unroll
+                for (int q = 0; q < QBS; ++q)
+                    s[q] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(kx, qx[q][j], s[q], 0, 0, 0, 0x7F7F7F7F, 0, 0x7F7F7F7F);
+            }
+        }
         // score register r of a block is key key0 + 8 (r / 4) + 4 hh + (r % 4) for query row l32
         if (key0 + 32 > kend) {
 #pragma unroll
@@ -296,19 +334,19 @@ void attn_stream_kernel(const AttnKernelArgs a)
         }
     };
 
-    // ---- tiles.  Tile t sits in ring slot t % 4.  Its barrier waits until this wave's loads of the (up to
-    // two) newer tiles are the only ones outstanding - i.e. tile t has landed - and tells that every wave is
-    // done with tile t-1, whose slot then receives tile t+3.  A wave takes the unit of its key phase.
+    // ---- tiles.  Tile t sits in ring slot t % kRing.  Its barrier waits until this wave's loads of the (up to
+    // kRing - 2) newer tiles are the only ones outstanding - i.e. tile t has landed - and tells that every wave is
+    // done with tile t-1, whose slot then receives tile t + kRing - 1.  A wave takes the unit of its key phase.
     for (int t = 0; t < ntiles; ++t) {
-        const int newer = ntiles - 1 - t;                    // tiles after t (all requested up to t + 2)
-        if (newer >= 2 || t == 0) asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(2 * 2 * NDMA) : "memory");
-        else if (newer == 1) asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(2 * NDMA) : "memory");
+        const int newer = ntiles - 1 - t;                    // tiles after t (all requested up to t + kRing - 2)
+        if (newer >= kRing - 2 || t == 0) asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"((kRing - 2) * NLOADS) : "memory");
+        else if (newer >= 1) asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(NLOADS) : "memory");
         else asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");
         if (t + kRing - 1 < ntiles) dma_tile(t + kRing - 1);
         if (wave_active) {
             const unsigned slot = (unsigned)(t % kRing);
             const int key0 = kbeg + t * TKS + 32 * ph;
-            if (key0 < kend) unit(lds0 + slot * TILEB + ph * 32 * ROWB, lds0 + (kRing + slot) * TILEB + ph * 32 * ROWB, key0);
+            if (key0 < kend) unit(lds0 + slot * KTILEB + ph * 32 * KROWB, lds0 + kRing * KTILEB + slot * TILEB + ph * 32 * ROWB, key0);
         }
     }
 
@@ -316,10 +354,10 @@ void attn_stream_kernel(const AttnKernelArgs a)
 #pragma unroll
     for (int q = 0; q < QBS; ++q) l_tot[q] = swap_sum(l_run[q]);
 
-    // ---- merge the two key phases of a row block through LDS: phase 1 parks its state in quarter `wave`
-    // of the ring (register r of chunk i at [i 16 + r][lane]), phase 0 adds it to its own
+    // ---- merge the two key phases of a row block through LDS: phase 1 parks its state in slot `wave`
+    // of the ring's memory (register r of chunk i at [i 16 + r][lane]), phase 0 adds it to its own
     __syncthreads();                                         // all waves are done with the ring; its loads have landed
-    float *region = reinterpret_cast<float *>(KV) + wave * (2 * TILEB / 4);
+    float *region = reinterpret_cast<float *>(KV) + wave * STATE;
     if (ph != 0 && wave_active) {
 #pragma unroll
         for (int i = 0; i < DC; ++i)
@@ -333,7 +371,7 @@ void attn_stream_kernel(const AttnKernelArgs a)
     __syncthreads();
     if (ph == 0 && wave_active) {
         const int w = wave + 2;
-        const float *src = reinterpret_cast<const float *>(KV) + w * (2 * TILEB / 4);
+        const float *src = reinterpret_cast<const float *>(KV) + w * STATE;
         const float mo = ml_sh[w][0][lane], lo = ml_sh[w][1][lane];
         const float mn = fmaxf(mc[0], mo);
         // a phase that saw no key at all has max -inf and weighs nothing
@@ -404,9 +442,12 @@ hipError_t launch_attention_stream(const AttnArgs &a, hipStream_t stream)
     // heads x 1024 keys (134 MB) 30.5 -> 27.0 us per call (4.7 -> 5.3 TB/s), 16 x 32 x 2048 (537 MB) 98.8 -> 88.3 us.  A
     // smaller one may still be there from the call before: 67 MB, in calls on four copies of it in turn, 20.9 us with plain
     // loads against 22.8 with the hint.  The verifier's rows share K/V between workgroups: never for them.
-    const bool nt = a.Nq != a.N && 2.0 * a.B * a.Hkv * a.N * a.d * 2 > kStreamPastCacheBytes;
-    const hipError_t e = a.d == 128 ? (nt ? launch(attn_stream_kernel<128, true>, grid, block, stream, k) : launch(attn_stream_kernel<128, false>, grid, block, stream, k))
-                                    : (nt ? launch(attn_stream_kernel<64, true>, grid, block, stream, k) : launch(attn_stream_kernel<64, false>, grid, block, stream, k));
+    const bool fp8 = a.qk_dtype == 2;
+    const bool nt = a.Nq != a.N && (fp8 ? 3.0 : 4.0) * a.B * a.Hkv * a.N * a.d > kStreamPastCacheBytes;
+    hipError_t e;
+    if (fp8)             e = nt ? launch(attn_stream_kernel<128, true, true>, grid, block, stream, k) : launch(attn_stream_kernel<128, false, true>, grid, block, stream, k);
+    else if (a.d == 128) e = nt ? launch(attn_stream_kernel<128, true, false>, grid, block, stream, k) : launch(attn_stream_kernel<128, false, false>, grid, block, stream, k);
+    else                 e = nt ? launch(attn_stream_kernel<64, true, false>, grid, block, stream, k) : launch(attn_stream_kernel<64, false, false>, grid, block, stream, k);
     return e != hipSuccess ? e : finish_attention(a, k.splits, stream);
 }
 

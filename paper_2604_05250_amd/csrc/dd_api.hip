@@ -77,9 +77,8 @@ int attn_block_rows_per_wg(int block_len, int B, int H, int Hkv)
     return 128;
 }
 
-int attn_block_splits(int block_len, int B, int H, int Hkv, int N, int d)
+int attn_block_splits(int block_len, int B, int H, int Hkv, int N, int d, int qk_dtype)
 {
-    (void)d;
     const int group = H / Hkv;
     const int r = attn_block_rows_per_wg(block_len, B, H, Hkv);
     const long base = (long)B * Hkv * ((group * block_len + r - 1) / r);
@@ -87,6 +86,11 @@ int attn_block_splits(int block_len, int B, int H, int Hkv, int N, int d)
     // there is about one workgroup per compute unit.
     const int target = 256;
     long s = (target + base - 1) / base;
+    // The streaming kernel's bf16 form at d = 128 fills a compute unit's LDS, so there workgroup 257 is a second round of
+    // them all: one split less where the last one would cross that line.  us per call: 88 row tiles, 1237 keys 28.2 -> 20.1 (3
+    // splits -> 2), 96 row tiles, 1000 keys 23.4 -> 16.6, 104, 600 keys 18.3 -> 14.1, 20, 2048 keys 15.5 -> 14.2 (13 -> 12).  The
+    // other forms fit two workgroups on a compute unit.
+    if (qk_dtype == DD_BF16 && d == 128 && (long)group * block_len <= 64 && base <= target) s = target / base;
     const long forced = tune("DD_TUNE_BLOCK_SPLITS", 0);
     if (forced >= 1) s = forced;
     const long max_s = N / 128 > 1 ? N / 128 : 1;   // at least 128 keys per split
@@ -153,7 +157,7 @@ size_t dd_block_attention_cached_workspace_bytes(int block_len, int B, int H, in
     if (check_attention_common(B, H, Hkv, N, d, qk_dtype, v_dtype, (const float *)16, (const float *)16) != DD_OK) return 0;
     if (block_len < 1 || block_len > N) return 0;
     // which kernel serves the call also depends on block_start: enough for either plan
-    const size_t narrow = dd::attn_partial_bytes(B, H, block_len, d, dd::attn_block_splits(block_len, B, H, Hkv, N, d));
+    const size_t narrow = dd::attn_partial_bytes(B, H, block_len, d, dd::attn_block_splits(block_len, B, H, Hkv, N, d, qk_dtype));
     const size_t wide = dd::attn_partial_bytes(B, H, block_len, d, dd::attn_wide_block_splits(block_len, B, H, Hkv, N));
     return narrow > wide ? narrow : wide;
 }
@@ -208,7 +212,7 @@ static int block_attention(const void *Qblk, const void *Kc, const void *Vc, voi
     }
     const bool wide = dd::tune("DD_TUNE_BLOCK_WIDE", 1) != 0 && dd::attn_wide_block_fits(a);
     const int splits = wide ? dd::attn_wide_block_splits(block_len, B, H, Hkv, N)
-                            : dd::attn_block_splits(block_len, B, H, Hkv, N, d);
+                            : dd::attn_block_splits(block_len, B, H, Hkv, N, d, qk_dtype);
     rc = check_workspace(workspace, workspace_bytes, dd::attn_partial_bytes(B, H, block_len, d, splits));
     if (rc != DD_OK) return rc;
     a.splits = splits;

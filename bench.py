@@ -18,6 +18,7 @@ launches; `traffic` is the HBM bytes per call recorded in profiles/ for the kern
 from __future__ import annotations
 
 import argparse
+import dataclasses
 import json
 import math
 import os
@@ -179,7 +180,6 @@ def run_config(args, config_id):
     cfg = wl.CONFIGS[config_id]
     fp8v = bool(getattr(args, "fp8v", False))
     if fp8v:
-        import dataclasses
         cfg = dataclasses.replace(cfg, name=cfg.name + "_fp8v", qk_dtype=wl.FP8_E4M3, v_dtype=wl.FP8_E4M3)
     mx = bool(getattr(args, "mx", False))
     if mx and fp8v:

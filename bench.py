@@ -434,10 +434,11 @@ def run_config(args, config_id):
         heads, rows = c.B * c.Hkv, (c.H // c.Hkv) * c.N
         fp8 = c.qk_dtype == wl.FP8_E4M3
         one_round = {r: heads * -(-rows // r) <= 256 for r in (64, 128)}
-        fold = not fp8 and c.N >= 1024              # bf16 without per-head scales: the folded-scale form
+        # bf16 without per-head scales, enough row tiles: the folded-scale form
+        fold = not fp8 and c.N >= 1024 and heads * -(-rows // 256) >= 192
         if not fp8 or c.d == 128:
             if one_round[128] and (c.N >= 448 or (c.N >= 192 and (fp8 or not one_round[64]))):
-                return f"attn_wide_kernel<{c.d}, {'true' if fp8 else 'false'}, true, {'true' if fold else 'false'}, 1, {stored_v}>"
+                return f"attn_wide_kernel<{c.d}, {'true' if fp8 else 'false'}, true, false, 1, {stored_v}>"
             if not one_round[128] and c.N >= 448:
                 return f"attn_wide_kernel<{c.d}, {'true' if fp8 else 'false'}, false, {'true' if fold else 'false'}, 2, {stored_v}>"
         if not fp8 and one_round[64]:

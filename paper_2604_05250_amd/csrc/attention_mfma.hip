@@ -763,16 +763,20 @@ hipError_t launch_attention_mfma(const AttnArgs &a, hipStream_t stream)
     if (!blk && (!fp8 || a.d == 128) && a.N >= 64) {           // (the wide kernel's K/V tiles are 64 whole rows)
         // One round of 128-row workgroups: the wide kernel on 128-row tiles, which has twice the workgroups of its
         // 256-row tiles, each 0.7 of one's time per key.  More: its 256-row tiles (persistent).  Measured against the
-        // kernel such calls ran on before (us, bf16 / fp8 Q and K): 1 x 32 heads, N 512 14.1 -> 12.7 / 15.5 -> 11.6, N 900
-        // 27.4 -> 24.3 / 24.3 -> 20.5; 1 x 28 (4 kv), N 1100 30.5 -> 23.6 / 27.8 -> 21.2; 1 x 16, N 2048 50.5 -> 38.7 /
-        // 45.4 -> 33.0; past the round 256-row tiles win at once: 1 x 32, N 1100 42.8 -> 31.2 / 38.7 -> 27.2 (128-row
-        // tiles 43.4 / 38.4).  Below about 450 keys the fill and drain of either weigh more than the shorter loop saves:
+        // kernel such calls ran on before (us, bf16 / fp8 Q and K): 1 x 32 heads, N 512 15.1 -> 12.8 / 15.5 -> 11.6, N 900
+        // 26.2 -> 23.1 / 24.3 -> 20.5; 1 x 28 (4 kv), N 1100 48.6 -> 23.3 / 27.8 -> 21.2; 1 x 16, N 2048 49.0 -> 37.2 /
+        // 45.4 -> 33.0; past the round 256-row tiles win at once: 1 x 32, N 1100 42.1 -> 31.1 / 38.7 -> 27.2 (128-row
+        // tiles 43.4 / 38.4).  d = 64: 1 x 32, N 300 9.1 -> 7.4, N 512 10.2 -> 9.3, N 600 21.8 -> 11.4, 8 x 32, N 500 30.2 -> 25.6.  Below about 450 keys the fill and drain of either weigh more than the shorter loop saves:
         // one round of 64-row bf16 workgroups streams (N 300 10.6 against 11.7), a call with more than one round of
         // 128-row workgroups (8 x 32, N 200: 17.6 against 17.7; N 300, where 256-row tiles pad most: 28.2 against 31.8)
         // or under 192 keys (N 150: 9.4 against 10.5) stays on the kernel of this file.
         const int by_size = one_round128 ? (a.N >= 448 || (a.N >= 192 && (fp8 || !one_round64)) ? 2 : 0) : (a.N >= 448 ? 1 : 0);
-        const int pick = tune("DD_TUNE_ATTN_WIDE", by_size);
-        if (pick == 1) return launch_attention_wide(a, stream);
+        const int forced = tune("DD_TUNE_ATTN_WIDE", -1), pick = forced >= 0 ? forced : by_size;
+        // Folding the softmax scale into bf16 Q rounds Q a second time, an error that grows with the scores: 2.3e-3 ->
+        // 2.9e-3 of the result's 2-norm for Q, K ~ N(0, 1), 1.9e-3 -> 5.0e-3 with Q eight times that (1 x 32 heads, N
+        // 1100, against fp64).  Only calls of 192 row tiles or more take it.
+        const bool may_fold = forced == 1 || heads * ((rows + 255) / 256) >= 192;
+        if (pick == 1) return launch_attention_wide(a, stream, may_fold);
         if (pick == 2) return launch_attention_wide_narrow(a, stream);
     }
     if (a.q_mx != nullptr) {

@@ -1152,7 +1152,7 @@ void attn_wide_kernel(const AttnKernelArgs a)
 
 }  // namespace
 
-hipError_t launch_attention_wide(const AttnArgs &a, hipStream_t stream)
+hipError_t launch_attention_wide(const AttnArgs &a, hipStream_t stream, bool may_fold)
 {
     if (a.N < TKW) return hipErrorInvalidValue;            // a K/V tile is 64 whole rows
     AttnKernelArgs k;
@@ -1176,14 +1176,15 @@ hipError_t launch_attention_wide(const AttnArgs &a, hipStream_t stream)
         return launch(attn_wide_kernel<128, true, false>, grid, block, stream, k);
     }
     // bf16 without per-head scales, long key ranges: the form with the softmax scale folded into Q
-    const bool fold = a.q_scale == nullptr && a.k_scale == nullptr && a.N >= kFoldMinKeys;
+    const bool fold = may_fold && a.q_scale == nullptr && a.k_scale == nullptr && a.N >= kFoldMinKeys;
     if (a.d == 128) return fold ? launch(attn_wide_kernel<128, false, false, true>, grid, block, stream, k)
                                 : launch(attn_wide_kernel<128, false, false>, grid, block, stream, k);
     return fold ? launch(attn_wide_kernel<64, false, false, true>, grid, block, stream, k)
                 : launch(attn_wide_kernel<64, false, false>, grid, block, stream, k);
 }
 
-// The verifier's call on 128-row tiles: the drafter's form with a key stream of one part and no splits.
+// The verifier's call on 128-row tiles: the drafter's form with a key stream of one part and no splits.  Q stays as stored:
+// see the dispatch (launch_attention_mfma) for what folding the scale into it costs in accuracy.
 hipError_t launch_attention_wide_narrow(const AttnArgs &a, hipStream_t stream)
 {
     if (a.N < TKW) return hipErrorInvalidValue;            // a K/V tile is 64 whole rows
@@ -1196,11 +1197,8 @@ hipError_t launch_attention_wide_narrow(const AttnArgs &a, hipStream_t stream)
         if (a.v_dtype == 2) return launch(attn_wide_kernel<128, true, true, false, 1, kVE4m3>, grid, block, stream, k);
         return launch(attn_wide_kernel<128, true, true, false, 1>, grid, block, stream, k);
     }
-    const bool fold = a.q_scale == nullptr && a.k_scale == nullptr && a.N >= kFoldMinKeys;
-    if (a.d == 128) return fold ? launch(attn_wide_kernel<128, false, true, true, 1>, grid, block, stream, k)
-                                : launch(attn_wide_kernel<128, false, true, false, 1>, grid, block, stream, k);
-    return fold ? launch(attn_wide_kernel<64, false, true, true, 1>, grid, block, stream, k)
-                : launch(attn_wide_kernel<64, false, true, false, 1>, grid, block, stream, k);
+    return a.d == 128 ? launch(attn_wide_kernel<128, false, true, false, 1>, grid, block, stream, k)
+                      : launch(attn_wide_kernel<64, false, true, false, 1>, grid, block, stream, k);
 }
 
 // The drafter's call on the wide kernel: worth it from 65 query rows per kv head (GQA groups times the block

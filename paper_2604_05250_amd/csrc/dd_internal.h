@@ -29,7 +29,8 @@ inline hipError_t launch(void (*kernel)(Params...), dim3 grid, dim3 block, hipSt
 // Test hooks.  The kernel a call runs on is chosen from its shape alone; so that the tests can reach every
 // kernel with every shape, a process started with DD_TUNE=1 in its environment (looked at once) lets the
 // variables below override single choices, read at every call.  Without DD_TUNE no call reads the environment.
-//   DD_TUNE_ATTN_WIDE=0/1/2    verifier attention off / on the wide-wave kernel's 256-row tiles / on its 128-row tiles
+//   DD_TUNE_ATTN_WIDE=0/1/2    verifier attention off / on the wide-wave kernel's 256-row tiles (folded-scale form where
+//                              it exists) / on its 128-row tiles
 //   DD_TUNE_ATTN_WIDE_GRID=n   at most n persistent workgroups on that kernel
 //   DD_TUNE_BIDIR_STREAM=0/1   small bf16 verifier calls off / on the streaming kernel
 //   DD_TUNE_BLOCK_STREAM=0     drafter calls with few query rows off the streaming kernel
@@ -100,7 +101,8 @@ int attn_block_rows_per_wg(int block_len, int B, int H, int Hkv);
 size_t attn_partial_bytes(int B, int H, int Nq, int d, int splits);
 hipError_t launch_attention_mfma(const AttnArgs &a, hipStream_t stream);   // bf16 / fp8 inputs
 hipError_t launch_attention_f32(const AttnArgs &a, hipStream_t stream);    // fp32 inputs
-hipError_t launch_attention_wide(const AttnArgs &a, hipStream_t stream);   // verifier form, 64 rows per wave
+// verifier form, 64 rows per wave; may_fold: the softmax scale may be folded into bf16 Q (a second rounding of it)
+hipError_t launch_attention_wide(const AttnArgs &a, hipStream_t stream, bool may_fold);
 hipError_t launch_attention_wide_narrow(const AttnArgs &a, hipStream_t stream);   // verifier form on 128-row tiles
 hipError_t launch_attention_stream(const AttnArgs &a, hipStream_t stream);  // bf16 drafter form, few query rows
 // drafter form on the wide kernel (a few hundred query rows per kv head): whether the call qualifies, the

@@ -65,7 +65,7 @@ def test_block_decoded_v(monkeypatch, B, H, Hkv, N, bl, bs, rows):
 
 
 # verifier calls on 128-row tiles (one per workgroup): (B, H, Hkv, N, d) - one key tile, overlapping last tiles, rows of
-# a kv head that end inside a wave / inside a workgroup, and (1025 keys) the folded-scale form
+# a kv head that end inside a wave / inside a workgroup, and 1025 keys (17 tiles: a stand-in)
 NARROW = [(1, 2, 2, 64, 128), (1, 2, 1, 65, 64), (2, 3, 1, 127, 128), (1, 4, 4, 129, 64), (1, 5, 1, 191, 128), (2, 2, 2, 320, 128),
           (1, 2, 1, 1025, 128), (1, 2, 1, 1025, 64)]
 
@@ -84,3 +84,25 @@ def test_bidir_128_row_tiles(monkeypatch, qk, B, H, Hkv, N, d):
     torch.cuda.synchronize()
     ref = oracle.bidir_attention(inp["Q"], inp["K"], inp["V"], qk, wl.BF16, inp["q_scale"], inp["k_scale"])
     assert_attention_close(out_to_f64(O, wl.BF16), ref, qk, f"128-row tiles {B}x{H}/{Hkv}x{N}x{d}")
+
+
+# Verifier calls of 1024 keys or more on few row tiles: Q is multiplied as stored.  What a result then loses is two
+# roundings to bf16, the weights' and its own.  One has a relative error uniform in +-2^-8 / m for a mantissa m in [1, 2),
+# whose rms over log-uniform m is 2^-8 sqrt(1/3) sqrt(3 / (8 ln 2)) = 1.66e-3; two of them 2.35e-3.  (Q rounded once more
+# with the softmax scale in it: 2.86e-3 already for N(0, 1) inputs, and growing with the scores.)
+TWO_ROUNDINGS = 2.0 ** 0.5 * 2.0 ** -8 * (1 / 3) ** 0.5 * (3 / (8 * np.log(2))) ** 0.5
+
+
+@pytest.mark.parametrize("B,H,Hkv,N,d", [(1, 4, 4, 1024, 128), (1, 16, 16, 2048, 64), (1, 28, 4, 1100, 128), (1, 32, 32, 1100, 128)])
+@pytest.mark.parametrize("sharp", [1, 4])
+def test_bidir_q_is_rounded_once(sharp, B, H, Hkv, N, d):
+    import torch
+    rng = np.random.default_rng(N + d + sharp)
+    Q, K, V = (wl.f32_to_bf16_bits(s * rng.standard_normal((B, h, N, d), dtype=np.float32)) for s, h in ((sharp, H), (1, Hkv), (1, Hkv)))
+    O = out_to_f64(dd.dd_bidir_attention(to_dev(Q), to_dev(K), to_dev(V)), wl.BF16)
+    torch.cuda.synchronize()
+    rows = np.stack([np.zeros(512, int), rng.integers(0, H, 512), rng.integers(0, N, 512)], 1)
+    ref = oracle.bidir_attention(Q, K, V, wl.BF16, wl.BF16, rows=rows)
+    got = O[rows[:, 0], rows[:, 1], rows[:, 2]]
+    # (32768 sampled values or more: the 2-norm of their errors scatters by well under 2 %)
+    assert np.linalg.norm(got - ref) <= 1.05 * TWO_ROUNDINGS * np.linalg.norm(ref)

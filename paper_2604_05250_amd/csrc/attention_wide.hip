@@ -179,6 +179,9 @@ __device__ __forceinline__ void static_for(F &&f)
         static_for<N, I + 1>(f);
     }
 }
+// the V rows of a stand-in tile
+[[maybe_unused]] __device__ const uint4 kZeroTile[TKW * 256 / 16] = {};
+
 using T_ = std::true_type;
 using F_ = std::false_type;
 
@@ -351,17 +354,19 @@ void attn_wide_kernel(const AttnKernelArgs a)
     const unsigned dma_voff = VDEC ? wave * 1024 + lane * 16 : dma_row0 * ROWB + ((lane % CH) ^ ((dma_row0 & (CH / 4 - 1)) << 2)) * 16;
     // Tile `tile` of this workgroup's pass: where its 64 rows start in memory (K and V side), and which of them
     // count: rows [vlo, vhi) of the tile.  A tile is always 64 whole rows of its source (the cache, or the block
-    // tensors): the window is pushed back into the source where the nominal rows 64 T .. of the part would hang
-    // over its end, so a last tile repeats rows of its predecessor, and the tile of a part shorter than 64 rows
-    // holds rows of the neighbouring part as well - all of those are masked in the scores, as is every row of a
-    // stand-in tile past the end of the pass.  All of it is scalar arithmetic.
+    // tensors): the window is pushed back into the part where the nominal rows 64 T .. would hang over its end, so a
+    // last tile repeats rows of its predecessor; the tile of a part shorter than 64 rows holds rows of the source
+    // around it as well - all of those are masked in the scores, as is every row of a stand-in tile past the end of
+    // the pass.  All of it is scalar arithmetic.
+    // where a part's windows must end: with the part, or (shorter than a tile) with its source
+    const int end_a = BLOCK && len_a >= TKW ? len_a : nkeys, end_b = BLOCK && len_b >= TKW ? blk_first + len_b : a.block_len;
     struct TileAt { const uint8_t *k, *v; int vlo, vhi, row; };              // row: the first one of the source (MX)
     auto tile_at = [&](const Tile &t, int tile) __attribute__((always_inline)) {
         // (every captured value is copied before any choice is made between them: the compiler otherwise
         // turns "choose one of several loaded values" into a load through a chosen address, which pins the
         // captured variables in scratch memory)
         const int la = len_a, lb = len_b, lc = len_c, na = nt_a, nb = nt_b, nl = nt_local, tf = t_first;
-        const int c_row0 = blk_hi, b_row0 = blk_first, nk = nkeys, bl = a.block_len;
+        const int c_row0 = blk_hi, b_row0 = blk_first, nk = nkeys, ea = end_a, eb = end_b;
         const uint8_t *const ck = t.k, *const cv = t.v, *const bk = t.kb, *const bv = t.vb;
         const bool standin = tile >= nl;
         int T = tf + min(tile, nl - 1);                                      // position in the list
@@ -369,13 +374,14 @@ void attn_wide_kernel(const AttnKernelArgs a)
         T -= in_c ? na + nb : in_b ? na : 0;                                 // position in its part
         const int len = in_c ? lc : in_b ? lb : la;                          // rows of the part
         const int off = in_c ? c_row0 : in_b ? b_row0 : 0;                   // its first row in its source
-        const int src_rows = in_b ? bl : nk;                                 // rows of the source (>= 64: the launcher checks)
+        const int end = in_c ? nk : in_b ? eb : ea;                          // (sources have 64 rows or more: the launcher checks)
         const uint8_t *kp = in_b ? bk : ck, *vp = in_b ? bv : cv;
         const int first = off + T * TKW;                                     // nominal first row of the tile
-        const int win = min(first, src_rows - TKW);                          // first row actually loaded
+        const int win = min(first, end - TKW);                               // first row actually loaded
         TileAt r;
         r.k = kp + (size_t)win * KROWB;
-        r.v = vp + (size_t)win * VSROWB;
+        // (a stand-in's V rows are zeros: zero times an infinity or a NaN would be a NaN)
+        r.v = standin ? reinterpret_cast<const uint8_t *>(kZeroTile) : vp + (size_t)win * VSROWB;
         r.row = win;
         r.vlo = standin ? TKW : first - win;
         r.vhi = standin ? TKW : off + min(T * TKW + TKW, len) - win;
@@ -408,13 +414,15 @@ void attn_wide_kernel(const AttnKernelArgs a)
     // Wait until at most `pending` of this wave's memory operations are outstanding, then meet the other
     // waves.  (The barrier by itself is no fence for the compiler: the empty statements keep it from
     // moving LDS accesses across.)
-    auto wait_loads_and_sync = [&](auto pending) __attribute__((always_inline)) {
+    auto wait_loads_and_sync = [&](auto pending, auto &&before_sync) __attribute__((always_inline)) {
         asm volatile("" ::: "memory");
         // (with decoded V tiles also until this wave's LDS writes are done)
         __builtin_amdgcn_s_waitcnt(VDEC ? waitcnt_vm(decltype(pending)::value) & ~(15 << 8) : waitcnt_vm(decltype(pending)::value));
+        before_sync();
         __builtin_amdgcn_s_barrier();
         asm volatile("" ::: "memory");
     };
+    auto nothing = []() __attribute__((always_inline)) {};
     auto dma_tile = [&](uint4 *dst, const uint8_t *glob, unsigned lane_off, auto n) __attribute__((always_inline)) {
 #pragma unroll
         for (int i = 0; i < decltype(n)::value; ++i) dma_one(dst, glob, lane_off, i);
@@ -487,6 +495,49 @@ void attn_wide_kernel(const AttnKernelArgs a)
         if constexpr (MX) r = decode_e2m1x8(w[k], dec_scale[i]);
         else r = decode_e4m3x8(w[(2 * k) & 3], w[(2 * k + 1) & 3]);
         *reinterpret_cast<uint4 *>(reinterpret_cast<char *>(dst) + i * (256 / VSCH) * ROWB + dec_off[k]) = r;
+    };
+
+    // Rows of a V tile that do not count (see tile_at) have weight zero, but zero times an infinity or a NaN is a NaN.  They are
+    // zeroed in LDS once the tile has landed, by the lanes that put them there, before the barrier that hands the tile to the
+    // other waves, where what they hold is not the call's (the tile of a part shorter than 64 rows: the cache rows under fresh
+    // block rows may never have been written) and in the verifier's last tile, whose rows of the tile before may be infinite.
+    // `dirty` is the next such tile, so a stage pays one comparison: 1 x 32 heads, 512 keys 12.9 -> 13.1 us, 515 keys (the last
+    // tile is one) 15.6 -> 16.0.  (Asking every tile at the stage's end: 13.4, a test in each load, whose lanes then fetch
+    // zeros: 14.1.)
+    auto dirty_after = [&](int tile) __attribute__((always_inline)) {
+        int e = 0x7FFFFFFF;
+        const int next = t_first + tile + 1;
+        if (!BLOCK || a.block_len == 0) {
+            if (nkeys % TKW != 0) e = nt_all - 1;
+        } else {
+            if (len_c > 0 && len_c < TKW && next <= nt_a + nt_b) e = nt_a + nt_b;
+            if (len_b > 0 && len_b < TKW && next <= nt_a) e = nt_a;
+            if (len_a > 0 && len_a < TKW && next <= 0) e = 0;
+        }
+        return __builtin_amdgcn_readfirstlane(e - t_first);
+    };
+    int dirty = dirty_after(-1);
+    auto zero_masked_rows = [&](uint4 *vb, const Tile &t, int tile) __attribute__((always_inline)) {
+        if (__builtin_expect(tile != dirty, 1)) return;      // uniform
+        if (BLOCK) dirty = dirty_after(tile);
+        const TileAt at = tile_at(t, tile);
+        int ln = lane;
+        asm volatile("" : "+v"(ln));
+        const uint4 z = make_uint4(0u, 0u, 0u, 0u);
+        if constexpr (VDEC) {
+            const int row0 = wave * (64 / VSCH) + ln / VSCH;
+#pragma unroll
+            for (int i = 0; i < DEC_R; ++i)
+                if (row0 + i * (256 / VSCH) < at.vlo || row0 + i * (256 / VSCH) >= at.vhi)
+#pragma unroll
+                    for (int k = 0; k < DEC_W; ++k) *reinterpret_cast<uint4 *>(reinterpret_cast<char *>(vb) + i * (256 / VSCH) * ROWB + dec_off[k]) = z;
+        } else {
+            const int row0 = wave * DMA_ROWS + ln / CH;
+#pragma unroll
+            for (int i = 0; i < NDMA_V; ++i)
+                if (row0 + i * 4 * DMA_ROWS < at.vlo || row0 + i * 4 * DMA_ROWS >= at.vhi) vb[(4 * i + wave) * 64 + ln] = z;
+        }
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     };
 
     // ---- per-lane state of the two query blocks
@@ -726,7 +777,8 @@ void attn_wide_kernel(const AttnKernelArgs a)
     // Pipeline step.  In: s_cur = S(u), pk_prev = P(u-1).  Out: pk_cur = P(u), s_nxt = S(u+1).
     // kb / ksub: tile buffer and unit of K(u+1); vb / vsub: those of V(u-1).
     // Every step has the same shape: units at or past the end of the keys are computed on finite
-    // stand-in rows and masked to -inf, so they contribute exact zeros; P(-1) is zero.
+    // stand-in rows and masked to -inf, so they contribute exact zeros (V rows that do not count are zeros,
+    // see zero_masked_rows); P(-1) is zero.
     // `chain`: the next step reads unit 1 of the same tile buffers, so its first K fragments are fetched
     // in this step's last pieces; `primed`: the previous step did that for this one.
     // `dma`: this step also issues the tile loads of its stage (the K tile at kg into dk, the V tile at vg into dv).
@@ -932,8 +984,9 @@ void attn_wide_kernel(const AttnKernelArgs a)
 #pragma unroll
                 for (int q = 0; q < QB; ++q) {
                     const uint4 pw = make_uint4(pk_prev[q][st][0], pk_prev[q][st][1], pk_prev[q][st][2], pk_prev[q][st][3]);
-                    acc[q][i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vfr[jv % RD], __builtin_bit_cast(bf16x8, pw),
-                                                                        acc[q][i], 0, 0, 0);
+                    // (step 0 has no P(u-1): zeros on both sides, as zero times a value that is infinite is a NaN)
+                    const bf16x8 vw = FIRST && !CANFIN ? __builtin_bit_cast(bf16x8, pw) : vfr[jv % RD];
+                    acc[q][i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vw, __builtin_bit_cast(bf16x8, pw), acc[q][i], 0, 0, 0);
                     if (q == QB - 1) {
                         if (jv + RD < 2 * DC) vfr[jv % RD] = v_frag(vb, vsub, jv + RD);
                         else if (CHAIN) {
@@ -1039,11 +1092,15 @@ void attn_wide_kernel(const AttnKernelArgs a)
         // order, so the requests issued after those loads - the next tile's Q rows, the finished tile's
         // output rows - can stay in flight: wait until only that many are outstanding.
         constexpr int NST = kRowsWave / (64 / (ROWB / 16));  // output stores per wave
-        if (!BLOCK && KIND == 1 && has_next) wait_loads_and_sync(I_<NQDMA>{});
+        // (the tile that the next stage multiplies; the last stage's is tile 0 of the next row tile, all of it rows that count)
+        auto masked = [&]() __attribute__((always_inline)) {
+            if constexpr (!last && (BLOCK || decltype(maskable)::value)) zero_masked_rows(vbuf(I_<1 - PAR>{}), cur, sp + 1);
+        };
+        if (!BLOCK && KIND == 1 && has_next) wait_loads_and_sync(I_<NQDMA>{}, masked);
         else if (last && cur.v0 + kRowsWG <= rows_total) {
-            wait_loads_and_sync(I_<NST>{});
+            wait_loads_and_sync(I_<NST>{}, nothing);
         }
-        else wait_loads_and_sync(I_<0>{});
+        else wait_loads_and_sync(I_<0>{}, masked);
     };
 
     if (BLOCK && nt_local <= 0) {
@@ -1078,7 +1135,7 @@ void attn_wide_kernel(const AttnKernelArgs a)
     __builtin_amdgcn_s_waitcnt(waitcnt_vm(2 * NDMA_K + (VDEC ? 2 : 1) * NDMA_V));
     asm volatile("" ::: "memory");
     install_q(cur);
-    wait_loads_and_sync(I_<0>{});
+    wait_loads_and_sync(I_<0>{}, [&]() __attribute__((always_inline)) { if constexpr (BLOCK && !VDEC) zero_masked_rows(V0, cur, 0); });
 #pragma unroll
     for (int q = 0; q < QB; ++q) c[q] = c_next[q];
     if constexpr (VDEC) {                            // the first V tile (the others: a stage ahead of their use)
@@ -1088,7 +1145,7 @@ void attn_wide_kernel(const AttnKernelArgs a)
         for (int i = 0; i < DEC_R; ++i)
 #pragma unroll
             for (int k = 0; k < DEC_W; ++k) dec_store(V0, i, k);
-        wait_loads_and_sync(I_<0>{});
+        wait_loads_and_sync(I_<0>{}, [&]() __attribute__((always_inline)) { if constexpr (BLOCK) zero_masked_rows(V0, cur, 0); });
     }
     unsigned ksw0 = 0u;                              // MX: K scales of the first unit
     if constexpr (MX) {
@@ -1132,10 +1189,14 @@ void attn_wide_kernel(const AttnKernelArgs a)
         if (!BLOCK && has_next) nxt = tile_of(t_cur + t_stride);
         int sp = 0;
         // stages sp <= nt_even - 4 only touch units of tiles <= nt_even - 3 <= nt_local - 2: never the last
-        // tile of the key range, the only one of the verifier's pass that can overlap its predecessor
-        for (; sp + 4 < nt_even; sp += 2) {
-            stage(sp, I_<0>{}, I_<0>{}, F_{});
-            stage(sp + 1, I_<1>{}, I_<0>{}, F_{});
+        // tile of the key range, the only one of the verifier's pass that can overlap its predecessor.  (BLOCK: every
+        // stage looks for rows to mask, so this loop would be the next one again, instructions that a short call fetches
+        // for a few uses each.)
+        if constexpr (!BLOCK) {
+            for (; sp + 4 < nt_even; sp += 2) {
+                stage(sp, I_<0>{}, I_<0>{}, F_{});
+                stage(sp + 1, I_<1>{}, I_<0>{}, F_{});
+            }
         }
         for (; sp + 2 < nt_even; sp += 2) {
             stage(sp, I_<0>{}, I_<0>{}, T_{});

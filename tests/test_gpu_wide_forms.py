@@ -106,3 +106,70 @@ def test_bidir_q_is_rounded_once(sharp, B, H, Hkv, N, d):
     got = O[rows[:, 0], rows[:, 1], rows[:, 2]]
     # (32768 sampled values or more: the 2-norm of their errors scatters by well under 2 %)
     assert np.linalg.norm(got - ref) <= 1.05 * TWO_ROUNDINGS * np.linalg.norm(ref)
+
+
+def _poison(t, rows):
+    """NaN in the given cache rows: the e4m3 code, or the bf16 bit pattern"""
+    t = t.clone()
+    t[:, :, rows] = 0x7F if t.element_size() == 1 else 0x7FC0
+    return t
+
+
+# (B, H, Hkv, N, block_len, block_start, rows per workgroup): the block at either end, inside the first tile, across tiles
+@pytest.mark.parametrize("B,H,Hkv,N,bl,bs,rows", [(1, 8, 2, 515, 64, 5, "128"), (1, 8, 2, 515, 64, 451, "256"), (1, 4, 2, 333, 70, 0, "128"),
+                                                  (2, 4, 1, 700, 80, 200, "256"), (1, 2, 2, 1237, 100, 1130, "128")])
+@pytest.mark.parametrize("store", ["bf16", "fp8", "fp8v"])
+def test_rows_under_the_block_are_not_looked_at(monkeypatch, store, B, H, Hkv, N, bl, bs, rows):
+    # cache rows that fresh block rows stand in for - and, for a window, rows outside it - may hold anything, NaN included:
+    # the tiles of 64 rows that are loaded reach into them, the result may not
+    import torch
+    monkeypatch.setenv("DD_TUNE_BLOCK_WIDE_ROWS", rows)
+    qk, v = (wl.BF16, wl.BF16) if store == "bf16" else (FP8, FP8 if store == "fp8v" else wl.BF16)
+    cfg = wl.custom_config(B=B, H=H, Hkv=Hkv, N=N, d=128, qk_dtype=qk, v_dtype=v, bl=bl, prompt=0, G=N)
+    cache = wl.cache_inputs(cfg, seed=bs + N)
+    blk = wl.block_inputs(cfg, bs, 0, k_scale=cache["k_scale"], v_scale=cache.get("v_scale"))
+    Q, Kb, Vb, K, V = (to_dev(x) for x in (blk["Qblk"], blk["Kblk"], blk["Vblk"], cache["Kc"], cache["Vc"]))
+    stale = slice(bs, bs + bl)
+    K2, V2 = _poison(K, stale), _poison(V, stale)
+    qs, ks = to_dev(blk["q_scale"]), to_dev(cache["k_scale"])
+    if store == "fp8v":
+        vs = to_dev(cache["v_scale"])
+        calls = [(lambda k, v: dd.dd_block_attention_cached_fp8v(Q, k, v, bs, qs, ks, vs, Kblk=Kb, Vblk=Vb), K2, V2)]
+    else:
+        kw = {"q_scale": qs, "k_scale": ks, "qk_dtype": qk, "v_dtype": v}
+        w0 = max(0, bs - 3)
+        wn = min(N - w0, bl + 70)
+        starts = torch.full((B,), bs, dtype=torch.int32, device="cuda:0")
+        Kw, Vw = (_poison(_poison(t, slice(0, w0)), slice(w0 + wn, N)) for t in (K2, V2))
+        calls = [(lambda k, v: dd.dd_block_attention_cached(Q, k, v, bs, Kblk=Kb, Vblk=Vb, **kw), K2, V2),
+                 (lambda k, v: dd.dd_block_attention_batched(Q, k, v, starts, Kb, Vb, **kw), K2, V2),
+                 (lambda k, v: dd.dd_block_attention_refresh(Q, k.clone(), v.clone(), bs, Kb, Vb, **kw), K2, V2),
+                 (lambda k, v: dd.dd_block_attention_window(Q, k, v, bs, w0, wn, Kblk=Kb, Vblk=Vb, **kw), Kw, Vw)]
+    for i, (call, k, v) in enumerate(calls):
+        clean, poisoned = call(K, V), call(k, v)
+        torch.cuda.synchronize()
+        assert torch.equal(clean.view(torch.int16), poisoned.view(torch.int16)), f"{store} call {i}: {B}x{H}/{Hkv} N{N} bl{bl}@{bs}"
+
+
+# (odd and even tile counts, a last tile that repeats rows, the folded-scale form)
+@pytest.mark.parametrize("B,H,Hkv,N,d", [(1, 2, 2, 65, 128), (1, 2, 1, 128, 64), (1, 3, 1, 191, 128), (1, 2, 2, 515, 128), (1, 2, 1, 1100, 128)])
+@pytest.mark.parametrize("qk", [wl.BF16, FP8])
+@pytest.mark.parametrize("tile", ["1", "2"])
+def test_bidir_infinite_value(monkeypatch, tile, qk, B, H, Hkv, N, d):
+    # one infinite value: infinite in its dimension for every query (all weights are positive here), the same bits elsewhere
+    import torch
+    if qk == FP8 and d == 64:
+        pytest.skip("fp8 with 64 head dims has no wide form")
+    monkeypatch.setenv("DD_TUNE_ATTN_WIDE", tile)
+    cfg = wl.custom_config(B=B, H=H, Hkv=Hkv, N=N, d=d, qk_dtype=qk, v_dtype=wl.BF16, prompt=0, G=N, bl=min(16, N))
+    inp = wl.attention_inputs(cfg, seed=N + d)
+    Q, K, V = (to_dev(inp[k]) for k in "QKV")
+    kw = {"q_scale": to_dev(inp["q_scale"]), "k_scale": to_dev(inp["k_scale"]), "qk_dtype": qk, "v_dtype": wl.BF16}
+    want = dd.dd_bidir_attention(Q, K, V, **kw).clone()
+    want[..., 5] = 0x7F80
+    for row in (0, 3, max(0, N - 70), N - 20, N - 1):
+        V2 = V.clone()
+        V2[:, :, row, 5] = 0x7F80
+        got = dd.dd_bidir_attention(Q, K, V2, **kw)
+        torch.cuda.synchronize()
+        assert torch.equal(got, want), f"tile {tile}, {B}x{H}/{Hkv}x{N}x{d}, row {row}"

@@ -65,7 +65,7 @@ __global__ __launch_bounds__(kThreadsF) void attn_f32_kernel(const AttnKernelArg
 
     floatx4 qf[RB][NJ], acc[RB][NO], kf[2][NJ], vf[2][4][NH];
     float c[RB], m_run[RB], l_run[RB];
-    // rows past the end of the range repeat its last one (their scores are masked)
+    // rows past the end of the range repeat its last one (their scores are masked, their values zeroed before use)
     auto load_unit = [&](int u, floatx4 (&k)[NJ], floatx4 (&v)[4][NH]) __attribute__((always_inline)) {
         const int j0 = k_begin + u * kUnitF;
         {
@@ -101,8 +101,15 @@ __global__ __launch_bounds__(kThreadsF) void attn_f32_kernel(const AttnKernelArg
         for (int i = 0; i < NO; ++i) acc[q][i] = floatx4{0.f, 0.f, 0.f, 0.f};
     }
 
-    auto unit = [&](int u, const floatx4 (&k)[NJ], const floatx4 (&v)[4][NH]) __attribute__((always_inline)) {
+    auto unit = [&](int u, const floatx4 (&k)[NJ], floatx4 (&v)[4][NH]) __attribute__((always_inline)) {
         const int j0 = k_begin + u * kUnitF;
+        if (j0 + kUnitF > k_end) {                           // (zero times an infinite value would be a NaN)
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+                if (j0 + 4 * g + r >= k_end)
+#pragma unroll
+                    for (int h = 0; h < NH; ++h) v[r][h] = floatx4{0.f, 0.f, 0.f, 0.f};
+        }
 #pragma unroll
         for (int q = 0; q < RB; ++q) {
             floatx4 s = {0.f, 0.f, 0.f, 0.f};

@@ -37,3 +37,20 @@ def test_block_f32(B, H, Hkv, N, d, bl, bs):
         torch.cuda.synchronize()
         ref = oracle.block_attention_cached(blk["Qblk"], cache["Kc"], cache["Vc"], bs, F32, F32, Kb, Vb)
         assert_attention_close(out_to_f64(O, F32), ref, F32, f"fp32 block {B}x{H}/{Hkv} N{N} d{d} bl{bl}@{bs} fresh={fresh}")
+
+
+@pytest.mark.parametrize("N,d", [(1, 64), (15, 128), (100, 64), (333, 128), (515, 64)])
+def test_infinite_value_f32(N, d):
+    # one infinite value in any row, the last one of a ragged range included: infinite in its dimension for every query
+    import torch
+    cfg = wl.custom_config(B=1, H=2, Hkv=1, N=N, d=d, qk_dtype=F32, v_dtype=F32, prompt=0, G=N, bl=min(16, N))
+    inp = wl.attention_inputs(cfg, seed=N)
+    Q, K, V = (to_dev(inp[k]) for k in "QKV")
+    want = dd.dd_bidir_attention(Q, K, V).clone()
+    want[..., 5] = float("inf")
+    for row in (0, N // 2, N - 1):
+        V2 = V.clone()
+        V2[:, :, row, 5] = float("inf")
+        got = dd.dd_bidir_attention(Q, K, V2)
+        torch.cuda.synchronize()
+        assert torch.equal(got, want), f"{N} keys, d {d}, row {row}"

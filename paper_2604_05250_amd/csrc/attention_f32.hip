@@ -126,7 +126,9 @@ __global__ __launch_bounds__(kThreadsF) void attn_f32_kernel(const AttnKernelArg
             t = fmaxf(t, __shfl_xor(t, 16));
             t = fmaxf(t, __shfl_xor(t, 32));
             const float m_new = fmaxf(m_run[q], t);
-            const float corr = fast_exp2((m_run[q] - m_new) * c[q]), mc = m_new * c[q];
+            // (a unit whose scores are all -inf before any finite one: weights 0, not 2^(-inf + inf))
+            const float m_ref = m_new == -INFINITY ? 0.f : m_new;
+            const float corr = fast_exp2((m_run[q] - m_ref) * c[q]), mc = m_ref * c[q];
             m_run[q] = m_new;
             float p[4];
 #pragma unroll

@@ -54,3 +54,23 @@ def test_infinite_value_f32(N, d):
         got = dd.dd_bidir_attention(Q, K, V2)
         torch.cuda.synchronize()
         assert torch.equal(got, want), f"{N} keys, d {d}, row {row}"
+
+
+@pytest.mark.parametrize("N,d,first,last", [(100, 64, 0, 16), (128, 64, 16, 32), (133, 128, 66, 133), (333, 128, 0, 70), (515, 64, 257, 515),
+                                            (1100, 128, 0, 600)])
+def test_keys_that_score_minus_infinity_f32(N, d, first, last):
+    # a run of keys out of reach (an infinite component against positive queries), a wave's whole 16-key units among them:
+    # the result is that of the other keys alone
+    import torch
+    cfg = wl.custom_config(B=1, H=2, Hkv=2, N=N, d=d, qk_dtype=F32, v_dtype=F32, prompt=0, G=N, bl=min(16, N))
+    inp = wl.attention_inputs(cfg, seed=N)
+    Q, K, V = (inp[k].copy() for k in "QKV")
+    Q[..., 5] = abs(Q[..., 5]) + 0.1
+    K[:, :, first:last, :] = 0
+    K[:, :, first:last, 5] = -float("inf")
+    O = dd.dd_bidir_attention(to_dev(Q), to_dev(K), to_dev(V))
+    torch.cuda.synchronize()
+    keep = [j for j in range(N) if not first <= j < last]
+    bl = min(N, 16)
+    ref = oracle.block_attention_cached(Q[:, :, :bl].copy(), K[:, :, keep].copy(), V[:, :, keep].copy(), 0, F32, F32)
+    assert_attention_close(out_to_f64(O, F32)[:, :, :bl], ref, F32, f"{N} keys, [{first}, {last}) at -inf")

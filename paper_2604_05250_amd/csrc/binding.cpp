@@ -9,13 +9,15 @@
 //
 // Every function takes positional arguments only (the Python wrappers own names and defaults), absent tensors as None,
 // absent dtype tags as -1, and raises what the wrappers' documentation says: ValueError for a bad shape or placement,
-// TypeError for a bad element type, the registered error class for a status of the library.
+// TypeError for a bad element type, the registered error class for a status of the library, torch's own classes for what
+// torch throws (torch.OutOfMemoryError when an output or the scratch memory cannot be allocated).
 #define PY_SSIZE_T_CLEAN
 #include <Python.h>
 
 #include <ATen/ATen.h>
 #include <c10/hip/HIPStream.h>
 #include <hip/hip_runtime_api.h>
+#include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/python_variable.h>
 
 #include <map>
@@ -525,8 +527,8 @@ PyObject *entry(PyObject *, PyObject *const *a, Py_ssize_t n)
         return F(a, n);
     } catch (const Raised &) {
         return nullptr;
-    } catch (const std::exception &e) {
-        PyErr_SetString(PyExc_RuntimeError, e.what());
+    } catch (...) {                                          // as torch itself raises it: torch.OutOfMemoryError for an allocation
+        torch::translate_exception_to_python(std::current_exception());
         return nullptr;
     }
 }

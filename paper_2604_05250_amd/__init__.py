@@ -127,10 +127,6 @@ def native():
     return mod
 
 
-def _tag(dtype: Optional[int]) -> int:
-    return -1 if dtype is None else dtype
-
-
 def reset_workspace_peak() -> None:
     native().reset_workspace_peak()
 
@@ -165,7 +161,7 @@ def dd_bidir_attention_workspace_bytes(B, H, Hkv, N, d, qk_dtype, v_dtype) -> in
 def dd_bidir_attention(Q, K, V, O=None, q_scale=None, k_scale=None, qk_dtype: Optional[int] = None,
                        v_dtype: Optional[int] = None):
     """Verifier attention over all positions.  Q [B,H,N,d], K,V [B,Hkv,N,d] -> O [B,H,N,d] (V's type)."""
-    return native().bidir(Q, K, V, O, q_scale, k_scale, _tag(qk_dtype), _tag(v_dtype))
+    return native().bidir(Q, K, V, O, q_scale, k_scale, qk_dtype, v_dtype)
 
 
 def dd_block_attention_cached_workspace_bytes(block_len, B, H, Hkv, N, d, qk_dtype, v_dtype) -> int:
@@ -178,7 +174,7 @@ def dd_block_attention_cached(Qblk, Kc, Vc, block_start: int, O=None, Kblk=None,
     """Drafter attention: the active block's queries over cached K/V.
     Qblk [B,H,bl,d], Kc,Vc [B,Hkv,N,d], optional Kblk,Vblk [B,Hkv,bl,d] -> O [B,H,bl,d]."""
     return native().block(1 if _refresh else 0, Qblk, Kc, Vc, block_start, 0, 0, O, Kblk, Vblk, q_scale, k_scale,
-                          _tag(qk_dtype), _tag(v_dtype))
+                          qk_dtype, v_dtype)
 
 
 def dd_bidir_attention_fp8v(Q, K, V, q_scale, k_scale, v_scale, O=None):
@@ -220,19 +216,19 @@ def dd_block_attention_window(Qblk, Kc, Vc, block_start: int, win_start: int, wi
     """Drafter attention over the key rows [win_start, win_start + win_len) of the cache only.
     Shapes as for dd_block_attention_cached (Kc, Vc are the whole cache)."""
     return native().block(2, Qblk, Kc, Vc, block_start, win_start, win_len, O, Kblk, Vblk, q_scale, k_scale,
-                          _tag(qk_dtype), _tag(v_dtype))
+                          qk_dtype, v_dtype)
 
 
 def dd_block_attention_batched(Qblk, Kc, Vc, block_starts, Kblk, Vblk, O=None, q_scale=None, k_scale=None,
                                qk_dtype: Optional[int] = None, v_dtype: Optional[int] = None):
     """Drafter attention with one block position per batch entry: block_starts [B] i32 on the device."""
-    return native().block(3, Qblk, Kc, Vc, block_starts, 0, 0, O, Kblk, Vblk, q_scale, k_scale, _tag(qk_dtype), _tag(v_dtype))
+    return native().block(3, Qblk, Kc, Vc, block_starts, 0, 0, O, Kblk, Vblk, q_scale, k_scale, qk_dtype, v_dtype)
 
 
 def dd_cache_insert_rows(Kc, Vc, Krows, Vrows, positions, qk_dtype: Optional[int] = None, v_dtype: Optional[int] = None):
     """Kc/Vc [B,Hkv,N,d] <- rows of Krows/Vrows [B,Hkv,n,d] at positions [B,n] (i32, on the device; entries outside
     [0, N) skip their row).  In place; returns None."""
-    native().cache_insert(Kc, Vc, Krows, Vrows, positions, _tag(qk_dtype), _tag(v_dtype))
+    native().cache_insert(Kc, Vc, Krows, Vrows, positions, qk_dtype, v_dtype)
 
 
 def dd_verify_remask_workspace_bytes(B, G, V, logit_dtype) -> int:
@@ -244,17 +240,15 @@ def dd_verify_remask(logits_d, logits_v, mask, mode: int, threshold: float, seed
     """Verification rule over the vocabulary.  logits [B*G, V]; mask [B*G] u8 (1 = still masked).
     Returns (out_mask u8, out_tokens i32, out_scores f32)."""
     return native().verify_remask(0, logits_d, logits_v, mask, mode, threshold, seed, B, G, out_mask, out_tokens, out_scores,
-                                  _tag(logit_dtype))
+                                  logit_dtype)
 
 
 def dd_verify_remask_static(logits_d, logits_v, mask, mode: int, threshold: float, seed: int, B: int, G: int,
                             out_mask, out_tokens, out_scores, logit_dtype: Optional[int] = None):
     """dd_verify_remask without a workspace: the library's static device array holds the partial states.  The
     three output tensors are the caller's (nothing is allocated here either).  Returns them."""
-    if out_mask is None or out_tokens is None or out_scores is None:
-        raise TypeError("dd_verify_remask_static: the three output tensors are the caller's")
     return native().verify_remask(1, logits_d, logits_v, mask, mode, threshold, seed, B, G, out_mask, out_tokens, out_scores,
-                                  _tag(logit_dtype))
+                                  logit_dtype)
 
 
 def dd_unmask_workspace_bytes(B, G, V, logit_dtype) -> int:
@@ -265,7 +259,7 @@ def dd_unmask(logits_d, mask, mode: int, threshold: float, B: int, G: int, x_tok
               out_tokens=None, out_conf=None, logit_dtype: Optional[int] = None):
     """One drafter unmasking step.  logits_d [B*G, V]; mask [B*G] u8 (1 = still masked); x_tokens [B*G] i32
     (optional, updated in place where a position is revealed).  Returns (out_mask u8, out_tokens i32, out_conf f32)."""
-    return native().unmask(logits_d, mask, mode, threshold, B, G, x_tokens, out_mask, out_tokens, out_conf, _tag(logit_dtype))
+    return native().unmask(logits_d, mask, mode, threshold, B, G, x_tokens, out_mask, out_tokens, out_conf, logit_dtype)
 
 
 def dd_verify_scores_workspace_bytes(P, V, logit_dtype) -> int:
@@ -275,4 +269,4 @@ def dd_verify_scores_workspace_bytes(P, V, logit_dtype) -> int:
 def dd_verify_scores(logits_d, logits_v, drafter: bool = True, logit_dtype: Optional[int] = None):
     """Divergence, both confidences and both argmax tokens of every row in one pass.  logits_d, logits_v [P, V].
     Returns (kl f32, conf_v f32, tok_v i32, conf_d f32 | None, tok_d i32 | None)."""
-    return native().verify_scores(logits_d, logits_v, drafter, _tag(logit_dtype))
+    return native().verify_scores(logits_d, logits_v, drafter, logit_dtype)

@@ -8,15 +8,15 @@
 // of 512 positions (18 calls), host bound before, went from 268 to 211 us.
 //
 // Every function takes positional arguments only (the Python wrappers own names and defaults), absent tensors as None,
-// absent dtype tags as -1, and raises what the wrappers' documentation says: ValueError for a bad shape or placement,
+// absent dtype tags as None, and raises what the wrappers' documentation says: ValueError for a bad shape or placement,
 // TypeError for a bad element type, the registered error class for a status of the library, torch's own classes for what
 // torch throws (torch.OutOfMemoryError when an output or the scratch memory cannot be allocated).
 #define PY_SSIZE_T_CLEAN
 #include <Python.h>
 
 #include <ATen/ATen.h>
+#include <c10/hip/HIPGraphsC10Utils.h>
 #include <c10/hip/HIPStream.h>
-#include <hip/hip_runtime_api.h>
 #include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/python_variable.h>
 
@@ -53,25 +53,35 @@ const at::Tensor &tensor(PyObject *o, const char *what)
     }
     return *t;
 }
-long integer(PyObject *o)
+// int(o), and the value as a C int (its low bits, as through ctypes)
+int integer(PyObject *o)
 {
-    if (PyLong_CheckExact(o)) {
-        const long v = PyLong_AsLong(o);
-        if (v == -1 && PyErr_Occurred()) throw Raised{};
-        return v;
-    }
     PyObject *n = PyNumber_Long(o);
     if (n == nullptr) throw Raised{};
-    const long v = PyLong_AsLong(n);
+    const unsigned long v = PyLong_AsUnsignedLongMask(n);
     Py_DECREF(n);
-    if (v == -1 && PyErr_Occurred()) throw Raised{};
-    return v;
+    return (int)(unsigned)v;
 }
+// float(o)
 double real(PyObject *o)
 {
-    const double v = PyFloat_AsDouble(o);
-    if (v == -1.0 && PyErr_Occurred()) throw Raised{};
+    PyObject *n = PyNumber_Float(o);
+    if (n == nullptr) throw Raised{};
+    const double v = PyFloat_AS_DOUBLE(n);
+    Py_DECREF(n);
     return v;
+}
+// an integer as it stands: a float is refused, with the error ctypes has for it
+PyObject *exact_integer(PyObject *o, const char *what)
+{
+    PyObject *n = PyNumber_Index(o);
+    if (n != nullptr) return n;
+    PyErr_Clear();
+    PyObject *ctypes = PyImport_ImportModule("ctypes"), *cls = ctypes ? PyObject_GetAttrString(ctypes, "ArgumentError") : nullptr;
+    if (cls != nullptr) PyErr_Format(cls, "%s: an integer is required, not %s", what, Py_TYPE(o)->tp_name);
+    Py_XDECREF(cls);
+    Py_XDECREF(ctypes);
+    throw Raised{};
 }
 
 // device pointer of a tensor in GPU memory (nullptr for an absent one)
@@ -97,8 +107,27 @@ int dtype_tag(const at::Tensor &t, const char *what)
 }
 int tag_or(PyObject *given, const at::Tensor &t, const char *what)
 {
-    const long v = integer(given);
-    return v >= 0 ? (int)v : dtype_tag(t, what);
+    if (given == Py_None) return dtype_tag(t, what);
+    PyObject *n = exact_integer(given, "dtype tag");
+    const unsigned long v = PyLong_AsUnsignedLongMask(n);
+    Py_DECREF(n);
+    return (int)(unsigned)v;                                  // (the library refuses what is no tag)
+}
+// B and G of a verification or unmasking call, whose logits have P rows
+std::pair<int64_t, int64_t> batch_and_rows(PyObject *pb, PyObject *pg, int64_t P, const char *rows_msg)
+{
+    long long v[2];
+    PyObject *const o[2] = {pb, pg};
+    bool fits = true;
+    for (int i = 0; i < 2; ++i) {
+        PyObject *n = exact_integer(o[i], i == 0 ? "B" : "G");
+        int over = 0;
+        v[i] = PyLong_AsLongLongAndOverflow(n, &over);
+        Py_DECREF(n);
+        fits = fits && over == 0;
+    }
+    if (!fits || (__int128)v[0] * v[1] != P) value_error("", rows_msg);
+    return {v[0], v[1]};
 }
 void one_byte(const at::Tensor &t, const char *what, const char *msg)
 {
@@ -160,9 +189,7 @@ at::Tensor workspace(size_t nbytes, const at::Device &device, hipStream_t stream
         }
         return s.fixed;
     }
-    hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(stream, &capturing) != hipSuccess) (void)hipGetLastError();
-    if (capturing != hipStreamCaptureStatusNone) {
+    if (c10::hip::currentStreamCaptureStatusMayInitCtx() != c10::hip::CaptureStatus::None) {
         // memory allocated under capture would come from that graph's private pool and a cached tensor of it
         // could be handed to a later, unrelated call: the scratch memory of captured calls is allocated beforehand
         PyErr_SetString(PyExc_RuntimeError,
@@ -229,7 +256,7 @@ enum { kCached = 0, kRefresh = 1, kWindow = 2, kBatched = 3 };
 PyObject *block(PyObject *const *a, Py_ssize_t n)
 {
     want(n, 14);
-    const int kind = (int)integer(a[0]);
+    const int kind = integer(a[0]);
     const at::Tensor &Q = tensor(a[1], "Qblk"), &Kc = tensor(a[2], "Kc"), &Vc = tensor(a[3], "Vc");
     const at::Tensor *O = opt_tensor(a[7], "O"), *Kb = opt_tensor(a[8], "Kblk"), *Vb = opt_tensor(a[9], "Vblk");
     const at::Tensor *qs = opt_tensor(a[10], "q_scale"), *ks = opt_tensor(a[11], "k_scale");
@@ -245,11 +272,11 @@ PyObject *block(PyObject *const *a, Py_ssize_t n)
         starts = &tensor(a[4], "block_starts");
         if (starts->scalar_type() != at::kInt || starts->numel() != B) value_error("", "block_starts must be int32 with B entries");
     } else {
-        bs = (int)integer(a[4]);
+        bs = integer(a[4]);
     }
     if (kind == kWindow) {
-        ws0 = (int)integer(a[5]);
-        wsn = (int)integer(a[6]);
+        ws0 = integer(a[5]);
+        wsn = integer(a[6]);
     }
     void *const q = dev(Q, "Qblk"), *const k = dev(Kc, "Kc"), *const v = dev(Vc, "Vc"), *const kb = dev(Kb, "Kblk"), *const vb = dev(Vb, "Vblk");
     const at::Tensor out = O ? *O : empty_like_type({B, H, bl, d}, Vc.scalar_type(), Vc);
@@ -328,7 +355,7 @@ PyObject *block_fp8v(PyObject *const *a, Py_ssize_t n)
 {
     want(n, 10);
     const at::Tensor &Q = tensor(a[0], "Qblk"), &Kc = tensor(a[1], "Kc"), &Vc = tensor(a[2], "Vc");
-    const int bs = (int)integer(a[3]);
+    const int bs = integer(a[3]);
     const at::Tensor *qs = opt_tensor(a[4], "q_scale"), *ks = opt_tensor(a[5], "k_scale"), *vs = opt_tensor(a[6], "v_scale");
     const at::Tensor *O = opt_tensor(a[7], "O"), *Kb = opt_tensor(a[8], "Kblk"), *Vb = opt_tensor(a[9], "Vblk");
     if (Q.dim() != 4 || Kc.dim() != 4) value_error("", "Qblk, Kc, Vc must have four dimensions");
@@ -384,17 +411,17 @@ PyObject *verify_remask(PyObject *const *a, Py_ssize_t n)
     const at::Tensor *D = opt_tensor(a[1], "logits_d");
     const at::Tensor &L = tensor(a[2], "logits_v");
     const at::Tensor *mask = opt_tensor(a[3], "mask"), *om = opt_tensor(a[9], "out_mask"), *ot = opt_tensor(a[10], "out_tokens"), *os = opt_tensor(a[11], "out_scores");
-    const int mode = (int)integer(a[4]);
+    const int mode = integer(a[4]);
     const float threshold = (float)real(a[5]);
     PyObject *seed_int = PyNumber_Long(a[6]);
     if (seed_int == nullptr) throw Raised{};
     const uint64_t seed = PyLong_AsUnsignedLongLongMask(seed_int);
     Py_DECREF(seed_int);
     if (PyErr_Occurred()) throw Raised{};
-    const int64_t B = integer(a[7]), G = integer(a[8]);
     if (L.dim() != 2) value_error("", "logits_v must have two dimensions");
     const int64_t P = L.size(0), V = L.size(1);
-    if (P != B * G) value_error("", "logits_v must have B*G rows");
+    const std::pair<int64_t, int64_t> bg = batch_and_rows(a[7], a[8], P, "logits_v must have B*G rows");
+    const int64_t B = bg.first, G = bg.second;
     if (D && !has_shape(*D, {P, V})) value_error("", "logits_d shape must match logits_v");
     const dd_dtype dt = (dd_dtype)tag_or(a[12], L, "logits_v");
     check_vec(mask, P, at::kByte, "mask");
@@ -402,12 +429,12 @@ PyObject *verify_remask(PyObject *const *a, Py_ssize_t n)
     check_vec(ot, P, at::kInt, "out_tokens");
     check_vec(os, P, at::kFloat, "out_scores");
     void *const ld = dev(D, "logits_d"), *const lv = dev(L, "logits_v"), *const mk = dev(mask, "mask");
-    const at::Tensor rm = om || fixed_scratch ? *om : empty_like_type({P}, at::kByte, L);
-    const at::Tensor rt = ot || fixed_scratch ? *ot : empty_like_type({P}, at::kInt, L);
-    const at::Tensor rs = os || fixed_scratch ? *os : empty_like_type({P}, at::kFloat, L);
-    uint8_t *const pm = (uint8_t *)dev(rm, "out_mask");
-    int32_t *const pt = (int32_t *)dev(rt, "out_tokens");
-    float *const ps = (float *)dev(rs, "out_scores");
+    // (with the static scratch an absent output stays absent: the library says what it makes of that)
+    auto output = [&](const at::Tensor *given, at::ScalarType type) { return given ? *given : fixed_scratch ? at::Tensor() : empty_like_type({P}, type, L); };
+    const at::Tensor rm = output(om, at::kByte), rt = output(ot, at::kInt), rs = output(os, at::kFloat);
+    uint8_t *const pm = (uint8_t *)dev(rm.defined() ? &rm : nullptr, "out_mask");
+    int32_t *const pt = (int32_t *)dev(rt.defined() ? &rt : nullptr, "out_tokens");
+    float *const ps = (float *)dev(rs.defined() ? &rs : nullptr, "out_scores");
     if (fixed_scratch) {
         const hipStream_t stream = current_stream();
         check(unlocked([&] { return dd_verify_remask_static(ld, lv, (const uint8_t *)mk, (dd_mode)mode, threshold, seed, pm, pt, ps, B, G, V, dt, stream); }),
@@ -427,12 +454,12 @@ PyObject *unmask(PyObject *const *a, Py_ssize_t n)
     const at::Tensor &L = tensor(a[0], "logits_d");
     const at::Tensor *mask = opt_tensor(a[1], "mask"), *x = opt_tensor(a[6], "x_tokens");
     const at::Tensor *om = opt_tensor(a[7], "out_mask"), *ot = opt_tensor(a[8], "out_tokens"), *oc = opt_tensor(a[9], "out_conf");
-    const int mode = (int)integer(a[2]);
+    const int mode = integer(a[2]);
     const float threshold = (float)real(a[3]);
-    const int64_t B = integer(a[4]), G = integer(a[5]);
     if (L.dim() != 2) value_error("", "logits_d must have two dimensions");
     const int64_t P = L.size(0), V = L.size(1);
-    if (P != B * G) value_error("", "logits_d must have B*G rows");
+    const std::pair<int64_t, int64_t> bg = batch_and_rows(a[4], a[5], P, "logits_d must have B*G rows");
+    const int64_t B = bg.first, G = bg.second;
     const dd_dtype dt = (dd_dtype)tag_or(a[10], L, "logits_d");
     check_vec(mask, P, at::kByte, "mask");
     check_vec(x, P, at::kInt, "x_tokens");
@@ -463,7 +490,7 @@ PyObject *verify_scores(PyObject *const *a, Py_ssize_t n)
     if (L.dim() != 2) value_error("", "logits_v must have two dimensions");
     const int64_t P = L.size(0), V = L.size(1);
     if (!has_shape(D, {P, V})) value_error("", "logits_d and logits_v must have the same shape");
-    const bool given = integer(a[3]) >= 0;
+    const bool given = a[3] != Py_None;
     const dd_dtype dt = (dd_dtype)tag_or(a[3], L, "logits_v");
     if (!given && dtype_tag(D, "logits_d") != dt) value_error("", "logits_d and logits_v must have the same dtype");
     void *const ld = dev(D, "logits_d"), *const lv = dev(L, "logits_v");

@@ -27,3 +27,76 @@ def test_failed_allocations_are_out_of_memory_errors(call):
             torch.cuda.set_per_process_memory_fraction(1.0)
     assert dd.dd_bidir_attention(q, kv, kv).shape == q.shape
     torch.cuda.synchronize()
+
+
+def _verify_args(B=2, G=8, V=1024):
+    import torch
+    logits = torch.randn(B * G, V, device="cuda:0")
+    return logits, logits.clone(), torch.zeros(B * G, dtype=torch.uint8, device="cuda:0")
+
+
+def test_dtype_tags_are_passed_on():
+    # only None means "from the tensor"; a number that is no tag is the library's to refuse, a float is no number
+    import ctypes
+    import torch
+    x = torch.randn(1, 2, 64, 64, device="cuda:0").bfloat16()
+    ld, lv, mask = _verify_args()
+    calls = {"bidir": lambda t: dd.dd_bidir_attention(x, x, x, qk_dtype=t), "bidir v": lambda t: dd.dd_bidir_attention(x, x, x, v_dtype=t),
+             "block": lambda t: dd.dd_block_attention_cached(x, x, x, 0, qk_dtype=t),
+             "insert": lambda t: dd.dd_cache_insert_rows(x, x, x[:, :, :1].contiguous(), x[:, :, :1].contiguous(),
+                                                         torch.zeros(1, dtype=torch.int32, device="cuda:0"), qk_dtype=t),
+             "verify": lambda t: dd.dd_verify_remask(ld, lv, mask, dd.TRUST, 0.0, 0, 2, 8, logit_dtype=t),
+             "unmask": lambda t: dd.dd_unmask(ld, mask, dd.UNMASK_THRESH, 0.5, 2, 8, logit_dtype=t),
+             "scores": lambda t: dd.dd_verify_scores(ld, lv, logit_dtype=t)}
+    for name, call in calls.items():
+        for tag in (-1, -2 ** 31, 7):
+            with pytest.raises(dd.DDError) as e:
+                call(tag)
+            assert e.value.status == -3, (name, tag)
+        with pytest.raises(ctypes.ArgumentError):
+            call(1.0)
+        call(None)
+    torch.cuda.synchronize()
+
+
+def test_batch_sizes_are_integers():
+    import ctypes
+    import numpy as np
+    import torch
+    ld, lv, mask = _verify_args()
+    out = [torch.empty(16, dtype=t, device="cuda:0") for t in (torch.uint8, torch.int32, torch.float32)]
+    calls = [lambda B, G: dd.dd_verify_remask(ld, lv, mask, dd.KL_THRESH, 0.5, 0, B, G),
+             lambda B, G: dd.dd_verify_remask_static(ld, lv, mask, dd.KL_THRESH, 0.5, 0, B, G, *out),
+             lambda B, G: dd.dd_unmask(ld, mask, dd.UNMASK_THRESH, 0.5, B, G)]
+    for call in calls:
+        for B, G in ((2.0, 8), (2, 8.0)):
+            with pytest.raises(ctypes.ArgumentError):
+                call(B, G)
+        with pytest.raises((ctypes.ArgumentError, ValueError)):
+            call("2", 8)
+        for B, G in ((2, 7), (2 ** 64 + 2, 8), (-2, -9), (2 ** 32, 2 ** 32)):
+            with pytest.raises(ValueError):
+                call(B, G)
+        call(np.int64(2), torch.tensor(8))
+    torch.cuda.synchronize()
+
+
+def test_rule_arguments_convert_as_python_does():
+    # mode, seed and block_start as int() takes them, the threshold as float() does
+    import torch
+    ld, lv, mask = _verify_args()
+    want = dd.dd_verify_remask(ld, lv, mask, dd.KL_PROB, 0.5, 7, 2, 8)
+    got = dd.dd_verify_remask(ld, lv, mask, float(dd.KL_PROB), "0.5", 7 - 2 ** 64, 2, 8)
+    assert all(torch.equal(a, b) for a, b in zip(want, got))
+    x = torch.randn(1, 2, 64, 64, device="cuda:0").bfloat16()
+    q = x[:, :, :4].contiguous()
+    assert torch.equal(dd.dd_block_attention_cached(q, x, x, 3), dd.dd_block_attention_cached(q, x, x, torch.tensor(3.0)))
+
+
+def test_static_entry_point_without_outputs():
+    ld, lv, mask = _verify_args()
+    with pytest.raises(dd.DDError) as e:
+        dd.dd_verify_remask_static(ld, lv, mask, dd.TRUST, 0.0, 0, 2, 8, None, None, None)
+    assert e.value.status == -1
+    none = ld[:0], lv[:0], mask[:0]
+    assert dd.dd_verify_remask_static(*none, dd.TRUST, 0.0, 0, 0, 8, None, None, None) == (None, None, None)

@@ -136,6 +136,32 @@ void one_byte(const at::Tensor &t, const char *what, const char *msg)
         throw Raised{};
     }
 }
+// Shapes say how many elements the library reads and writes, dtype tags how large they are: a tensor that holds fewer bytes
+// than that never gets to a launch.
+int64_t tag_bytes(int tag) { return tag == DD_F32 ? 4 : tag == DD_BF16 ? 2 : tag == DD_FP8_E4M3 ? 1 : 0; }
+void elements_of(const at::Tensor *t, int tag, const char *what)
+{
+    if (t == nullptr || tag_bytes(tag) == 0 || (int64_t)t->element_size() == tag_bytes(tag)) return;   // (no tag: the library refuses it)
+    PyErr_Format(PyExc_TypeError, "%s: elements of %lld bytes expected, has %s", what, (long long)tag_bytes(tag), c10::toString(t->scalar_type()));
+    throw Raised{};
+}
+void room_for(const at::Tensor *t, int64_t elements, int64_t bytes_each, const char *what)
+{
+    if (t == nullptr || (__int128)t->numel() * t->element_size() >= (__int128)elements * bytes_each) return;
+    PyErr_Format(PyExc_ValueError, "%s: too small for %lld elements of %lld bytes", what, (long long)elements, (long long)bytes_each);
+    throw Raised{};
+}
+int64_t out_bytes(int v_tag) { return v_tag == DD_F32 ? 4 : 2; }
+// per-head scales
+void scales_of(const at::Tensor *t, int64_t heads, const char *what)
+{
+    if (t == nullptr) return;
+    if (t->scalar_type() != at::kFloat) {
+        PyErr_Format(PyExc_TypeError, "%s: float32 expected, has %s", what, c10::toString(t->scalar_type()));
+        throw Raised{};
+    }
+    room_for(t, heads, 4, what);
+}
 bool has_shape(const at::Tensor &t, std::initializer_list<int64_t> s) { return t.sizes() == at::IntArrayRef(s.begin(), s.size()); }
 
 // a per-position vector: n elements of the given type
@@ -241,6 +267,9 @@ PyObject *bidir(PyObject *const *a, Py_ssize_t n)
     const int64_t B = Q.size(0), H = Q.size(1), N = Q.size(2), d = Q.size(3), Hkv = K.size(1);
     if (!has_shape(K, {B, Hkv, N, d}) || !has_shape(V, {B, Hkv, N, d})) value_error("", "K/V shape must be [B,Hkv,N,d] matching Q");
     const int qk = tag_or(a[6], Q, "Q"), vd = tag_or(a[7], V, "V");
+    elements_of(&Q, qk, "Q"); elements_of(&K, qk, "K"); elements_of(&V, vd, "V");
+    room_for(O, B * H * N * d, out_bytes(vd), "O");
+    scales_of(qs, B * H, "q_scale"); scales_of(ks, B * Hkv, "k_scale");
     void *const q = dev(Q, "Q"), *const k = dev(K, "K"), *const v = dev(V, "V");
     const at::Tensor out = O ? *O : empty_like_type({B, H, N, d}, V.scalar_type(), V);
     void *const o = dev(out, "O");
@@ -266,6 +295,10 @@ PyObject *block(PyObject *const *a, Py_ssize_t n)
     if (kind == kBatched && (!Kb || !Vb)) value_error("", "Kblk and Vblk are required");
     if (Kb && !(has_shape(*Kb, {B, Hkv, bl, d}) && Vb && has_shape(*Vb, {B, Hkv, bl, d}))) value_error("", "Kblk/Vblk shape must be [B,Hkv,block_len,d]");
     const int qk = tag_or(a[12], Q, "Qblk"), vd = tag_or(a[13], Vc, "Vc");
+    elements_of(&Q, qk, "Qblk"); elements_of(&Kc, qk, "Kc"); elements_of(&Vc, vd, "Vc");
+    elements_of(Kb, qk, "Kblk"); elements_of(Vb, vd, "Vblk");
+    room_for(O, B * H * bl * d, out_bytes(vd), "O");
+    scales_of(qs, B * H, "q_scale"); scales_of(ks, B * Hkv, "k_scale");
     const at::Tensor *starts = nullptr;
     int bs = 0, ws0 = 0, wsn = 0;
     if (kind == kBatched) {
@@ -318,6 +351,8 @@ PyObject *bidir_fp8v(PyObject *const *a, Py_ssize_t n)
     if (!has_shape(K, {B, Hkv, N, d}) || !has_shape(V, {B, Hkv, N, d})) value_error("", "K/V shape must be [B,Hkv,N,d] matching Q");
     const char *msg = "one byte per element (e4m3 codes) expected";
     one_byte(Q, "Q", msg); one_byte(K, "K", msg); one_byte(V, "V", msg);
+    room_for(O, B * H * N * d, 2, "O");
+    scales_of(qs, B * H, "q_scale"); scales_of(ks, B * Hkv, "k_scale"); scales_of(vs, B * Hkv, "v_scale");
     void *const q = dev(Q, "Q"), *const k = dev(K, "K"), *const v = dev(V, "V");
     const at::Tensor out = O ? *O : empty_like_type({B, H, N, d}, at::kShort, V);
     void *const o = dev(out, "O");
@@ -342,6 +377,7 @@ PyObject *bidir_mx(PyObject *const *a, Py_ssize_t n)
     const char *msg = "one byte per entry expected";
     one_byte(Q, "Q", msg); one_byte(K, "K", msg); one_byte(V, "V", msg);
     one_byte(Qs, "Qs", msg); one_byte(Ks, "Ks", msg); one_byte(Vs, "Vs", msg);
+    room_for(O, B * H * N * d, 2, "O");
     void *const q = dev(Q, "Q"), *const q_s = dev(Qs, "Qs"), *const k = dev(K, "K"), *const k_s = dev(Ks, "Ks"), *const v = dev(V, "V"), *const v_s = dev(Vs, "Vs");
     const at::Tensor out = O ? *O : empty_like_type({B, H, N, d}, at::kShort, V);
     void *const o = dev(out, "O");
@@ -364,6 +400,9 @@ PyObject *block_fp8v(PyObject *const *a, Py_ssize_t n)
     if (Kb && !(has_shape(*Kb, {B, Hkv, bl, d}) && Vb && has_shape(*Vb, {B, Hkv, bl, d}))) value_error("", "Kblk/Vblk shape must be [B,Hkv,block_len,d]");
     const char *msg = "one byte per element (e4m3 codes) expected";
     one_byte(Q, "Qblk", msg); one_byte(Kc, "Kc", msg); one_byte(Vc, "Vc", msg);
+    if (Kb) { one_byte(*Kb, "Kblk", msg); one_byte(*Vb, "Vblk", msg); }
+    room_for(O, B * H * bl * d, 2, "O");
+    scales_of(qs, B * H, "q_scale"); scales_of(ks, B * Hkv, "k_scale"); scales_of(vs, B * Hkv, "v_scale");
     void *const q = dev(Q, "Qblk"), *const k = dev(Kc, "Kc"), *const v = dev(Vc, "Vc"), *const kb = dev(Kb, "Kblk"), *const vb = dev(Vb, "Vblk");
     const at::Tensor out = O ? *O : empty_like_type({B, H, bl, d}, at::kShort, Vc);
     void *const o = dev(out, "O");
@@ -386,6 +425,7 @@ PyObject *cache_insert(PyObject *const *a, Py_ssize_t n)
         value_error("", "shapes must be Kc,Vc [B,Hkv,N,d] and Krows,Vrows [B,Hkv,n,d]");
     if (pos.scalar_type() != at::kInt || pos.numel() != B * rows) value_error("", "positions must be int32 with B*n entries");
     const int qk = tag_or(a[5], Kc, "Kc"), vd = tag_or(a[6], Vc, "Vc");
+    elements_of(&Kc, qk, "Kc"); elements_of(&Kr, qk, "Krows"); elements_of(&Vc, vd, "Vc"); elements_of(&Vr, vd, "Vrows");
     void *const k = dev(Kc, "Kc"), *const v = dev(Vc, "Vc"), *const kr = dev(Kr, "Krows"), *const vr = dev(Vr, "Vrows"), *const p = dev(pos, "positions");
     const hipStream_t stream = current_stream();
     check(unlocked([&] { return dd_cache_insert_rows(k, v, kr, vr, (const int32_t *)p, rows, B, Hkv, N, d, (dd_dtype)qk, (dd_dtype)vd, stream); }),
@@ -424,6 +464,8 @@ PyObject *verify_remask(PyObject *const *a, Py_ssize_t n)
     const int64_t B = bg.first, G = bg.second;
     if (D && !has_shape(*D, {P, V})) value_error("", "logits_d shape must match logits_v");
     const dd_dtype dt = (dd_dtype)tag_or(a[12], L, "logits_v");
+    elements_of(&L, dt, "logits_v");
+    if (mode == DD_KL_THRESH || mode == DD_KL_PROB || mode == DD_KL_TOPK) elements_of(D, dt, "logits_d");   // (the other rules do not read them)
     check_vec(mask, P, at::kByte, "mask");
     check_vec(om, P, at::kByte, "out_mask");
     check_vec(ot, P, at::kInt, "out_tokens");
@@ -461,6 +503,7 @@ PyObject *unmask(PyObject *const *a, Py_ssize_t n)
     const std::pair<int64_t, int64_t> bg = batch_and_rows(a[4], a[5], P, "logits_d must have B*G rows");
     const int64_t B = bg.first, G = bg.second;
     const dd_dtype dt = (dd_dtype)tag_or(a[10], L, "logits_d");
+    elements_of(&L, dt, "logits_d");
     check_vec(mask, P, at::kByte, "mask");
     check_vec(x, P, at::kInt, "x_tokens");
     check_vec(om, P, at::kByte, "out_mask");
@@ -493,6 +536,7 @@ PyObject *verify_scores(PyObject *const *a, Py_ssize_t n)
     const bool given = a[3] != Py_None;
     const dd_dtype dt = (dd_dtype)tag_or(a[3], L, "logits_v");
     if (!given && dtype_tag(D, "logits_d") != dt) value_error("", "logits_d and logits_v must have the same dtype");
+    elements_of(&L, dt, "logits_v"); elements_of(&D, dt, "logits_d");
     void *const ld = dev(D, "logits_d"), *const lv = dev(L, "logits_v");
     const at::Tensor kl = empty_like_type({P}, at::kFloat, L), cv = empty_like_type({P}, at::kFloat, L), tv = empty_like_type({P}, at::kInt, L);
     const at::Tensor cd = drafter ? empty_like_type({P}, at::kFloat, L) : at::Tensor(), td = drafter ? empty_like_type({P}, at::kInt, L) : at::Tensor();

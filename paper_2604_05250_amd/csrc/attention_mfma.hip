@@ -739,7 +739,8 @@ void fill_kernel_args(const AttnArgs &a, AttnKernelArgs &k, int rows_per_wg, int
     k.keys_per_split = per;
     // drop trailing splits that would be empty after rounding the split length up to whole tiles
     k.splits = (a.N + per - 1) / per;
-    k.block_start = a.block_start; k.block_len = a.block_len;
+    k.block_start = a.block_start;
+    k.block_len = a.Kblk != nullptr ? a.block_len : 0;                     // 0: no row is taken from block tensors
     k.block_starts = a.block_starts;
     k.scale_log2 = 1.44269504088896340736f / sqrtf((float)a.d);
     const size_t rows = (size_t)a.B * a.H * a.Nq;
@@ -755,7 +756,6 @@ hipError_t launch_attention_mfma(const AttnArgs &a, hipStream_t stream)
     fill_kernel_args(a, k, blk && a.Nq != a.N ? attn_block_rows_per_wg(a.Nq, a.B, a.H, a.Hkv) : kRowsPerWG, TK);
     const long blocks = (long)a.B * a.Hkv * k.row_tiles * k.splits;
     const dim3 grid((unsigned)blocks), block(kAttnThreads);
-    if (a.Kblk == nullptr) k.block_len = 0;                                // no row is taken from block tensors
     hipError_t e;
     // Verifier calls: do workgroups of 64 / 128 query rows fit the chip's 256 compute units in one round?
     const long heads = (long)a.B * a.Hkv, rows = (long)(a.H / a.Hkv) * a.Nq;

@@ -436,7 +436,6 @@ hipError_t launch_attention_stream(const AttnArgs &a, hipStream_t stream)
 {
     AttnKernelArgs k;
     fill_kernel_args(a, k, 2 * kRowsWaveS, TKS);
-    if (a.Kblk == nullptr) k.block_len = 0;                 // no row is taken from the block tensors
     const dim3 grid((unsigned)((long)a.B * a.Hkv * k.row_tiles * k.splits)), block(kAttnThreads);
     // A cache too large to survive in the 256 MB last-level cache until it is read again is streamed past it: 8 x 32
     // heads x 1024 keys (134 MB) 30.5 -> 27.0 us per call (4.7 -> 5.3 TB/s), 16 x 32 x 2048 (537 MB) 98.8 -> 88.3 us.  A

@@ -1309,7 +1309,6 @@ hipError_t launch_attention_wide_block(const AttnArgs &a, hipStream_t stream)
     AttnKernelArgs k;
     const bool narrow = attn_wide_block_rows(a.Nq, a.B, a.H, a.Hkv, a.N) == kRowsWGNarrow;
     fill_kernel_args(a, k, narrow ? kRowsWGNarrow : kRowsWGWide, TKW);
-    if (a.Kblk == nullptr) k.block_len = 0;                // no row is taken from the block tensors
     // the kernel splits the LIST of tiles (not the key range) evenly
     int splits;
     if (a.block_starts != nullptr) {

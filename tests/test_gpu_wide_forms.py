@@ -173,3 +173,22 @@ def test_bidir_infinite_value(monkeypatch, tile, qk, B, H, Hkv, N, d):
         got = dd.dd_bidir_attention(Q, K, V2, **kw)
         torch.cuda.synchronize()
         assert torch.equal(got, want), f"tile {tile}, {B}x{H}/{Hkv}x{N}x{d}, row {row}"
+
+
+@pytest.mark.parametrize("call", ["cached", "window"])
+def test_whole_sequence_block_without_fresh_rows(monkeypatch, call):
+    # a block as long as its cache (or window) takes the verifier's path; with no block rows given, every row is the cache's
+    import torch
+    monkeypatch.setenv("DD_TUNE_ATTN_WIDE", "2")
+    N = 64
+    cfg = wl.custom_config(B=1, H=2, Hkv=2, N=N, d=128, qk_dtype=wl.BF16, v_dtype=wl.BF16, prompt=0, G=N, bl=N)
+    inp = wl.attention_inputs(cfg, seed=N)
+    Q, K, V = (to_dev(inp[k]) for k in "QKV")
+    if call == "cached":
+        O = dd.dd_block_attention_cached(Q, K, V, 0)
+    else:
+        pad = torch.zeros_like(K[:, :, :5])
+        O = dd.dd_block_attention_window(Q, torch.cat([pad, K], 2), torch.cat([pad, V], 2), 5, 5, N)
+    torch.cuda.synchronize()
+    ref = oracle.bidir_attention(inp["Q"], inp["K"], inp["V"], wl.BF16, wl.BF16)
+    assert_attention_close(out_to_f64(O, wl.BF16), ref, wl.BF16, call)

@@ -356,6 +356,8 @@ void attn_stream_kernel(const AttnKernelArgs a)
 
     // ---- merge the two key phases of a row block through LDS: phase 1 parks its state in slot `wave`
     // of the ring's memory (register r of chunk i at [i 16 + r][lane]), phase 0 adds it to its own
+    // (with a single tile the stand-ins behind it may still be on their way, and a barrier by itself waits for nobody's loads)
+    __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));
     __syncthreads();                                         // all waves are done with the ring; its loads have landed
     float *region = reinterpret_cast<float *>(KV) + wave * STATE;
     if (ph != 0 && wave_active) {

@@ -5,9 +5,9 @@
 // With a few dozen query rows per head this call is bound by reading K and V once, so the kernel is
 // built around the memory pipeline, not the matrix cores:
 //   - K/V tiles of 64 keys go from global memory straight into LDS (global_load_lds_dwordx4, no
-//     staging registers) through a ring of four tile buffers (fp8: three): three tiles (96 KB per compute unit) are
-//     always in flight while a fourth is consumed.  The barrier that opens a tile only waits until the
-//     two newest tiles are the only loads outstanding (memory operations complete in order).  The
+//     staging registers) through a ring of four tile buffers (fp8: three): three tiles (96 KB per compute unit; fp8: two
+//     of 24 KB, twice per compute unit) are always in flight while another is consumed.  The barrier that opens a tile only
+//     waits until the newest two (fp8: the newest) are the only loads outstanding (memory operations complete in order).  The
 //     compiler would wait for every outstanding LDS load before any read of such a buffer, so the
 //     operand reads of the tiles are written as inline assembly with their own wait;
 //   - one workgroup = 4 waves (one per SIMD) owns up to 64 query rows of one (batch, kv head): wave w holds
@@ -439,12 +439,14 @@ hipError_t launch_attention_stream(const AttnArgs &a, hipStream_t stream)
     AttnKernelArgs k;
     fill_kernel_args(a, k, 2 * kRowsWaveS, TKS);
     const dim3 grid((unsigned)((long)a.B * a.Hkv * k.row_tiles * k.splits)), block(kAttnThreads);
-    // A cache too large to survive in the 256 MB last-level cache until it is read again is streamed past it: 8 x 32
-    // heads x 1024 keys (134 MB) 30.5 -> 27.0 us per call (4.7 -> 5.3 TB/s), 16 x 32 x 2048 (537 MB) 98.8 -> 88.3 us.  A
-    // smaller one may still be there from the call before: 67 MB, in calls on four copies of it in turn, 20.9 us with plain
-    // loads against 22.8 with the hint.  The verifier's rows share K/V between workgroups: never for them.
+    // A model's layers take their turns, each with a cache of its own, so a large one has left the 256 MB last-level cache
+    // when it is read again: above 100 MB it is streamed past it.  us per call with plain loads -> with the hint, four
+    // copies in turn (two of the largest): 67 MB 20.7 -> 22.0, 101 MB 24.9 -> 23.6, 134 MB 29.2 -> 26.6, 252 MB 54.4 -> 50.8,
+    // 537 MB 110 -> 101; fp8 101 MB 21.8 -> 20.4, 201 MB 40.9 -> 38.3.  A caller that reads one and the same copy again and
+    // again gives up what the cache would have kept of it: 134 MB 24.8 -> 25.3, 252 MB 47.4 -> 50.3, fp8 201 MB 34.7 -> 36.4
+    // (537 MB: 117 -> 109).  The verifier's rows share K/V between workgroups: never for them.
     const bool fp8 = a.qk_dtype == 2;
-    const bool nt = a.Nq != a.N && (fp8 ? 3.0 : 4.0) * a.B * a.Hkv * a.N * a.d > kStreamPastCacheBytes;
+    const bool nt = tune("DD_TUNE_STREAM_NT", a.Nq != a.N && (fp8 ? 3.0 : 4.0) * a.B * a.Hkv * a.N * a.d > kStreamPastCacheBytes) != 0;
     hipError_t e;
     if (fp8)             e = nt ? launch(attn_stream_kernel<128, true, true>, grid, block, stream, k) : launch(attn_stream_kernel<128, false, true>, grid, block, stream, k);
     else if (a.d == 128) e = nt ? launch(attn_stream_kernel<128, true, false>, grid, block, stream, k) : launch(attn_stream_kernel<128, false, false>, grid, block, stream, k);

@@ -33,6 +33,7 @@ inline hipError_t launch(void (*kernel)(Params...), dim3 grid, dim3 block, hipSt
 //                              it exists) / on its 128-row tiles
 //   DD_TUNE_ATTN_WIDE_GRID=n   at most n persistent workgroups on that kernel
 //   DD_TUNE_BIDIR_STREAM=0/1   small bf16 verifier calls off / on the streaming kernel
+//   DD_TUNE_STREAM_NT=0/1      that kernel's K/V loads without / with the non-temporal hint
 //   DD_TUNE_BLOCK_STREAM=0     drafter calls with few query rows off the streaming kernel
 //   DD_TUNE_BLOCK_WIDE=0       drafter calls with many query rows off the wide-wave kernel
 //   DD_TUNE_BLOCK_SPLITS=n     key splits of a drafter call on the streaming / MFMA kernels (still at least 128 keys each)

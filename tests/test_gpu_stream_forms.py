@@ -30,3 +30,12 @@ def check_block(B, H, Hkv, N, d, qk, bl, bs, what):
 @pytest.mark.parametrize("qk,d", FORMS)
 def test_one_tile(qk, d, N, bl):
     check_block(16, 32, 32, N, d, qk, bl, N - bl, "one tile")
+
+
+# tiles loaded with and without the non-temporal hint: less than a tile, the ring's depth and more, key splits, GQA
+@pytest.mark.parametrize("B,H,Hkv,N,bl,bs", [(2, 4, 2, 33, 16, 5), (1, 4, 4, 193, 33, 100), (1, 8, 2, 1237, 16, 900)])
+@pytest.mark.parametrize("qk,d", FORMS)
+@pytest.mark.parametrize("hint", ["0", "1"])
+def test_non_temporal_loads(monkeypatch, hint, qk, d, B, H, Hkv, N, bl, bs):
+    monkeypatch.setenv("DD_TUNE_STREAM_NT", hint)
+    check_block(B, H, Hkv, N, d, qk, bl, bs, f"hint {hint}")

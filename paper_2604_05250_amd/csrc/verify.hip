@@ -561,9 +561,11 @@ __global__ __launch_bounds__(256) void unmask_select_kernel(const float *__restr
 
 // Split path with a per-sequence rule (Eq. 6, the budgeted rules, the unmasking step): one workgroup per
 // sequence first finishes the rows of its sequence from their partial states, then applies the rule to them
-// - the second and third launch of such a call in one.  The split path has fewer than 192 rows, so a sequence's scores,
+// - the second and third launch of such a call in one.  The split path has fewer than kFusedMinRows rows, so a sequence's scores,
 // tokens and mask bytes stay in LDS between the two: reading them back from memory was a third of this kernel's time.
-constexpr int kSeqThreads = 1024, kSeqMaxRows = 192;
+constexpr int kFusedMinRows = 192;            // calls of fewer rows split them over several workgroups each
+constexpr int kSeqThreads = 1024, kSeqMaxRows = kFusedMinRows;
+static_assert(kSeqMaxRows % 64 == 0 && kSeqMaxRows <= 2 * (kSeqThreads / 8), "whole waves of rows, ranked in two passes at most");
 __global__ __launch_bounds__(kSeqThreads) void verify_finalize_seq_kernel(const VerifyPartial *__restrict__ part, int S, int G,
                                                                   const uint8_t *__restrict__ mask, int mode,
                                                                   float threshold, uint64_t seed, int kl_mode,
@@ -611,7 +613,7 @@ __global__ __launch_bounds__(kSeqThreads) void verify_finalize_seq_kernel(const 
     const int n16 = (G + 15) & ~15;
     if (tid < n16) bad_sh[tid] = candidate ? sign * score_sh[tid] : kNegInf;
     __syncthreads();
-    // eight lanes per row, each a part of the comparisons (G <= 192: two passes of 128 rows at most)
+    // eight lanes per row, each a part of the comparisons: passes of 128 rows
     const float budget = mode == kModeUnmaskThresh ? 0.f : floorf(threshold);
     for (int g0 = 0; g0 < G; g0 += kSeqThreads / 8) {
         const int g = g0 + tid / 8, sub = tid % 8;
@@ -647,7 +649,7 @@ __global__ __launch_bounds__(kSeqThreads) void verify_finalize_seq_kernel(const 
 // chip; the workgroup grows as the row count shrinks so that the bytes in flight stay about constant.
 int verify_fused_threads(int P)
 {
-    if (P < 192) return 0;               // too few rows: split them over several workgroups instead
+    if (P < kFusedMinRows) return 0;               // too few rows: split them over several workgroups instead
     return P >= 2048 ? 256 : 512;        // measured: 512 lanes per row stream best for 256..1024 rows
 }
 

@@ -431,3 +431,53 @@ def test_all_scores_identical_models_and_empty():
     empty = torch.empty(0, 2048, dtype=torch.bfloat16, device="cuda:0")
     out = dd.dd_verify_scores(empty, empty)
     assert all(o.numel() == 0 for o in out)
+
+
+# ------------------------------------------------------------------ few rows: one workgroup ranks a sequence in LDS
+def _tied(cfg, seed):
+    """identical rows give bit-identical scores: 8 distinct rows in turn, so a budget ends inside a group of equal scores"""
+    inp = wl.verify_inputs(cfg, seed=seed)
+    for name in ("logits_d", "logits_v"):
+        a = inp[name].reshape(cfg.B, cfg.G, -1)
+        a[:, 8:, :] = a[:, np.arange(8, cfg.G) % 8, :]
+    return inp
+
+
+# (rows in one pass of 128, at its edge and past it; 191 is the largest call on this path)
+@pytest.mark.parametrize("G", [96, 127, 128, 129, 191])
+@pytest.mark.parametrize("tied", [False, True])
+def test_sequence_rules_of_few_rows(G, tied):
+    cfg = wl.custom_config(B=1, G=G, V=1024, logit_dtype=wl.BF16, sigma_d=3.0, sigma_n=1.0, decoded_frac=0.8)
+    inp = _tied(cfg, G) if tied else wl.verify_inputs(cfg, seed=G)
+    mask = np.zeros(G, np.uint8)
+    mask[5::11] = 1
+    inp["mask"] = mask
+    eligible = int((mask == 0).sum())
+    for k in (0, 1, 13, G // 2, 120, eligible - 1, eligible, 10 * G):
+        for mode in (wl.KL_TOPK, wl.CONF_TOPK):
+            om, osc = check_budgeted(inp, mode, k, 1, G, wl.BF16, f"budget {k} mode {mode} G{G}")
+            assert np.array_equal(om, oracle.remask_decide(osc, mask, mode, float(k), 0, 1, G)[0])   # on its own scores: exact
+    for seed in (1, 2, 3):
+        check_against_oracle(inp, wl.KL_PROB, 0.0, seed, 1, G, wl.BF16, f"Eq. 6, G{G}")
+    todo = (1 - mask).astype(np.uint8)
+    x0 = np.full(G, 126336, np.int32)
+    for k in (0, 1, 13, G // 2, 120, eligible, 10 * G):
+        check_unmask(inp, todo, wl.UNMASK_TOPK, float(k), 1, G, wl.BF16, f"unmask {k} G{G}", x0=x0)
+    for thr in (0.0, float(np.median(oracle.verify_scores(None, inp["logits_d"], wl.BF16)[1])), 2.0):
+        check_unmask(inp, todo, wl.UNMASK_THRESH, thr, 1, G, wl.BF16, f"unmask above {thr} G{G}", x0=x0)
+
+
+def test_sequence_rules_of_several_short_sequences():
+    # three sequences of 63 rows (189 in all), one of them finished, ties across the budget in each
+    cfg = wl.custom_config(B=3, G=63, V=1024, logit_dtype=wl.BF16, sigma_d=3.0, sigma_n=1.0)
+    inp = _tied(cfg, 4)
+    mask = np.zeros(cfg.P, np.uint8)
+    mask[3::7] = 1
+    mask.reshape(3, 63)[1] = 1
+    inp["mask"] = mask
+    for k in (1, 13, 30):
+        for mode in (wl.KL_TOPK, wl.CONF_TOPK):
+            om, osc = check_budgeted(inp, mode, k, 3, 63, wl.BF16, f"budget {k} mode {mode}")
+            assert np.array_equal(om, oracle.remask_decide(osc, mask, mode, float(k), 0, 3, 63)[0])
+        check_unmask(inp, (1 - mask).astype(np.uint8), wl.UNMASK_TOPK, float(k), 3, 63, wl.BF16, f"unmask {k}")
+    check_against_oracle(inp, wl.KL_PROB, 0.0, 9, 3, 63, wl.BF16, "Eq. 6, three sequences")

@@ -99,3 +99,41 @@ def test_bidir_mx_cfg5_shape():
     ref = ora_bidir(inp, rows=rows)
     idx = np.asarray(rows)
     assert_attention_close(got[idx[:, 0], idx[:, 1], idx[:, 2]], ref, FP8, f"MX cfg5 shape ({len(rows)} rows)")
+
+
+# every way the values are decoded: 128-row MFMA kernel, the wide kernel's 256- and 128-row tiles
+@pytest.mark.parametrize("kernel", ["0", "1", "2"])
+def test_bidir_mx_v_scales_over_the_contract(monkeypatch, kernel):
+    # decoding is exact for scale codes 27 to 230: with one code everywhere the output is that of code 127 times a power of
+    # two, bit for bit; codes mixed within a row and between rows against the oracle (a code's blocks only add up with
+    # blocks of the same head dimensions, so each 32 dimensions are judged against their own largest value)
+    monkeypatch.setenv("DD_TUNE_ATTN_WIDE", kernel)
+    cfg = wl.custom_config(B=1, H=4, Hkv=2, N=333, d=128, prompt=0, G=333)
+    inp = wl.mx_attention_inputs(cfg, 21)
+    plain = gpu_bidir(dict(inp, Vs=np.full_like(inp["Vs"], 127)))
+    for code in range(27, 231):
+        got = gpu_bidir(dict(inp, Vs=np.full_like(inp["Vs"], code)))
+        assert np.array_equal(got, plain * 2.0 ** (code - 127)), f"kernel {kernel}, code {code}"
+    rng = np.random.default_rng(22)
+    Vs = rng.integers(27, 231, size=inp["Vs"].shape, dtype=np.uint8)
+    got, ref = gpu_bidir(dict(inp, Vs=Vs)), ora_bidir(dict(inp, Vs=Vs))
+    for b in range(4):
+        g, r = got[..., 32 * b:32 * b + 32], ref[..., 32 * b:32 * b + 32]
+        s = np.abs(r).max(axis=(2, 3), keepdims=True)                # per head: its values are of the largest codes' size
+        assert np.linalg.norm((g - r) / s) <= 5e-3 * np.linalg.norm(r / s), f"kernel {kernel}, dims {32 * b}.."
+
+
+def test_bidir_mx_v_scales_on_the_calls_own_route():
+    # the same mixed codes where the library's size rules, not a hook, pick the decode: 200 keys on 128-row tiles, 512 on
+    # either tile
+    for (B, H, Hkv, N) in ((1, 32, 8, 200), (1, 8, 4, 512), (4, 32, 8, 512)):
+        cfg = wl.custom_config(B=B, H=H, Hkv=Hkv, N=N, d=128, prompt=0, G=N)
+        inp = wl.mx_attention_inputs(cfg, N)
+        rng = np.random.default_rng(N)
+        inp["Vs"] = rng.integers(27, 231, size=inp["Vs"].shape, dtype=np.uint8)
+        rows = np.stack([rng.integers(0, n, 256) for n in (B, H, N)], 1)
+        got, ref = gpu_bidir(inp)[rows[:, 0], rows[:, 1], rows[:, 2]], ora_bidir(inp, rows=rows)
+        for b in range(4):
+            g, r = got[:, 32 * b:32 * b + 32], ref[:, 32 * b:32 * b + 32]
+            s = np.abs(r).max(axis=1, keepdims=True)                 # per query row
+            assert np.linalg.norm((g - r) / s) <= 5e-3 * np.linalg.norm(r / s), f"{B}x{H}/{Hkv}x{N}, dims {32 * b}.."

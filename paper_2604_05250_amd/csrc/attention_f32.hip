@@ -39,6 +39,10 @@ __global__ __launch_bounds__(kThreadsF) void attn_f32_kernel(const AttnKernelArg
 {
     constexpr int NJ = D / 16;                      // 16-byte fragments of a Q / K row per lane
     constexpr int NH = D / 64;                      // ... of a V row
+    // Partial sums of a score, 16 or 32 products each: one chain of d products rounds d times, against fp64 1.0e-6 of the
+    // result (d = 128, Q three times N(0, 1), 8 / 2 heads x 16 rows x 700 keys) where four give 4.2e-7 and the vector-ALU
+    // kernel, whose lanes summed 32 products each, gave 4.6e-7.  (Two on the 32-row form: 200 us against 203.)
+    constexpr int NS = RB == 2 ? 2 : 4;
     constexpr int NO = NH * 4;                      // 16-byte pieces of an O row per lane
     __shared__ floatx4 states[kWavesF * RB * NO * 64];
     __shared__ float ml[kWavesF][RB][2][16];        // per wave: (max in use, sum) of its query rows
@@ -112,11 +116,15 @@ __global__ __launch_bounds__(kThreadsF) void attn_f32_kernel(const AttnKernelArg
         }
 #pragma unroll
         for (int q = 0; q < RB; ++q) {
-            floatx4 s = {0.f, 0.f, 0.f, 0.f};
+            floatx4 part[NS];
+#pragma unroll
+            for (int e = 0; e < NS; ++e) part[e] = floatx4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
             for (int i = 0; i < NJ; ++i)
 #pragma unroll
-                for (int e = 0; e < 4; ++e) s = __builtin_amdgcn_mfma_f32_16x16x4f32(k[i][e], qf[q][i][e], s, 0, 0, 0);
+                for (int e = 0; e < 4; ++e) part[e % NS] = __builtin_amdgcn_mfma_f32_16x16x4f32(k[i][e], qf[q][i][e], part[e % NS], 0, 0, 0);
+            floatx4 s = part[0] + part[1];
+            if constexpr (NS == 4) s += part[2] + part[3];
             if (j0 + kUnitF > k_end) {
 #pragma unroll
                 for (int r = 0; r < 4; ++r)

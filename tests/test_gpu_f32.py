@@ -74,3 +74,27 @@ def test_keys_that_score_minus_infinity_f32(N, d, first, last):
     bl = min(N, 16)
     ref = oracle.block_attention_cached(Q[:, :, :bl].copy(), K[:, :, keep].copy(), V[:, :, keep].copy(), 0, F32, F32)
     assert_attention_close(out_to_f64(O, F32)[:, :, :bl], ref, F32, f"{N} keys, [{first}, {last}) at -inf")
+
+
+# The error of a sharp softmax is that of its scores: an absolute error of one is a relative error of its weight.  Summing n
+# products of rms sigma in a chain, rounding by u / sqrt(3) rms (u = 2^-24) of a partial sum that grows as sqrt(k), loses
+# u sigma sqrt(n^2 / 6); scores of d = 128 in four chains of 32, added in pairs, lose 28 u sigma before the division by
+# sqrt(d), 2.5 u sigma after it: 4.4e-7 of the result at sigma = 3.  (One chain of 128: 4.6 u sigma, 8.3e-7.)  The exponential
+# and the weighted sum add about 2 u each.
+@pytest.mark.parametrize("B,H,Hkv,N,d,bl", [(1, 4, 4, 128, 64, 0), (16, 32, 32, 128, 64, 0), (1, 4, 2, 333, 128, 16), (1, 8, 2, 700, 128, 64),
+                                            (1, 4, 2, 333, 128, 0), (1, 2, 2, 2050, 128, 16)])
+def test_error_of_sharp_scores_f32(B, H, Hkv, N, d, bl):
+    import numpy as np
+    import torch
+    rng = np.random.default_rng(N + d)
+    Q, K, V = (rng.standard_normal((B, h, n, d), dtype=np.float32) for h, n in ((H, bl or N), (Hkv, N), (Hkv, N)))
+    Q *= 3
+    t = [to_dev(x) for x in (Q, K, V)]
+    O = out_to_f64(dd.dd_block_attention_cached(*t, 5) if bl else dd.dd_bidir_attention(*t), F32)
+    torch.cuda.synchronize()
+    if bl:
+        ref = oracle.block_attention_cached(Q, K, V, 5, F32, F32)
+    else:
+        rows = np.stack([rng.integers(0, n, 512) for n in (B, H, N)], 1)
+        O, ref = O[rows[:, 0], rows[:, 1], rows[:, 2]], oracle.bidir_attention(Q, K, V, F32, F32, rows=rows)
+    assert np.linalg.norm(O - ref) <= 7e-7 * np.linalg.norm(ref)     # sqrt(4.4^2 + 1.2^2 + 1.2^2) = 4.7, half as much again for scatter

@@ -114,7 +114,9 @@ __device__ __forceinline__ void qk_first(floatx16 &s, const KT kf, const QT qfra
 template <typename KT, typename QT>
 __device__ __forceinline__ void qk_first_from(floatx16 &s, const KT kf, const QT qfrag, const floatx16 &init)
 {
-    asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %3" : "=&v"(s) : "v"(kf), "a"(qfrag), "v"(init));
+    // (the compiler writes or copies `init` with vector instructions right before this statement and does not know that a
+    // matrix instruction, which needs two wait states after those, reads it)
+    asm volatile("s_nop 1\n\tv_mfma_f32_32x32x16_bf16 %0, %1, %2, %3" : "=&v"(s) : "v"(kf), "a"(qfrag), "v"(init));
 }
 template <bool FP8, typename KT, typename QT>
 __device__ __forceinline__ void qk_next(floatx16 &s, const KT kf, const QT qfrag)

@@ -79,6 +79,12 @@ __device__ __forceinline__ unsigned pack_bf16_rne(float lo, float hi)
     floatx2 f = {lo, hi};
     return __builtin_bit_cast(unsigned, __builtin_convertvector(f, bf16x2));
 }
+__device__ __forceinline__ float half_swap_sum(float x)
+{
+    typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+    const u32x2 r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    return __uint_as_float(r.x) + __uint_as_float(r.y);
+}
 __device__ __forceinline__ float half_swap_max(float x)
 {
     typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
@@ -549,12 +555,17 @@ void attn_wide_kernel(const AttnKernelArgs a)
     float c[QB], c_next[QB];                         // scores are exponentiated as 2^(s*c); the next row tile's factor
     using qfrag_t = std::conditional_t<FP8, intx8, intx4>;
     qfrag_t qf[QB][KS];                              // B operands of S^T = K Q^T (one per instruction), kept in accumulation VGPRs
-    // O^T (unnormalised), and the row sums of the weights.  The sums come from a 16x16x32 matrix instruction (half the
-    // matrix-core time of the 32x32x16 one) that takes the weights' B fragment as it is.  Read as that instruction's
-    // 16 x 32 B operand, lane l (column l % 16, k = 8 (l / 16) ..) holds, for column n: k 0-7 and 16-23 = the sixteen
-    // keys of row n, k 8-15 and 24-31 = those of row n + 16.  An A operand whose row 0 is one on the first kind of k and
-    // whose row 1 is one on the second (all else zero) therefore gives C[0][n] = sum of row n, C[1][n] = sum of row
-    // n + 16: lane n < 16 holds them in registers 0 and 1, every other lane and register holds zero.
+    // O^T (unnormalised), and the row sums of the weights.
+    // QB = 1: the sums come from the matrix instruction of sixteen 4 x 4 blocks, which takes the weights' B fragment as it is:
+    // lane l is column l % 4 of block l / 4 with four values of k, so with an A operand of ones every lane gets the sum of
+    // its own weights, in all four registers; the lane halves hold different keys of a row and are added at the end.
+    // QB = 2: from a 16x16x32 matrix instruction (half the matrix-core time of the 32x32x16 one), likewise.  Read as that
+    // instruction's 16 x 32 B operand, lane l (column l % 16, k = 8 (l / 16) ..) holds, for column n: k 0-7 and 16-23 = the
+    // sixteen keys of row n, k 8-15 and 24-31 = those of row n + 16.  An A operand whose row 0 is one on the first kind of k
+    // and whose row 1 is one on the second (all else zero) therefore gives C[0][n] = sum of row n, C[1][n] = sum of row
+    // n + 16: lane n < 16 holds them in registers 0 and 1, every other lane and register holds zero.  A NaN query row
+    // reaches the row 16 away through those zeros; the other instruction, twice as many for the same matrix-core time,
+    // takes 1.0-1.7 % more here (8 x 32 heads x 1024 keys 130.9 -> 132.4 us) and nothing at QB = 1.
     floatx16 acc[QB][DC];
     floatx4 acc_l[QB];
     auto clear_acc = [&]() __attribute__((always_inline)) {
@@ -599,12 +610,15 @@ void attn_wide_kernel(const AttnKernelArgs a)
 #pragma unroll
             for (int r = 0; r < 16; ++r) cinit[q][r] = 0.f;
     }
-    // A operand of the row-sum instruction (see acc_l): lane l holds A[l % 16][8 (l / 16) .. + 7]
-    const int lsel_on = (lane == 0 || lane == 32 || lane == 17 || lane == 49) ? 0x3F803F80 : 0;   // bf16 1.0 twice, or zero
-    intx4 ones = {lsel_on, lsel_on, lsel_on, lsel_on};
+    // A operand of the row-sum instruction (see acc_l); QB = 2: lane l holds A[l % 16][8 (l / 16) .. + 7]
+    const int lsel_on = QB == 1 || lane == 0 || lane == 32 || lane == 17 || lane == 49 ? 0x3F803F80 : 0;   // bf16 1.0 twice, or zero
+    std::conditional_t<QB == 1, intx2, intx4> ones;
+#pragma unroll
+    for (int k = 0; k < (QB == 1 ? 2 : 4); ++k) ones[k] = lsel_on;
     asm volatile("" : "+v"(ones));                   // held in registers instead of being rebuilt per use
-    // the sum of this lane's row (l32) of row block q: from lane l32 % 16, register l32 / 16 (every lane must call it)
+    // the sum of this lane's row (l32) of row block q; QB = 2: from lane l32 % 16, register l32 / 16 (every lane must call it)
     auto row_sum = [&](int q) __attribute__((always_inline)) {
+        if constexpr (QB == 1) return half_swap_sum(acc_l[q][0]);
         const float lo = __shfl(acc_l[q][0], lane & 15), hi = __shfl(acc_l[q][1], lane & 15);
         return (lane & 16) ? hi : lo;
     };
@@ -1001,9 +1015,16 @@ void attn_wide_kernel(const AttnKernelArgs a)
             }
 #pragma unroll
             for (int q = 0; q < QB; ++q) {
-                const uint4 pw = make_uint4(pk_prev[q][st][0], pk_prev[q][st][1], pk_prev[q][st][2], pk_prev[q][st][3]);
-                acc_l[q] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, ones),
-                                                                   __builtin_bit_cast(bf16x8, pw), acc_l[q], 0, 0, 0);
+                if constexpr (QB == 1) {
+#pragma unroll
+                    for (int h = 0; h < 2; ++h)
+                        acc_l[q] = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(__builtin_bit_cast(short4v, ones),
+                            __builtin_bit_cast(short4v, make_uint2(pk_prev[q][st][2 * h], pk_prev[q][st][2 * h + 1])), acc_l[q], 0, 0, 0);
+                } else {
+                    const uint4 pw = make_uint4(pk_prev[q][st][0], pk_prev[q][st][1], pk_prev[q][st][2], pk_prev[q][st][3]);
+                    acc_l[q] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, ones),
+                                                                       __builtin_bit_cast(bf16x8, pw), acc_l[q], 0, 0, 0);
+                }
                 piece(NQK + st * (DC + 1) * QB + DC * QB + q);
             }
         }
@@ -1026,10 +1047,10 @@ void attn_wide_kernel(const AttnKernelArgs a)
                 // (sixteen registers at a time, each block back in accumulation registers before the next is read:
                 // left alone, the compiler holds all 160 products in vector registers at once)
                 asm volatile("" : "+a"(acc_l[q]));
-                // (register 0 of lanes 0-15 is the sum of the lane's own row, register 1 that of the row sixteen on,
-                // whose factor lane + 16 holds; everything else is zero)
+                // (QB = 2: register 0 of lanes 0-15 is the sum of the lane's own row, register 1 that of the row sixteen on,
+                // whose factor lane + 16 holds; everything else is zero.  QB = 1: register 0 is the one that is read)
                 acc_l[q][0] *= corr[q];
-                acc_l[q][1] *= __shfl(corr[q], (lane + 16) & 63);
+                if constexpr (QB == 2) acc_l[q][1] *= __shfl(corr[q], (lane + 16) & 63);
                 asm volatile("" : "+a"(acc_l[q]));
                 __builtin_amdgcn_sched_barrier(0);
 #pragma unroll

@@ -192,3 +192,36 @@ def test_whole_sequence_block_without_fresh_rows(monkeypatch, call):
     torch.cuda.synchronize()
     ref = oracle.bidir_attention(inp["Q"], inp["K"], inp["V"], wl.BF16, wl.BF16)
     assert_attention_close(out_to_f64(O, wl.BF16), ref, wl.BF16, call)
+
+
+# (the verifier's form; the drafter's with one and with several key splits)
+@pytest.mark.parametrize("B,H,Hkv,N,bl,rows", [(1, 2, 2, 191, 0, None), (1, 8, 2, 1025, 0, None), (1, 8, 2, 333, 32, "128"), (1, 4, 1, 1000, 64, "128")])
+@pytest.mark.parametrize("store", ["bf16", "fp8", "fp8v"])
+def test_nan_query_stays_in_its_row(monkeypatch, store, B, H, Hkv, N, bl, rows):
+    # on 128-row tiles: a NaN in a query row makes that row of the output NaN and changes no other
+    import torch
+    monkeypatch.setenv("DD_TUNE_ATTN_WIDE", "2")
+    if rows:
+        monkeypatch.setenv("DD_TUNE_BLOCK_WIDE_ROWS", rows)
+    qk, v = (wl.BF16, wl.BF16) if store == "bf16" else (FP8, FP8 if store == "fp8v" else wl.BF16)
+    cfg = wl.custom_config(B=B, H=H, Hkv=Hkv, N=N, d=128, qk_dtype=qk, v_dtype=v, bl=bl or 16, prompt=0, G=N)
+    inp = wl.attention_inputs(cfg, seed=N)
+    Q, K, V = (to_dev(inp[k]) for k in "QKV")
+    if bl:
+        Q = Q[:, :, :bl].contiguous()
+    qs, ks = to_dev(inp["q_scale"]), to_dev(inp["k_scale"])
+
+    def call(q):
+        if store == "fp8v":
+            vs = to_dev(inp["v_scale"])
+            return dd.dd_block_attention_cached_fp8v(q, K, V, 3, qs, ks, vs) if bl else dd.dd_bidir_attention_fp8v(q, K, V, qs, ks, vs)
+        kw = {"q_scale": qs, "k_scale": ks, "qk_dtype": qk, "v_dtype": v}
+        return dd.dd_block_attention_cached(q, K, V, 3, **kw) if bl else dd.dd_bidir_attention(q, K, V, **kw)
+    want = call(Q)
+    q2 = Q.clone()
+    q2[0, 1, 5] = 0x7F if qk == FP8 else 0x7FC0
+    got = call(q2)
+    torch.cuda.synchronize()
+    assert torch.isnan(got[0, 1, 5].view(torch.bfloat16)).all()
+    got[0, 1, 5] = want[0, 1, 5]
+    assert torch.equal(got, want), f"{store} {B}x{H}/{Hkv} N{N} bl{bl}"

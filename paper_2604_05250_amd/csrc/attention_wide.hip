@@ -878,7 +878,8 @@ void attn_wide_kernel(const AttnKernelArgs a)
                     for (int r = 2; r < 16; r += 2) rm = vmax3(rm, s_cur[q][r], s_cur[q][r + 1]);
                     rm = half_swap_max(rm);                  // both lane halves hold keys of the same query row
                     float delta = rm + kFoldMargin;
-                    if (opening) delta = rm == -INFINITY ? 0.f : delta;  // a wholly masked unit leaves the reference alone
+                    // a wholly masked unit leaves the reference alone, and a NaN row's is not passed on to the next row tile
+                    if (opening) delta = rm > -INFINITY ? delta : 0.f;
                     else delta = delta > 0.f ? delta : 0.f;
                     if (q == 0) {                            // masks are the same for every row
                         ref_unset = opening && __builtin_amdgcn_ballot_w64(rm != -INFINITY) == 0;

@@ -58,7 +58,7 @@ typedef enum {
 typedef enum {
     DD_F32 = 0,        /* IEEE binary32 */
     DD_BF16 = 1,       /* upper 16 bits of binary32 */
-    DD_FP8_E4M3 = 2,   /* OCP e4m3 (bias 7, max 448, no infinities); Q and K only */
+    DD_FP8_E4M3 = 2,   /* OCP e4m3 (bias 7, max 448, no infinities); V too in the _fp8v calls */
     DD_DTYPE_INT_RANGE_LO = -0x7fffffff - 1, DD_DTYPE_INT_RANGE_HI = 0x7fffffff
 } dd_dtype;
 
@@ -114,6 +114,8 @@ size_t dd_bidir_attention_workspace_bytes(int B, int H, int Hkv, int N, int d,
  * of the active block; key/value row j is
  *     Kblk/Vblk[b,g,j-block_start,:]  if Kblk != NULL and block_start <= j < block_start+block_len
  *     Kc/Vc[b,g,j,:]                  otherwise (whatever the cache holds, stale or not).
+ * Cache rows under given block rows (and, for a window, outside it) do not reach the result and may hold anything, NaN
+ * included; inputs that do are finite.
  * With Kblk == Vblk == NULL the caller has already refreshed the block's rows in the cache.
  *
  *   Qblk [B,H,block_len,d] qk_dtype     Kc [B,Hkv,N,d] qk_dtype    Vc [B,Hkv,N,d] v_dtype

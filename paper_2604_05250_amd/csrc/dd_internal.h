@@ -105,7 +105,7 @@ hipError_t launch_attention_f32(const AttnArgs &a, hipStream_t stream);    // fp
 // verifier form, 64 rows per wave; may_fold: the softmax scale may be folded into bf16 Q (a second rounding of it)
 hipError_t launch_attention_wide(const AttnArgs &a, hipStream_t stream, bool may_fold);
 hipError_t launch_attention_wide_narrow(const AttnArgs &a, hipStream_t stream);   // verifier form on 128-row tiles
-hipError_t launch_attention_stream(const AttnArgs &a, hipStream_t stream);  // bf16 drafter form, few query rows
+hipError_t launch_attention_stream(const AttnArgs &a, hipStream_t stream);  // few query rows: drafter form (bf16, or fp8 Q/K), small bf16 verifier calls
 // drafter form on the wide kernel (a few hundred query rows per kv head): whether the call qualifies, the
 // key splits it then uses (a.splits must hold them), the launch (+ merge kernel)
 bool attn_wide_block_fits(const AttnArgs &a);

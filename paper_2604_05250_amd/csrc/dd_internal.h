@@ -92,7 +92,8 @@ struct AttnArgs {
     void *workspace;         // partial states when splits > 1
     // Block-completion refresh: when set (both or neither; Kblk/Vblk then required) the rows
     // [block_start, block_start + block_len) of the cache are overwritten with Kblk / Vblk by the same call.
-    // No workgroup of the call reads those cache rows, so the copy may run at any point of it.
+    // No workgroup of the call uses those cache rows (a tile of the wide kernel may load some of them, which then neither
+    // score nor count), so the copy may run at any point of it.
     void *K_refresh = nullptr;   // = K, writable
     void *V_refresh = nullptr;   // = V, writable
 };

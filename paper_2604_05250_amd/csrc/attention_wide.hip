@@ -187,6 +187,7 @@ __device__ __forceinline__ void static_for(F &&f)
         static_for<N, I + 1>(f);
     }
 }
+
 // the V rows of a stand-in tile
 [[maybe_unused]] __device__ const uint4 kZeroTile[TKW * 256 / 16] = {};
 
@@ -388,8 +389,8 @@ void attn_wide_kernel(const AttnKernelArgs a)
         const int win = min(first, end - TKW);                               // first row actually loaded
         TileAt r;
         r.k = kp + (size_t)win * KROWB;
-        // (a stand-in's V rows are zeros: zero times an infinity or a NaN would be a NaN)
-        r.v = standin ? reinterpret_cast<const uint8_t *>(kZeroTile) : vp + (size_t)win * VSROWB;
+        // (BLOCK: a stand-in's V rows are zeros, see zero_masked_rows)
+        r.v = BLOCK && standin ? reinterpret_cast<const uint8_t *>(kZeroTile) : vp + (size_t)win * VSROWB;
         r.row = win;
         r.vlo = standin ? TKW : first - win;
         r.vhi = standin ? TKW : off + min(T * TKW + TKW, len) - win;
@@ -509,11 +510,13 @@ void attn_wide_kernel(const AttnKernelArgs a)
     // zeroed in LDS once the tile has landed, by the lanes that put them there, before the barrier that hands the tile to the
     // other waves, where what they hold is not the call's (the tile of a part shorter than 64 rows: the cache rows under fresh
     // block rows may never have been written) and in the verifier's last tile, whose rows of the tile before may be infinite.
-    // `dirty` is the next such tile, so a stage pays one comparison: 1 x 32 heads, 512 keys 12.9 -> 13.1 us, 515 keys (the last
-    // tile is one) 15.6 -> 16.0.  (Asking every tile at the stage's end: 13.4, a test in each load, whose lanes then fetch
-    // zeros: 14.1.)
+    // `dirty` is the next such tile, so a stage pays one comparison: 1 x 32 heads, 512 keys 12.4 -> 12.5 us, 515 keys (the
+    // last tile is one) 15.6 -> 15.9.  (Asking every tile at the stage's end: half a microsecond, a test in each load, whose
+    // lanes then fetch zeros: more than one.)  A stand-in is such a tile too; BLOCK forms, short calls mostly, load it from a
+    // block of zeros instead, a choice of addresses in every stage (that costs 0.2-0.4 % of the persistent form's large
+    // calls, the zeroing 2 % of a BLOCK form's short ones).
     auto dirty_after = [&](int tile) __attribute__((always_inline)) {
-        int e = 0x7FFFFFFF;
+        int e = !BLOCK && nt_local != nt_even ? nt_all : 0x7FFFFFFF;          // the stand-in, or none
         const int next = t_first + tile + 1;
         if (!BLOCK || a.block_len == 0) {
             if (nkeys % TKW != 0) e = nt_all - 1;
@@ -526,7 +529,7 @@ void attn_wide_kernel(const AttnKernelArgs a)
     };
     int dirty = dirty_after(-1);
     auto zero_masked_rows = [&](uint4 *vb, const Tile &t, int tile) __attribute__((always_inline)) {
-        if (__builtin_expect(tile != dirty, 1)) return;      // uniform
+        if (__builtin_expect(BLOCK ? tile != dirty : tile < dirty, 1)) return;   // uniform (not BLOCK: every tile from it on)
         if (BLOCK) dirty = dirty_after(tile);
         const TileAt at = tile_at(t, tile);
         int ln = lane;

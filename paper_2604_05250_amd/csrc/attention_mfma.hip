@@ -760,6 +760,16 @@ hipError_t launch_attention_mfma(const AttnArgs &a, hipStream_t stream)
     // Verifier calls: do workgroups of 64 / 128 query rows fit the chip's 256 compute units in one round?
     const long heads = (long)a.B * a.Hkv, rows = (long)(a.H / a.Hkv) * a.Nq;
     const bool one_round64 = heads * ((rows + 63) / 64) <= 256, one_round128 = heads * ((rows + 127) / 128) <= 256;
+    if (!blk && attn_duo_serves(a) && tune("DD_TUNE_ATTN_WIDE", -1) < 0 && tune("DD_TUNE_BIDIR_STREAM", -1) < 0) {
+        // One round of 64-row workgroups: the two-waves-per-SIMD kernel, whose eight waves share a workgroup's keys.  us, before ->
+        // there (bf16 / fp8 Q and K): 1 x 32 heads, N 150 8.0 -> 7.7 / 8.4 -> 7.9 (N 130), N 512 13.2 -> 11.4 / 11.9 -> 11.2,
+        // 1 x 28 (4 kv), N 580 15.4 -> 12.6 / 13.7 -> 11.6, 1 x 16, N 1024 19.5 -> 15.9 / 18.0 -> 14.6; N 64 6.0 -> 6.5 / 5.0 -> 6.7.
+        // d = 64: N 150 5.7 -> 6.5, N 300 7.5 -> 7.3, 1 x 16, N 1000 15.9 -> 11.8.  On its 128-row workgroups, one round of them:
+        // 32 x N 1024 23.5 -> 24.4, 16 x N 2048 40.2 -> 40.2, fp8 32.6 -> 33.4: no.
+        const int forced = tune("DD_TUNE_DUO", -1);
+        const int blocks = forced >= 0 ? forced : one_round64 && a.N >= (a.d == 64 ? 256 : 100) ? 2 : 0;
+        if (blocks == 2 || blocks == 4) return launch_attention_duo(a, blocks, stream);
+    }
     if (!blk && (!fp8 || a.d == 128) && a.N >= 64) {           // (the wide kernel's K/V tiles are 64 whole rows)
         // One round of 128-row workgroups: the wide kernel on 128-row tiles, which has twice the workgroups of its
         // 256-row tiles, each 0.7 of one's time per key.  More: its 256-row tiles (persistent).  Measured against the

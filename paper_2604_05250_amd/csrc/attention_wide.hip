@@ -1289,9 +1289,9 @@ hipError_t launch_attention_wide_narrow(const AttnArgs &a, hipStream_t stream)
                       : launch(attn_wide_kernel<64, false, true, false, 1>, grid, block, stream, k);
 }
 
-// The drafter's call on the wide kernel: worth it from 65 query rows per kv head (GQA groups times the block
-// length; up to 64 the bf16 call streams), which makes the call compute bound.  Every part of the key stream must
-// be empty or at least one tile long.
+// The drafter's call on the wide kernel: with e4m3 values from 65 query rows per kv head (GQA groups times the block
+// length), which makes the call compute bound, with bf16 values where 128-row workgroups would need a second round of the
+// chip's compute units (up to there attention_duo.hip serves it).
 bool attn_wide_block_fits(const AttnArgs &a)
 {
     if (a.qk_dtype == 0 || a.q_mx != nullptr || (a.qk_dtype == 2 && a.d != 128)) return false;
@@ -1363,10 +1363,8 @@ hipError_t launch_attention_wide_block(const AttnArgs &a, hipStream_t stream)
                    : launch(attn_wide_kernel<128, true, true, false, 2, kVE4m3>, grid, block, stream, k);
     else if (narrow)
         e = a.qk_dtype == 2 ? launch(attn_wide_kernel<128, true, true, false, 1>, grid, block, stream, k)
-          : a.d == 128 ? (fold ? launch(attn_wide_kernel<128, false, true, true, 1>, grid, block, stream, k)
-                               : launch(attn_wide_kernel<128, false, true, false, 1>, grid, block, stream, k))
-                       : (fold ? launch(attn_wide_kernel<64, false, true, true, 1>, grid, block, stream, k)
-                               : launch(attn_wide_kernel<64, false, true, false, 1>, grid, block, stream, k));
+          : a.d == 128 ? launch(attn_wide_kernel<128, false, true, false, 1>, grid, block, stream, k)
+                       : launch(attn_wide_kernel<64, false, true, false, 1>, grid, block, stream, k);
     else
         e = a.qk_dtype == 2 ? launch(attn_wide_kernel<128, true, true>, grid, block, stream, k)
           : a.d == 128 ? (fold ? launch(attn_wide_kernel<128, false, true, true>, grid, block, stream, k)

@@ -159,10 +159,19 @@ size_t dd_block_attention_cached_workspace_bytes(int block_len, int B, int H, in
     // which kernel serves the call also depends on block_start: enough for either plan
     const size_t narrow = dd::attn_partial_bytes(B, H, block_len, d, dd::attn_block_splits(block_len, B, H, Hkv, N, d, qk_dtype));
     const size_t wide = dd::attn_partial_bytes(B, H, block_len, d, dd::attn_wide_block_splits(block_len, B, H, Hkv, N));
-    return narrow > wide ? narrow : wide;
+    const size_t duo = dd::attn_partial_bytes(B, H, block_len, d, dd::attn_duo_plan((long)(H / Hkv) * block_len, (long)B * Hkv, N, qk_dtype == DD_FP8_E4M3 || d == 64).splits);
+    const size_t most = narrow > wide ? narrow : wide;
+    return duo > most ? duo : most;
 }
 
 }  // extern "C"
+
+// test hooks: a drafter call is sent to one of the kernels it may run on besides the two-waves-per-SIMD one
+static bool other_kernel_forced()
+{
+    return dd::tune("DD_TUNE_BLOCK_WIDE", -1) >= 0 || dd::tune("DD_TUNE_BLOCK_STREAM", -1) >= 0 || dd::tune("DD_TUNE_BLOCK_WIDE_ROWS", 0) > 0 ||
+           dd::tune("DD_TUNE_BLOCK_WIDE_MIN_ROWS", 0) > 0;
+}
 
 // the drafter's call, with (refresh) or without the block's rows written back into the cache, over the
 // whole cache (win_len == 0) or over the key rows [win_start, win_start + win_len) only
@@ -211,11 +220,23 @@ static int block_attention(const void *Qblk, const void *Kc, const void *Vc, voi
         a.V_refresh = const_cast<void *>(Vc);
     }
     const bool wide = dd::tune("DD_TUNE_BLOCK_WIDE", 1) != 0 && dd::attn_wide_block_fits(a);
-    const int splits = wide ? dd::attn_wide_block_splits(block_len, B, H, Hkv, N)
+    const long rows = (long)(H / Hkv) * block_len, heads = (long)B * Hkv;
+    dd::DuoPlan duo{0, 1};
+    if (dd::attn_duo_serves(a) && (rows > 64 || dd::tune("DD_TUNE_DUO", 0) > 0) && !other_kernel_forced()) {
+        duo = dd::attn_duo_plan(rows, heads, N, qk_dtype == DD_FP8_E4M3 || d == 64);
+        // Past one round of 128-row workgroups the wide kernel's 256-row tiles are faster (24 x 32/8 heads, 64 rows, 1024 keys
+        // 43.3 against 48.5 us, fp8 36.3 / 42.5), its 128-row tiles, for up to 128 rows, are not (40 x 16/8: 60.9 / 52.6, fp8
+        // 51.7 / 45.0); the MFMA kernel, where the wide one cannot take the call, is (64 x 32/8, 32 rows: 62.8 / 66.8).
+        if (duo.blocks == 0 && wide && rows <= 128 && dd::tune("DD_TUNE_DUO", -1) != 0) duo.blocks = 4;
+    }
+    const int splits = duo.blocks ? duo.splits
+                     : wide ? dd::attn_wide_block_splits(block_len, B, H, Hkv, N)
                             : dd::attn_block_splits(block_len, B, H, Hkv, N, d, qk_dtype);
     rc = check_workspace(workspace, workspace_bytes, dd::attn_partial_bytes(B, H, block_len, d, splits));
     if (rc != DD_OK) return rc;
     a.splits = splits;
+    if (duo.blocks)
+        return dd::launch_attention_duo(a, duo.blocks, static_cast<hipStream_t>(stream)) == hipSuccess ? DD_OK : DD_ERR_LAUNCH;
     if (wide)
         return dd::launch_attention_wide_block(a, static_cast<hipStream_t>(stream)) == hipSuccess ? DD_OK : DD_ERR_LAUNCH;
     const hipError_t e = (qk_dtype == DD_F32) ? dd::launch_attention_f32(a, static_cast<hipStream_t>(stream))

@@ -34,6 +34,8 @@ inline hipError_t launch(void (*kernel)(Params...), dim3 grid, dim3 block, hipSt
 //   DD_TUNE_ATTN_WIDE_GRID=n   at most n persistent workgroups on that kernel
 //   DD_TUNE_BIDIR_STREAM=0/1   small bf16 verifier calls off / on the streaming kernel
 //   DD_TUNE_STREAM_NT=0/1      that kernel's K/V loads without / with the non-temporal hint
+//   DD_TUNE_DUO=0/2/4          no call on the two-waves-per-SIMD kernel / every one it can serve, with 2 or 4 row blocks (the
+//                              hooks of the other kernels, where set, come first)
 //   DD_TUNE_BLOCK_STREAM=0     drafter calls with few query rows off the streaming kernel
 //   DD_TUNE_BLOCK_WIDE=0       drafter calls with many query rows off the wide-wave kernel
 //   DD_TUNE_BLOCK_SPLITS=n     key splits of a drafter call on the streaming / MFMA kernels (still at least 128 keys each)
@@ -114,6 +116,13 @@ int attn_wide_block_splits(int block_len, int B, int H, int Hkv, int N);
 int attn_wide_block_rows(int block_len, int B, int H, int Hkv, int N);      // 256 or 128 query rows per workgroup
 hipError_t launch_attention_wide_block(const AttnArgs &a, hipStream_t stream);
 bool attn_stream_fits(const AttnArgs &a);
+// Two waves per SIMD: drafter calls with more than 64 query rows per kv head, verifier calls that fit one round of 64-row
+// workgroups.  Which storage types and head dims it serves; how it takes a drafter call with `rows` query rows in each of
+// `heads` (batch, kv head) pairs: 32-row blocks per workgroup (2 or 4; 0: not at all) and key splits; the launch (+ merge).
+struct DuoPlan { int blocks, splits; };
+bool attn_duo_serves(const AttnArgs &a);
+DuoPlan attn_duo_plan(long rows, long heads, int N, bool light);   // light: fp8 keys or 64 head dims
+hipError_t launch_attention_duo(const AttnArgs &a, int blocks, hipStream_t stream);
 
 // ---- cache maintenance (cache.hip) ----------------------------------------------
 // Row r of Krows/Vrows [B, Hkv, n, d] replaces cache row pos[b * n + r] of every kv head of batch b

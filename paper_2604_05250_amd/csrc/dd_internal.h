@@ -36,6 +36,7 @@ inline hipError_t launch(void (*kernel)(Params...), dim3 grid, dim3 block, hipSt
 //   DD_TUNE_STREAM_NT=0/1      that kernel's K/V loads without / with the non-temporal hint
 //   DD_TUNE_DUO=0/2/4          no call on the two-waves-per-SIMD kernel / every one it can serve, with 2 or 4 row blocks (the
 //                              hooks of the other kernels, where set, come first)
+//   DD_TUNE_SEQ_ROUNDS=n       per-sequence rules on rows that are not split: in one launch up to n load rounds per workgroup
 //   DD_TUNE_BLOCK_STREAM=0     drafter calls with few query rows off the streaming kernel
 //   DD_TUNE_BLOCK_WIDE=0       drafter calls with many query rows off the wide-wave kernel
 //   DD_TUNE_BLOCK_SPLITS=n     key splits of a drafter call on the streaming / MFMA kernels (still at least 128 keys each)

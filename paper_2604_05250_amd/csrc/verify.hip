@@ -566,39 +566,32 @@ __global__ __launch_bounds__(256) void unmask_select_kernel(const float *__restr
 constexpr int kFusedMinRows = 192;            // calls of fewer rows split them over several workgroups each
 constexpr int kSeqThreads = 1024, kSeqMaxRows = kFusedMinRows;
 static_assert(kSeqMaxRows % 64 == 0 && kSeqMaxRows <= 2 * (kSeqThreads / 8), "whole waves of rows, ranked in two passes at most");
-__global__ __launch_bounds__(kSeqThreads) void verify_finalize_seq_kernel(const VerifyPartial *__restrict__ part, int S, int G,
-                                                                  const uint8_t *__restrict__ mask, int mode,
-                                                                  float threshold, uint64_t seed, int kl_mode,
-                                                                  uint8_t *__restrict__ out_mask,
-                                                                  int32_t *__restrict__ out_tokens,
-                                                                  float *__restrict__ out_scores,
-                                                                  int32_t *__restrict__ x_tokens)
+struct SequenceShared {
+    __attribute__((aligned(16))) float score[kSeqMaxRows], bad[kSeqMaxRows];
+    double red[kSeqThreads / 64];
+    int token[kSeqMaxRows];
+    uint8_t mask[kSeqMaxRows];
+};
+
+// The rule of one sequence, rows [base, base + G), whose scores and tokens are in `sh` (a barrier after they were written is part of
+// this); lane g holds row g's mask byte.  Called by all lanes of the workgroup.
+__device__ __forceinline__ void apply_sequence_rule(SequenceShared &sh, uint8_t mbyte, size_t base, int G, int mode, float threshold,
+                                                    uint64_t seed, int kl_mode, uint8_t *__restrict__ out_mask,
+                                                    int32_t *__restrict__ x_tokens)
 {
-    __shared__ __attribute__((aligned(16))) float score_sh[kSeqMaxRows], bad_sh[kSeqMaxRows];
-    __shared__ int token_sh[kSeqMaxRows];
-    __shared__ uint8_t mask_sh[kSeqMaxRows];
-    __shared__ double red[kSeqThreads / 64];
     const int tid = threadIdx.x;
-    const size_t base = (size_t)blockIdx.x * G;
-    const uint8_t mbyte = tid < G ? mask[base + tid] : 0;    // lane g holds row g's mask byte (requested with the states)
-    constexpr int kRowsPerPass = kSeqThreads / kFinalizeLanes;
-    for (int g0 = 0; g0 < G; g0 += kRowsPerPass) {           // uniform trip count
-        const int g = g0 + tid / kFinalizeLanes;
-        merge_splits_and_finish(part, S, (long)base + g, g < G, tid % kFinalizeLanes, mask, mode, threshold, seed, kl_mode,
-                                out_mask, out_tokens, out_scores, VerifyExtra{}, &score_sh[min(g, G - 1)], &token_sh[min(g, G - 1)]);
-    }
-    if (tid < G) mask_sh[tid] = mbyte;
+    if (tid < G) sh.mask[tid] = mbyte;
     __syncthreads();
     if (mode == 3) {                                         // Eq. 6: sum of the eligible rows' divergences, then the draws
-        const float s = tid < G ? score_sh[tid] : 0.f;
+        const float s = tid < G ? sh.score[tid] : 0.f;
         const double k = s > 0.0f ? (double)s : 0.0;
         double local = mbyte == 0 ? k : 0.0;
 #pragma unroll
         for (int o = 32; o > 0; o >>= 1) local += __shfl_xor(local, o);
-        if ((tid & 63) == 0) red[tid >> 6] = local;
+        if ((tid & 63) == 0) sh.red[tid >> 6] = local;
         __syncthreads();
         double total = 0.0;
-        for (int w = 0; w < kSeqMaxRows / 64; ++w) total += red[w];          // (later waves hold no row)
+        for (int w = 0; w < kSeqMaxRows / 64; ++w) total += sh.red[w];       // (later waves hold no row)
         if (tid < G) {
             const double p = total > 0.0 ? k / total : 0.0;
             const bool remask = mbyte == 0 && row_uniform(seed, (uint64_t)(base + tid)) < p;
@@ -611,16 +604,16 @@ __global__ __launch_bounds__(kSeqThreads) void verify_finalize_seq_kernel(const 
     const bool candidate = tid < G && (mbyte != 0) == unmasking && (!unmasking || mbyte == 1);
     const float sign = unmasking || kl_mode ? 1.0f : -1.0f;
     const int n16 = (G + 15) & ~15;
-    if (tid < n16) bad_sh[tid] = candidate ? sign * score_sh[tid] : kNegInf;
+    if (tid < n16) sh.bad[tid] = candidate ? sign * sh.score[tid] : kNegInf;
     __syncthreads();
     // eight lanes per row, each a part of the comparisons: passes of 128 rows
     const float budget = mode == kModeUnmaskThresh ? 0.f : floorf(threshold);
     for (int g0 = 0; g0 < G; g0 += kSeqThreads / 8) {
         const int g = g0 + tid / 8, sub = tid % 8;
-        const float bad = g < G ? bad_sh[g] : kNegInf;
+        const float bad = g < G ? sh.bad[g] : kNegInf;
         int rank = 0;
         for (int j = 4 * sub; j < n16; j += 32) {
-            const float4 o = *reinterpret_cast<const float4 *>(&bad_sh[j]);
+            const float4 o = *reinterpret_cast<const float4 *>(&sh.bad[j]);
             rank += (o.x > bad || (o.x == bad && j < g)) ? 1 : 0;
             rank += (o.y > bad || (o.y == bad && j + 1 < g)) ? 1 : 0;
             rank += (o.z > bad || (o.z == bad && j + 2 < g)) ? 1 : 0;
@@ -630,17 +623,89 @@ __global__ __launch_bounds__(kSeqThreads) void verify_finalize_seq_kernel(const 
         rank += __shfl_xor(rank, 2);
         rank += __shfl_xor(rank, 4);
         if (g < G && sub == 0) {
-            const uint8_t m = mask_sh[g];
+            const uint8_t m = sh.mask[g];
             const bool is = unmasking ? m == 1 : m == 0;
             if (unmasking) {
-                const bool take = is && (mode == kModeUnmaskThresh ? (rank == 0 || score_sh[g] > threshold) : (float)rank < budget);
+                const bool take = is && (mode == kModeUnmaskThresh ? (rank == 0 || sh.score[g] > threshold) : (float)rank < budget);
                 out_mask[base + g] = (uint8_t)(m != 0 && !take);
-                if (take && x_tokens) x_tokens[base + g] = token_sh[g];
+                if (take && x_tokens) x_tokens[base + g] = sh.token[g];
             } else {
                 out_mask[base + g] = (uint8_t)(m != 0 || (is && (float)rank < budget));
             }
         }
     }
+}
+
+__global__ __launch_bounds__(kSeqThreads) void verify_finalize_seq_kernel(const VerifyPartial *__restrict__ part, int S, int G,
+                                                                  const uint8_t *__restrict__ mask, int mode,
+                                                                  float threshold, uint64_t seed, int kl_mode,
+                                                                  uint8_t *__restrict__ out_mask,
+                                                                  int32_t *__restrict__ out_tokens,
+                                                                  float *__restrict__ out_scores,
+                                                                  int32_t *__restrict__ x_tokens)
+{
+    __shared__ SequenceShared sh;
+    const int tid = threadIdx.x;
+    const size_t base = (size_t)blockIdx.x * G;
+    const uint8_t mbyte = tid < G ? mask[base + tid] : 0;    // (requested with the states)
+    constexpr int kRowsPerPass = kSeqThreads / kFinalizeLanes;
+    for (int g0 = 0; g0 < G; g0 += kRowsPerPass) {           // uniform trip count
+        const int g = g0 + tid / kFinalizeLanes;
+        merge_splits_and_finish(part, S, (long)base + g, g < G, tid % kFinalizeLanes, mask, mode, threshold, seed, kl_mode,
+                                out_mask, out_tokens, out_scores, VerifyExtra{}, &sh.score[min(g, G - 1)], &sh.token[min(g, G - 1)]);
+    }
+    apply_sequence_rule(sh, mbyte, base, G, mode, threshold, seed, kl_mode, out_mask, x_tokens);
+}
+
+// A per-sequence rule on few short rows, in one launch: a workgroup per sequence whose sixteen waves take whole rows and then
+// apply the rule.  Such a call is launches and round trips; seq_rounds says where it wins.
+template <bool BF16, bool KL>
+__global__ __launch_bounds__(kSeqThreads) void verify_seq_kernel(const uint4 *__restrict__ logits_d, const uint4 *__restrict__ logits_v,
+                                                                 int nvec, int G, const uint8_t *__restrict__ mask, int mode,
+                                                                 float threshold, uint64_t seed, uint8_t *__restrict__ out_mask,
+                                                                 int32_t *__restrict__ out_tokens, float *__restrict__ out_scores,
+                                                                 int32_t *__restrict__ x_tokens)
+{
+    constexpr int E = VecTraits<BF16>::kElems;
+    __shared__ SequenceShared sh;
+    __shared__ WaveState rows_sh[kSeqMaxRows];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const size_t base = (size_t)blockIdx.x * G;
+    const uint8_t mbyte = tid < G ? mask[base + tid] : 0;
+    for (int g = tid >> 6; g < G; g += kSeqThreads / 64) {
+        const uint4 *const pv = logits_v + (base + g) * nvec, *const pd = KL ? logits_d + (base + g) * nvec : nullptr;
+        LaneState st;
+        for (int v0 = 0; v0 < nvec; v0 += 64 * kUnroll) {
+            uint4 rv[kUnroll], rd[kUnroll];
+#pragma unroll
+            for (int u = 0; u < kUnroll; ++u) {
+                const int idx = v0 + u * 64 + lane;
+                rv[u] = rd[u] = make_uint4(0, 0, 0, 0);
+                if (idx < nvec) {
+                    rv[u] = stream_load16(pv + idx);
+                    if (KL) rd[u] = stream_load16(pd + idx);
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < kUnroll; ++u) {
+                const int idx = v0 + u * 64 + lane;
+                consume<BF16, KL, false>(rv[u], rd[u], idx < nvec, idx * E, st);
+            }
+        }
+        WaveState w;
+        w.ref_d = st.ref_d; w.best_v = st.best_v; w.idx = st.idx_v; w.idx_d = st.idx_d;
+        w.s_v = wave_sum(st.s_v);
+        w.s_d = KL ? wave_sum(st.s_d) : 0.f;
+        w.a = KL ? wave_sum(st.a) : 0.f;
+        if (lane == 0) rows_sh[g] = w;
+    }
+    __syncthreads();
+    if (tid < G) {                                           // G <= kSeqMaxRows: a lane per row
+        const WaveState r = rows_sh[tid];
+        finish_row((int)base + tid, (double)r.ref_d, (double)r.s_d, (double)r.a, (double)r.best_v, (double)r.s_v, r.idx, mask, mode,
+                   threshold, seed, KL ? 1 : 0, out_mask, out_tokens, out_scores, 0, VerifyExtra{}, &sh.score[tid], &sh.token[tid]);
+    }
+    apply_sequence_rule(sh, mbyte, base, G, mode, threshold, seed, KL ? 1 : 0, out_mask, x_tokens);
 }
 
 }  // namespace
@@ -676,6 +741,16 @@ int verify_splits(int P, int V, int elem_bytes)
     const long s = (nvec + chunk - 1) / chunk;
     return (int)(s < 1 ? 1 : s);
 }
+
+// Dependent load rounds of verify_seq_kernel (sixteen rows of 64 kUnroll vectors each), and up to how many it is taken: a round costs
+// its one workgroup 2.5 us (KL 4), the launch that it saves 3.  us per call in a stream of them, two launches -> one, fp32:
+// unmasking 16 x 1024 7.3 -> 4.6, 16 x 2048 or 32 x 1024 (two rounds) 7.5 -> 6.3 - 7.3, 16 x 4096 8.0 / 8.9; Eq. 6 16 x 1024 8.3 -> 7.2,
+// 16 x 2048 8.8 / 10.7. 
+static int seq_rounds(int G, int nvec)
+{
+    return (G + kSeqThreads / 64 - 1) / (kSeqThreads / 64) * ((nvec + 64 * kUnroll - 1) / (64 * kUnroll));
+}
+constexpr int kSeqMaxRounds = 2, kSeqMaxRoundsKl = 1;
 
 size_t verify_workspace_bytes(int P, int V, int elem_bytes)
 {
@@ -729,6 +804,25 @@ hipError_t launch_verify(const void *logits_d, const void *logits_v, const uint8
         const int chunk = verify_split_chunk(P, V, eb);
         VerifyPartial *part = static_cast<VerifyPartial *>(workspace);
         const dim3 grid((unsigned)((long)P * S)), block(kThreads);
+        const bool per_sequence = mode == 3 || mode == 5 || mode == 6 || mode == kModeUnmaskThresh || mode == kModeUnmaskTopk;
+        // Rows that are not split leave nothing to merge: rules of one row finish it in the launch that streams it, ...
+        if (S == 1 && !per_sequence && !track_d) {
+            const dim3 rows((unsigned)P);
+            if (logit_is_bf16)
+                return kl ? launch_row_kernel<true, true>(kThreads, rows, stream, ld, lv, nvec, mask, mode, threshold, seed, out_mask, out_tokens, out_scores, ex)
+                          : launch_row_kernel<true, false>(kThreads, rows, stream, ld, lv, nvec, mask, mode, threshold, seed, out_mask, out_tokens, out_scores, ex);
+            return kl ? launch_row_kernel<false, true>(kThreads, rows, stream, ld, lv, nvec, mask, mode, threshold, seed, out_mask, out_tokens, out_scores, ex)
+                      : launch_row_kernel<false, false>(kThreads, rows, stream, ld, lv, nvec, mask, mode, threshold, seed, out_mask, out_tokens, out_scores, ex);
+        }
+        // ... rules of a sequence stream its rows in the workgroup that applies the rule, as long as that is a few round trips
+        if (S == 1 && per_sequence && seq_rounds(G, nvec) <= tune("DD_TUNE_SEQ_ROUNDS", kl ? kSeqMaxRoundsKl : kSeqMaxRounds)) {
+            const dim3 seqs((unsigned)B), lanes(kSeqThreads);
+            if (logit_is_bf16)
+                return kl ? launch(verify_seq_kernel<true, true>, seqs, lanes, stream, ld, lv, nvec, G, mask, mode, threshold, seed, out_mask, out_tokens, out_scores, x_tokens)
+                          : launch(verify_seq_kernel<true, false>, seqs, lanes, stream, ld, lv, nvec, G, mask, mode, threshold, seed, out_mask, out_tokens, out_scores, x_tokens);
+            return kl ? launch(verify_seq_kernel<false, true>, seqs, lanes, stream, ld, lv, nvec, G, mask, mode, threshold, seed, out_mask, out_tokens, out_scores, x_tokens)
+                      : launch(verify_seq_kernel<false, false>, seqs, lanes, stream, ld, lv, nvec, G, mask, mode, threshold, seed, out_mask, out_tokens, out_scores, x_tokens);
+        }
         if (track_d) {
             e = logit_is_bf16 ? launch(verify_partial_kernel<true, true, true>, grid, block, stream, ld, lv, nvec, S, chunk, part)
                               : launch(verify_partial_kernel<false, true, true>, grid, block, stream, ld, lv, nvec, S, chunk, part);
@@ -740,7 +834,7 @@ hipError_t launch_verify(const void *logits_d, const void *logits_v, const uint8
             else    e = launch(verify_partial_kernel<false, false>, grid, block, stream, ld, lv, nvec, S, chunk, part);
         }
         if (e != hipSuccess) return e;
-        if (mode == 3 || mode == 5 || mode == 6 || mode == kModeUnmaskThresh || mode == kModeUnmaskTopk)
+        if (per_sequence)
             return launch(verify_finalize_seq_kernel, dim3((unsigned)B), dim3(kSeqThreads), stream, (const VerifyPartial *)part, S,
                           G, mask, mode, threshold, seed, kl ? 1 : 0, out_mask, out_tokens, out_scores, x_tokens);
         e = launch(verify_finalize_kernel, dim3((unsigned)(((long)P * kFinalizeLanes + 255) / 256)), dim3(256), stream,

@@ -481,3 +481,26 @@ def test_sequence_rules_of_several_short_sequences():
             assert np.array_equal(om, oracle.remask_decide(osc, mask, mode, float(k), 0, 3, 63)[0])
         check_unmask(inp, (1 - mask).astype(np.uint8), wl.UNMASK_TOPK, float(k), 3, 63, wl.BF16, f"unmask {k}")
     check_against_oracle(inp, wl.KL_PROB, 0.0, 9, 3, 63, wl.BF16, "Eq. 6, three sequences")
+
+
+# ------------------------------------------------------------------ rows that are not split: one launch
+# (one row; a wave's share of rows and one more; the largest call on this path; one vector, a lane's worth and one more, a full
+# round and one more, the longest row; bf16 8192 and fp32 4096 logits are the last that are not split)
+@pytest.mark.parametrize("B,G,V,dtype", [(1, 1, 8, wl.BF16), (1, 16, 1024, wl.F32), (2, 17, 1028, wl.F32), (1, 191, 520, wl.BF16),
+                                         (3, 63, 4, wl.F32), (1, 33, 2056, wl.BF16), (2, 16, 4096, wl.F32), (1, 15, 8192, wl.BF16),
+                                         (190, 1, 1024, wl.F32)])
+@pytest.mark.parametrize("rounds", [0, 1000])
+def test_sequence_rules_of_unsplit_rows(monkeypatch, rounds, B, G, V, dtype):
+    monkeypatch.setenv("DD_TUNE_SEQ_ROUNDS", str(rounds))
+    cfg = wl.custom_config(B=B, G=G, V=V, logit_dtype=dtype, sigma_d=3.0, sigma_n=1.0, decoded_frac=0.7)
+    inp = wl.verify_inputs(cfg, seed=G + V)
+    mask = inp["mask"]
+    what = f"B{B} G{G} V{V} rounds {rounds}"
+    for mode, tau in ALL_MODES:
+        check_against_oracle(inp, mode, tau, 3, B, G, dtype, f"{what} mode {mode}")
+    for mode in (wl.KL_TOPK, wl.CONF_TOPK):
+        om, osc = check_budgeted(inp, mode, G // 3, B, G, dtype, f"{what} budget, mode {mode}")
+        assert np.array_equal(om, oracle.remask_decide(osc, mask, mode, float(G // 3), 0, B, G)[0])
+    x0 = np.full(B * G, V, np.int32)
+    for mode, thr in ((wl.UNMASK_TOPK, 3.0), (wl.UNMASK_THRESH, 0.5)):
+        check_unmask(inp, (1 - mask).astype(np.uint8), mode, thr, B, G, dtype, f"{what} unmask {mode}", x0=x0)

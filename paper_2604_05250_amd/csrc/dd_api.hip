@@ -166,11 +166,11 @@ size_t dd_block_attention_cached_workspace_bytes(int block_len, int B, int H, in
 
 }  // extern "C"
 
-// test hooks: a drafter call is sent to one of the kernels it may run on besides the two-waves-per-SIMD one
+// test hooks: a drafter call is sent to one of the kernels it may run on besides attention_duo.hip's and attention_solo.hip's
 static bool other_kernel_forced()
 {
     return dd::tune("DD_TUNE_BLOCK_WIDE", -1) >= 0 || dd::tune("DD_TUNE_BLOCK_STREAM", -1) >= 0 || dd::tune("DD_TUNE_BLOCK_WIDE_ROWS", 0) > 0 ||
-           dd::tune("DD_TUNE_BLOCK_WIDE_MIN_ROWS", 0) > 0;
+           dd::tune("DD_TUNE_BLOCK_WIDE_MIN_ROWS", 0) > 0 || dd::tune("DD_TUNE_STREAM_NT", -1) >= 0;
 }
 
 // the drafter's call, with (refresh) or without the block's rows written back into the cache, over the
@@ -229,14 +229,20 @@ static int block_attention(const void *Qblk, const void *Kc, const void *Vc, voi
         // 51.7 / 45.0); the MFMA kernel, where the wide one cannot take the call, is (64 x 32/8, 32 rows: 62.8 / 66.8).
         if (duo.blocks == 0 && wide && rows <= 128 && dd::tune("DD_TUNE_DUO", -1) != 0) duo.blocks = 4;
     }
-    const int splits = duo.blocks ? duo.splits
-                     : wide ? dd::attn_wide_block_splits(block_len, B, H, Hkv, N)
-                            : dd::attn_block_splits(block_len, B, H, Hkv, N, d, qk_dtype);
-    rc = check_workspace(workspace, workspace_bytes, dd::attn_partial_bytes(B, H, block_len, d, splits));
+    const int narrow_splits = dd::attn_block_splits(block_len, B, H, Hkv, N, d, qk_dtype);
+    dd::SoloPlan solo{false, 1};
+    if (!duo.blocks && rows <= 64 && dd::attn_duo_serves(a) && !other_kernel_forced())
+        solo = dd::attn_solo_plan(rows, heads, N, d, qk_dtype == DD_FP8_E4M3, narrow_splits);
+    const int general = wide ? dd::attn_wide_block_splits(block_len, B, H, Hkv, N) : narrow_splits;
+    const int splits = duo.blocks ? duo.splits : solo.take ? solo.splits : general;
+    // (what the kernels of every shape ask for is asked for here too, whichever serves the call)
+    rc = check_workspace(workspace, workspace_bytes, dd::attn_partial_bytes(B, H, block_len, d, splits > general ? splits : general));
     if (rc != DD_OK) return rc;
     a.splits = splits;
     if (duo.blocks)
         return dd::launch_attention_duo(a, duo.blocks, static_cast<hipStream_t>(stream)) == hipSuccess ? DD_OK : DD_ERR_LAUNCH;
+    if (solo.take)
+        return dd::launch_attention_solo(a, static_cast<hipStream_t>(stream)) == hipSuccess ? DD_OK : DD_ERR_LAUNCH;
     if (wide)
         return dd::launch_attention_wide_block(a, static_cast<hipStream_t>(stream)) == hipSuccess ? DD_OK : DD_ERR_LAUNCH;
     const hipError_t e = (qk_dtype == DD_F32) ? dd::launch_attention_f32(a, static_cast<hipStream_t>(stream))

@@ -11,6 +11,20 @@
 
 namespace dd {
 
+// Block-completion refresh of the cache (Sec. 2.3: the cache is brought up to date when a block is done):
+// the block's K and V rows, dense in [B*Hkv, block_len, d], replace rows block_start.. of every (batch, kv head)
+// of the cache.  Everything in 16-byte chunks; workgroups `first_wg`.. of a launch do the copying: the one that merges
+// partial states, or, where the key range is not split, the attention's own (no workgroup of it uses the rows that are written).
+struct RefreshArgs {
+    const uint4 *src[2];       // Kblk, Vblk
+    uint4 *dst[2];             // Kc, Vc at row 0 of (batch 0, kv head 0)
+    int per_bh[2];             // chunks of the block per (batch, kv head)
+    long bh_stride[2];         // chunks between consecutive (batch, kv head) in the cache
+    long offset[2];            // chunks from a cache (batch, kv head) base to row block_start
+    int wgs_per_bh;            // copying workgroups per (batch, kv head)
+    int first_wg;              // workgroups below this one attend / merge partial states
+};
+
 struct AttnKernelArgs {
     const void *Q, *K, *V, *Kblk, *Vblk;
     void *O;                   // final output (splits == 1)
@@ -31,10 +45,29 @@ struct AttnKernelArgs {
     float scale_log2;          // log2(e) / sqrt(d)
 };
 
+__device__ __forceinline__ void refresh_cache_rows(const RefreshArgs &r)
+{
+    const int cw = (int)blockIdx.x - r.first_wg;
+    const int bh = cw / r.wgs_per_bh;
+    const int first = (cw - bh * r.wgs_per_bh) * (int)blockDim.x + (int)threadIdx.x;
+    const int step = r.wgs_per_bh * (int)blockDim.x;
+#pragma unroll
+    for (int w = 0; w < 2; ++w) {
+        const uint4 *src = r.src[w] + (long)bh * r.per_bh[w];
+        uint4 *dst = r.dst[w] + (long)bh * r.bh_stride[w] + r.offset[w];
+        for (int in = first; in < r.per_bh[w]; in += step) dst[in] = src[in];
+    }
+}
+
 constexpr int kAttnThreads = 256;
 
 struct AttnArgs;
 // Host side: derive the launch decomposition (row tiles, key splits, partial buffers).
 void fill_kernel_args(const AttnArgs &a, AttnKernelArgs &k, int rows_per_wg, int key_tile);
+// Host side: where the block-completion copy of a call goes from and to, by at most about `most_wgs` workgroups; returns how many (0:
+// nothing to copy).
+long fill_refresh(const AttnArgs &a, RefreshArgs &r, long most_wgs);
+// An attending workgroup's LDS is set aside for a copying one of its launch too: about one of these per compute unit.
+constexpr long kCopyWgs = 256;
 
 }  // namespace dd

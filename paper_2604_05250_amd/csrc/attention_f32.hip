@@ -35,7 +35,7 @@ __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_ex
 
 // RB: 16-row query blocks per workgroup
 template <int D, int RB>
-__global__ __launch_bounds__(kThreadsF) void attn_f32_kernel(const AttnKernelArgs a)
+__device__ __forceinline__ void attn_f32(const AttnKernelArgs &a)
 {
     constexpr int NJ = D / 16;                      // 16-byte fragments of a Q / K row per lane
     constexpr int NH = D / 64;                      // ... of a V row
@@ -216,6 +216,24 @@ __global__ __launch_bounds__(kThreadsF) void attn_f32_kernel(const AttnKernelArg
     }
 }
 
+template <int D, int RB>
+__global__ __launch_bounds__(kThreadsF) void attn_f32_kernel(const AttnKernelArgs a)
+{
+    attn_f32<D, RB>(a);
+}
+
+// The same launch with the block-completion copy on the workgroups past the attending ones: for a call without key splits, which has no
+// merge launch to take it along (a launch of its own for it: 61.8 us per cycle of 4 heads and 128 keys, here 58.5).
+template <int D, int RB>
+__global__ __launch_bounds__(kThreadsF) void attn_f32_refresh_kernel(const AttnKernelArgs a, const RefreshArgs r)
+{
+    if ((int)blockIdx.x >= r.first_wg) {            // uniform: these only copy
+        refresh_cache_rows(r);
+        return;
+    }
+    attn_f32<D, RB>(a);
+}
+
 }  // namespace
 
 hipError_t launch_attention_f32(const AttnArgs &a, hipStream_t stream)
@@ -233,7 +251,17 @@ hipError_t launch_attention_f32(const AttnArgs &a, hipStream_t stream)
     const long most = a.N / kSplitKeys < 256 / wgs ? a.N / kSplitKeys : 256 / wgs;
     if (s.splits > most) s.splits = most > 1 ? (int)most : 1;
     fill_kernel_args(s, k, rows_per_wg, kUnitF);
-    const dim3 grid((unsigned)(heads * k.row_tiles * k.splits)), block(kThreadsF);
+    const long attending = heads * k.row_tiles * k.splits;
+    const dim3 block(kThreadsF);
+    RefreshArgs r{};
+    const long copy_wgs = k.splits == 1 ? fill_refresh(s, r, kCopyWgs) : 0;
+    if (copy_wgs > 0) {
+        r.first_wg = (int)attending;
+        const dim3 grid((unsigned)(attending + copy_wgs));
+        return a.d == 128 ? launch(attn_f32_refresh_kernel<128, 1>, grid, block, stream, k, r)
+             : two ? launch(attn_f32_refresh_kernel<64, 2>, grid, block, stream, k, r) : launch(attn_f32_refresh_kernel<64, 1>, grid, block, stream, k, r);
+    }
+    const dim3 grid((unsigned)attending);
     const hipError_t e = a.d == 128 ? launch(attn_f32_kernel<128, 1>, grid, block, stream, k)
                        : two ? launch(attn_f32_kernel<64, 2>, grid, block, stream, k) : launch(attn_f32_kernel<64, 1>, grid, block, stream, k);
     return e != hipSuccess ? e : finish_attention(s, k.splits, stream);

@@ -1,5 +1,5 @@
 // Attention of few query rows whose waves stream keys of their own: the drafter's call with at most 64 rows per kv head where
-// workgroups are few (Sec. 2.3), bf16 or fp8 Q/K.
+// workgroups are few (Sec. 2.3), bf16 or fp8 Q/K, bf16 or (with fp8 Q/K) e4m3 V.
 //     O = softmax(Q K^T / sqrt(d_k)) V   (Eq. 3)
 // One workgroup = four waves on one block of 32 query rows; wave w takes every fourth 32-key unit of the key range with a state
 // (reference, sum, O) of its own, and the states are merged through LDS at the end, every wave finishing a quarter of the head dims.
@@ -50,6 +50,13 @@ __device__ __forceinline__ const uint8_t *solo_scalar(const uint8_t *p)         
     const unsigned lo = __builtin_amdgcn_readfirstlane((unsigned)v), hi = __builtin_amdgcn_readfirstlane((unsigned)(v >> 32));
     return reinterpret_cast<const uint8_t *>(((unsigned long long)hi << 32) | lo);
 }
+__device__ __forceinline__ uint4 solo_decode(unsigned w0, unsigned w1)           // eight e4m3 codes to bf16, exactly
+{
+    return make_uint4(__builtin_bit_cast(unsigned, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(w0, 1.0f, false)),
+                      __builtin_bit_cast(unsigned, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(w0, 1.0f, true)),
+                      __builtin_bit_cast(unsigned, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(w1, 1.0f, false)),
+                      __builtin_bit_cast(unsigned, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(w1, 1.0f, true)));
+}
 template <int I, int N, typename F> __device__ __forceinline__ void static_for(F &&f)
 {
     if constexpr (I < N) {
@@ -60,11 +67,13 @@ template <int I, int N, typename F> __device__ __forceinline__ void static_for(F
 
 constexpr int kSoloWaves = 4;
 
-template <int D, bool FP8>
-__global__ __launch_bounds__(64 * kSoloWaves) __attribute__((amdgpu_waves_per_eu(2, 2)))
-void attn_solo_kernel(const AttnKernelArgs a)
+// V8: V is stored as e4m3 codes.  They travel to LDS as they are and the wave decodes its own 4 KB into its V buffer, exactly, when
+// they arrive (32 conversions of two elements per lane and unit); v_scale multiplies the result once.
+// `wgs`: the launch's attending workgroups.
+template <int D, bool FP8, bool V8>
+__device__ __forceinline__ void attn_solo(const AttnKernelArgs &a, const int wgs)
 {
-    // (device pass only: the host pass needs the handle, not assembly it cannot check)
+    // (device pass only: the host pass needs the kernels' handles, not assembly it cannot check)
 #if defined(__HIP_DEVICE_COMPILE__)
     constexpr int NW = kSoloWaves, U = 32;           // keys per unit
     constexpr int CH = D / 8;                        // 16-byte chunks per V / O row
@@ -73,13 +82,14 @@ void attn_solo_kernel(const AttnKernelArgs a)
     constexpr int KROWB = FP8 ? D : ROWB, KCH = KROWB / 16;   // Q / K as stored: bytes and chunks per row
     constexpr int KF = KROWB / 32;                   // 16-byte K fragments per lane and unit
     constexpr int KB = U * KROWB, VB = U * ROWB;     // bytes of a wave's K / V buffer
-    constexpr int NK = KB / 1024, NV = VB / 1024;    // wave-wide loads per buffer (1 KB each)
-    constexpr int VDMA_ROWS = 1024 / ROWB, KDMA_ROWS = 1024 / KROWB;         // rows per load
+    constexpr int VSROWB = V8 ? D : ROWB, VSCH = VSROWB / 16, VSB = V8 ? U * VSROWB : 0;   // V as stored; its own buffer if decoded
+    constexpr int NK = KB / 1024, NV = U * VSROWB / 1024;                    // wave-wide loads per buffer (1 KB each)
+    constexpr int VDMA_ROWS = 1024 / VSROWB, KDMA_ROWS = 1024 / KROWB;       // rows per load
     constexpr int G = DC * 4, GP = G / NW;           // groups of four O registers per lane, ... that a wave finishes
-    static_assert(!FP8 || D == 128, "fp8 rows are 128 bytes");
+    static_assert((!FP8 && !V8) || (FP8 && D == 128), "fp8 rows are 128 bytes");
     static_assert(GP % 2 == 0, "groups are stored in pairs");
     static_assert(NK <= 8 && NV <= 8, "a buffer is within the loads' immediate offsets");
-    constexpr int SLOTB = KB + VB;
+    constexpr int SLOTB = KB + VB + VSB;
     constexpr int PARKB = NW * (NW - 1) * GP * 1024; // the parked states share the buffers' memory
     constexpr int LDSB = (NW * SLOTB > PARKB ? NW * SLOTB : PARKB);
     // per wave: K [key][chunk ^ (key & 7)], then V [key][chunk ^ ((key % (CH/4)) << 2)]
@@ -95,7 +105,7 @@ void attn_solo_kernel(const AttnKernelArgs a)
     // ---- which (batch, kv head, row tile, key split); same XCD for workgroups that share K/V
     int bid = blockIdx.x;
     {
-        const int total = gridDim.x, per = total >> 3, rem = total & 7;
+        const int total = wgs, per = total >> 3, rem = total & 7;
         const int xcd = bid & 7, slot = bid >> 3;
         bid = xcd * per + min(xcd, rem) + slot;
     }
@@ -115,18 +125,18 @@ void attn_solo_kernel(const AttnKernelArgs a)
 
     const size_t kv_head = (size_t)b * a.Hkv + kvh;
     const uint8_t *const kc = static_cast<const uint8_t *>(a.K) + kv_head * a.kv_stride * (size_t)KROWB;
-    const uint8_t *const vc = static_cast<const uint8_t *>(a.V) + kv_head * a.kv_stride * (size_t)ROWB;
+    const uint8_t *const vc = static_cast<const uint8_t *>(a.V) + kv_head * a.kv_stride * (size_t)VSROWB;
     const uint8_t *const kb_ = blen ? static_cast<const uint8_t *>(a.Kblk) + kv_head * blen * (size_t)KROWB : nullptr;
-    const uint8_t *const vb_ = blen ? static_cast<const uint8_t *>(a.Vblk) + kv_head * blen * (size_t)ROWB : nullptr;
+    const uint8_t *const vb_ = blen ? static_cast<const uint8_t *>(a.Vblk) + kv_head * blen * (size_t)VSROWB : nullptr;
     auto lds_addr = [&](const void *p) __attribute__((always_inline)) { return (unsigned)(size_t)(__attribute__((address_space(3))) const void *)p; };
-    char *const kbuf = reinterpret_cast<char *>(KV) + wave * SLOTB, *const vbuf = kbuf + KB;
-    const unsigned kdst = lds_addr(KV) + wave * SLOTB, vdst = kdst + KB;
+    char *const kbuf = reinterpret_cast<char *>(KV) + wave * SLOTB, *const vbuf = kbuf + KB, *const vstored = vbuf + VB;
+    const unsigned kdst = lds_addr(KV) + wave * SLOTB, vdst = kdst + KB + (V8 ? VB : 0);
     // load i of a buffer fills its rows i * DMA_ROWS ..; lane l lands at chunk position l % CH of row l / CH and fetches the
     // chunk the swizzle maps there (with 256-byte rows K's depends on whether i is odd)
-    const int vrow0 = lane / CH, krow0 = lane / KCH;
+    const int vrow0 = lane / VSCH, krow0 = lane / KCH;
     auto kchunk = [&](int i) __attribute__((always_inline)) { return (unsigned)(((lane % KCH) ^ ((i * KDMA_ROWS + krow0) & 7)) * 16); };
-    const unsigned vchunk = ((lane % CH) ^ ((vrow0 & (CH / 4 - 1)) << 2)) * 16;
-    const unsigned koff[2] = {krow0 * KROWB + kchunk(0), krow0 * KROWB + kchunk(1)}, voff = vrow0 * ROWB + vchunk;
+    const unsigned vchunk = V8 ? lane % VSCH * 16 : ((lane % CH) ^ ((vrow0 & (CH / 4 - 1)) << 2)) * 16;   // (codes lie as in memory)
+    const unsigned koff[2] = {krow0 * KROWB + kchunk(0), krow0 * KROWB + kchunk(1)}, voff = vrow0 * VSROWB + vchunk;
     int blk0 = 0, blk1 = 0;                          // units outside [blk0, blk1) hold rows of the cache only
     if (blen) {
         const long s0 = min(max((long)bstart, (long)kbeg), (long)kend), s1 = min(max((long)bstart + blen, (long)kbeg), (long)kend);
@@ -140,7 +150,7 @@ void attn_solo_kernel(const AttnKernelArgs a)
     // its last one (finite stand-ins, masked or zeroed below).
     auto load_rows = [&](auto is_k, int u) __attribute__((always_inline)) {
         constexpr bool K = decltype(is_k)::value;
-        constexpr int NL = K ? NK : NV, BIAS = NL > 4 ? 4096 : 0, PITCH = K ? KROWB : ROWB;
+        constexpr int NL = K ? NK : NV, BIAS = NL > 4 ? 4096 : 0, PITCH = K ? KROWB : VSROWB;
         const unsigned dst = (K ? kdst : vdst) + BIAS;
         const int k0 = kbeg + u * U;
         if (u < whole && (unsigned)(u - blk0) >= (unsigned)(blk1 - blk0)) {
@@ -261,7 +271,26 @@ void attn_solo_kernel(const AttnKernelArgs a)
         }
         if (more) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(NK) : "memory");
         else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        if (u == whole) {
+        if constexpr (V8) {
+            // 16 codes of a row per load and lane, two 16-byte chunks of the row's bf16 form; rows past the end are zero (a weight of
+            // zero times an infinity is a NaN)
+            uint4 codes[NV];
+#pragma unroll
+            for (int i = 0; i < NV; ++i) codes[i] = *reinterpret_cast<const uint4 *>(vstored + i * 1024 + lane * 16);
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+            if (more) load_rows(of_v, u + NW);
+#pragma unroll
+            for (int i = 0; i < NV; ++i) {
+                const int row = i * VDMA_ROWS + vrow0, chunk = lane % VSCH * 2;
+                const bool ok = u != whole || kbeg + u * U + row < kend;
+                const uint4 lo = ok ? solo_decode(codes[i].x, codes[i].y) : make_uint4(0u, 0u, 0u, 0u);
+                const uint4 hi = ok ? solo_decode(codes[i].z, codes[i].w) : make_uint4(0u, 0u, 0u, 0u);
+                const int swz = (row & (CH / 4 - 1)) << 2;
+                *reinterpret_cast<uint4 *>(vbuf + (row * CH + (chunk ^ swz)) * 16) = lo;
+                *reinterpret_cast<uint4 *>(vbuf + (row * CH + ((chunk + 1) ^ swz)) * 16) = hi;
+            }
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        } else if (u == whole) {
             // V rows past the end have weight zero, but zero times an infinity is a NaN: zeroed by the lanes that loaded them
 #pragma unroll
             for (int i = 0; i < NV; ++i)
@@ -315,7 +344,7 @@ void attn_solo_kernel(const AttnKernelArgs a)
                 pk[r >> 3][(r & 7) >> 1] = solo_pack(solo_exp2(fmaf(s[r], c, use)), solo_exp2(fmaf(s[r + 1], c, use)));
         }
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-        if (more) load_rows(of_v, u + NW);
+        if (!V8 && more) load_rows(of_v, u + NW);
 #pragma unroll
         for (int st = 0; st < 2; ++st) {
             const uint4 pw = make_uint4(pk[st][0], pk[st][1], pk[st][2], pk[st][3]);
@@ -383,6 +412,13 @@ void attn_solo_kernel(const AttnKernelArgs a)
                 o[g][0] += x.x * wgt[q]; o[g][1] += x.y * wgt[q]; o[g][2] += x.z * wgt[q]; o[g][3] += x.w * wgt[q];
             }
         }
+    if constexpr (V8) {
+        const float vs = a.v_scale[kv_head];         // the decoded values times this are the real ones
+#pragma unroll
+        for (int g = 0; g < GP; ++g)
+#pragma unroll
+            for (int k = 0; k < 4; ++k) o[g][k] *= vs;
+    }
     // ---- output: group g of this wave is dims 8 (wave GP + g) + 4 hh .. + 3 of query row l32
     const size_t orow = row_base + v;
     if (a.splits == 1) {
@@ -408,18 +444,54 @@ void attn_solo_kernel(const AttnKernelArgs a)
 #endif
 }
 
+template <int D, bool FP8, bool V8>
+__global__ __launch_bounds__(64 * kSoloWaves) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_solo_kernel(const AttnKernelArgs a)
+{
+    attn_solo<D, FP8, V8>(a, gridDim.x);
+}
+
+// The same launch with the block-completion copy on the workgroups past the attending ones: for a call without key splits, which has no
+// merge launch to take it along.  (A kernel of its own: the look at where the copying workgroups start costs a plain call 0.4 us.)
+template <int D, bool FP8, bool V8>
+__global__ __launch_bounds__(64 * kSoloWaves) __attribute__((amdgpu_waves_per_eu(2, 2)))
+void attn_solo_refresh_kernel(const AttnKernelArgs a, const RefreshArgs r)
+{
+    if ((int)blockIdx.x >= r.first_wg) {             // uniform: these only copy
+        refresh_cache_rows(r);
+        return;
+    }
+    attn_solo<D, FP8, V8>(a, r.first_wg);
+}
+
+template <int D, bool FP8, bool V8> hipError_t launch_solo(const AttnArgs &a, hipStream_t stream)
+{
+    AttnKernelArgs k;
+    fill_kernel_args(a, k, 32, 32);
+    const long wgs = (long)a.B * a.Hkv * k.row_tiles * k.splits;
+    const dim3 block(64 * kSoloWaves);
+    RefreshArgs r{};
+    const long copy_wgs = k.splits == 1 ? fill_refresh(a, r, kCopyWgs) : 0;
+    if (copy_wgs > 0) {
+        r.first_wg = (int)wgs;
+        return launch(attn_solo_refresh_kernel<D, FP8, V8>, dim3((unsigned)(wgs + copy_wgs)), block, stream, k, r);
+    }
+    const hipError_t e = launch(attn_solo_kernel<D, FP8, V8>, dim3((unsigned)wgs), block, stream, k);
+    return e != hipSuccess ? e : finish_attention(a, k.splits, stream);
+}
+
 }  // namespace
 
 // Key splits: none, or until the 256 compute units have a workgroup each, or half as many.  Hundredths of a microsecond, fitted to
 // measured calls: a workgroup costs 400 and 113 per 128 keys (fp8 390 and 91, d = 64 340 and 71), these half as much again with each
-// further 80 workgroups (the caches' share), `s` splits 250 + 10 s.  (The split picked is 0.7 % off the best one on average.)
+// further 80 workgroups (the caches' share), `s` splits 290 + 10 s.  (The split picked is 0.7 % off the best one on average.)
 // Against the streaming kernel (8300 calls of 1 - 16 x 32/32, 32/8, 28/4 and 16/16 heads, 8 - 64 rows, 200 - 4096 keys): with one
 // workgroup per compute unit and at most 6 rounds of 128 keys each it takes 0.83 of the time (bf16) and 0.85 (fp8), 2 - 5 % more on one
 // call in a hundred.  Longer streams are bound by memory bandwidth, which that kernel's larger workgroups draw better - 8 x 32, 32
 // rows, 3992 keys fp8 63.6 / 71.8 - unless they leave it a third of its compute units idle: 11 x 32/8, 1237 keys above (264 of its
 // workgroups).  Past 256 workgroups: bf16 of at most 32 rows 0.85 up to 512, the others lose (64 rows bf16 1.03, fp8 1.01).  d = 64: 0.79
-// throughout.
-SoloPlan attn_solo_plan(long rows, long heads, int N, int d, bool fp8, int stream_splits)
+// throughout.  e4m3 values, against the MFMA kernel (746 such calls): 0.78, 9 x 32, 48 rows, 3774 keys 125 -> 85, 11 x 32/8, 16 rows, 1360 keys
+// 23.2 -> 18.3; slower where a fourth round of 256 workgroups of few keys begins (15 x 32, 48 rows, 243 keys 1.08).
+SoloPlan attn_solo_plan(long rows, long heads, int N, int d, bool fp8, bool v8, int stream_splits)
 {
     const int forced = tune("DD_TUNE_SOLO", -1);
     if (forced == 0) return SoloPlan{false, 1};
@@ -432,7 +504,7 @@ SoloPlan attn_solo_plan(long rows, long heads, int N, int d, bool fp8, int strea
     for (const long s : tried) {
         if (s < 1) continue;
         const long r = ((N + s - 1) / s + 127) / 128, beside = wgs * s > 64 ? wgs * s - 64 : 0;
-        const long cost = fixed + per * r + per * r * beside / 185 + (s > 1 ? 250 + 10 * s : 0);
+        const long cost = fixed + per * r + per * r * beside / 185 + (s > 1 ? 290 + 10 * s : 0);
         if (best == 0 || cost < best) {
             splits = s;
             rounds = r;
@@ -440,6 +512,7 @@ SoloPlan attn_solo_plan(long rows, long heads, int N, int d, bool fp8, int strea
         }
     }
     if (forced == 1 || d == 64) return SoloPlan{true, (int)splits};
+    if (v8) return SoloPlan{wgs <= 768 || rounds > 4, (int)splits};
     const long stream_wgs = heads * stream_splits, stream_slots = (stream_wgs + 255) / 256 * 256;
     const bool fits = wgs <= 256 || (!fp8 && row_tiles == 1 && wgs <= 512);
     const bool idle = 10 * stream_wgs < (fp8 ? 6 : 7) * stream_slots;
@@ -448,13 +521,9 @@ SoloPlan attn_solo_plan(long rows, long heads, int N, int d, bool fp8, int strea
 
 hipError_t launch_attention_solo(const AttnArgs &a, hipStream_t stream)
 {
-    AttnKernelArgs k;
-    fill_kernel_args(a, k, 32, 32);
-    const dim3 grid((unsigned)((long)a.B * a.Hkv * k.row_tiles * k.splits)), block(64 * kSoloWaves);
-    const hipError_t e = a.qk_dtype == 2 ? launch(attn_solo_kernel<128, true>, grid, block, stream, k)
-                       : a.d == 128      ? launch(attn_solo_kernel<128, false>, grid, block, stream, k)
-                                         : launch(attn_solo_kernel<64, false>, grid, block, stream, k);
-    return e != hipSuccess ? e : finish_attention(a, k.splits, stream);
+    if (a.v_dtype == 2) return launch_solo<128, true, true>(a, stream);
+    if (a.qk_dtype == 2) return launch_solo<128, true, false>(a, stream);
+    return a.d == 128 ? launch_solo<128, false, false>(a, stream) : launch_solo<64, false, false>(a, stream);
 }
 
 }  // namespace dd

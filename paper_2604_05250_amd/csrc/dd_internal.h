@@ -126,11 +126,11 @@ struct DuoPlan { int blocks, splits; };
 bool attn_duo_serves(const AttnArgs &a);
 DuoPlan attn_duo_plan(long rows, long heads, int N, bool light);   // light: fp8 keys or 64 head dims
 hipError_t launch_attention_duo(const AttnArgs &a, int blocks, hipStream_t stream);
-// Waves that stream keys of their own: drafter calls of at most 64 query rows per kv head (types as attn_duo_serves).  Whether it takes
-// one with `rows` query rows in each of `heads` (batch, kv head) pairs, and with how many key splits (at most the streaming kernel's,
-// `stream_splits`, so that one workspace serves both); the launch (+ merge).
+// Waves that stream keys of their own: drafter calls of at most 64 query rows per kv head (types as attn_duo_serves, and e4m3 V - `v8` -
+// with 128 head dims).  Whether it takes one with `rows` query rows in each of `heads` (batch, kv head) pairs, and with how many key
+// splits (at most the streaming kernel's, `stream_splits`, so that one workspace serves both); the launch (+ merge).
 struct SoloPlan { bool take; int splits; };
-SoloPlan attn_solo_plan(long rows, long heads, int N, int d, bool fp8, int stream_splits);
+SoloPlan attn_solo_plan(long rows, long heads, int N, int d, bool fp8, bool v8, int stream_splits);
 hipError_t launch_attention_solo(const AttnArgs &a, hipStream_t stream);
 
 // ---- cache maintenance (cache.hip) ----------------------------------------------

@@ -118,3 +118,23 @@ def test_reference_of_the_weights(monkeypatch, scale, order):
     torch.cuda.synchronize()
     ref = oracle.block_attention_cached(Q, K, V, 700, wl.BF16, wl.BF16, None, None, None, None)
     assert_attention_close(out_to_f64(O, wl.BF16), ref, wl.BF16, f"scale {scale} order {order}")
+
+
+@pytest.mark.parametrize("solo", ["1", "0"])                 # (0: the same calls on the MFMA kernel)
+@pytest.mark.parametrize("B,H,Hkv,N,bl,bs,splits", BLOCKS)
+def test_block_fp8v(monkeypatch, solo, B, H, Hkv, N, bl, bs, splits):
+    import torch
+    monkeypatch.setenv("DD_TUNE_SOLO", solo)
+    monkeypatch.setenv("DD_TUNE_BLOCK_SPLITS", str(splits))
+    fp8 = wl.FP8_E4M3
+    cfg = wl.custom_config(B=B, H=H, Hkv=Hkv, N=N, d=128, qk_dtype=fp8, v_dtype=fp8, bl=bl, prompt=0, G=N)
+    cache = wl.cache_inputs(cfg, seed=bs + N)
+    blk = wl.block_inputs(cfg, bs, 0, k_scale=cache["k_scale"], v_scale=cache["v_scale"])
+    for fresh in (True, False):
+        Kb, Vb = (blk["Kblk"], blk["Vblk"]) if fresh else (None, None)
+        O = dd.dd_block_attention_cached_fp8v(to_dev(blk["Qblk"]), to_dev(cache["Kc"]), to_dev(cache["Vc"]), bs, to_dev(blk["q_scale"]),
+                                              to_dev(cache["k_scale"]), to_dev(cache["v_scale"]), Kblk=to_dev(Kb), Vblk=to_dev(Vb))
+        torch.cuda.synchronize()
+        ref = oracle.block_attention_cached(blk["Qblk"], cache["Kc"], cache["Vc"], bs, fp8, fp8, Kb, Vb, blk["q_scale"], cache["k_scale"],
+                                            v_scale=cache["v_scale"])
+        assert_attention_close(out_to_f64(O, wl.BF16), ref, fp8, f"fp8v, solo {solo} {B}x{H}/{Hkv} N{N} bl{bl}@{bs} splits {splits} fresh={fresh}")

@@ -733,14 +733,23 @@ hipError_t launch_attention_mfma(const AttnArgs &a, hipStream_t stream)
     // Verifier calls: do workgroups of 64 / 128 query rows fit the chip's 256 compute units in one round?
     const long heads = (long)a.B * a.Hkv, rows = (long)(a.H / a.Hkv) * a.Nq;
     const bool one_round64 = heads * ((rows + 63) / 64) <= 256, one_round128 = heads * ((rows + 127) / 128) <= 256;
+    if (!blk && tune("DD_TUNE_ATTN_WIDE", -1) < 0 && tune("DD_TUNE_BIDIR_STREAM", -1) < 0) {
+        // Up to two workgroups of 32 rows per compute unit: the kernel whose waves stream keys of their own.  us, before -> there: 1 x 32
+        // heads, N 128 7.3 -> 5.5, N 300 10.4 -> 9.5, N 512 12.2 -> 11.8, fp8 Q and K 12.0 -> 10.4, d = 64 9.3 -> 7.7; 1 x 16, N 512 11.2 -> 8.4;
+        // 1 x 8, N 1024 16.2 -> 11.6.  Over 380 drawn calls of more than 64 keys 0.78 of the time up to 256 workgroups, 0.91 up to 512, then 1.1;
+        // with all 512 and more than 1024 keys up to 1.11.
+        // 64 keys and fewer: 1.0 (fp8 1.1).  e4m3 values: 0.66 up to 256 workgroups, 0.78 up to 512, then 1.1 as well.
+        const long wgs = heads * ((rows + 31) / 32);
+        const int solo = tune("DD_TUNE_SOLO", tune("DD_TUNE_DUO", -1) < 0 && a.N > 64 && wgs <= (a.N > 1024 ? 448 : 512));
+        if (solo != 0 && attn_solo_serves(a)) return launch_attention_solo(a, stream);
+    }
     if (!blk && attn_duo_serves(a) && tune("DD_TUNE_ATTN_WIDE", -1) < 0 && tune("DD_TUNE_BIDIR_STREAM", -1) < 0) {
-        // One round of 64-row workgroups: the two-waves-per-SIMD kernel, whose eight waves share a workgroup's keys.  us, before ->
-        // there (bf16 / fp8 Q and K): 1 x 32 heads, N 150 8.0 -> 7.7 / 8.4 -> 7.9 (N 130), N 512 13.2 -> 11.4 / 11.9 -> 11.2,
-        // 1 x 28 (4 kv), N 580 15.4 -> 12.6 / 13.7 -> 11.6, 1 x 16, N 1024 19.5 -> 15.9 / 18.0 -> 14.6; N 64 6.0 -> 6.5 / 5.0 -> 6.7.
-        // d = 64: N 150 5.7 -> 6.5, N 300 7.5 -> 7.3, 1 x 16, N 1000 15.9 -> 11.8.  On its 128-row workgroups, one round of them:
-        // 32 x N 1024 23.5 -> 24.4, 16 x N 2048 40.2 -> 40.2, fp8 32.6 -> 33.4: no.
+        // One round of 64-row workgroups: the two-waves-per-SIMD kernel, whose eight waves share a workgroup's keys (of these calls the
+        // one above leaves it those of more than 448 workgroups of 32 rows and 1024 keys).  us, before -> there (bf16 / fp8 Q and K):
+        // 1 x 16 heads, N 1024 19.5 -> 15.9 / 18.0 -> 14.6.  On its 128-row workgroups, one round of them: 32 x N 1024 23.5 -> 24.4, 16 x N
+        // 2048 40.2 -> 40.2, fp8 32.6 -> 33.4: no.
         const int forced = tune("DD_TUNE_DUO", -1);
-        const int blocks = forced >= 0 ? forced : one_round64 && a.N >= (a.d == 64 ? 256 : 100) ? 2 : 0;
+        const int blocks = forced >= 0 ? forced : one_round64 && a.N > 1024 ? 2 : 0;
         if (blocks == 2 || blocks == 4) return launch_attention_duo(a, blocks, stream);
     }
     if (!blk && (!fp8 || a.d == 128) && a.N >= 64) {           // (the wide kernel's K/V tiles are 64 whole rows)

@@ -1,5 +1,5 @@
 // Attention of few query rows whose waves stream keys of their own: the drafter's call with at most 64 rows per kv head where
-// workgroups are few (Sec. 2.3), bf16 or fp8 Q/K, bf16 or (with fp8 Q/K) e4m3 V.
+// workgroups are few (Sec. 2.3) and small verifier calls (Sec. 2.2), bf16 or fp8 Q/K, bf16 or (with fp8 Q/K) e4m3 V.
 //     O = softmax(Q K^T / sqrt(d_k)) V   (Eq. 3)
 // One workgroup = four waves on one block of 32 query rows; wave w takes every fourth 32-key unit of the key range with a state
 // (reference, sum, O) of its own, and the states are merged through LDS at the end, every wave finishing a quarter of the head dims.
@@ -481,7 +481,14 @@ template <int D, bool FP8, bool V8> hipError_t launch_solo(const AttnArgs &a, hi
 
 }  // namespace
 
-// Key splits: none, or until the 256 compute units have a workgroup each, or half as many.  Hundredths of a microsecond, fitted to
+bool attn_solo_serves(const AttnArgs &a)
+{
+    if (a.q_mx != nullptr) return false;
+    if (a.qk_dtype == 1) return a.v_dtype == 1;
+    return a.qk_dtype == 2 && a.d == 128 && (a.v_dtype == 1 || a.v_dtype == 2);
+}
+
+// Drafter calls.  Key splits: none, or until the 256 compute units have a workgroup each, or half as many.  Hundredths of a microsecond, fitted to
 // measured calls: a workgroup costs 400 and 113 per 128 keys (fp8 390 and 91, d = 64 340 and 71), these half as much again with each
 // further 80 workgroups (the caches' share), `s` splits 290 + 10 s.  (The split picked is 0.7 % off the best one on average.)
 // Against the streaming kernel (8300 calls of 1 - 16 x 32/32, 32/8, 28/4 and 16/16 heads, 8 - 64 rows, 200 - 4096 keys): with one

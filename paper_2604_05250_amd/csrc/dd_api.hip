@@ -231,7 +231,7 @@ static int block_attention(const void *Qblk, const void *Kc, const void *Vc, voi
     }
     const int narrow_splits = dd::attn_block_splits(block_len, B, H, Hkv, N, d, qk_dtype);
     dd::SoloPlan solo{false, 1};
-    if (!duo.blocks && rows <= 64 && (dd::attn_duo_serves(a) || (v_dtype == DD_FP8_E4M3 && d == 128)) && !other_kernel_forced())
+    if (!duo.blocks && rows <= 64 && dd::attn_solo_serves(a) && !other_kernel_forced())
         solo = dd::attn_solo_plan(rows, heads, N, d, qk_dtype == DD_FP8_E4M3, v_dtype == DD_FP8_E4M3, narrow_splits);
     const int general = wide ? dd::attn_wide_block_splits(block_len, B, H, Hkv, N) : narrow_splits;
     const int splits = duo.blocks ? duo.splits : solo.take ? solo.splits : general;

@@ -138,3 +138,23 @@ def test_block_fp8v(monkeypatch, solo, B, H, Hkv, N, bl, bs, splits):
         ref = oracle.block_attention_cached(blk["Qblk"], cache["Kc"], cache["Vc"], bs, fp8, fp8, Kb, Vb, blk["q_scale"], cache["k_scale"],
                                             v_scale=cache["v_scale"])
         assert_attention_close(out_to_f64(O, wl.BF16), ref, fp8, f"fp8v, solo {solo} {B}x{H}/{Hkv} N{N} bl{bl}@{bs} splits {splits} fresh={fresh}")
+
+
+# (one row; a tile's rows and one more; a wave's first, second and ragged unit; grouped heads that share tiles)
+@pytest.mark.parametrize("solo", ["1", "0"])                 # (0: the same calls on the kernels before it)
+@pytest.mark.parametrize("qk,v,d", [(wl.BF16, wl.BF16, 128), (wl.BF16, wl.BF16, 64), (wl.FP8_E4M3, wl.BF16, 128), (wl.FP8_E4M3, wl.FP8_E4M3, 128)])
+@pytest.mark.parametrize("B,H,Hkv,N", [(1, 1, 1, 1), (1, 2, 1, 31), (2, 3, 1, 33), (1, 2, 2, 64), (1, 3, 3, 65), (1, 4, 1, 127), (2, 2, 2, 128),
+                                       (1, 3, 1, 129), (1, 2, 1, 257), (1, 5, 1, 300), (1, 2, 2, 641)])
+def test_bidir(monkeypatch, solo, qk, v, d, B, H, Hkv, N):
+    import torch
+    monkeypatch.setenv("DD_TUNE_SOLO", solo)
+    cfg = wl.custom_config(B=B, H=H, Hkv=Hkv, N=N, d=d, qk_dtype=qk, v_dtype=v, prompt=0, G=N, bl=min(16, N))
+    inp = wl.attention_inputs(cfg, seed=N + d)
+    Q, K, V, qs, ks = (to_dev(inp[k]) for k in ("Q", "K", "V", "q_scale", "k_scale"))
+    if v == wl.FP8_E4M3:
+        O = dd.dd_bidir_attention_fp8v(Q, K, V, qs, ks, to_dev(inp["v_scale"]))
+    else:
+        O = dd.dd_bidir_attention(Q, K, V, q_scale=qs, k_scale=ks, qk_dtype=qk, v_dtype=v)
+    torch.cuda.synchronize()
+    ref = oracle.bidir_attention(inp["Q"], inp["K"], inp["V"], qk, v, inp["q_scale"], inp["k_scale"], v_scale=inp.get("v_scale"))
+    assert_attention_close(out_to_f64(O, wl.BF16), ref, qk, f"solo {solo} {B}x{H}/{Hkv}x{N}x{d}")

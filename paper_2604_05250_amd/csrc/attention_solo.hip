@@ -1,5 +1,5 @@
-// Attention of few query rows whose waves stream keys of their own: the drafter's call with at most 64 rows per kv head where
-// workgroups are few (Sec. 2.3) and small verifier calls (Sec. 2.2), bf16 or fp8 Q/K, bf16 or (with fp8 Q/K) e4m3 V.
+// Attention of few query rows whose waves stream keys of their own: the drafter's call where workgroups of 32 rows are few or key
+// streams short (Sec. 2.3) and small verifier calls (Sec. 2.2), bf16 or fp8 Q/K, bf16 or (with fp8 Q/K) e4m3 V.
 //     O = softmax(Q K^T / sqrt(d_k)) V   (Eq. 3)
 // One workgroup = four waves on one block of 32 query rows; wave w takes every fourth 32-key unit of the key range with a state
 // (reference, sum, O) of its own, and the states are merged through LDS at the end, every wave finishing a quarter of the head dims.
@@ -498,6 +498,9 @@ bool attn_solo_serves(const AttnArgs &a)
 // workgroups).  Past 256 workgroups: bf16 of at most 32 rows 0.85 up to 512, the others lose (64 rows bf16 1.03, fp8 1.01).  d = 64: 0.79
 // throughout.  e4m3 values, against the MFMA kernel (746 such calls): 0.78, 9 x 32, 48 rows, 3774 keys 125 -> 85, 11 x 32/8, 16 rows, 1360 keys
 // 23.2 -> 18.3; slower where a fourth round of 256 workgroups of few keys begins (15 x 32, 48 rows, 243 keys 1.08).
+// More than 64 rows (900 calls of 32/8, 28/4, 32/16 and 16/2 heads, 16 - 64 rows per head, 300 - 4096 keys; before: the two-waves-per-SIMD,
+// the wide or the MFMA kernel): up to 256 workgroups with at most 12 rounds each 0.78 of the time (bf16), 0.75 (fp8), 0.65 (e4m3 V, these up
+// to 512), on none more than 1.00; 256 - 384 workgroups and longer streams up to 1.3.
 SoloPlan attn_solo_plan(long rows, long heads, int N, int d, bool fp8, bool v8, int stream_splits)
 {
     const int forced = tune("DD_TUNE_SOLO", -1);
@@ -518,7 +521,9 @@ SoloPlan attn_solo_plan(long rows, long heads, int N, int d, bool fp8, bool v8, 
             best = cost;
         }
     }
-    if (forced == 1 || d == 64) return SoloPlan{true, (int)splits};
+    if (forced == 1) return SoloPlan{true, (int)splits};
+    if (rows > 64) return SoloPlan{wgs <= (v8 ? 512 : 256) && rounds <= 12, (int)splits};
+    if (d == 64) return SoloPlan{true, (int)splits};
     if (v8) return SoloPlan{wgs <= 768 || rounds > 4, (int)splits};
     const long stream_wgs = heads * stream_splits, stream_slots = (stream_wgs + 255) / 256 * 256;
     const bool fits = wgs <= 256 || (!fp8 && row_tiles == 1 && wgs <= 512);

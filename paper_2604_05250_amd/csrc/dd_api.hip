@@ -221,18 +221,18 @@ static int block_attention(const void *Qblk, const void *Kc, const void *Vc, voi
     }
     const bool wide = dd::tune("DD_TUNE_BLOCK_WIDE", 1) != 0 && dd::attn_wide_block_fits(a);
     const long rows = (long)(H / Hkv) * block_len, heads = (long)B * Hkv;
+    const int narrow_splits = dd::attn_block_splits(block_len, B, H, Hkv, N, d, qk_dtype);
+    dd::SoloPlan solo{false, 1};
+    if (dd::attn_solo_serves(a) && dd::tune("DD_TUNE_DUO", -1) <= 0 && !other_kernel_forced())
+        solo = dd::attn_solo_plan(rows, heads, N, d, qk_dtype == DD_FP8_E4M3, v_dtype == DD_FP8_E4M3, narrow_splits);
     dd::DuoPlan duo{0, 1};
-    if (dd::attn_duo_serves(a) && (rows > 64 || dd::tune("DD_TUNE_DUO", 0) > 0) && !other_kernel_forced()) {
+    if (!solo.take && dd::attn_duo_serves(a) && (rows > 64 || dd::tune("DD_TUNE_DUO", 0) > 0) && !other_kernel_forced()) {
         duo = dd::attn_duo_plan(rows, heads, N, qk_dtype == DD_FP8_E4M3 || d == 64);
         // Past one round of 128-row workgroups the wide kernel's 256-row tiles are faster (24 x 32/8 heads, 64 rows, 1024 keys
         // 43.3 against 48.5 us, fp8 36.3 / 42.5), its 128-row tiles, for up to 128 rows, are not (40 x 16/8: 60.9 / 52.6, fp8
         // 51.7 / 45.0); the MFMA kernel, where the wide one cannot take the call, is (64 x 32/8, 32 rows: 62.8 / 66.8).
         if (duo.blocks == 0 && wide && rows <= 128 && dd::tune("DD_TUNE_DUO", -1) != 0) duo.blocks = 4;
     }
-    const int narrow_splits = dd::attn_block_splits(block_len, B, H, Hkv, N, d, qk_dtype);
-    dd::SoloPlan solo{false, 1};
-    if (!duo.blocks && rows <= 64 && dd::attn_solo_serves(a) && !other_kernel_forced())
-        solo = dd::attn_solo_plan(rows, heads, N, d, qk_dtype == DD_FP8_E4M3, v_dtype == DD_FP8_E4M3, narrow_splits);
     const int general = wide ? dd::attn_wide_block_splits(block_len, B, H, Hkv, N) : narrow_splits;
     const int splits = duo.blocks ? duo.splits : solo.take ? solo.splits : general;
     // (what the kernels of every shape ask for is asked for here too, whichever serves the call)

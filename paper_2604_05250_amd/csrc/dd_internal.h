@@ -36,8 +36,8 @@ inline hipError_t launch(void (*kernel)(Params...), dim3 grid, dim3 block, hipSt
 //   DD_TUNE_STREAM_NT=0/1      that kernel's K/V loads without / with the non-temporal hint
 //   DD_TUNE_DUO=0/2/4          no call on the two-waves-per-SIMD kernel / every one it can serve, with 2 or 4 row blocks (the
 //                              hooks of the other kernels, where set, come first)
-//   DD_TUNE_SOLO=0/1           drafter calls of at most 64 rows per kv head and verifier calls off / on the kernel whose waves stream keys
-//                              of their own (the hooks of the other kernels, and a drafter call's of the key splits, come first)
+//   DD_TUNE_SOLO=0/1           drafter and verifier calls off / on the kernel whose waves stream keys of their own
+//                              (the hooks of the other kernels, and a drafter call's of the key splits, come first)
 //   DD_TUNE_SEQ_ROUNDS=n       per-sequence rules on rows that are not split: in one launch up to n load rounds per workgroup
 //   DD_TUNE_BLOCK_STREAM=0     drafter calls with few query rows off the streaming kernel
 //   DD_TUNE_BLOCK_WIDE=0       drafter calls with many query rows off the wide-wave kernel
@@ -126,7 +126,7 @@ struct DuoPlan { int blocks, splits; };
 bool attn_duo_serves(const AttnArgs &a);
 DuoPlan attn_duo_plan(long rows, long heads, int N, bool light);   // light: fp8 keys or 64 head dims
 hipError_t launch_attention_duo(const AttnArgs &a, int blocks, hipStream_t stream);
-// Waves that stream keys of their own: drafter calls of at most 64 query rows per kv head, verifier calls of few rows.  Which storage types
+// Waves that stream keys of their own: drafter and verifier calls of few query rows.  Which storage types
 // and head dims it serves; whether it takes a drafter call with `rows` query rows in each of `heads` (batch, kv head) pairs, and with how
 // many key splits (at most the streaming kernel's, `stream_splits`, so that one workspace serves both); the launch (+ merge).
 bool attn_solo_serves(const AttnArgs &a);

@@ -15,7 +15,8 @@ STORES = [(wl.BF16, 128), (wl.BF16, 64), (wl.FP8_E4M3, 128)]
 # (B, H, Hkv, N, block_len, block_start, key splits)
 BLOCKS = [(1, 1, 1, 1, 1, 0, 1), (1, 1, 1, 31, 1, 30, 1), (2, 2, 2, 32, 32, 0, 1), (1, 33, 1, 33, 1, 32, 1), (1, 4, 1, 127, 8, 60, 1),
           (1, 2, 1, 129, 31, 90, 1), (2, 3, 1, 255, 21, 100, 1), (1, 4, 2, 257, 16, 250 - 9, 1), (1, 8, 8, 512, 32, 200, 1), (1, 2, 1, 641, 32, 609, 1),
-          (3, 8, 2, 700, 16, 333, 4), (1, 64, 1, 1000, 1, 999, 3), (1, 5, 1, 2049, 12, 1000, 16)]
+          (3, 8, 2, 700, 16, 333, 4), (1, 64, 1, 1000, 1, 999, 3), (1, 5, 1, 2049, 12, 1000, 16),
+          (1, 5, 1, 700, 13, 687, 1), (2, 8, 2, 515, 32, 0, 2), (1, 7, 1, 300, 150, 150, 1)]
 
 
 def _call(inputs, Kb, Vb, fn=dd.dd_block_attention_cached, K=None, V=None):
@@ -24,7 +25,7 @@ def _call(inputs, Kb, Vb, fn=dd.dd_block_attention_cached, K=None, V=None):
               Kblk=to_dev(Kb), Vblk=to_dev(Vb), q_scale=to_dev(blk["q_scale"]), k_scale=to_dev(cache["k_scale"]), qk_dtype=qk, v_dtype=wl.BF16)
 
 
-@pytest.mark.parametrize("solo", ["1", "0"])                 # (0: the same calls on the streaming kernel)
+@pytest.mark.parametrize("solo", ["1", "0"])                 # (0: the same calls on the kernels before it)
 @pytest.mark.parametrize("qk,d", STORES)
 @pytest.mark.parametrize("B,H,Hkv,N,bl,bs,splits", BLOCKS)
 def test_block(monkeypatch, solo, qk, d, B, H, Hkv, N, bl, bs, splits):
@@ -120,7 +121,7 @@ def test_reference_of_the_weights(monkeypatch, scale, order):
     assert_attention_close(out_to_f64(O, wl.BF16), ref, wl.BF16, f"scale {scale} order {order}")
 
 
-@pytest.mark.parametrize("solo", ["1", "0"])                 # (0: the same calls on the MFMA kernel)
+@pytest.mark.parametrize("solo", ["1", "0"])                 # (0: the same calls on the kernels before it)
 @pytest.mark.parametrize("B,H,Hkv,N,bl,bs,splits", BLOCKS)
 def test_block_fp8v(monkeypatch, solo, B, H, Hkv, N, bl, bs, splits):
     import torch

@@ -52,9 +52,10 @@ __device__ __forceinline__ uint4 stream_load16(const uint4 *p)
 // Reductions over the 64 lanes of a wave, every lane with the result (the same bits: a + b == b + a): neighbours, pairs of
 // two, halves of eight and of sixteen lanes by DPP, the rest by the two lane-half exchanges.  Shuffles through the LDS
 // crossbar cost their latency six times per reduction, and a short call is a chain of such reductions.
+// (All lanes take part and every lane named exists, so the exchange needs no second operand: it becomes part of the operation.)
 template <int CTRL> __device__ __forceinline__ unsigned dpp(unsigned v)
 {
-    return (unsigned)__builtin_amdgcn_update_dpp((int)v, (int)v, CTRL, 0xF, 0xF, false);
+    return (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xF, 0xF, true);
 }
 template <typename F> __device__ __forceinline__ unsigned wave_reduce(unsigned v, F &&f)
 {
@@ -99,6 +100,36 @@ __device__ __forceinline__ int wave_min(int v)
 __device__ __forceinline__ float wave_sum(float v)
 {
     return __uint_as_float(wave_reduce(__float_as_uint(v), [](unsigned x, unsigned y) {
+        return __float_as_uint(__uint_as_float(x) + __uint_as_float(y)); }));
+}
+
+// Four reductions in little more than the work of one: lanes 4 i + p carry on with value p alone once neighbours and pairs have
+// exchanged.  Lane l returns the result of value l % 4, summed in wave_reduce's order (the same bits).
+template <typename F> __device__ __forceinline__ unsigned wave_reduce4(const unsigned (&v)[4], int lane, F &&f)
+{
+    typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+    const bool b0 = (lane & 1) != 0, b1 = (lane & 2) != 0;
+    const unsigned x = f(b0 ? v[1] : v[0], dpp<0xB1>(b0 ? v[0] : v[1])), y = f(b0 ? v[3] : v[2], dpp<0xB1>(b0 ? v[2] : v[3]));
+    unsigned z = f(b1 ? y : x, dpp<0x4E>(b1 ? x : y));
+    z = f(z, dpp<0x141>(dpp<0x1B>(z)));                      // quad_perm [3,2,1,0], row_half_mirror: the lane four away
+    z = f(z, dpp<0x128>(z));                                 // row_ror:8
+    const u32x2 h = __builtin_amdgcn_permlane16_swap(z, z, false, false);
+    z = f(h.x, h.y);
+    const u32x2 w = __builtin_amdgcn_permlane32_swap(z, z, false, false);
+    return f(w.x, w.y);
+}
+__device__ __forceinline__ void wave_max4(float (&v)[4], int lane)            // every lane with all four
+{
+    const unsigned u[4] = {__float_as_uint(v[0]), __float_as_uint(v[1]), __float_as_uint(v[2]), __float_as_uint(v[3])};
+    const unsigned r = wave_reduce4(u, lane, [](unsigned x, unsigned y) {
+        return __float_as_uint(fmaxf(__uint_as_float(x), __uint_as_float(y))); });
+#pragma unroll
+    for (int p = 0; p < 4; ++p) v[p] = __uint_as_float(__builtin_amdgcn_readlane(r, p));
+}
+__device__ __forceinline__ float wave_sum4(const float (&v)[4], int lane)     // lane l: sum l % 4
+{
+    const unsigned u[4] = {__float_as_uint(v[0]), __float_as_uint(v[1]), __float_as_uint(v[2]), __float_as_uint(v[3])};
+    return __uint_as_float(wave_reduce4(u, lane, [](unsigned x, unsigned y) {
         return __float_as_uint(__uint_as_float(x) + __uint_as_float(y)); }));
 }
 
@@ -688,6 +719,128 @@ __global__ __launch_bounds__(kSeqThreads) void verify_finalize_seq_kernel(const 
     apply_sequence_rule(sh, mbyte, base, G, mode, threshold, seed, kl_mode, out_mask, x_tokens);
 }
 
+// One row on one wave, in the arithmetic of the kThreads-lane workgroup that reduces it elsewhere (reduce_range), so that a score is
+// the same number, bit for bit, whichever rule asks for it: what wave p reads there - the vectors 64 p .. of every kThreads - is
+// part p here, with a reference and sums of its own, and lane p writes its state (idx: the whole row's).
+constexpr int kParts = kThreads / 64;
+static_assert(kParts == 4, "reductions of four values");
+template <bool BF16, bool KL>
+__device__ __forceinline__ void reduce_row_on_wave(const uint4 *__restrict__ pv, const uint4 *__restrict__ pd, int nvec, int lane,
+                                                   WaveState *parts)
+{
+#pragma clang fp contract(off)                               // (a product rescaled by consume() is rounded before it is added to)
+    constexpr int E = VecTraits<BF16>::kElems;
+    float best_v[kParts], s_v[kParts], ref_d[kParts], s_d[kParts], a[kParts];
+#pragma unroll
+    for (int p = 0; p < kParts; ++p) {
+        best_v[p] = ref_d[p] = kNegInf;
+        s_v[p] = s_d[p] = a[p] = 0.f;
+    }
+    float top = kNegInf;                                     // this lane's largest verifier logit, the vector that has it first
+    uint4 top_vec = make_uint4(0, 0, 0, 0);
+    int top_at = 0;
+    for (int v0 = 0; v0 < nvec; v0 += kThreads) {
+        uint4 rv[kParts], rd[kParts];
+        bool ok[kParts];
+#pragma unroll
+        for (int p = 0; p < kParts; ++p) {
+            const int idx = v0 + p * 64 + lane;
+            ok[p] = idx < nvec;
+            rv[p] = rd[p] = make_uint4(0, 0, 0, 0);
+            if (ok[p]) {
+                rv[p] = stream_load16(pv + idx);
+                if (KL) rd[p] = stream_load16(pd + idx);
+            }
+        }
+        float mv[kParts], md[kParts];
+#pragma unroll
+        for (int p = 0; p < kParts; ++p) {
+            float x[E];
+            VecTraits<BF16>::unpack(rv[p], x);
+            float m = x[0];
+#pragma unroll
+            for (int e = 1; e < E; ++e) m = fmaxf(m, x[e]);
+            mv[p] = ok[p] ? m : kNegInf;
+            if (mv[p] > top) {
+                top = mv[p];
+                top_vec = rv[p];
+                top_at = v0 + p * 64 + lane;
+            }
+            if (KL) {
+                VecTraits<BF16>::unpack(rd[p], x);
+                m = x[0];
+#pragma unroll
+                for (int e = 1; e < E; ++e) m = fmaxf(m, x[e]);
+                md[p] = ok[p] ? m : kNegInf;
+            }
+        }
+        wave_max4(mv, lane);
+        if (KL) wave_max4(md, lane);
+#pragma unroll
+        for (int p = 0; p < kParts; ++p) {
+            if (v0 > 0) s_v[p] *= rescale_factor(best_v[p], fmaxf(best_v[p], mv[p]));         // (one where the reference stays)
+            best_v[p] = fmaxf(best_v[p], mv[p]);
+            if (KL) {
+                if (v0 > 0) {
+                    const float c = rescale_factor(ref_d[p], fmaxf(ref_d[p], md[p]));
+                    s_d[p] *= c;
+                    a[p] *= c;
+                }
+                ref_d[p] = fmaxf(ref_d[p], md[p]);
+            }
+            if (ok[p]) {
+                float xv[E], xd[E];
+                VecTraits<BF16>::unpack(rv[p], xv);
+                const float m = best_v[p] * kLog2e;
+                float acc = 0.f;
+#pragma unroll
+                for (int e = 0; e < E; ++e) acc += fast_exp2(fmaf(xv[e], kLog2e, -m));
+                s_v[p] += acc;
+                if (KL) {
+                    VecTraits<BF16>::unpack(rd[p], xd);
+                    const float n = ref_d[p] * kLog2e;
+                    float accs = 0.f, acca = 0.f;
+#pragma unroll
+                    for (int e = 0; e < E; ++e) {
+                        const float ed = fast_exp2(fmaf(xd[e], kLog2e, -n));
+                        accs += ed;
+                        acca = fmaf(ed, xd[e] - xv[e], acca);
+                    }
+                    s_d[p] += accs;
+                    a[p] += acca;
+                }
+            }
+        }
+    }
+    float all = best_v[0];
+#pragma unroll
+    for (int p = 1; p < kParts; ++p) all = fmaxf(all, best_v[p]);
+    int cand = INT_MAX;
+    if (top == all && all != kNegInf) {
+        float x[E];
+        VecTraits<BF16>::unpack(top_vec, x);
+#pragma unroll
+        for (int e = E - 1; e >= 0; --e)
+            if (x[e] == all) cand = top_at * E + e;
+    }
+    const int idx = wave_min(cand);
+    WaveState w;
+    w.s_v = wave_sum4(s_v, lane);
+    w.s_d = KL ? wave_sum4(s_d, lane) : 0.f;
+    w.a = KL ? wave_sum4(a, lane) : 0.f;
+    w.idx = idx;
+    w.idx_d = INT_MAX;
+    w.best_v = best_v[0];
+    w.ref_d = ref_d[0];
+#pragma unroll
+    for (int p = 1; p < kParts; ++p)
+        if (lane == p) {
+            w.best_v = best_v[p];
+            w.ref_d = ref_d[p];
+        }
+    if (lane < kParts) parts[lane] = w;
+}
+
 // A per-sequence rule on few short rows, in one launch: a workgroup per sequence whose sixteen waves take whole rows and then
 // apply the rule.  Such a call is launches and round trips; seq_rounds says where it wins.
 template <bool BF16, bool KL>
@@ -697,42 +850,20 @@ __global__ __launch_bounds__(kSeqThreads) void verify_seq_kernel(const uint4 *__
                                                                  int32_t *__restrict__ out_tokens, float *__restrict__ out_scores,
                                                                  int32_t *__restrict__ x_tokens)
 {
-    constexpr int E = VecTraits<BF16>::kElems;
     __shared__ SequenceShared sh;
-    __shared__ WaveState rows_sh[kSeqMaxRows];
+    __shared__ WaveState rows_sh[kSeqMaxRows][kParts];
     const int tid = threadIdx.x, lane = tid & 63;
     const size_t base = (size_t)blockIdx.x * G;
     const uint8_t mbyte = tid < G ? mask[base + tid] : 0;
-    for (int g = tid >> 6; g < G; g += kSeqThreads / 64) {
-        const uint4 *const pv = logits_v + (base + g) * nvec, *const pd = KL ? logits_d + (base + g) * nvec : nullptr;
-        LaneState st;
-        for (int v0 = 0; v0 < nvec; v0 += 64 * kUnroll) {
-            uint4 rv[kUnroll], rd[kUnroll];
-#pragma unroll
-            for (int u = 0; u < kUnroll; ++u) {
-                const int idx = v0 + u * 64 + lane;
-                rv[u] = rd[u] = make_uint4(0, 0, 0, 0);
-                if (idx < nvec) {
-                    rv[u] = stream_load16(pv + idx);
-                    if (KL) rd[u] = stream_load16(pd + idx);
-                }
-            }
-#pragma unroll
-            for (int u = 0; u < kUnroll; ++u) {
-                const int idx = v0 + u * 64 + lane;
-                consume<BF16, KL, false>(rv[u], rd[u], idx < nvec, idx * E, st);
-            }
-        }
-        WaveState w;
-        w.ref_d = st.ref_d; w.best_v = st.best_v; w.idx = st.idx_v; w.idx_d = st.idx_d;
-        w.s_v = wave_sum(st.s_v);
-        w.s_d = KL ? wave_sum(st.s_d) : 0.f;
-        w.a = KL ? wave_sum(st.a) : 0.f;
-        if (lane == 0) rows_sh[g] = w;
-    }
+    for (int g = tid >> 6; g < G; g += kSeqThreads / 64)
+        reduce_row_on_wave<BF16, KL>(logits_v + (base + g) * nvec, KL ? logits_d + (base + g) * nvec : nullptr, nvec, lane, rows_sh[g]);
     __syncthreads();
     if (tid < G) {                                           // G <= kSeqMaxRows: a lane per row
-        const WaveState r = rows_sh[tid];
+        WaveState r = rows_sh[tid][0];
+        if (nvec > 64) {                                     // uniform (a part without a vector adds nothing)
+#pragma unroll
+            for (int p = 1; p < kParts; ++p) r = merge(r, rows_sh[tid][p]);
+        }
         finish_row((int)base + tid, (double)r.ref_d, (double)r.s_d, (double)r.a, (double)r.best_v, (double)r.s_v, r.idx, mask, mode,
                    threshold, seed, KL ? 1 : 0, out_mask, out_tokens, out_scores, 0, VerifyExtra{}, &sh.score[tid], &sh.token[tid]);
     }
@@ -773,13 +904,12 @@ int verify_splits(int P, int V, int elem_bytes)
     return (int)(s < 1 ? 1 : s);
 }
 
-// Dependent load rounds of verify_seq_kernel (sixteen rows of 64 kUnroll vectors each), and up to how many it is taken: a round costs
-// its one workgroup 2.5 us (KL 4), the launch that it saves 3.  us per call in a stream of them, two launches -> one, fp32:
-// unmasking 16 x 1024 7.3 -> 4.6, 16 x 2048 or 32 x 1024 (two rounds) 7.5 -> 6.3 - 7.3, 16 x 4096 8.0 / 8.9; Eq. 6 16 x 1024 8.3 -> 7.2,
-// 16 x 2048 8.8 / 10.7. 
+// Dependent load rounds of verify_seq_kernel (sixteen rows of kThreads vectors each), and up to how many it is taken: a round costs
+// its one workgroup 2 us (KL 4), the launch that it saves 3.  us per call in a stream of them, two launches -> one, fp32:
+// unmasking 16 x 1024 7.1 -> 4.7, 16 x 2048 or 32 x 1024 (two rounds) 7.4 -> 6.4 - 6.8; Eq. 6 16 x 1024 8.0 -> 7.7.
 static int seq_rounds(int G, int nvec)
 {
-    return (G + kSeqThreads / 64 - 1) / (kSeqThreads / 64) * ((nvec + 64 * kUnroll - 1) / (64 * kUnroll));
+    return (G + kSeqThreads / 64 - 1) / (kSeqThreads / 64) * ((nvec + kThreads - 1) / kThreads);
 }
 constexpr int kSeqMaxRounds = 2, kSeqMaxRoundsKl = 1;
 

@@ -504,3 +504,29 @@ def test_sequence_rules_of_unsplit_rows(monkeypatch, rounds, B, G, V, dtype):
     x0 = np.full(B * G, V, np.int32)
     for mode, thr in ((wl.UNMASK_TOPK, 3.0), (wl.UNMASK_THRESH, 0.5)):
         check_unmask(inp, (1 - mask).astype(np.uint8), mode, thr, B, G, dtype, f"{what} unmask {mode}", x0=x0)
+
+
+# (one row and one vector; a part of a row's lanes, a full round of 256 vectors, one more, the last row that is not split; a sequence of
+# one wave's rows, of a wave with two, many short sequences; rows that are split)
+@pytest.mark.parametrize("B,G,V,dtype", [(1, 1, 8, wl.BF16), (1, 16, 1024, wl.F32), (2, 17, 1000, wl.F32), (3, 11, 1032, wl.BF16),
+                                         (1, 16, 2048, wl.BF16), (2, 15, 2056, wl.BF16), (1, 9, 2044, wl.F32), (190, 1, 1028, wl.F32),
+                                         (1, 12, 8192, wl.BF16), (2, 8, 4096, wl.F32), (1, 20, 12000, wl.BF16)])
+@pytest.mark.parametrize("rounds", [0, None, 1000])
+def test_scores_do_not_depend_on_the_rule(monkeypatch, rounds, B, G, V, dtype):
+    # the numbers of dd_verify_scores, bit for bit, from every rule and from the unmasking step, on either route of unsplit rows
+    import torch
+    if rounds is not None:
+        monkeypatch.setenv("DD_TUNE_SEQ_ROUNDS", str(rounds))
+    cfg = wl.custom_config(B=B, G=G, V=V, logit_dtype=dtype, sigma_d=3.0, sigma_n=1.0)
+    inp = wl.verify_inputs(cfg, seed=G + V)
+    inp["logits_v"][-1] = inp["logits_d"][-1]                          # (a row whose divergence is exactly zero)
+    ld, lv, mask = to_dev(inp["logits_d"]), to_dev(inp["logits_v"]), to_dev(np.zeros(B * G, np.uint8))
+    kl, cv, tv, cd, td = dd.dd_verify_scores(ld, lv, logit_dtype=dtype)
+    assert kl[-1] == 0
+    for mode in range(7):
+        want = kl if mode in (wl.KL_THRESH, wl.KL_PROB, wl.KL_TOPK) else cv
+        _, ot, osc = dd.dd_verify_remask(ld, lv, mask, mode, 1.0, 5, B, G, logit_dtype=dtype)
+        assert torch.equal(osc, want) and torch.equal(ot, tv), f"mode {mode}: {int((osc != want).sum())} scores differ"
+    for mode in (wl.UNMASK_THRESH, wl.UNMASK_TOPK):
+        _, ot, oc = dd.dd_unmask(ld, 1 - mask, mode, 1.0, B, G, logit_dtype=dtype)
+        assert torch.equal(oc, cd) and torch.equal(ot, td), f"unmask {mode}: {int((oc != cd).sum())} confidences differ"

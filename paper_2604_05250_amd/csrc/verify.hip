@@ -472,9 +472,19 @@ __global__ __launch_bounds__(256) void verify_finalize_kernel(const VerifyPartia
                             out_tokens, out_scores, ex);
 }
 
+// The state of a row that is finished where it is reduced, as the merge of split rows reads one: without a reference (no logit
+// above -inf) its sums count as zero, so that a confidence is 1 / 0 and ranks, and is not a NaN that every rank ignores.
+__device__ __forceinline__ WaveState as_merged(WaveState r)
+{
+    if (r.best_v == kNegInf) r.s_v = 0.f;
+    if (r.ref_d == kNegInf) r.s_d = r.a = 0.f;
+    return r;
+}
+
 // One workgroup per row: stream the whole row and finish it in the same kernel (no partial states,
-// no second launch).  Used whenever there are enough rows to fill the chip with such workgroups.
-template <bool BF16, bool KL, int THREADS, bool TRACKD = false>
+// no second launch).  Used whenever there are enough rows to fill the chip with such workgroups, and (UNSPLIT) for fewer rows
+// that are too short to split.
+template <bool BF16, bool KL, int THREADS, bool TRACKD = false, bool UNSPLIT = false>
 __global__ __launch_bounds__(THREADS) void verify_row_kernel(const uint4 *__restrict__ logits_d,
                                                              const uint4 *__restrict__ logits_v, int nvec,
                                                              const uint8_t *__restrict__ mask, int mode,
@@ -486,9 +496,11 @@ __global__ __launch_bounds__(THREADS) void verify_row_kernel(const uint4 *__rest
     const int row = blockIdx.x;
     const size_t rbase = (size_t)row * (size_t)nvec;
     WaveState r;
-    if (reduce_range<BF16, KL, THREADS, TRACKD>(logits_v + rbase, KL ? logits_d + rbase : nullptr, 0, nvec, r))
+    if (reduce_range<BF16, KL, THREADS, TRACKD>(logits_v + rbase, KL ? logits_d + rbase : nullptr, 0, nvec, r)) {
+        if (UNSPLIT) r = as_merged(r);
         finish_row(row, (double)r.ref_d, (double)r.s_d, (double)r.a, (double)r.best_v, (double)r.s_v, r.idx,
                    mask, mode, threshold, seed, KL ? 1 : 0, out_mask, out_tokens, out_scores, r.idx_d, ex);
+    }
 }
 
 // Eq. 6: one workgroup per sequence sums the divergences of its eligible rows, then draws
@@ -864,6 +876,7 @@ __global__ __launch_bounds__(kSeqThreads) void verify_seq_kernel(const uint4 *__
 #pragma unroll
             for (int p = 1; p < kParts; ++p) r = merge(r, rows_sh[tid][p]);
         }
+        r = as_merged(r);
         finish_row((int)base + tid, (double)r.ref_d, (double)r.s_d, (double)r.a, (double)r.best_v, (double)r.s_v, r.idx, mask, mode,
                    threshold, seed, KL ? 1 : 0, out_mask, out_tokens, out_scores, 0, VerifyExtra{}, &sh.score[tid], &sh.token[tid]);
     }
@@ -968,12 +981,12 @@ hipError_t launch_verify(const void *logits_d, const void *logits_v, const uint8
         const bool per_sequence = mode == 3 || mode == 5 || mode == 6 || mode == kModeUnmaskThresh || mode == kModeUnmaskTopk;
         // Rows that are not split leave nothing to merge: rules of one row finish it in the launch that streams it, ...
         if (S == 1 && !per_sequence && !track_d) {
-            const dim3 rows((unsigned)P);
+            const dim3 rows((unsigned)P), lanes(kThreads);
             if (logit_is_bf16)
-                return kl ? launch_row_kernel<true, true>(kThreads, rows, stream, ld, lv, nvec, mask, mode, threshold, seed, out_mask, out_tokens, out_scores, ex)
-                          : launch_row_kernel<true, false>(kThreads, rows, stream, ld, lv, nvec, mask, mode, threshold, seed, out_mask, out_tokens, out_scores, ex);
-            return kl ? launch_row_kernel<false, true>(kThreads, rows, stream, ld, lv, nvec, mask, mode, threshold, seed, out_mask, out_tokens, out_scores, ex)
-                      : launch_row_kernel<false, false>(kThreads, rows, stream, ld, lv, nvec, mask, mode, threshold, seed, out_mask, out_tokens, out_scores, ex);
+                return kl ? launch(verify_row_kernel<true, true, kThreads, false, true>, rows, lanes, stream, ld, lv, nvec, mask, mode, threshold, seed, out_mask, out_tokens, out_scores, ex)
+                          : launch(verify_row_kernel<true, false, kThreads, false, true>, rows, lanes, stream, ld, lv, nvec, mask, mode, threshold, seed, out_mask, out_tokens, out_scores, ex);
+            return kl ? launch(verify_row_kernel<false, true, kThreads, false, true>, rows, lanes, stream, ld, lv, nvec, mask, mode, threshold, seed, out_mask, out_tokens, out_scores, ex)
+                      : launch(verify_row_kernel<false, false, kThreads, false, true>, rows, lanes, stream, ld, lv, nvec, mask, mode, threshold, seed, out_mask, out_tokens, out_scores, ex);
         }
         // ... rules of a sequence stream its rows in the workgroup that applies the rule, as long as that is a few round trips
         if (S == 1 && per_sequence && seq_rounds(G, nvec) <= tune("DD_TUNE_SEQ_ROUNDS", kl ? kSeqMaxRoundsKl : kSeqMaxRounds)) {

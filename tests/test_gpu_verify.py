@@ -530,3 +530,22 @@ def test_scores_do_not_depend_on_the_rule(monkeypatch, rounds, B, G, V, dtype):
     for mode in (wl.UNMASK_THRESH, wl.UNMASK_TOPK):
         _, ot, oc = dd.dd_unmask(ld, 1 - mask, mode, 1.0, B, G, logit_dtype=dtype)
         assert torch.equal(oc, cd) and torch.equal(ot, td), f"unmask {mode}: {int((oc != cd).sum())} confidences differ"
+
+@pytest.mark.parametrize("V", [1024, 8192])                            # (bf16: one round of loads, and the longest unsplit row)
+@pytest.mark.parametrize("rounds", [0, 1000])
+def test_rows_without_a_finite_logit(monkeypatch, rounds, V):
+    # Fewer than 192 rows: no sum, so a confidence of 1 / 0, whichever rule asks, and a step of k positions still reveals k.
+    import torch
+    monkeypatch.setenv("DD_TUNE_SEQ_ROUNDS", str(rounds))
+    G = 13
+    cfg = wl.custom_config(B=1, G=G, V=V, logit_dtype=wl.BF16, sigma_d=3.0, sigma_n=1.0)
+    x = to_dev(wl.verify_inputs(cfg, seed=V)["logits_v"]).view(torch.bfloat16).clone()
+    x[[2, 7]] = float("-inf")
+    mask = torch.zeros(G, dtype=torch.uint8, device="cuda:0")
+    for mode in (wl.TRUST, wl.CONF_THRESH, wl.CONF_PROB, wl.CONF_TOPK):
+        om, _, osc = dd.dd_verify_remask(None, x, mask, mode, 3.0, 5, 1, G)
+        assert torch.isposinf(osc[[2, 7]]).all() and int(torch.isfinite(osc).sum()) == G - 2, f"mode {mode}: {osc.tolist()}"
+        if mode == wl.CONF_TOPK:
+            assert int(om.sum()) == 3 and not om[[2, 7]].any()
+    om, _, _ = dd.dd_unmask(x, 1 - mask, wl.UNMASK_TOPK, 4.0, 1, G)
+    assert int((om == 0).sum()) == 4 and not om[[2, 7]].any()

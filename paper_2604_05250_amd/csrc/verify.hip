@@ -424,35 +424,41 @@ __device__ __forceinline__ void merge_splits_and_finish(const VerifyPartial *__r
     VerifyPartial p;
     p.ref_d = kNegInf; p.s_d = 0.f; p.a = 0.f; p.best_v = kNegInf; p.s_v = 0.f; p.idx = INT_MAX; p.idx_d = INT_MAX;
     if (have) p = part[(size_t)row * S + sp];
-    float mv = p.best_v, md = kl_mode ? p.ref_d : kNegInf;
+    float mv = p.best_v, md = kNegInf;
     int idx = p.idx, idx_d = p.idx_d;
-    for_steps<4>([&](auto step) __attribute__((always_inline)) {
-        constexpr int STEP = decltype(step)::value;
-        const float ov = other16<STEP>(mv);
-        const int oi = other16<STEP>(idx);
-        if (ov > mv || (ov == mv && oi < idx)) { mv = ov; idx = oi; }
-    });
+    double sv = 0.0, sd = 0.0, a = 0.0;
+    // (KL's exchanges beside the verifier's, not after them: a sequence of 63 rows keeps sixteen waves busy with them, Eq. 6 on 3 x 63 rows
+    // of 256 fp32 logits 10.7 us through LDS shuffles, 11.3 one after the other, 10.7 side by side; 3 x 48 rows 9.9, 9.9, 9.2)
     if (kl_mode) {                                         // uniform
+        md = p.ref_d;
         for_steps<4>([&](auto step) __attribute__((always_inline)) {
             constexpr int STEP = decltype(step)::value;
-            const float od = other16<STEP>(md);
-            const int oid = other16<STEP>(idx_d);
+            const float ov = other16<STEP>(mv), od = other16<STEP>(md);
+            const int oi = other16<STEP>(idx), oid = other16<STEP>(idx_d);
+            if (ov > mv || (ov == mv && oi < idx)) { mv = ov; idx = oi; }
             if (od > md || (od == md && oid < idx_d)) { md = od; idx_d = oid; }
         });
-    }
-    double sv = 0.0, sd = 0.0, a = 0.0;
-    if (p.best_v != kNegInf) sv = (double)p.s_v * exp((double)p.best_v - (double)mv);
-    if (kl_mode && p.ref_d != kNegInf) {
-        const double c = exp((double)p.ref_d - (double)md);
-        sd = (double)p.s_d * c;
-        a = (double)p.a * c;
-    }
-    for_steps<4>([&](auto step) __attribute__((always_inline)) { sv += other16<decltype(step)::value>(sv); });
-    if (kl_mode) {
+        if (p.best_v != kNegInf) sv = (double)p.s_v * exp((double)p.best_v - (double)mv);
+        if (p.ref_d != kNegInf) {
+            const double c = exp((double)p.ref_d - (double)md);
+            sd = (double)p.s_d * c;
+            a = (double)p.a * c;
+        }
         for_steps<4>([&](auto step) __attribute__((always_inline)) {
-            sd += other16<decltype(step)::value>(sd);
-            a += other16<decltype(step)::value>(a);
+            constexpr int STEP = decltype(step)::value;
+            sv += other16<STEP>(sv);
+            sd += other16<STEP>(sd);
+            a += other16<STEP>(a);
         });
+    } else {
+        for_steps<4>([&](auto step) __attribute__((always_inline)) {
+            constexpr int STEP = decltype(step)::value;
+            const float ov = other16<STEP>(mv);
+            const int oi = other16<STEP>(idx);
+            if (ov > mv || (ov == mv && oi < idx)) { mv = ov; idx = oi; }
+        });
+        if (p.best_v != kNegInf) sv = (double)p.s_v * exp((double)p.best_v - (double)mv);
+        for_steps<4>([&](auto step) __attribute__((always_inline)) { sv += other16<decltype(step)::value>(sv); });
     }
     if (sp == 0 && row_ok)
         finish_row((int)row, md, sd, a, mv, sv, idx, mask, mode, threshold, seed, kl_mode, out_mask, out_tokens,

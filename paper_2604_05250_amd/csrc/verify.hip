@@ -931,6 +931,14 @@ static int seq_rounds(int G, int nvec)
     return (G + kSeqThreads / 64 - 1) / (kSeqThreads / 64) * ((nvec + kThreads - 1) / kThreads);
 }
 constexpr int kSeqMaxRounds = 2, kSeqMaxRoundsKl = 1;
+// A bf16 vector is eight logits, so full rounds of them take longer: above 5120 vectors per sequence (KL 2560) two launches are as
+// fast or faster - unmasking 29 x 1744 8.1 against 8.7, 32 x 1480 7.7 / 8.2, KL 13 x 1552 7.9 / 8.3, 13 x 1832 8.1 / 8.6.
+static bool seq_in_one_launch(int G, int nvec, bool bf16, bool kl)
+{
+    const int forced = tune("DD_TUNE_SEQ_ROUNDS", -1), rounds = seq_rounds(G, nvec);
+    if (forced >= 0) return rounds <= forced;
+    return rounds <= (kl ? kSeqMaxRoundsKl : kSeqMaxRounds) && (!bf16 || (long)G * nvec <= (kl ? 2560 : 5120));
+}
 
 size_t verify_workspace_bytes(int P, int V, int elem_bytes)
 {
@@ -995,7 +1003,7 @@ hipError_t launch_verify(const void *logits_d, const void *logits_v, const uint8
                       : launch(verify_row_kernel<false, false, kThreads, false, true>, rows, lanes, stream, ld, lv, nvec, mask, mode, threshold, seed, out_mask, out_tokens, out_scores, ex);
         }
         // ... rules of a sequence stream its rows in the workgroup that applies the rule, as long as that is a few round trips
-        if (S == 1 && per_sequence && seq_rounds(G, nvec) <= tune("DD_TUNE_SEQ_ROUNDS", kl ? kSeqMaxRoundsKl : kSeqMaxRounds)) {
+        if (S == 1 && per_sequence && seq_in_one_launch(G, nvec, logit_is_bf16 != 0, kl)) {
             const dim3 seqs((unsigned)B), lanes(kSeqThreads);
             if (logit_is_bf16)
                 return kl ? launch(verify_seq_kernel<true, true>, seqs, lanes, stream, ld, lv, nvec, G, mask, mode, threshold, seed, out_mask, out_tokens, out_scores, x_tokens)

@@ -488,12 +488,19 @@ bool attn_solo_serves(const AttnArgs &a)
     return a.qk_dtype == 2 && a.d == 128 && (a.v_dtype == 1 || a.v_dtype == 2);
 }
 
-// Drafter calls.  Key splits: none, or until the 256 compute units have a workgroup each, or half as many.  Hundredths of a microsecond, fitted to
-// measured calls: a workgroup costs 400 and 113 per 128 keys (fp8 390 and 91, d = 64 340 and 71), these half as much again with each
-// further 80 workgroups (the caches' share), `s` splits 290 + 10 s.  (The split picked is 0.7 % off the best one on average.)
+// Drafter calls.  Key splits: those of least cost while every workgroup has a compute unit, in hundredths of a microsecond, fitted per
+// storage type to some 35000 timings of 19500 calls at one to sixteen splits: a workgroup, its rounds of 128 keys, these again by the
+// workgroups beside the first 64 (the caches' share), a merge launch, its splits and the partial states' rows.  (The split picked is
+// 0.1 % off the best one on average.  Decoded e4m3 values cost a round more and share less, so they split earlier: 1 x 32 heads, block 8,
+// 801 keys 12.0 unsplit, 9.3 with four splits, 11.1 on the MFMA kernel; bf16 5 x 8 heads, 7 rows, 724 keys 11.3 unsplit, 9.8 with four.)
+namespace {
+struct SoloCost { long fixed, round, beside, merge, split, krows; };
+constexpr SoloCost kSoloBf16 = {400, 90, 258, 257, 4, 5}, kSoloFp8 = {390, 86, 569, 286, 11, 14}, kSoloD64 = {340, 136, 1351, 581, 20, 7},
+                   kSoloV8 = {405, 117, 1110, 223, 7, 27};
+}  // namespace
 // Against the streaming kernel (8300 calls of 1 - 16 x 32/32, 32/8, 28/4 and 16/16 heads, 8 - 64 rows, 200 - 4096 keys): with one
-// workgroup per compute unit and at most 6 rounds of 128 keys each it takes 0.83 of the time (bf16) and 0.85 (fp8), 2 - 5 % more on one
-// call in a hundred.  Longer streams are bound by memory bandwidth, which that kernel's larger workgroups draw better - 8 x 32, 32
+// workgroup per compute unit and at most 7 rounds of 128 keys each (8 unsplit) it takes 0.83 of the time (bf16) and 0.87 (fp8), up to 3 %
+// more on one call in a hundred.  Longer streams are bound by memory bandwidth, which that kernel's larger workgroups draw better - 8 x 32, 32
 // rows, 3992 keys fp8 63.6 / 71.8 - unless they leave it a third of its compute units idle: 11 x 32/8, 1237 keys above (264 of its
 // workgroups).  Past 256 workgroups: bf16 of at most 32 rows 0.85 up to 512, the others lose (64 rows bf16 1.03, fp8 1.01).  d = 64: 0.79
 // throughout.  e4m3 values, against the MFMA kernel (746 such calls): 0.78, 9 x 32, 48 rows, 3774 keys 125 -> 85, 11 x 32/8, 16 rows, 1360 keys
@@ -507,14 +514,12 @@ SoloPlan attn_solo_plan(long rows, long heads, int N, int d, bool fp8, bool v8, 
     if (forced == 0) return SoloPlan{false, 1};
     if (tune("DD_TUNE_BLOCK_SPLITS", 0) >= 1) return SoloPlan{forced == 1, stream_splits};
     const long row_tiles = (rows + 31) / 32, wgs = heads * row_tiles;
-    const long fixed = d == 64 ? 340 : fp8 ? 390 : 400, per = d == 64 ? 71 : fp8 ? 91 : 113;
+    const SoloCost &c = d == 64 ? kSoloD64 : v8 ? kSoloV8 : fp8 ? kSoloFp8 : kSoloBf16;
     const long most = wgs >= 256 ? 1 : 256 / wgs < stream_splits ? 256 / wgs : stream_splits;
     long splits = 1, rounds = 0, best = 0;
-    const long tried[3] = {1, most, most / 2};
-    for (const long s : tried) {
-        if (s < 1) continue;
+    for (long s = 1; s <= most; ++s) {
         const long r = ((N + s - 1) / s + 127) / 128, beside = wgs * s > 64 ? wgs * s - 64 : 0;
-        const long cost = fixed + per * r + per * r * beside / 185 + (s > 1 ? 290 + 10 * s : 0);
+        const long cost = c.fixed + c.round * r + c.round * r * beside / c.beside + (s > 1 ? c.merge + c.split * s + c.krows * heads * rows * s / 1000 : 0);
         if (best == 0 || cost < best) {
             splits = s;
             rounds = r;
@@ -528,7 +533,7 @@ SoloPlan attn_solo_plan(long rows, long heads, int N, int d, bool fp8, bool v8, 
     const long stream_wgs = heads * stream_splits, stream_slots = (stream_wgs + 255) / 256 * 256;
     const bool fits = wgs <= 256 || (!fp8 && row_tiles == 1 && wgs <= 512);
     const bool idle = 10 * stream_wgs < (fp8 ? 6 : 7) * stream_slots;
-    return SoloPlan{fits && (rounds <= 6 || idle), (int)splits};
+    return SoloPlan{fits && (rounds <= (splits == 1 ? 8 : 7) || idle), (int)splits};
 }
 
 hipError_t launch_attention_solo(const AttnArgs &a, hipStream_t stream)

@@ -489,14 +489,14 @@ bool attn_solo_serves(const AttnArgs &a)
 }
 
 // Drafter calls.  Key splits: those of least cost while every workgroup has a compute unit, in hundredths of a microsecond, fitted per
-// storage type to some 35000 timings of 19500 calls at one to sixteen splits: a workgroup, its rounds of 128 keys, these again by the
-// workgroups beside the first 64 (the caches' share), a merge launch, its splits and the partial states' rows.  (The split picked is
-// 0.1 % off the best one on average.  Decoded e4m3 values cost a round more and share less, so they split earlier: 1 x 32 heads, block 8,
+// storage type to some 35000 timings of 19500 calls at one to sixteen splits: a workgroup, its rounds of 128 keys, both again by
+// the workgroups beside it (the caches' share), a merge launch, that again by its workgroups up to 48 and by the rows of the
+// partial states.  (The split picked is 0.1 % off the best one on average.  Decoded e4m3 values cost a round more and share less, so they split earlier: 1 x 32 heads, block 8,
 // 801 keys 12.0 unsplit, 9.3 with four splits, 11.1 on the MFMA kernel; bf16 5 x 8 heads, 7 rows, 724 keys 11.3 unsplit, 9.8 with four.)
 namespace {
-struct SoloCost { long fixed, round, beside, merge, split, krows; };
-constexpr SoloCost kSoloBf16 = {400, 90, 258, 257, 4, 5}, kSoloFp8 = {390, 86, 569, 286, 11, 14}, kSoloD64 = {340, 136, 1351, 581, 20, 7},
-                   kSoloV8 = {405, 117, 1110, 223, 7, 27};
+struct SoloCost { long fixed, fixed_beside, round, round_beside, merge, merge_beside, krows; };     // (beside: per 100 workgroups; merge: 48)
+constexpr SoloCost kSoloBf16 = {441, 23, 80, 28, 214, 57, 4}, kSoloFp8 = {412, 20, 70, 20, 214, 43, 12}, kSoloD64 = {351, 17, 54, 16, 206, 48, 1},
+                   kSoloV8 = {388, 37, 108, 4, 202, 46, 16};
 }  // namespace
 // Against the streaming kernel (8300 calls of 1 - 16 x 32/32, 32/8, 28/4 and 16/16 heads, 8 - 64 rows, 200 - 4096 keys): with one
 // workgroup per compute unit and at most 7 rounds of 128 keys each (8 unsplit) it takes 0.83 of the time (bf16) and 0.87 (fp8), up to 3 %
@@ -518,8 +518,9 @@ SoloPlan attn_solo_plan(long rows, long heads, int N, int d, bool fp8, bool v8, 
     const long most = wgs >= 256 ? 1 : 256 / wgs < stream_splits ? 256 / wgs : stream_splits;
     long splits = 1, rounds = 0, best = 0;
     for (long s = 1; s <= most; ++s) {
-        const long r = ((N + s - 1) / s + 127) / 128, beside = wgs * s > 64 ? wgs * s - 64 : 0;
-        const long cost = c.fixed + c.round * r + c.round * r * beside / c.beside + (s > 1 ? c.merge + c.split * s + c.krows * heads * rows * s / 1000 : 0);
+        const long r = ((N + s - 1) / s + 127) / 128, w = wgs * s;
+        long cost = c.fixed + c.round * r + (c.fixed_beside + c.round_beside * r) * w / 100;
+        if (s > 1) cost += c.merge + c.merge_beside * (w < 48 ? w : 48) / 48 + c.krows * heads * rows * s / 1000;
         if (best == 0 || cost < best) {
             splits = s;
             rounds = r;

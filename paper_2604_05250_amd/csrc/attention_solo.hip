@@ -505,10 +505,13 @@ constexpr SoloCost kSoloBf16 = {441, 23, 80, 28, 214, 57, 4}, kSoloFp8 = {412, 2
 // workgroups).  Past 256 workgroups: bf16 of at most 32 rows 0.85 up to 512, the others lose (64 rows bf16 1.03, fp8 1.01).  d = 64: 0.79
 // throughout.  e4m3 values, against the MFMA kernel (746 such calls): 0.78, 9 x 32, 48 rows, 3774 keys 125 -> 85, 11 x 32/8, 16 rows, 1360 keys
 // 23.2 -> 18.3; slower where a fourth round of 256 workgroups of few keys begins (15 x 32, 48 rows, 243 keys 1.08).
+// At most 64 keys are one tile of the kernels before, and nothing for waves to stream: few rows of up to 256 heads are faster there, fp8 8
+// rows, 37 - 62 keys 4.2 against 4.9 here, bf16 4.5 - 4.8 / 4.9 - 5.3, as is anything past 512 workgroups where a head's rows are two
+// (d = 64 272 heads, 48 rows, 48 keys 5.3 / 7.6); with the cache refresh, a launch of its own there, 7.2 / 5.1, with 64 rows 6.1 / 5.1 (fp8).
 // More than 64 rows (900 calls of 32/8, 28/4, 32/16 and 16/2 heads, 16 - 64 rows per head, 300 - 4096 keys; before: the two-waves-per-SIMD,
 // the wide or the MFMA kernel): up to 256 workgroups with at most 12 rounds each 0.78 of the time (bf16), 0.75 (fp8), 0.65 (e4m3 V, these up
 // to 512), on none more than 1.00; 256 - 384 workgroups and longer streams up to 1.3.
-SoloPlan attn_solo_plan(long rows, long heads, int N, int d, bool fp8, bool v8, int stream_splits)
+SoloPlan attn_solo_plan(long rows, long heads, int N, int d, bool fp8, bool v8, bool refresh, int stream_splits)
 {
     const int forced = tune("DD_TUNE_SOLO", -1);
     if (forced == 0) return SoloPlan{false, 1};
@@ -528,6 +531,8 @@ SoloPlan attn_solo_plan(long rows, long heads, int N, int d, bool fp8, bool v8, 
         }
     }
     if (forced == 1) return SoloPlan{true, (int)splits};
+    if (rows <= 64 && N <= 64 && (wgs > 512 ? row_tiles == 2 : !refresh && heads <= 256 && rows <= (d == 64 || fp8 ? 48 : 32)))
+        return SoloPlan{false, 1};
     if (rows > 64) return SoloPlan{wgs <= (v8 ? 512 : 256) && rounds <= 12, (int)splits};
     if (d == 64) return SoloPlan{true, (int)splits};
     if (v8) return SoloPlan{wgs <= 768 || rounds > 4, (int)splits};

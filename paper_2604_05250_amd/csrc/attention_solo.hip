@@ -504,7 +504,8 @@ constexpr SoloCost kSoloBf16 = {441, 23, 80, 28, 214, 57, 4}, kSoloFp8 = {412, 2
 // rows, 3992 keys fp8 63.6 / 71.8 - unless they leave it a third of its compute units idle: 11 x 32/8, 1237 keys above (264 of its
 // workgroups).  Past 256 workgroups: bf16 of at most 32 rows 0.85 up to 512, the others lose (64 rows bf16 1.03, fp8 1.01).  d = 64: 0.79
 // throughout.  e4m3 values, against the MFMA kernel (746 such calls): 0.78, 9 x 32, 48 rows, 3774 keys 125 -> 85, 11 x 32/8, 16 rows, 1360 keys
-// 23.2 -> 18.3; slower where a fourth round of 256 workgroups of few keys begins (15 x 32, 48 rows, 243 keys 1.08).
+// 23.2 -> 18.3.  Slower, up to 1.13, where a kv head's rows are two workgroups, more than 512 in all, and few keys leave both launches their
+// ramps: 11 x 32, 63 rows, 90 keys 9.3 / 10.5; from a fourth round on and with one workgroup per head it is not.
 // At most 64 keys are one tile of the kernels before, and nothing for waves to stream: few rows of up to 256 heads are faster there, fp8 8
 // rows, 37 - 62 keys 4.2 against 4.9 here, bf16 4.5 - 4.8 / 4.9 - 5.3, as is anything past 512 workgroups where a head's rows are two
 // (d = 64 272 heads, 48 rows, 48 keys 5.3 / 7.6); with the cache refresh, a launch of its own there, 7.2 / 5.1, with 64 rows 6.1 / 5.1 (fp8).
@@ -535,7 +536,7 @@ SoloPlan attn_solo_plan(long rows, long heads, int N, int d, bool fp8, bool v8, 
         return SoloPlan{false, 1};
     if (rows > 64) return SoloPlan{wgs <= (v8 ? 512 : 256) && rounds <= 12, (int)splits};
     if (d == 64) return SoloPlan{true, (int)splits};
-    if (v8) return SoloPlan{wgs <= 768 || rounds > 4, (int)splits};
+    if (v8) return SoloPlan{wgs <= 512 || (wgs <= 768 && (row_tiles == 1 || rounds > 3)) || rounds > 4, (int)splits};
     const long stream_wgs = heads * stream_splits, stream_slots = (stream_wgs + 255) / 256 * 256;
     const bool fits = wgs <= 256 || (!fp8 && row_tiles == 1 && wgs <= 512);
     const bool idle = 10 * stream_wgs < (fp8 ? 6 : 7) * stream_slots;

@@ -228,6 +228,11 @@ static int block_attention(const void *Qblk, const void *Kc, const void *Vc, voi
     dd::DuoPlan duo{0, 1};
     if (!solo.take && dd::attn_duo_serves(a) && (rows > 64 || dd::tune("DD_TUNE_DUO", 0) > 0) && !other_kernel_forced()) {
         duo = dd::attn_duo_plan(rows, heads, N, qk_dtype == DD_FP8_E4M3 || d == 64);
+        // Where the wide kernel cannot take the call (block rows spliced in from a block shorter than a tile), the MFMA kernel's 128-row
+        // workgroups, two to a compute unit, are faster on few keys: than 128-row ones here below 256 keys, where it splits (bf16 176 heads, 80 rows, 178
+        // keys 11.0 against 12.1, 192 x 96 rows, 123 keys 10.1 / 11.1; d = 64 144 x 110, 94 keys 6.2 / 6.9), than 64-row ones up to 64 keys
+        // (bf16 112 x 80, 40 keys 6.4 / 7.2) and, with 64 head dims, 128 (96 x 96, 89 keys 5.7 / 6.4; 128 x 128, 81 keys 6.1 / 6.5).
+        if (!wide && N <= (duo.blocks == 4 ? 255 : d == 64 ? 128 : 64) && dd::tune("DD_TUNE_DUO", -1) < 0) duo.blocks = 0;
         // Past one round of 128-row workgroups the wide kernel's 256-row tiles are faster (24 x 32/8 heads, 64 rows, 1024 keys
         // 43.3 against 48.5 us, fp8 36.3 / 42.5), its 128-row tiles, for up to 128 rows, are not (40 x 16/8: 60.9 / 52.6, fp8
         // 51.7 / 45.0); the MFMA kernel, where the wide one cannot take the call, is (64 x 32/8, 32 rows: 62.8 / 66.8).

@@ -238,6 +238,14 @@ static int block_attention(const void *Qblk, const void *Kc, const void *Vc, voi
         // 51.7 / 45.0); the MFMA kernel, where the wide one cannot take the call, is (64 x 32/8, 32 rows: 62.8 / 66.8).
         if (duo.blocks == 0 && wide && rows <= 128 && dd::tune("DD_TUNE_DUO", -1) != 0) duo.blocks = 4;
     }
+    // Long bf16 streams that the splits here leave a fifth of the compute units without: the wide kernel's larger tiles split finer (48 heads x 192
+    // rows, 3709 keys: 39.2 on 240 workgroups against 43.3 on 192; 24 x 512, 3857 keys 43.1 / 46.3; at 2600 keys still 0.96).
+    if (duo.splits > 1 && wide && qk_dtype == DD_BF16 && d == 128 && N >= 3072 && dd::tune("DD_TUNE_DUO", -1) < 0) {
+        const int per_wg = dd::attn_wide_block_rows(block_len, B, H, Hkv, N);
+        const long here = heads * ((rows + 32 * duo.blocks - 1) / (32 * duo.blocks)) * duo.splits;
+        const long there = heads * ((rows + per_wg - 1) / per_wg) * dd::attn_wide_block_splits(block_len, B, H, Hkv, N);
+        if (5 * here <= 4 * there) duo.blocks = 0;
+    }
     const int general = wide ? dd::attn_wide_block_splits(block_len, B, H, Hkv, N) : narrow_splits;
     const int splits = duo.blocks ? duo.splits : solo.take ? solo.splits : general;
     // (what the kernels of every shape ask for is asked for here too, whichever serves the call)

@@ -740,7 +740,7 @@ hipError_t launch_attention_mfma(const AttnArgs &a, hipStream_t stream)
         // with all 512 and more than 1024 keys up to 1.11.
         // 64 keys and fewer: 1.0 (fp8 1.1).  e4m3 values: 0.66 up to 256 workgroups, 0.78 up to 512, then 1.1 as well.
         const long wgs = heads * ((rows + 31) / 32);
-        const int solo = tune("DD_TUNE_SOLO", tune("DD_TUNE_DUO", -1) < 0 && a.N > 64 && wgs <= (a.N > 1024 ? 448 : 512));
+        const int solo = tune("DD_TUNE_SOLO", tune("DD_TUNE_DUO", -1) <= 0 && a.N > 64 && wgs <= (a.N > 1024 ? 448 : 512));
         if (solo != 0 && attn_solo_serves(a)) return launch_attention_solo(a, stream);
     }
     if (!blk && attn_duo_serves(a) && tune("DD_TUNE_ATTN_WIDE", -1) < 0 && tune("DD_TUNE_BIDIR_STREAM", -1) < 0) {

@@ -126,3 +126,25 @@ def test_reference_of_the_weights(monkeypatch, blocks, scale, order):
     torch.cuda.synchronize()
     ref = oracle.bidir_attention(Q, K, V, wl.BF16, wl.BF16)
     assert_attention_close(out_to_f64(O, wl.BF16), ref, wl.BF16, f"{blocks} blocks, scale {scale} order {order}")
+
+
+@pytest.mark.parametrize("call", ["bidir", "block"])
+def test_switching_this_kernel_off_moves_no_other_call(monkeypatch, call):
+    # a call of the kernel whose waves stream keys of their own, by the rule: the same bits without this kernel, others when it is off
+    import torch
+    N, bl = 301, 301 if call == "bidir" else 16
+    cfg = wl.custom_config(B=1, H=4, Hkv=2, N=N, d=128, qk_dtype=wl.BF16, v_dtype=wl.BF16, bl=bl, prompt=0, G=N)
+    cache, blk = wl.cache_inputs(cfg, seed=N), wl.block_inputs(cfg, 0, 0)
+    Q, K, V = to_dev(blk["Qblk"]), to_dev(cache["Kc"]), to_dev(cache["Vc"])
+
+    def run(**env):
+        for k in ("DD_TUNE_DUO", "DD_TUNE_SOLO"):
+            monkeypatch.delenv(k, raising=False)
+        for k, v in env.items():
+            monkeypatch.setenv(k, v)
+        O = dd.dd_bidir_attention(Q, K, V) if call == "bidir" else dd.dd_block_attention_cached(Q, K, V, 0)
+        torch.cuda.synchronize()
+        return O
+    rule = run()
+    assert torch.equal(rule, run(DD_TUNE_SOLO="1"))
+    assert torch.equal(rule, run(DD_TUNE_DUO="0")) and not torch.equal(rule, run(DD_TUNE_SOLO="0"))

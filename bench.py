@@ -35,7 +35,8 @@ PEAK_FP8_TFLOPS = 5000.0      # MI355X dense fp8 MFMA
 PEAK_FP32_VALU_TFLOPS = 157.3 # MI355X fp32 vector
 PEAK_HBM_GBPS = 8000.0        # MI355X HBM3E
 LLC_ROTATE_BYTES = 600e6      # rotate input sets until their total exceeds 2x the 256 MB last-level cache
-KERNEL_SOURCES = ("attention_wide.hip", "attention_mfma.hip", "attention_stream.hip", "attention_common.h", "verify.hip")
+KERNEL_SOURCES = ("attention_wide.hip", "attention_mfma.hip", "attention_stream.hip", "attention_duo.hip", "attention_solo.hip",
+                  "attention_common.h", "verify.hip")
 
 
 def kernel_source_digest():
@@ -436,8 +437,14 @@ def run_config(args, config_id):
         one_round = {r: heads * -(-rows // r) <= 256 for r in (64, 128)}
         # bf16 without per-head scales, enough row tiles: the folded-scale form
         fold = not fp8 and c.N >= 1024 and heads * -(-rows // 256) >= 192
+        tf = {False: "false", True: "true"}
+        if (not fp8 or c.d == 128) and stored_v != 2:
+            if c.N > 64 and heads * -(-rows // 32) <= (448 if c.N > 1024 else 512):
+                return f"attn_solo_kernel<{c.d}, {tf[fp8]}, {tf[stored_v == 1]}>"
+            if stored_v == 0 and one_round[64] and c.N > 1024:
+                return f"attn_duo_kernel<{c.d}, {tf[fp8]}, 2, {3 if fp8 else 2 if c.d == 128 else 4}>"
         if not fp8 or c.d == 128:
-            if one_round[128] and (c.N >= 448 or (c.N >= 192 and (fp8 or not one_round[64]))):
+            if one_round[128] and c.N >= 192:
                 return f"attn_wide_kernel<{c.d}, {'true' if fp8 else 'false'}, true, false, 1, {stored_v}>"
             if not one_round[128] and c.N >= 448:
                 return f"attn_wide_kernel<{c.d}, {'true' if fp8 else 'false'}, false, {'true' if fold else 'false'}, 2, {stored_v}>"
@@ -512,9 +519,12 @@ def run_config(args, config_id):
                      "back_to_back_achieved": round(attn_stream_tflops, 3),
                      "traffic": profiled_traffic(config_id, "attention"),
                      "algorithmic_flops": attn_flops, "algorithmic_bytes": attn_bytes},
-        "roofline_verify": {"kernel": ("verify_row_kernel" if cfg.P >= 192 else "verify_partial_kernel + verify_finalize_kernel")
-                                      + {wl.KL_PROB: " + verify_klprob_kernel", wl.KL_TOPK: " + verify_topk_kernel",
-                                         wl.CONF_TOPK: " + verify_topk_kernel"}.get(mode, "") + " (dd_verify_remask)",
+        "roofline_verify": {"kernel": (("verify_row_kernel" + {wl.KL_PROB: " + verify_klprob_kernel", wl.KL_TOPK: " + verify_topk_kernel",
+                                                              wl.CONF_TOPK: " + verify_topk_kernel"}.get(mode, "")) if cfg.P >= 192 else
+                                      "verify_seq_kernel / verify_partial_kernel + verify_finalize_seq_kernel"
+                                      if mode in (wl.KL_PROB, wl.KL_TOPK, wl.CONF_TOPK) else
+                                      "verify_row_kernel" if cfg.V * eb_l <= 16384 else
+                                      "verify_partial_kernel + verify_finalize_kernel") + " (dd_verify_remask)",
                             "bound": "hbm", "achieved": round(ver_gbps, 1), "peak": PEAK_HBM_GBPS, "unit": "GB/s",
                             "frac": round(ver_gbps / PEAK_HBM_GBPS, 4),
                             "launch_us": round(t_ver * 1e3, 2),
@@ -524,8 +534,8 @@ def run_config(args, config_id):
                             "algorithmic_bytes": verify_bytes},
     }
 
-    out["roofline_block"] = {"kernel": "dd_block_attention_cached (attn_stream_kernel / attn_wide_kernel<.., BLOCK> / "
-                                       "attn_mfma_kernel + attn_combine_kernel, by shape)",
+    out["roofline_block"] = {"kernel": "dd_block_attention_cached (attn_solo_kernel / attn_stream_kernel / attn_duo_kernel / "
+                                       "attn_wide_kernel<.., BLOCK> / attn_mfma_kernel, + attn_combine_kernel, by shape)",
                              "bound": "hbm", "achieved": round(blk_gbps, 1), "peak": PEAK_HBM_GBPS, "unit": "GB/s",
                              "frac": round(blk_gbps / PEAK_HBM_GBPS, 4), "traffic": profiled_traffic(config_id, "block"),
                              "launch_us": round(t_block / cfg.K * 1e3, 2),
@@ -549,7 +559,8 @@ def run_config(args, config_id):
     if "unmask" in parts:
         um_gbps = unmask_bytes / (max(t_unmask, 1e-9) / cfg.K * 1e-3) / 1e9
         out["components_ms"]["unmask_xK"] = round(t_unmask, 4)
-        out["roofline_unmask"] = {"kernel": "verify_row_kernel / verify_partial_kernel + unmask_select_kernel (dd_unmask)",
+        out["roofline_unmask"] = {"kernel": "verify_row_kernel + unmask_select_kernel / verify_partial_kernel + verify_finalize_seq_kernel / "
+                                            "verify_seq_kernel (dd_unmask, by rows)",
                                   "bound": "hbm", "achieved": round(um_gbps, 1), "peak": PEAK_HBM_GBPS, "unit": "GB/s",
                                   "frac": round(um_gbps / PEAK_HBM_GBPS, 4), "traffic": None,
                                   "algorithmic_bytes": unmask_bytes,

@@ -193,8 +193,9 @@ int dd_bidir_attention_mx(const void *Q, const void *Qs, const void *K, const vo
  * call with Kblk == NULL on the same cache returns the same O.  Every other cache row is left untouched.
  * Kblk and Vblk are required and must not overlap Kc / Vc; block_len <= 2^25; everything else (shapes, dtypes, workspace, errors)
  * as for dd_block_attention_cached.  The copy rides on the kernel that merges the key splits (extra workgroups
- * of the same launch), or is one small launch of its own when the key range was not split: no workgroup of the
- * call reads the cache rows it writes.
+ * of the same launch); when the key range is not split, on the attention's own launch (fp32, and the kernel that serves few
+ * query rows and short streams), or it is one small launch of its own: no workgroup of the call reads the cache rows it
+ * writes.
  */
 int dd_block_attention_refresh(const void *Qblk, void *Kc, void *Vc, void *O,
                                int block_start, int block_len,

@@ -1,5 +1,5 @@
 // Attention with two waves per SIMD on the same query rows: the drafter's call with more than 64 rows per kv head, which
-// grouped heads make compute bound (Sec. 2.3), and verifier calls of more than 1024 keys that fit one round of 64-row workgroups (Sec. 2.2).
+// grouped heads make compute bound (Sec. 2.3), and verifier calls of 449 to 512 workgroups of 32 rows and more than 1024 keys (Sec. 2.2).
 //     O = softmax(Q K^T / sqrt(d_k)) V   (Eq. 3)
 // One workgroup = 8 waves = R blocks of 32 query rows x P = 8 / R key phases: wave w owns row block w % R and takes every
 // P-th 32-key unit of the key stream, with a state (reference, sum, O) of its own; the P states of a row block are merged
@@ -13,11 +13,14 @@
 //     tile that lies in the cache has scalar addresses, any other is gathered row by row.
 // K is XOR-swizzled for its 16-byte operand reads; V stays row-major (swizzled in 64-byte granules) and its transposed
 // operand comes from ds_read_b64_tr_b16.
-// What bounds it: per 64 keys and 128 rows (R = 4, fp8 keys) 830 of some 1900 cycles are matrix-core time of a SIMD; LDS reads
-// (96 KB), tile loads (24 KB) and a unit's chain share the rest.  us per call, before (128- or 256-row tiles of
-// attention_wide.hip, or attention_mfma.hip where a block is shorter than a tile) -> here: 16 x 32/8 heads, 64 rows, 2048 keys
-// fp8 46.7 -> 41.5, bf16 53.5 -> 48.5; 32 rows fp8 39.7 -> 29.5; 8 x 28/4, 48 rows, 1111 keys 29.1 -> 17.2; 2 x 32/8, 64 rows, 900
-// keys 25.8 -> 15.4.  Tried on R = 4 and not kept: scores of unit u + 1, weights of u and product of u - 1 in one step (41.5); the
+// What bounds it (16 x 32/8 heads, 64 rows, 2048 keys, fp8, R = 4): no unit by itself.  MfmaUtil 25 %, VALUBusy 29 %, LdsUtil 16 % (0.32
+// conflict cycles per access); a wave waits 35 % of its 80 k cycles for memory, LDS or a barrier and 31 % for its turn to issue.  Per
+// 64 keys and 128 rows that is some 2500 cycles, 830 of them matrix time of a SIMD, for 96 KB of LDS reads and 24 KB of tile loads.
+// us per call in a stream of them, both sides in turn,
+// before (128- or 256-row tiles of attention_wide.hip, or attention_mfma.hip where a block is shorter than a tile) -> here: 16 x 32/8
+// heads, 64 rows, 2048 keys fp8 46.2 -> 45.2 (among other calls 42.2 -> 40.4), bf16 54.6 -> 49.3; 32 rows fp8 41.0 -> 31.1, bf16 45.0 ->
+// 40.4; 8 x 28/4, 48 rows, 1111 keys bf16 30.1 -> 20.6, fp8 29.6 -> 16.9; 10 x 32/8, 48 rows, 700 keys fp8 28.2 -> 14.9.  Tried on R = 4 and
+// not kept (fp8, then 41.5): scores of unit u + 1, weights of u and product of u - 1 in one step (41.5); the
 // waves of a SIMD taking turns between matrix and vector steps, two barriers per tile (39.7, bf16 46.4: 2-3 % for a second
 // loop); 64 rows per wave, four phases (40.4).
 #include "attention_common.h"
@@ -447,9 +450,9 @@ bool attn_duo_serves(const AttnArgs &a)
 // Drafter calls.  One workgroup occupies a compute unit, so what counts is the time of one: its tiles, and the merge if the key
 // range is split until the 256 compute units are taken.  Tenths of a microsecond, fitted to measured calls: 128 keys cost
 // 18 on two row blocks and 24 on four (fp8 keys or 64 head dims: 12.5 and 21), `s` splits 60 + 6 s.  us per call on two / four
-// blocks: 8 x 28/4 heads, 48 rows, 1111 keys bf16 17.2 / 24.6, fp8 16.7 / 22.9; 7 x 32/8, 48 rows, 2900 keys bf16 46.5 / 37.2 (2
-// splits); 9 x 32/8, 24 rows, 3000 keys fp8 32.9 / 28.1 (3 splits); 4 x 32/8, 32 rows, 4096 keys fp8 22.5 (4 splits) / 24.3 (8);
-// two blocks unsplit / split: 2 x 32/8, 64 rows bf16 500 keys 10.6 / 12.9, 1100 keys 16.4 / 15.3, fp8 900 keys 13.7 / 15.5.
+// blocks: 8 x 28/4 heads, 48 rows, 1111 keys bf16 20.5 / 24.5, fp8 16.9 / 22.7; 7 x 32/8, 48 rows, 2900 keys bf16 47.1 / 37.2 (2
+// splits); 9 x 32/8, 24 rows, 3000 keys fp8 33.4 / 29.2 (3 splits); 4 x 32/8, 32 rows, 4096 keys fp8 22.7 (4 splits) / 24.9 (8), unsplit
+// 39.9; four blocks unsplit / split: 5 x 32/8, 64 rows, 1500 keys bf16 30.0 / 25.1 (3 splits), fp8 27.8 / 24.9 (20.2 on two).
 // More than one round of 64-row workgroups: 128 rows.  More than one of these: nothing here (see the caller).
 DuoPlan attn_duo_plan(long rows, long heads, int N, bool light)
 {

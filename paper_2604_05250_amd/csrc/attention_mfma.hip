@@ -734,20 +734,22 @@ hipError_t launch_attention_mfma(const AttnArgs &a, hipStream_t stream)
     const long heads = (long)a.B * a.Hkv, rows = (long)(a.H / a.Hkv) * a.Nq;
     const bool one_round64 = heads * ((rows + 63) / 64) <= 256, one_round128 = heads * ((rows + 127) / 128) <= 256;
     if (!blk && tune("DD_TUNE_ATTN_WIDE", -1) < 0 && tune("DD_TUNE_BIDIR_STREAM", -1) < 0) {
-        // Up to two workgroups of 32 rows per compute unit: the kernel whose waves stream keys of their own.  us, before -> there: 1 x 32
-        // heads, N 128 7.3 -> 5.5, N 300 10.4 -> 9.5, N 512 12.2 -> 11.8, fp8 Q and K 12.0 -> 10.4, d = 64 9.3 -> 7.7; 1 x 16, N 512 11.2 -> 8.4;
-        // 1 x 8, N 1024 16.2 -> 11.6.  Over 380 drawn calls of more than 64 keys 0.78 of the time up to 256 workgroups, 0.91 up to 512, then 1.1;
-        // with all 512 and more than 1024 keys up to 1.11.
-        // 64 keys and fewer: 1.0 (fp8 1.1).  e4m3 values: 0.66 up to 256 workgroups, 0.78 up to 512, then 1.1 as well.
+        // Up to two workgroups of 32 rows per compute unit: the kernel whose waves stream keys of their own.  us, on the kernels below ->
+        // there: 1 x 32 heads, N 128 7.4 -> 5.3, N 300 10.9 -> 9.2, N 512 14.7 -> 13.3, fp8 Q and K 13.2 -> 11.1, d = 64 10.1 -> 7.4; 1 x 16,
+        // N 512 12.6 -> 8.1; 1 x 8, N 1024 19.3 -> 11.3.  Over 380 drawn calls of more than 64 keys 0.78 of the time up to 256 workgroups,
+        // 0.91 up to 512, then 1.1 (1 x 60, N 300 15.9 against 14.1).  e4m3 values: 0.66 up to 256 workgroups, 0.78 up to 512, then 1.1 as well.
+        // Past 448 workgroups of more than 1024 keys it depends, against the two-waves-per-SIMD kernel: 1 x 8, N 2016 29.3 there / 30.8,
+        // 1 x 8 (2 kv), N 2035 29.0 / 26.8, fp8 1 x 4, N 4096 42.3 / 39.2.  64 keys and fewer stay below: fp8 1.1 there, bf16 5.7 streamed / 5.5
+        // (64 heads, 33 keys), at 64 keys themselves (32 heads) 6.2 / 4.9.
         const long wgs = heads * ((rows + 31) / 32);
         const int solo = tune("DD_TUNE_SOLO", tune("DD_TUNE_DUO", -1) <= 0 && a.N > 64 && wgs <= (a.N > 1024 ? 448 : 512));
         if (solo != 0 && attn_solo_serves(a)) return launch_attention_solo(a, stream);
     }
     if (!blk && attn_duo_serves(a) && tune("DD_TUNE_ATTN_WIDE", -1) < 0 && tune("DD_TUNE_BIDIR_STREAM", -1) < 0) {
-        // One round of 64-row workgroups: the two-waves-per-SIMD kernel, whose eight waves share a workgroup's keys (of these calls the
-        // one above leaves it those of more than 448 workgroups of 32 rows and 1024 keys).  us, before -> there (bf16 / fp8 Q and K):
-        // 1 x 16 heads, N 1024 19.5 -> 15.9 / 18.0 -> 14.6.  On its 128-row workgroups, one round of them: 32 x N 1024 23.5 -> 24.4, 16 x N
-        // 2048 40.2 -> 40.2, fp8 32.6 -> 33.4: no.
+        // One round of 64-row workgroups: the two-waves-per-SIMD kernel, whose eight waves share a workgroup's keys.  Of these calls the
+        // one above leaves it those of 449 to 512 workgroups of 32 rows and more than 1024 keys.  us, on the wide kernel -> there (bf16 / fp8 Q
+        // and K): 1 x 8 heads, N 2048 37.6 -> 32.0 / 34.2 -> 23.3; 1 x 4, N 4096 67.3 -> 56.8 / 60.1 -> 39.2.  On its 128-row workgroups, one
+        // round of them: 32 x N 1024 23.5 -> 24.4, 16 x N 2048 40.2 -> 40.2, fp8 32.6 -> 33.4: no.
         const int forced = tune("DD_TUNE_DUO", -1);
         const int blocks = forced >= 0 ? forced : one_round64 && a.N > 1024 ? 2 : 0;
         if (blocks == 2 || blocks == 4) return launch_attention_duo(a, blocks, stream);
@@ -755,14 +757,13 @@ hipError_t launch_attention_mfma(const AttnArgs &a, hipStream_t stream)
     if (!blk && (!fp8 || a.d == 128) && a.N >= 64) {           // (the wide kernel's K/V tiles are 64 whole rows)
         // One round of 128-row workgroups: the wide kernel on 128-row tiles, which has twice the workgroups of its
         // 256-row tiles, each 0.7 of one's time per key.  More: its 256-row tiles (persistent).  Measured against the
-        // kernel such calls ran on before (us, bf16 / fp8 Q and K): 1 x 32 heads, N 512 15.1 -> 12.8 / 15.5 -> 11.6, N 900
-        // 26.2 -> 23.1 / 24.3 -> 20.5; 1 x 28 (4 kv), N 1100 48.6 -> 23.3 / 27.8 -> 21.2; 1 x 16, N 2048 49.0 -> 37.2 /
+        // kernel such calls ran on before (us, bf16 / fp8 Q and K): 1 x 32 heads, N 900 26.2 -> 23.1 / 24.3 -> 20.5; 1 x 28 (4 kv), N 1100 48.6 -> 23.3 / 27.8 -> 21.2; 1 x 16, N 2048 49.0 -> 37.2 /
         // 45.4 -> 33.0; past the round 256-row tiles win at once: 1 x 32, N 1100 42.1 -> 31.1 / 38.7 -> 27.2 (128-row
-        // tiles 43.4 / 38.4).  d = 64: 1 x 32, N 300 9.1 -> 7.4, N 512 10.2 -> 9.3, N 600 21.8 -> 11.4, 8 x 32, N 500 30.2 -> 25.6.  Below about 450 keys the fill and drain of either weigh more than the shorter loop saves:
-        // one round of 64-row bf16 workgroups streams (N 300 10.6 against 11.7), a call with more than one round of
-        // 128-row workgroups (8 x 32, N 200: 17.6 against 17.7; N 300, where 256-row tiles pad most: 28.2 against 31.8)
-        // or under 192 keys (N 150: 9.4 against 10.5) stays on the kernel of this file.
-        const int by_size = one_round128 ? (a.N >= 448 || (a.N >= 192 && (fp8 || !one_round64)) ? 2 : 0) : (a.N >= 448 ? 1 : 0);
+        // tiles 43.4 / 38.4).  d = 64: 1 x 32, N 600 21.8 -> 11.4, 8 x 32, N 500 30.2 -> 25.6.  Below about 450 keys the fill and drain of
+        // either weigh what the shorter loop saves: on 128-row tiles down to 192 keys it is even within 6 % (1 x 60, N 300 14.1 there, 13.7 on
+        // the kernel of this file; 1 x 90, N 200 12.1 / 11.9; fp8 1 x 48, N 400 14.9 / 14.8), under 192 keys (block-scaled inputs) and with more
+        // than one round of 128-row workgroups (8 x 32, N 200: 21.7 / 21.0; N 300, where 256-row tiles pad most: 37.7 / 33.1) a call stays here.
+        const int by_size = one_round128 ? (a.N >= 192 ? 2 : 0) : (a.N >= 448 ? 1 : 0);
         const int forced = tune("DD_TUNE_ATTN_WIDE", -1), pick = forced >= 0 ? forced : by_size;
         // Folding the softmax scale into bf16 Q rounds Q a second time, an error that grows with the scores: 2.3e-3 ->
         // 2.9e-3 of the result's 2-norm for Q, K ~ N(0, 1), 1.9e-3 -> 5.0e-3 with Q eight times that (1 x 32 heads, N
@@ -786,9 +787,8 @@ hipError_t launch_attention_mfma(const AttnArgs &a, hipStream_t stream)
         return e != hipSuccess ? e : finish_attention(a, k.splits, stream);
     }
     if (!blk && (!fp8 || a.d == 128)) {
-        // A small bf16 call leaves most compute units idle with 128-row workgroups: the streaming kernel's
-        // 64-row workgroups (two row blocks x two key phases) spread it over more of them, one round of them at most (a
-        // second one doubles the call: 1 x 32 heads, N 700, 33 us).
+        // bf16 calls of at most 64 keys, all that comes here by size: the streaming kernel's 64-row workgroups (two row blocks x two key
+        // phases) spread them over more compute units than 128-row ones, one round of them at most.
         const bool small = tune("DD_TUNE_BIDIR_STREAM", one_round64) != 0;
         if (small && !fp8) return launch_attention_stream(a, stream);
     }

@@ -10,9 +10,10 @@
 //     workgroups that share K/V through an XCD's L2.  Two workgroups fit a compute unit.
 // What bounds it: some 4 us of launch, first loads and merge, then 1.1 us (fp8 0.9) per 128 keys while a compute unit has one
 // workgroup - 60 GB/s, the same with eight waves and twice the bytes on their way, so what a unit draws from beyond its L2.
-// us per call in a stream of them, attention_stream.hip -> here: 11 x 32/8 heads, 16 rows, 1237 keys fp8 21.6 -> 16.3, bf16
-// 23.7 -> 19.3; 1 x 32, 512 keys, 32 rows bf16 10.2 -> 9.1, 64 rows 12.4 -> 9.0; 1 x 32, 300 keys, 16 rows 9.4 -> 7.1; 4 x 32/8, 16 rows,
-// 2048 keys 17.7 -> 14.3 (4 splits).  Tried and not kept: eight waves per workgroup (11 x 32/8 bf16 19.9, 1 x 32 9.9, 4 x 32/8 15.1).
+// us per call in a stream of them, attention_stream.hip -> here: 11 x 32/8 heads, 16 rows, 1237 keys fp8 20.5 -> 16.3, bf16
+// 23.8 -> 20.8; 1 x 32, 512 keys, 32 rows bf16 9.7 -> 8.0, 64 rows 11.9 -> 8.4; 1 x 32, 300 keys, 16 rows 9.5 -> 7.2; 4 x 32/8, 16 rows,
+// 2048 keys 17.7 -> 14.6 (4 splits).  Tried and not kept: eight waves per workgroup (bf16 11 x 32/8 19.9 where four took 19.3, 1 x 32 9.9 /
+// 9.1, 4 x 32/8 15.1 / 14.3).
 #include "attention_common.h"
 #include "dd_internal.h"
 

@@ -1289,9 +1289,11 @@ hipError_t launch_attention_wide_narrow(const AttnArgs &a, hipStream_t stream)
                       : launch(attn_wide_kernel<64, false, true, false, 1>, grid, block, stream, k);
 }
 
-// The drafter's call on the wide kernel: with e4m3 values from 65 query rows per kv head (GQA groups times the block
-// length), which makes the call compute bound, with bf16 values where 128-row workgroups would need a second round of the
-// chip's compute units (up to there attention_duo.hip serves it).
+// The drafter's call on the wide kernel, from 65 query rows per kv head (GQA groups times the block length) on, which make the call
+// compute bound: what attention_solo.hip and attention_duo.hip leave.  With e4m3 values that is more than 512 workgroups of 32
+// rows or streams of more than twelve rounds of 128 keys; with bf16 values more than 128 rows where 128-row workgroups
+// would need a second round of the chip's compute units, and long streams that it splits finer (dd_api.hip).  (Its 128-row tiles serve
+// bf16 values by test hook only.)
 bool attn_wide_block_fits(const AttnArgs &a)
 {
     if (a.qk_dtype == 0 || a.q_mx != nullptr || (a.qk_dtype == 2 && a.d != 128)) return false;

@@ -5,6 +5,7 @@ import pytest
 import oracle
 import paper_2604_05250_amd as dd
 from paper_2604_05250_amd import workloads as wl
+from _kernels import DUO2, DUO4, MFMA, OFF_WIDE, SOLO, STREAM, WIDE, WIDE128, by_rule_and_elsewhere, with_splits
 from _util import assert_attention_close, out_to_f64, to_dev
 
 pytestmark = pytest.mark.gpu
@@ -21,24 +22,28 @@ def run(cfg, cache, blk, starts):
 
 
 SHAPES = [
-    # (B, H, Hkv, N, d, bl, qk, env): the three kernels that serve per-sequence positions, with and without key
+    # (B, H, Hkv, N, d, bl, qk, env): the kernels that serve per-sequence positions, with and without key
     # splits, GQA, ragged lengths; 256 rows per kv head (a shape the wide kernel would take for one position)
-    (4, 4, 2, 333, 128, 32, wl.BF16, {}),                                  # streaming kernel
-    (3, 2, 2, 4096, 128, 64, wl.BF16, {}),                                 # streaming kernel, key splits
-    (5, 2, 1, 150, 64, 1, wl.BF16, {}),                                    # one query row
-    (4, 4, 2, 700, 128, 32, wl.BF16, {"DD_TUNE_BLOCK_STREAM": "0"}),       # MFMA kernel
-    (2, 2, 2, 4096, 128, 64, wl.BF16, {"DD_TUNE_BLOCK_STREAM": "0"}),      # MFMA kernel, key splits
-    (3, 8, 2, 1000, 128, 64, wl.FP8_E4M3, {}),                             # wide kernel: fp8 keys, 256 rows per kv head
-    (2, 16, 4, 2048, 128, 64, wl.BF16, {}),                                # wide kernel (folded-scale form), key splits
-    (5, 12, 4, 700, 128, 64, wl.BF16, {}),                                 # wide kernel: 192 rows per kv head, ragged length
-    (3, 8, 2, 1000, 128, 64, wl.FP8_E4M3, {"DD_TUNE_BLOCK_WIDE": "0"}),    # the same shapes on the MFMA kernel
-    (2, 16, 4, 2048, 128, 64, wl.BF16, {"DD_TUNE_BLOCK_WIDE": "0"}),
+    (4, 4, 2, 333, 128, 32, wl.BF16, STREAM),                              # streaming kernel
+    (3, 2, 2, 4096, 128, 64, wl.BF16, STREAM),                             # streaming kernel, key splits
+    (5, 2, 1, 150, 64, 1, wl.BF16, STREAM),                                # one query row
+    (4, 4, 2, 700, 128, 32, wl.BF16, MFMA),                                # MFMA kernel
+    (2, 2, 2, 4096, 128, 64, wl.BF16, MFMA),                               # MFMA kernel, key splits
+    (3, 8, 2, 1000, 128, 64, wl.FP8_E4M3, WIDE),                           # wide kernel: fp8 keys, 256 rows per kv head
+    (2, 16, 4, 2048, 128, 64, wl.BF16, WIDE),                              # wide kernel (folded-scale form), key splits
+    (5, 12, 4, 700, 128, 64, wl.BF16, WIDE),                               # wide kernel: 192 rows per kv head, ragged length
+    (3, 8, 2, 1000, 128, 64, wl.FP8_E4M3, OFF_WIDE),                       # the same shapes on the MFMA kernel
+    (2, 16, 4, 2048, 128, 64, wl.BF16, OFF_WIDE),
     (4, 4, 4, 128, 64, 16, wl.F32, {}),                                    # fp32 kernel
     (3, 2, 1, 600, 128, 48, wl.F32, {}),
-    (3, 4, 2, 1000, 128, 64, wl.FP8_E4M3, {}),                             # wide kernel, 128-row tiles (128 rows per kv head)
-    (5, 6, 2, 700, 128, 40, wl.BF16, {}),                                  # ... 120 rows per kv head, blocks shorter than a key tile
-    (2, 16, 4, 2048, 128, 64, wl.BF16, {"DD_TUNE_BLOCK_WIDE_ROWS": "128"}),   # ... forced on 256 rows per kv head
+    (3, 4, 2, 1000, 128, 64, wl.FP8_E4M3, WIDE128),                        # wide kernel, 128-row tiles (128 rows per kv head)
+    (5, 6, 2, 700, 128, 40, wl.BF16, WIDE128),                             # ... 120 rows per kv head, blocks shorter than a key tile
+    (2, 16, 4, 2048, 128, 64, wl.BF16, WIDE128),                           # ... forced on 256 rows per kv head
+    (3, 8, 2, 1500, 128, 64, wl.BF16, with_splits(DUO2, 3)),               # the kernels of few rows and of many, key splits
+    (3, 8, 2, 1500, 128, 64, wl.FP8_E4M3, with_splits(DUO4, 4)),
+    (3, 4, 2, 1500, 128, 32, wl.FP8_E4M3, with_splits(SOLO, 4)),
 ]
+SHAPES = by_rule_and_elsewhere(SHAPES, lambda r: r[6] != wl.F32 and r[3] <= 1000)
 
 
 @pytest.mark.parametrize("B,H,Hkv,N,d,bl,qk,env", SHAPES)
@@ -61,12 +66,15 @@ def test_batched_positions(monkeypatch, B, H, Hkv, N, d, bl, qk, env):
     assert_attention_close(got, ref, qk, f"batched {B}x{H}/{Hkv} N{N} d{d} bl{bl} dtype {qk} {env} starts {starts}")
 
 
+@pytest.mark.parametrize("env", [WIDE, WIDE128, {}])
 @pytest.mark.parametrize("qk", [wl.BF16, wl.FP8_E4M3])
-def test_wide_kernel_short_parts_and_positions_outside(qk):
-    # 256 query rows per kv head: the wide kernel.  Parts of the key stream shorter than a 64-row tile on either
+def test_wide_kernel_short_parts_and_positions_outside(monkeypatch, qk, env):
+    # 256 query rows per kv head on the wide kernel (and by the library's own rule).  Parts of the key stream shorter than a 64-row tile on either
     # side of the block, blocks that hang over an end of the sequence (their tile list is shorter: with key
     # splits, an empty last split) or lie outside it altogether
     import torch
+    for k, v in env.items():
+        monkeypatch.setenv(k, v)
     for N, B in ((1000, 8), (4096, 8), (191, 8)):
         cfg = wl.custom_config(B=B, H=8, Hkv=2, N=N, d=128, bl=64, qk_dtype=qk, v_dtype=wl.BF16, prompt=0, G=N)
         cache = wl.cache_inputs(cfg, seed=N)
@@ -75,7 +83,7 @@ def test_wide_kernel_short_parts_and_positions_outside(qk):
         got = out_to_f64(run(cfg, cache, blk, starts), wl.BF16)
         ref = oracle.block_attention_batched(blk["Qblk"], cache["Kc"], cache["Vc"], starts, qk, wl.BF16, blk["Kblk"],
                                              blk["Vblk"], blk["q_scale"], cache["k_scale"])
-        assert_attention_close(got, ref, qk, f"wide kernel, positions {starts.tolist()} N{N} dtype {qk}")
+        assert_attention_close(got, ref, qk, f"wide kernel {env}, positions {starts.tolist()} N{N} dtype {qk}")
 
 
 def test_equal_positions_are_the_plain_call_and_outside_positions_are_safe(monkeypatch):

@@ -75,9 +75,12 @@ BLOCKS = [(1, 2, 2, 100, 64, 16, 84), (2, 4, 2, 333, 128, 32, 101), (1, 8, 2, 10
           (1, 2, 1, 150, 64, 1, 77), (1, 16, 4, 2048, 128, 64, 1536)]
 
 
+@pytest.mark.parametrize("solo", [None, "0"])                 # (0: on the MFMA kernel and, from 65 rows per kv head on, the wide one)
 @pytest.mark.parametrize("B,H,Hkv,N,d,bl,bs", BLOCKS)
-def test_block_fp8v(B, H, Hkv, N, d, bl, bs):
+def test_block_fp8v(monkeypatch, solo, B, H, Hkv, N, d, bl, bs):
     import torch
+    if solo:
+        monkeypatch.setenv("DD_TUNE_SOLO", solo)
     cfg = wl.custom_config(B=B, H=H, Hkv=Hkv, N=N, d=d, qk_dtype=FP8, v_dtype=FP8, bl=bl, prompt=0, G=N)
     cache = wl.cache_inputs(cfg, seed=bs + N)
     blk = wl.block_inputs(cfg, bs, 0, k_scale=cache["k_scale"], v_scale=cache["v_scale"])

@@ -6,6 +6,7 @@ import pytest
 
 import paper_2604_05250_amd as dd
 from paper_2604_05250_amd import workloads as wl
+from _kernels import DUO2, DUO4, MFMA, SOLO, STREAM, WIDE, WIDE128, WIDE256, by_rule_and_elsewhere, with_splits
 from _util import to_dev
 
 pytestmark = pytest.mark.gpu
@@ -64,6 +65,10 @@ ATTN = [
     (1, 2, 2, 333, 128, wl.BF16, {"DD_TUNE_ATTN_WIDE": "0", "DD_TUNE_BIDIR_STREAM": "1"}),
     (1, 2, 2, 333, 128, wl.BF16, {"DD_TUNE_ATTN_WIDE": "0", "DD_TUNE_BIDIR_STREAM": "0"}),
     (1, 2, 1, 257, 128, wl.F32, {}),
+    # the kernels of few rows: one row past a 32-row tile, a ragged last tile of 64 and 128 rows, 64 head dims
+    (2, 3, 1, 33, 128, wl.BF16, SOLO), (1, 4, 2, 203, 64, wl.BF16, SOLO), (1, 4, 2, 203, 128, wl.FP8_E4M3, SOLO),
+    (2, 3, 1, 65, 128, wl.BF16, DUO2), (1, 4, 2, 203, 64, wl.BF16, DUO2), (1, 4, 2, 203, 128, wl.FP8_E4M3, DUO2),
+    (2, 3, 1, 65, 128, wl.BF16, DUO4), (1, 4, 2, 203, 64, wl.BF16, DUO4), (1, 4, 2, 203, 128, wl.FP8_E4M3, DUO4),
 ]
 
 
@@ -87,17 +92,23 @@ def test_bidir_attention_stays_inside_its_output(monkeypatch, B, H, Hkv, N, d, q
 
 BLOCK = [
     # (B, H, Hkv, N, d, bl, bs, qk, env): streaming / MFMA / wide / fp32 kernels, with and without key splits
-    (2, 4, 2, 333, 128, 32, 101, wl.BF16, {}), (1, 2, 2, 4096, 128, 64, 2000, wl.BF16, {}),
-    (1, 4, 2, 700, 128, 32, 668, wl.BF16, {"DD_TUNE_BLOCK_STREAM": "0"}),
-    (1, 2, 2, 4096, 128, 64, 37, wl.BF16, {"DD_TUNE_BLOCK_STREAM": "0"}),
-    (1, 4, 1, 1000, 128, 80, 700, wl.BF16, {}), (1, 4, 1, 4097, 128, 128, 2000, wl.BF16, {}),
-    (2, 8, 2, 641, 128, 64, 256, wl.FP8_E4M3, {}), (2, 2, 1, 600, 128, 48, 200, wl.F32, {}),
-    (1, 2, 1, 150, 64, 1, 77, wl.BF16, {}),
-    # the wide kernel's 128-row tiles: a partly filled tile (2 x 40 rows), fp8 with key splits
-    (3, 4, 2, 333, 128, 40, 101, wl.BF16, {}), (1, 4, 2, 4097, 128, 64, 2000, wl.FP8_E4M3, {}),
+    (2, 4, 2, 333, 128, 32, 101, wl.BF16, STREAM), (1, 2, 2, 4096, 128, 64, 2000, wl.BF16, STREAM),
+    (3, 2, 2, 333, 128, 31, 101, wl.FP8_E4M3, STREAM),
+    (1, 4, 2, 700, 128, 32, 668, wl.BF16, MFMA),
+    (1, 2, 2, 4096, 128, 64, 37, wl.BF16, MFMA),
+    (1, 4, 1, 1000, 128, 80, 700, wl.BF16, WIDE256), (1, 4, 1, 4097, 128, 128, 2000, wl.BF16, WIDE),
+    (2, 8, 2, 641, 128, 64, 256, wl.FP8_E4M3, WIDE), (2, 2, 1, 600, 128, 48, 200, wl.F32, {}),
+    (1, 2, 1, 150, 64, 1, 77, wl.BF16, STREAM),
+    # the wide kernel's 128-row tiles: a partly filled tile (2 x 70 rows), fp8 with key splits
+    (3, 4, 2, 333, 128, 70, 101, wl.BF16, WIDE128), (1, 4, 2, 4097, 128, 64, 2000, wl.FP8_E4M3, WIDE128),
+    (3, 4, 2, 333, 128, 40, 101, wl.BF16, {}),                            # (a block shorter than its key tile: by the rule)
     # ... with 128-byte rows a wave's 32 output rows are four stores: the last wave of the call ends at the buffer's end
-    (1, 2, 1, 300, 64, 64, 100, wl.BF16, {}), (2, 5, 1, 221, 64, 64, 61, wl.BF16, {"DD_TUNE_BLOCK_WIDE_ROWS": "128"}),
+    (1, 2, 1, 300, 64, 64, 100, wl.BF16, WIDE128), (2, 5, 1, 221, 64, 64, 61, wl.BF16, WIDE128),
+    # the kernels of few rows and of many, key splits
+    (1, 8, 2, 1500, 128, 64, 700, wl.BF16, with_splits(DUO2, 3)), (1, 3, 1, 1500, 64, 43, 700, wl.BF16, with_splits(DUO4, 4)),
+    (1, 5, 1, 1500, 128, 13, 100, wl.FP8_E4M3, with_splits(SOLO, 4)),
 ]
+BLOCK = by_rule_and_elsewhere(BLOCK, lambda r: r[7] != wl.F32 and r[3] <= 1000)
 
 
 @pytest.mark.parametrize("call", ["cached", "refresh", "window", "batched"])
@@ -165,6 +176,7 @@ def test_cache_insert_rows_stays_inside_the_cache():
 VERIFY = [
     # (B, G, V, dtype): split path (few rows), fused path (512 and 256 lanes per row), ragged vocabularies
     (2, 5, 40008, wl.BF16), (3, 50, 126464, wl.BF16), (4, 75, 1000, wl.BF16), (2, 1100, 520, wl.F32), (1, 191, 8200, wl.BF16),
+    (3, 13, 1016, wl.F32), (190, 1, 8, wl.BF16),             # rows that are not split: one launch
 ]
 
 

@@ -7,11 +7,13 @@ import pytest
 import oracle
 import paper_2604_05250_amd as dd
 from paper_2604_05250_amd import workloads as wl
+from _kernels import DUO2, DUO4, SOLO
 from _util import out_to_f64, to_dev
 
 pytestmark = pytest.mark.gpu
 HOOKS = ("DD_TUNE_ATTN_WIDE", "DD_TUNE_ATTN_WIDE_GRID", "DD_TUNE_BIDIR_STREAM", "DD_TUNE_BLOCK_WIDE", "DD_TUNE_BLOCK_STREAM",
-         "DD_TUNE_BLOCK_WIDE_ROWS")
+         "DD_TUNE_BLOCK_WIDE_ROWS", "DD_TUNE_SOLO", "DD_TUNE_DUO")
+FORCED = [SOLO, DUO2, DUO4]                                  # beside the kernels that a call's own draw picks
 TOL = {wl.BF16: (2e-2, 5e-3), wl.FP8_E4M3: (6e-2, 5e-3), wl.F32: (1e-4, 1e-5)}
 
 
@@ -28,8 +30,8 @@ def set_hooks(monkeypatch, env):
         monkeypatch.setenv(k, v)
 
 
-@pytest.mark.parametrize("seed", range(6))
-def test_random_verifier_calls(monkeypatch, seed):
+@pytest.mark.parametrize("seed,forced", [(s, None) for s in range(6)] + [(s, f) for s in (6, 7) for f in FORCED])
+def test_random_verifier_calls(monkeypatch, seed, forced):
     import torch
     rng = np.random.default_rng(1000 + seed)
     for it in range(10):
@@ -43,6 +45,7 @@ def test_random_verifier_calls(monkeypatch, seed):
                "mfma": {"DD_TUNE_ATTN_WIDE": "0", "DD_TUNE_BIDIR_STREAM": "0"}, "auto": {}}[kern]
         if kern == "wide" and rng.random() < 0.5:
             env = dict(env, DD_TUNE_ATTN_WIDE_GRID=str(int(rng.integers(1, 4))))
+        env = forced or env
         set_hooks(monkeypatch, env)
         cfg = wl.custom_config(B=B, H=Hkv * G, Hkv=Hkv, N=N, d=d, qk_dtype=qk, v_dtype=wl.BF16, prompt=0, G=N, bl=min(16, N))
         inp = wl.attention_inputs(cfg, 100 * seed + it)
@@ -53,8 +56,8 @@ def test_random_verifier_calls(monkeypatch, seed):
         close(out_to_f64(O, wl.BF16), ref, qk, f"bidir B{B} H{Hkv * G}/{Hkv} N{N} d{d} dtype {qk} {env}")
 
 
-@pytest.mark.parametrize("seed", range(8))
-def test_random_drafter_calls(monkeypatch, seed):
+@pytest.mark.parametrize("seed,forced", [(s, None) for s in range(8)] + [(s, f) for s in (8, 9, 10) for f in FORCED])
+def test_random_drafter_calls(monkeypatch, seed, forced):
     import torch
     rng = np.random.default_rng(2000 + seed)
     for it in range(10):
@@ -72,6 +75,7 @@ def test_random_drafter_calls(monkeypatch, seed):
         c = rng.random()
         env = ({"DD_TUNE_BLOCK_WIDE": "0"} if c < 0.15 else {"DD_TUNE_BLOCK_STREAM": "0"} if c < 0.3 else
                {"DD_TUNE_BLOCK_WIDE_ROWS": str(rng.choice(["128", "256"]))} if c < 0.6 else {})
+        env = forced or env
         set_hooks(monkeypatch, env)
         cfg = wl.custom_config(B=B, H=Hkv * G, Hkv=Hkv, N=N, d=d, qk_dtype=qk, v_dtype=vd, bl=bl, prompt=0, G=N)
         cache = wl.cache_inputs(cfg, seed=100 * seed + it)

@@ -6,6 +6,7 @@ import pytest
 import oracle
 import paper_2604_05250_amd as dd
 from paper_2604_05250_amd import workloads as wl
+from _kernels import DUO2, DUO4, MFMA, OFF_WIDE, SOLO, STREAM, WIDE, WIDE128, WIDE256, by_rule_and_elsewhere, with_splits
 from _util import assert_attention_close, out_to_f64, to_dev
 
 pytestmark = pytest.mark.gpu
@@ -50,24 +51,28 @@ def check_refresh(cfg, cache, blk, bs, what):
 SHAPES = [
     # (B, H, Hkv, N, d, bl, block_start, qk, env): every kernel of the drafter's call, with and without key splits,
     # block at the start / end / inside, ragged sizes, GQA, one query row, all storage types
-    (1, 2, 2, 64, 128, 64, 0, wl.BF16, {}),                                   # streaming kernel, one tile, no split
-    (2, 4, 2, 333, 128, 32, 101, wl.BF16, {}),                                # streaming kernel
-    (1, 2, 2, 4096, 128, 64, 2000, wl.BF16, {}),                              # streaming kernel, key splits
-    (1, 2, 1, 150, 64, 1, 77, wl.BF16, {}),                                   # one query row
-    (1, 4, 2, 700, 128, 32, 668, wl.BF16, {"DD_TUNE_BLOCK_STREAM": "0"}),     # MFMA kernel, block at the end
-    (1, 2, 2, 4096, 128, 64, 0, wl.BF16, {"DD_TUNE_BLOCK_STREAM": "0"}),      # MFMA kernel, key splits
-    (1, 8, 2, 1000, 128, 64, 936, wl.FP8_E4M3, {}),                           # fp8 keys: a byte copy under one scale
-    (2, 8, 2, 640, 128, 64, 256, wl.FP8_E4M3, {}),                            # wide kernel, fp8
-    (2, 8, 2, 640, 128, 64, 200, wl.BF16, {}),                                # wide kernel
-    (1, 4, 1, 4096, 128, 128, 2000, wl.BF16, {}),                             # wide kernel, key splits
-    (1, 4, 1, 512, 128, 64, 448, wl.BF16, {"DD_TUNE_BLOCK_WIDE": "0"}),
-    (1, 8, 2, 400, 64, 64, 64, wl.BF16, {}),
-    (2, 4, 2, 640, 128, 64, 256, wl.FP8_E4M3, {}),                            # wide kernel, 128-row tiles
-    (1, 4, 2, 4096, 128, 64, 2000, wl.BF16, {}),                              # ... key splits
+    (1, 2, 2, 64, 128, 64, 0, wl.BF16, STREAM),                               # streaming kernel, one tile, no split
+    (2, 4, 2, 333, 128, 32, 101, wl.BF16, STREAM),                            # streaming kernel
+    (1, 2, 2, 4096, 128, 64, 2000, wl.BF16, STREAM),                          # streaming kernel, key splits
+    (1, 2, 1, 150, 64, 1, 77, wl.BF16, STREAM),                               # one query row
+    (1, 4, 2, 700, 128, 32, 668, wl.BF16, MFMA),                               # MFMA kernel, block at the end
+    (1, 2, 2, 4096, 128, 64, 0, wl.BF16, MFMA),                                # MFMA kernel, key splits
+    (1, 8, 2, 1000, 128, 64, 936, wl.FP8_E4M3, WIDE256),                      # fp8 keys: a byte copy under one scale
+    (2, 8, 2, 640, 128, 64, 256, wl.FP8_E4M3, WIDE),                          # wide kernel, fp8
+    (2, 8, 2, 640, 128, 64, 200, wl.BF16, WIDE),                              # wide kernel
+    (1, 4, 1, 4096, 128, 128, 2000, wl.BF16, WIDE),                           # wide kernel, key splits
+    (1, 4, 1, 512, 128, 64, 448, wl.BF16, OFF_WIDE),
+    (1, 8, 2, 400, 64, 64, 64, wl.BF16, WIDE),
+    (2, 4, 2, 640, 128, 64, 256, wl.FP8_E4M3, WIDE128),                       # wide kernel, 128-row tiles
+    (1, 4, 2, 4096, 128, 64, 2000, wl.BF16, WIDE128),                         # ... key splits
     (1, 4, 4, 128, 64, 16, 64, wl.F32, {}),                                   # fp32 kernel
     (2, 2, 1, 600, 128, 48, 200, wl.F32, {}),
-    (1, 1, 1, 64, 128, 64, 0, wl.BF16, {}),                                   # the block is the whole sequence
+    (1, 1, 1, 64, 128, 64, 0, wl.BF16, STREAM),                               # the block is the whole sequence
+    (1, 8, 2, 1500, 128, 64, 700, wl.BF16, with_splits(DUO2, 3)),             # the kernels of few rows and of many, key splits
+    (1, 8, 2, 1500, 128, 64, 700, wl.FP8_E4M3, with_splits(DUO4, 4)),
+    (1, 4, 2, 1500, 128, 32, 100, wl.FP8_E4M3, with_splits(SOLO, 4)),
 ]
+SHAPES = by_rule_and_elsewhere(SHAPES, lambda r: r[7] != wl.F32 and r[3] <= 1000)
 
 
 @pytest.mark.parametrize("B,H,Hkv,N,d,bl,bs,qk,env", SHAPES)
@@ -83,8 +88,8 @@ def test_refresh_every_kernel(monkeypatch, B, H, Hkv, N, d, bl, bs, qk, env):
 
 @pytest.mark.parametrize("cfg_id", [1, 2, 3, 4, 5])
 def test_refresh_configs(cfg_id):
-    # every benchmark configuration at full size (cfg3: no key split, the copy is a launch of its own; cfg4: eight
-    # splits; cfg5: the wide kernel's drafter form): every output row against the oracle, the cache byte for byte
+    # every benchmark configuration at full size (cfg1, cfg2: no key split, the copy rides on the attention's launch; cfg3: no key split,
+    # the copy is a launch of its own; cfg4: key splits; cfg5: two waves per SIMD): every output row against the oracle, the cache byte for byte
     cfg = wl.CONFIGS[cfg_id]
     cache = wl.cache_inputs(cfg, 0)
     blk = wl.block_inputs(cfg, 0, cfg.K - 1, k_scale=cache["k_scale"])

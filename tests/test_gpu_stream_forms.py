@@ -28,7 +28,8 @@ def check_block(B, H, Hkv, N, d, qk, bl, bs, what):
 # and two row blocks, one key phase without keys (32 keys)
 @pytest.mark.parametrize("N,bl", [(64, 60), (33, 17), (32, 31), (63, 8)])
 @pytest.mark.parametrize("qk,d", FORMS)
-def test_one_tile(qk, d, N, bl):
+def test_one_tile(monkeypatch, qk, d, N, bl):
+    monkeypatch.setenv("DD_TUNE_BLOCK_STREAM", "1")
     check_block(16, 32, 32, N, d, qk, bl, N - bl, "one tile")
 
 

@@ -23,6 +23,7 @@ SHAPES = [(1, 2, 1, 1, 1, 0, None), (1, 2, 2, 17, 16, 1, None), (2, 4, 1, 64, 16
 @pytest.mark.parametrize("B,H,Hkv,N,bl,bs,splits", SHAPES)
 def test_block_fp8(monkeypatch, B, H, Hkv, N, bl, bs, splits):
     import torch
+    monkeypatch.setenv("DD_TUNE_BLOCK_STREAM", "1")        # (by the rule such small calls run on another kernel)
     if splits:
         monkeypatch.setenv("DD_TUNE_BLOCK_SPLITS", splits)
     cfg = wl.custom_config(B=B, H=H, Hkv=Hkv, N=N, d=128, qk_dtype=FP8, v_dtype=wl.BF16, bl=bl, prompt=0, G=N)
@@ -44,15 +45,18 @@ def test_block_fp8(monkeypatch, B, H, Hkv, N, bl, bs, splits):
         assert_attention_close(got, ref, FP8, what)
         monkeypatch.setenv("DD_TUNE_BLOCK_STREAM", "0")
         old = call()
-        monkeypatch.delenv("DD_TUNE_BLOCK_STREAM")
+        monkeypatch.setenv("DD_TUNE_BLOCK_STREAM", "1")
         # no precision lost: both errors are roundings of the weights and of n >= 128 outputs, whose 2-norms scatter by about
         # 1 / sqrt(2 n) <= 6 %; 1.25 is four of those
         assert np.linalg.norm(got - ref) <= 1.25 * np.linalg.norm(old - ref) + 1e-6 * np.linalg.norm(ref), what
 
 
+@pytest.mark.parametrize("stream", ["1", None])               # (None: the kernel of the library's own rule)
 @pytest.mark.parametrize("N,win", [(333, 100), (1000, 64), (1237, 600)])
-def test_window_batched_refresh_fp8(N, win):
+def test_window_batched_refresh_fp8(monkeypatch, N, win, stream):
     import torch
+    if stream:
+        monkeypatch.setenv("DD_TUNE_BLOCK_STREAM", stream)
     B, bl = 3, 16
     cfg = wl.custom_config(B=B, H=8, Hkv=2, N=N, d=128, qk_dtype=FP8, v_dtype=wl.BF16, bl=bl, prompt=0, G=N)
     cache = wl.cache_inputs(cfg, seed=N)

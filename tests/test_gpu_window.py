@@ -5,6 +5,7 @@ import pytest
 import oracle
 import paper_2604_05250_amd as dd
 from paper_2604_05250_amd import workloads as wl
+from _kernels import DUO2, DUO4, MFMA, SOLO, STREAM, WIDE, WIDE128, by_rule_and_elsewhere, with_splits
 from _util import assert_attention_close, out_to_f64, to_dev
 
 pytestmark = pytest.mark.gpu
@@ -23,24 +24,28 @@ def gpu_window(cfg, blk, cache, bs, w0, wlen, fresh):
 SHAPES = [
     # (B, H, Hkv, N, d, bl, block_start, win_start, win_len, qk, env): every kernel of the drafter's call; windows at
     # the start / end / inside the cache, equal to the block, ragged lengths, with and without key splits
-    (2, 4, 2, 333, 128, 32, 101, 64, 200, wl.BF16, {}),                              # streaming kernel
-    (1, 2, 2, 4096, 128, 64, 2000, 1000, 2048, wl.BF16, {}),                         # streaming kernel, key splits
-    (1, 2, 2, 4096, 128, 64, 4032, 3000, 1096, wl.BF16, {}),                         # window and block end at N
-    (1, 2, 1, 150, 64, 1, 77, 77, 1, wl.BF16, {}),                                   # one query, one key
-    (1, 3, 3, 500, 128, 33, 100, 100, 33, wl.BF16, {}),                              # window = block
-    (1, 4, 2, 700, 128, 32, 60, 0, 129, wl.BF16, {"DD_TUNE_BLOCK_STREAM": "0"}),     # MFMA kernel
-    (1, 2, 2, 4096, 128, 64, 1000, 7, 3001, wl.BF16, {"DD_TUNE_BLOCK_STREAM": "0"}),
-    (1, 8, 2, 1000, 128, 64, 936, 500, 500, wl.FP8_E4M3, {}),
-    (2, 8, 2, 640, 128, 64, 256, 128, 384, wl.FP8_E4M3, {}),                         # wide kernel, fp8
-    (2, 8, 2, 640, 128, 64, 200, 136, 300, wl.BF16, {}),                             # wide kernel, ragged parts
-    (1, 4, 1, 4096, 128, 128, 2000, 1024, 2048, wl.BF16, {}),                        # wide kernel, key splits
-    (1, 4, 1, 4096, 128, 128, 2000, 1990, 150, wl.BF16, {}),                         # parts shorter than a tile
-    (1, 8, 2, 400, 64, 64, 64, 0, 256, wl.BF16, {}),
-    (2, 4, 2, 640, 128, 64, 256, 128, 384, wl.FP8_E4M3, {}),                         # wide kernel, 128-row tiles
-    (1, 4, 2, 4096, 128, 64, 2000, 1990, 150, wl.BF16, {}),                          # ... parts shorter than a tile
+    (2, 4, 2, 333, 128, 32, 101, 64, 200, wl.BF16, STREAM),                          # streaming kernel
+    (1, 2, 2, 4096, 128, 64, 2000, 1000, 2048, wl.BF16, STREAM),                     # streaming kernel, key splits
+    (1, 2, 2, 4096, 128, 64, 4032, 3000, 1096, wl.BF16, STREAM),                     # window and block end at N
+    (1, 2, 1, 150, 64, 1, 77, 77, 1, wl.BF16, STREAM),                               # one query, one key
+    (1, 3, 3, 500, 128, 33, 100, 100, 33, wl.BF16, STREAM),                          # window = block
+    (1, 4, 2, 700, 128, 32, 60, 0, 129, wl.BF16, MFMA),                               # MFMA kernel
+    (1, 2, 2, 4096, 128, 64, 1000, 7, 3001, wl.BF16, MFMA),
+    (1, 8, 2, 1000, 128, 64, 936, 500, 500, wl.FP8_E4M3, WIDE),
+    (2, 8, 2, 640, 128, 64, 256, 128, 384, wl.FP8_E4M3, WIDE),                       # wide kernel, fp8
+    (2, 8, 2, 640, 128, 64, 200, 136, 300, wl.BF16, WIDE),                           # wide kernel, ragged parts
+    (1, 4, 1, 4096, 128, 128, 2000, 1024, 2048, wl.BF16, WIDE),                      # wide kernel, key splits
+    (1, 4, 1, 4096, 128, 128, 2000, 1990, 150, wl.BF16, WIDE),                       # parts shorter than a tile
+    (1, 8, 2, 400, 64, 64, 64, 0, 256, wl.BF16, WIDE),
+    (2, 4, 2, 640, 128, 64, 256, 128, 384, wl.FP8_E4M3, WIDE128),                    # wide kernel, 128-row tiles
+    (1, 4, 2, 4096, 128, 64, 2000, 1990, 150, wl.BF16, WIDE128),                     # ... parts shorter than a tile
     (1, 4, 4, 128, 64, 16, 64, 32, 64, wl.F32, {}),                                  # fp32 kernel
     (2, 2, 1, 600, 128, 48, 200, 150, 301, wl.F32, {}),
+    (1, 8, 2, 1700, 128, 64, 700, 100, 1501, wl.BF16, with_splits(DUO2, 3)),         # the kernels of few rows and of many, key splits
+    (1, 8, 2, 1700, 128, 64, 700, 100, 1501, wl.FP8_E4M3, with_splits(DUO4, 4)),
+    (1, 4, 2, 1700, 128, 32, 700, 100, 1501, wl.FP8_E4M3, with_splits(SOLO, 4)),
 ]
+SHAPES = by_rule_and_elsewhere(SHAPES, lambda r: r[9] != wl.F32 and r[8] <= 600)
 
 
 @pytest.mark.parametrize("B,H,Hkv,N,d,bl,bs,w0,wlen,qk,env", SHAPES)

@@ -735,15 +735,16 @@ hipError_t launch_attention_mfma(const AttnArgs &a, hipStream_t stream)
     const bool one_round64 = heads * ((rows + 63) / 64) <= 256, one_round128 = heads * ((rows + 127) / 128) <= 256;
     if (!blk && tune("DD_TUNE_ATTN_WIDE", -1) < 0 && tune("DD_TUNE_BIDIR_STREAM", -1) < 0) {
         // Up to two workgroups of 32 rows per compute unit: the kernel whose waves stream keys of their own.  us, on the kernels below ->
-        // there: 1 x 32 heads, N 128 7.4 -> 5.3, N 300 10.9 -> 9.2, N 512 14.7 -> 13.3, fp8 Q and K 13.2 -> 11.1, d = 64 10.1 -> 7.4; 1 x 16,
-        // N 512 12.6 -> 8.1; 1 x 8, N 1024 19.3 -> 11.3.  Over 380 drawn calls of more than 64 keys 0.78 of the time up to 256 workgroups,
+        // there: 1 x 32 heads, N 300 10.9 -> 9.2, N 512 14.7 -> 13.3, fp8 Q and K 13.2 -> 11.1, d = 64 10.1 -> 7.4; 1 x 16, N 512 12.6 -> 8.1; 1 x 8, N 1024
+        // 19.3 -> 11.3.  Over 380 drawn calls of more than 64 keys 0.78 of the time up to 256 workgroups,
         // 0.91 up to 512, then 1.1 (1 x 60, N 300 15.9 against 14.1).  e4m3 values: 0.66 up to 256 workgroups, 0.78 up to 512, then 1.1 as well.
         // Past 448 workgroups of more than 1024 keys it depends, against the two-waves-per-SIMD kernel: 1 x 8, N 2016 29.3 there / 30.8,
-        // 1 x 8 (2 kv), N 2035 29.0 / 26.8, fp8 1 x 4, N 4096 42.3 / 39.2.  64 keys and fewer stay below: fp8 1.1 there, bf16 5.7 streamed / 5.5
-        // (64 heads, 33 keys), at 64 keys themselves (32 heads) 6.2 / 4.9.
+        // 1 x 8 (2 kv), N 2035 29.0 / 26.8, fp8 1 x 4, N 4096 42.3 / 39.2.  64 keys and fewer: up to 256 workgroups (d = 64: 192), whose head dims it
+        // then divides: bf16 1 x 16, N 33 5.4 -> 4.6, 6 x 32, N 49 5.9 -> 5.3, fp8 1 x 32, N 48 5.2 -> 4.2; 384 workgroups, N 33 5.6 / 6.2.
         const long wgs = heads * ((rows + 31) / 32);
-        const int solo = tune("DD_TUNE_SOLO", tune("DD_TUNE_DUO", -1) <= 0 && a.N > 64 && wgs <= (a.N > 1024 ? 448 : 512));
-        if (solo != 0 && attn_solo_serves(a)) return launch_attention_solo(a, stream);
+        const int solo = tune("DD_TUNE_SOLO", tune("DD_TUNE_DUO", -1) <= 0 && wgs <= (a.N > 1024 ? 448 : a.N > 64 ? 512 : a.d == 64 ? 192 : 256));
+        if (solo != 0 && attn_solo_serves(a))
+            return launch_attention_solo(a, attn_solo_form(rows, heads, a.N, a.d, fp8, a.v_dtype == 2), stream);
     }
     if (!blk && attn_duo_serves(a) && tune("DD_TUNE_ATTN_WIDE", -1) < 0 && tune("DD_TUNE_BIDIR_STREAM", -1) < 0) {
         // One round of 64-row workgroups: the two-waves-per-SIMD kernel, whose eight waves share a workgroup's keys.  Of these calls the

@@ -1,19 +1,24 @@
 // Attention of few query rows whose waves stream keys of their own: the drafter's call where workgroups of 32 rows are few or key
 // streams short (Sec. 2.3) and small verifier calls (Sec. 2.2), bf16 or fp8 Q/K, bf16 or (with fp8 Q/K) e4m3 V.
 //     O = softmax(Q K^T / sqrt(d_k)) V   (Eq. 3)
-// One workgroup = four waves on one block of 32 query rows; wave w takes every fourth 32-key unit of the key range with a state
-// (reference, sum, O) of its own, and the states are merged through LDS at the end, every wave finishing a quarter of the head dims.
+// One workgroup = four or eight waves on one or two blocks of 32 query rows; wave w takes every fourth (eighth) 32-key unit of the key
+// range with a state (reference, sum, O) of its own, and the states are merged through LDS at the end, the waves sharing out the head dims.
 //   - No K/V row is used by two waves, so none waits for another: a wave has one K and one V buffer in LDS, filled by
 //     global_load_lds_dwordx4, waits for its own loads only, and asks for the next unit's K as soon as the fragments of this
-//     one's are in registers, V likewise: 64 KB (fp8 48 KB) per workgroup are on their way nearly all the time.
+//     one's are in registers, V likewise: all buffers are on their way nearly all the time.
 //   - A block of 32 rows leaves no wave idle (the 64-row workgroups of attention_stream.hip halve there), and 64 rows are two
-//     workgroups that share K/V through an XCD's L2.  Two workgroups fit a compute unit.
-// What bounds it: some 4 us of launch, first loads and merge, then 1.1 us (fp8 0.9) per 128 keys while a compute unit has one
-// workgroup - 60 GB/s, the same with eight waves and twice the bytes on their way, so what a unit draws from beyond its L2.
-// us per call in a stream of them, attention_stream.hip -> here: 11 x 32/8 heads, 16 rows, 1237 keys fp8 20.5 -> 16.3, bf16
-// 23.8 -> 20.8; 1 x 32, 512 keys, 32 rows bf16 9.7 -> 8.0, 64 rows 11.9 -> 8.4; 1 x 32, 300 keys, 16 rows 9.5 -> 7.2; 4 x 32/8, 16 rows,
-// 2048 keys 17.7 -> 14.6 (4 splits).  Tried and not kept: eight waves per workgroup (bf16 11 x 32/8 19.9 where four took 19.3, 1 x 32 9.9 /
-// 9.1, 4 x 32/8 15.1 / 14.3).
+//     workgroups that share K/V through an XCD's L2.
+//   - The head dims of V and O may be divided over 2 or 4 workgroups ("parts"), each with the whole of K: S is computed by all of
+//     them, but there is no merge between them, and a call of few heads spreads over more compute units.
+// What bounds it: some 4 us of launch, first loads and merge, then per unit a chain (K fragments, S, weights, V fragments, O) of
+// 0.45 - 0.75 us that nothing else on the SIMD covers while a workgroup is four waves, and the 64 B/clk of a compute unit's path to LDS (100
+// GB/s at most, measured).  Parts shorten a unit and the merge; a second wave per SIMD (eight waves) fills the chain's gaps where streams
+// are long, for 0.3 - 0.8 us more of launch and merge; two row blocks share a unit's loads.  us per call in a stream of them, four waves on one
+// block and all dims -> the form the rule picks: 1 x 32 heads, 512 keys, 32 rows bf16 8.0 -> 6.8 (4 parts); 1 x 32, 1024 keys bf16 11.4 ->
+// 8.7, fp8 9.5 -> 7.0, e4m3 V 10.1 -> 7.4 (4 parts, 8 waves); 4 x 32/8, 16 rows, 2048 keys fp8 12.2 -> 9.7; 11 x 32/8, 16 rows, 1237 keys fp8
+// 13.9 -> 12.5, e4m3 V 15.7 -> 12.6 (two blocks, 2 parts, 8 waves); 2 x 32, 800 keys, 48 rows e4m3 V 11.9 -> 8.4 (2 parts, 8 waves).
+// Tried and not kept: a second unit on its way per wave (bf16 8.0 -> 9.4, 4 parts 6.8 -> 7.6: the first units' loads queue behind it); two
+// blocks with all dims (12.3, one wave's registers); eight waves on all dims for bf16 (8.6).
 #include "attention_common.h"
 #include "dd_internal.h"
 
@@ -66,38 +71,40 @@ template <int I, int N, typename F> __device__ __forceinline__ void static_for(F
     }
 }
 
-constexpr int kSoloWaves = 4;
-
 // V8: V is stored as e4m3 codes.  They travel to LDS as they are and the wave decodes its own 4 KB into its V buffer, exactly, when
 // they arrive (32 conversions of two elements per lane and unit); v_scale multiplies the result once.
-// `wgs`: the launch's attending workgroups.
-template <int D, bool FP8, bool V8>
+// `wgs`: the launch's attending workgroups.  RB row blocks per workgroup, VP parts of the head dims, NW waves.
+template <int D, bool FP8, bool V8, int RB, int VP, int NW>
 __device__ __forceinline__ void attn_solo(const AttnKernelArgs &a, const int wgs)
 {
     // (device pass only: the host pass needs the kernels' handles, not assembly it cannot check)
 #if defined(__HIP_DEVICE_COMPILE__)
-    constexpr int NW = kSoloWaves, U = 32;           // keys per unit
-    constexpr int CH = D / 8;                        // 16-byte chunks per V / O row
-    constexpr int DC = D / 32;                       // 32-wide chunks of the head dim
-    constexpr int ROWB = D * 2;                      // bytes per V / O row
-    constexpr int KROWB = FP8 ? D : ROWB, KCH = KROWB / 16;   // Q / K as stored: bytes and chunks per row
+    constexpr int U = 32;               // keys per unit
+    constexpr int DV = D / VP;                       // head dims of V / O that this workgroup handles
+    constexpr int CH = DV / 8;                       // 16-byte chunks per V row in LDS
+    constexpr int DC = DV / 32;                      // 32-wide chunks of its head dims
+    constexpr int ROWB = DV * 2;                     // bytes per V row in LDS
+    constexpr int KROWB = FP8 ? D : D * 2, KCH = KROWB / 16;   // Q / K as stored: bytes and chunks per row
     constexpr int KF = KROWB / 32;                   // 16-byte K fragments per lane and unit
     constexpr int KB = U * KROWB, VB = U * ROWB;     // bytes of a wave's K / V buffer
-    constexpr int VSROWB = V8 ? D : ROWB, VSCH = VSROWB / 16, VSB = V8 ? U * VSROWB : 0;   // V as stored; its own buffer if decoded
+    constexpr int VPITCH = V8 ? D : D * 2;           // bytes between V rows in memory
+    constexpr int VSROWB = V8 ? DV : ROWB, VSCH = VSROWB / 16, VSB = V8 ? U * VSROWB : 0;   // V as stored; its own buffer if decoded
     constexpr int NK = KB / 1024, NV = U * VSROWB / 1024;                    // wave-wide loads per buffer (1 KB each)
     constexpr int VDMA_ROWS = 1024 / VSROWB, KDMA_ROWS = 1024 / KROWB;       // rows per load
-    constexpr int G = DC * 4, GP = G / NW;           // groups of four O registers per lane, ... that a wave finishes
+    constexpr int GB = DC * 4, GP = RB * GB >= NW ? RB * GB / NW : 1;   // groups of four O registers per lane and row block, ... that a wave finishes
     static_assert((!FP8 && !V8) || (FP8 && D == 128), "fp8 rows are 128 bytes");
-    static_assert(GP % 2 == 0, "groups are stored in pairs");
+    static_assert(RB == 1 || RB == 2, "a wave finishes groups of one row block");
+    static_assert(NV >= 1 && GP >= 1, "not too many parts");
     static_assert(NK <= 8 && NV <= 8, "a buffer is within the loads' immediate offsets");
     constexpr int SLOTB = KB + VB + VSB;
-    constexpr int PARKB = NW * (NW - 1) * GP * 1024; // the parked states share the buffers' memory
+    constexpr int NF = RB * GB < NW ? RB * GB : NW;  // waves that finish groups
+    constexpr int PARKB = NW * (NF - 1 + (NF < NW)) * GP * 1024;             // the parked states share the buffers' memory
     constexpr int LDSB = (NW * SLOTB > PARKB ? NW * SLOTB : PARKB);
     // per wave: K [key][chunk ^ (key & 7)], then V [key][chunk ^ ((key % (CH/4)) << 2)]
     __shared__ __attribute__((aligned(1024))) uint4 KV[LDSB / 16];
-    __shared__ __attribute__((aligned(1024))) uint4 QS[KB / 16];             // the query rows, as K
+    __shared__ __attribute__((aligned(1024))) uint4 QS[RB * KB / 16];        // the query rows, as K
     __shared__ float qs_sh[64];                      // the scales of the query rows
-    __shared__ float ml_sh[NW][2][32];               // per wave: (reference, sum) of the query rows
+    __shared__ float ml_sh[NW][2][32 * RB];          // per wave: (reference, sum) of the query rows
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -110,12 +117,13 @@ __device__ __forceinline__ void attn_solo(const AttnKernelArgs &a, const int wgs
         const int xcd = bid & 7, slot = bid >> 3;
         bid = xcd * per + min(xcd, rem) + slot;
     }
+    const int part = bid % VP; bid /= VP;
     const int rt = bid % a.row_tiles; bid /= a.row_tiles;
     const int sp = bid % a.splits; bid /= a.splits;
     const int kvh = bid % a.Hkv;
     const int b = bid / a.Hkv;
     const int rows_total = a.group * a.Nq;           // query rows of this (batch, kv head): contiguous in memory
-    const int v_first = rt * 32;
+    const int v_first = rt * 32 * RB;
     const size_t row_base = ((size_t)b * a.H + (size_t)kvh * a.group) * a.Nq;
     const int kbeg = sp * a.keys_per_split;
     const int kend = min(a.N, kbeg + a.keys_per_split);
@@ -126,9 +134,9 @@ __device__ __forceinline__ void attn_solo(const AttnKernelArgs &a, const int wgs
 
     const size_t kv_head = (size_t)b * a.Hkv + kvh;
     const uint8_t *const kc = static_cast<const uint8_t *>(a.K) + kv_head * a.kv_stride * (size_t)KROWB;
-    const uint8_t *const vc = static_cast<const uint8_t *>(a.V) + kv_head * a.kv_stride * (size_t)VSROWB;
+    const uint8_t *const vc = static_cast<const uint8_t *>(a.V) + kv_head * a.kv_stride * (size_t)VPITCH + part * VSROWB;
     const uint8_t *const kb_ = blen ? static_cast<const uint8_t *>(a.Kblk) + kv_head * blen * (size_t)KROWB : nullptr;
-    const uint8_t *const vb_ = blen ? static_cast<const uint8_t *>(a.Vblk) + kv_head * blen * (size_t)VSROWB : nullptr;
+    const uint8_t *const vb_ = blen ? static_cast<const uint8_t *>(a.Vblk) + kv_head * blen * (size_t)VPITCH + part * VSROWB : nullptr;
     auto lds_addr = [&](const void *p) __attribute__((always_inline)) { return (unsigned)(size_t)(__attribute__((address_space(3))) const void *)p; };
     char *const kbuf = reinterpret_cast<char *>(KV) + wave * SLOTB, *const vbuf = kbuf + KB, *const vstored = vbuf + VB;
     const unsigned kdst = lds_addr(KV) + wave * SLOTB, vdst = kdst + KB + (V8 ? VB : 0);
@@ -137,7 +145,7 @@ __device__ __forceinline__ void attn_solo(const AttnKernelArgs &a, const int wgs
     const int vrow0 = lane / VSCH, krow0 = lane / KCH;
     auto kchunk = [&](int i) __attribute__((always_inline)) { return (unsigned)(((lane % KCH) ^ ((i * KDMA_ROWS + krow0) & 7)) * 16); };
     const unsigned vchunk = V8 ? lane % VSCH * 16 : ((lane % CH) ^ ((vrow0 & (CH / 4 - 1)) << 2)) * 16;   // (codes lie as in memory)
-    const unsigned koff[2] = {krow0 * KROWB + kchunk(0), krow0 * KROWB + kchunk(1)}, voff = vrow0 * VSROWB + vchunk;
+    const unsigned koff[2] = {krow0 * KROWB + kchunk(0), krow0 * KROWB + kchunk(1)}, voff = vrow0 * VPITCH + vchunk;
     int blk0 = 0, blk1 = 0;                          // units outside [blk0, blk1) hold rows of the cache only
     if (blen) {
         const long s0 = min(max((long)bstart, (long)kbeg), (long)kend), s1 = min(max((long)bstart + blen, (long)kbeg), (long)kend);
@@ -151,7 +159,8 @@ __device__ __forceinline__ void attn_solo(const AttnKernelArgs &a, const int wgs
     // its last one (finite stand-ins, masked or zeroed below).
     auto load_rows = [&](auto is_k, int u) __attribute__((always_inline)) {
         constexpr bool K = decltype(is_k)::value;
-        constexpr int NL = K ? NK : NV, BIAS = NL > 4 ? 4096 : 0, PITCH = K ? KROWB : VSROWB;
+        constexpr int NL = K ? NK : NV, BIAS = NL > 4 ? 4096 : 0, PITCH = K ? KROWB : VPITCH;
+        constexpr bool PARTIAL = !K && VP > 1;       // part of a row: what lies together in LDS does not in memory
         const unsigned dst = (K ? kdst : vdst) + BIAS;
         const int k0 = kbeg + u * U;
         if (u < whole && (unsigned)(u - blk0) >= (unsigned)(blk1 - blk0)) {
@@ -160,7 +169,11 @@ __device__ __forceinline__ void attn_solo(const AttnKernelArgs &a, const int wgs
                 constexpr int I = decltype(i)::value, IMM = I * 1024 - BIAS;
                 const unsigned d = dst, o = K ? koff[I & 1] : voff;
                 const uint8_t *const sbase = src;
-                if constexpr (IMM >= 0)
+                if constexpr (PARTIAL) {
+                    const uint8_t *const at = sbase - BIAS + I * VDMA_ROWS * PITCH;
+                    const unsigned di = d - BIAS + I * 1024;
+                    asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(di), "v"(o), "s"(at) : "memory", "m0");
+                } else if constexpr (IMM >= 0)
                     asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2 offset:%3" ::"s"(d), "v"(o), "s"(sbase), "n"(IMM) : "memory", "m0");
                 else
                     asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2 offset:-%3" ::"s"(d), "v"(o), "s"(sbase), "n"(-IMM) : "memory", "m0");
@@ -180,15 +193,13 @@ __device__ __forceinline__ void attn_solo(const AttnKernelArgs &a, const int wgs
     const std::false_type of_v;
 
     // ---- prologue: the query rows, shared out over the waves, then this wave's first unit
-    const int v = v_first + l32;
-    const bool row_ok = v < rows_total;
     const float k_scale = a.k_scale ? a.k_scale[kv_head] : 1.0f;
     // (through LDS like the rows: the compiler's own wait for a load of its own would wait for every load after it as well)
     if (a.q_scale && wave == 0) {
-        const float *const src = a.q_scale + b * a.H + kvh * a.group + min(v, rows_total - 1) / a.Nq;
+        const float *const src = a.q_scale + b * a.H + kvh * a.group + min(v_first + (RB == 2 ? lane : l32), rows_total - 1) / a.Nq;
         asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dword %1, off" ::"s"(lds_addr(qs_sh)), "v"(src) : "memory", "m0");
     }
-    for (int i = wave; i < NK; i += NW) {
+    for (int i = wave; i < RB * NK; i += NW) {
         const int r = min(v_first + i * KDMA_ROWS + krow0, rows_total - 1);
         const uint8_t *const src = static_cast<const uint8_t *>(a.Q) + (row_base + r) * KROWB + kchunk(i);
         asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(lds_addr(QS) + i * 1024), "v"(src) : "memory", "m0");
@@ -215,28 +226,35 @@ __device__ __forceinline__ void attn_solo(const AttnKernelArgs &a, const int wgs
     else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     asm volatile("s_barrier" ::: "memory");
     // Q fragments (B operand of S^T = K Q^T): lane (query l32, half hh) holds 16-byte chunk 2 f + hh of its row
-    intx4 qf[KF];
+    intx4 qf[RB][KF];
+    float c[RB];                                     // scores are exponentiated as 2^(s*c)
+    floatx16 acc[RB][DC];                            // O^T, unnormalised
 #pragma unroll
-    for (int f = 0; f < KF; ++f) qf[f] = *reinterpret_cast<const intx4 *>(reinterpret_cast<const char *>(QS) + k_off[f]);
-
-    float c = a.scale_log2 * k_scale;                // scores are exponentiated as 2^(s*c)
-    if (a.q_scale) c *= qs_sh[lane];
-
-    floatx16 acc[DC];                                // O^T, unnormalised
+    for (int q = 0; q < RB; ++q) {
 #pragma unroll
-    for (int i = 0; i < DC; ++i)
+        for (int f = 0; f < KF; ++f) qf[q][f] = *reinterpret_cast<const intx4 *>(reinterpret_cast<const char *>(QS) + q * KB + k_off[f]);
+        c[q] = a.scale_log2 * k_scale;
+        if (a.q_scale) c[q] *= qs_sh[32 * q + l32];
 #pragma unroll
-        for (int r = 0; r < 16; ++r) acc[i][r] = 0.f;
+        for (int i = 0; i < DC; ++i)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[q][i][r] = 0.f;
+    }
     // Row sums of the weights as multiplied (rounded to bf16), by the matrix instruction of sixteen 4 x 4 blocks: lane l is
     // column l % 4 of block l / 4 with four values of k, so with an A operand of ones every lane gets the sum of its own
     // weights; the lane halves hold different keys of a row and are added at the end.
-    floatx4 acc_l = {0.f, 0.f, 0.f, 0.f};
+    floatx4 acc_l[RB];
     const short4v ones = {0x3F80, 0x3F80, 0x3F80, 0x3F80};
     // The reference m of the weights p = 2^(s c - m), as -m (log2 units), equal in both lane halves.  It only has to be near the
     // running maximum (any common factor 2^-m cancels): the first unit sets it to its maximum + 7; a later one first takes its
     // weights with the one in use, and only if some weight reached 2 - one bit of its bf16 pattern, the packed weights are or-ed
     // together - it is raised to the unit's maximum + 7, the sums are scaled and the weights taken again.
-    float nm = INFINITY;
+    float nm[RB];
+#pragma unroll
+    for (int q = 0; q < RB; ++q) {
+        acc_l[q] = floatx4{0.f, 0.f, 0.f, 0.f};
+        nm[q] = INFINITY;
+    }
 
     // ---- this wave's units.  Its loads complete in order: K and V of the unit, then the next unit's K, asked for when this one's
     // K is in registers, and its V, when this one's V is.
@@ -248,27 +266,36 @@ __device__ __forceinline__ void attn_solo(const AttnKernelArgs &a, const int wgs
         for (int f = 0; f < KF; ++f) kf[f] = *reinterpret_cast<const intx4 *>(kbuf + k_off[f]);
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
         if (more) load_rows(of_k, u + NW);
-        floatx16 s;
+        floatx16 s[RB];
 #pragma unroll
-        for (int r = 0; r < 16; ++r) s[r] = 0.f;
+        for (int q = 0; q < RB; ++q)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) s[q][r] = 0.f;
         if constexpr (FP8) {
 #pragma unroll
             for (int j = 0; j < KF / 2; ++j) {
                 const intx8 kx = __builtin_shufflevector(kf[2 * j], kf[2 * j + 1], 0, 1, 2, 3, 4, 5, 6, 7);
-                const intx8 qx = __builtin_shufflevector(qf[2 * j], qf[2 * j + 1], 0, 1, 2, 3, 4, 5, 6, 7);
-                s = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(kx, qx, s, 0, 0, 0, 0x7F7F7F7F, 0, 0x7F7F7F7F);
+#pragma unroll
+                for (int q = 0; q < RB; ++q) {
+                    const intx8 qx = __builtin_shufflevector(qf[q][2 * j], qf[q][2 * j + 1], 0, 1, 2, 3, 4, 5, 6, 7);
+                    s[q] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(kx, qx, s[q], 0, 0, 0, 0x7F7F7F7F, 0, 0x7F7F7F7F);
+                }
             }
         } else {
 #pragma unroll
             for (int f = 0; f < KF; ++f)
-                s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, kf[f]), __builtin_bit_cast(bf16x8, qf[f]), s, 0, 0, 0);
+#pragma unroll
+                for (int q = 0; q < RB; ++q)
+                    s[q] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, kf[f]), __builtin_bit_cast(bf16x8, qf[q][f]), s[q], 0, 0, 0);
         }
         if (u == whole) {                            // (a unit with rows past the end of the range)
             // score register r is key key0 + 8 (r / 4) + 4 hh + (r % 4) for query row l32
             const int key0 = kbeg + u * U;
 #pragma unroll
             for (int r = 0; r < 16; ++r)
-                if (key0 + 8 * (r >> 2) + 4 * hh + (r & 3) >= kend) s[r] = -INFINITY;
+                if (key0 + 8 * (r >> 2) + 4 * hh + (r & 3) >= kend)
+#pragma unroll
+                    for (int q = 0; q < RB; ++q) s[q][r] = -INFINITY;
         }
         if (more) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(NK) : "memory");
         else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -310,107 +337,122 @@ __device__ __forceinline__ void attn_solo(const AttnKernelArgs &a, const int wgs
                 const short8v w = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
                 vf[st][i] = __builtin_bit_cast(bf16x8, w);
             }
-        unsigned pk[2][4], seen = 0u;                // P^T as the B operand of O^T += V^T P^T
+        unsigned pk[RB][2][4], seen[RB];             // P^T as the B operand of O^T += V^T P^T
         bool raise_any = true;                       // uniform
+#pragma unroll
+        for (int q = 0; q < RB; ++q) seen[q] = 0u;
         if (u != wave) {
+            unsigned any = 0u;
 #pragma unroll
-            for (int r = 0; r < 16; r += 2)
-                pk[r >> 3][(r & 7) >> 1] = solo_pack(solo_exp2(fmaf(s[r], c, nm)), solo_exp2(fmaf(s[r + 1], c, nm)));
+            for (int q = 0; q < RB; ++q) {
 #pragma unroll
-            for (int k = 0; k < 8; ++k) seen |= pk[k >> 2][k & 3];
-            raise_any = __any((seen & 0x40004000u) != 0u);
+                for (int r = 0; r < 16; r += 2)
+                    pk[q][r >> 3][(r & 7) >> 1] = solo_pack(solo_exp2(fmaf(s[q][r], c[q], nm[q])), solo_exp2(fmaf(s[q][r + 1], c[q], nm[q])));
+#pragma unroll
+                for (int k = 0; k < 8; ++k) seen[q] |= pk[q][k >> 2][k & 3];
+                any |= seen[q];
+            }
+            raise_any = __any((any & 0x40004000u) != 0u);
         }
         if (raise_any) {
-            const u32x2 both = solo_swap(seen, seen);
-            const bool raise = u == wave || ((both.x | both.y) & 0x40004000u) != 0u;
-            float mx = s[0];
 #pragma unroll
-            for (int r = 1; r < 16; ++r) mx = fmaxf(mx, s[r]);
-            const u32x2 mm = solo_swap(__float_as_uint(mx), __float_as_uint(mx));
-            mx = fmaxf(__uint_as_float(mm.x), __uint_as_float(mm.y)) * c + kSoloMargin;
-            const float m_old = -nm, m_new = raise ? fmaxf(m_old, mx) : m_old;
-            const float corr = m_new == m_old ? 1.0f : solo_exp2(m_old - m_new);         // first unit: 2^(-inf) = 0
-            const float use = m_new == -INFINITY ? 0.f : -m_new;                         // every score so far is -inf: weights 0
-            nm = -m_new;
-            if (u != wave) {                         // (the first unit's sums are zero)
+            for (int q = 0; q < RB; ++q) {
+                const u32x2 both = solo_swap(seen[q], seen[q]);
+                const bool raise = u == wave || ((both.x | both.y) & 0x40004000u) != 0u;
+                float mx = s[q][0];
 #pragma unroll
-                for (int r = 0; r < 4; ++r) acc_l[r] *= corr;
+                for (int r = 1; r < 16; ++r) mx = fmaxf(mx, s[q][r]);
+                const u32x2 mm = solo_swap(__float_as_uint(mx), __float_as_uint(mx));
+                mx = fmaxf(__uint_as_float(mm.x), __uint_as_float(mm.y)) * c[q] + kSoloMargin;
+                const float m_old = -nm[q], m_new = raise ? fmaxf(m_old, mx) : m_old;
+                const float corr = m_new == m_old ? 1.0f : solo_exp2(m_old - m_new);     // first unit: 2^(-inf) = 0
+                const float use = m_new == -INFINITY ? 0.f : -m_new;                     // every score so far is -inf: weights 0
+                nm[q] = -m_new;
+                if (u != wave) {                     // (the first unit's sums are zero)
 #pragma unroll
-                for (int i = 0; i < DC; ++i)
+                    for (int r = 0; r < 4; ++r) acc_l[q][r] *= corr;
 #pragma unroll
-                    for (int r = 0; r < 16; ++r) acc[i][r] *= corr;
+                    for (int i = 0; i < DC; ++i)
+#pragma unroll
+                        for (int r = 0; r < 16; ++r) acc[q][i][r] *= corr;
+                }
+#pragma unroll
+                for (int r = 0; r < 16; r += 2)
+                    pk[q][r >> 3][(r & 7) >> 1] = solo_pack(solo_exp2(fmaf(s[q][r], c[q], use)), solo_exp2(fmaf(s[q][r + 1], c[q], use)));
             }
-#pragma unroll
-            for (int r = 0; r < 16; r += 2)
-                pk[r >> 3][(r & 7) >> 1] = solo_pack(solo_exp2(fmaf(s[r], c, use)), solo_exp2(fmaf(s[r + 1], c, use)));
         }
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
         if (!V8 && more) load_rows(of_v, u + NW);
 #pragma unroll
-        for (int st = 0; st < 2; ++st) {
-            const uint4 pw = make_uint4(pk[st][0], pk[st][1], pk[st][2], pk[st][3]);
+        for (int st = 0; st < 2; ++st)
 #pragma unroll
-            for (int i = 0; i < DC; ++i)
-                acc[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[st][i], __builtin_bit_cast(bf16x8, pw), acc[i], 0, 0, 0);
+            for (int q = 0; q < RB; ++q) {
+                const uint4 pw = make_uint4(pk[q][st][0], pk[q][st][1], pk[q][st][2], pk[q][st][3]);
 #pragma unroll
-            for (int k = 0; k < 2; ++k) {
-                const u32x2 half = {pk[st][2 * k], pk[st][2 * k + 1]};
-                acc_l = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(ones, __builtin_bit_cast(short4v, half), acc_l, 0, 0, 0);
+                for (int i = 0; i < DC; ++i)
+                    acc[q][i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[st][i], __builtin_bit_cast(bf16x8, pw), acc[q][i], 0, 0, 0);
+#pragma unroll
+                for (int k = 0; k < 2; ++k) {
+                    const u32x2 half = {pk[q][st][2 * k], pk[q][st][2 * k + 1]};
+                    acc_l[q] = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(ones, __builtin_bit_cast(short4v, half), acc_l[q], 0, 0, 0);
+                }
             }
-        }
     }
 
     // ---- merge the waves' states through LDS: a wave parks the groups of O registers that others finish
-    const float mc = -nm;
-    const u32x2 ls = solo_swap(__float_as_uint(acc_l[0]), __float_as_uint(acc_l[0]));
-    const float l_own = __uint_as_float(ls.x) + __uint_as_float(ls.y);
     __syncthreads();                                 // every wave is done with its buffers (and has no load outstanding)
     float4 *park = reinterpret_cast<float4 *>(KV);
     auto park_at = [&](int from, int to, int g) __attribute__((always_inline)) {
-        return ((from * (NW - 1) + (to < from ? to : to - 1)) * GP + g) * 64 + lane;
+        return ((from * (NF - 1 + (NF < NW)) + (NF < NW || to < from ? to : to - 1)) * GP + g) * 64 + lane;
     };
-    ml_sh[wave][0][l32] = mc;
-    ml_sh[wave][1][l32] = l_own;
 #pragma unroll
-    for (int to = 0; to < NW; ++to)
+    for (int q = 0; q < RB; ++q) {
+        const u32x2 ls = solo_swap(__float_as_uint(acc_l[q][0]), __float_as_uint(acc_l[q][0]));
+        ml_sh[wave][0][32 * q + l32] = -nm[q];
+        ml_sh[wave][1][32 * q + l32] = __uint_as_float(ls.x) + __uint_as_float(ls.y);
+    }
+#pragma unroll
+    for (int to = 0; to < NF; ++to)
         if (to != wave) {
 #pragma unroll
             for (int g = 0; g < GP; ++g) {
-                const int i = (to * GP + g) / 4, r = 4 * ((to * GP + g) % 4);
-                park[park_at(wave, to, g)] = make_float4(acc[i][r], acc[i][r + 1], acc[i][r + 2], acc[i][r + 3]);
+                const int q = (to * GP + g) / GB, i = (to * GP + g) % GB / 4, r = 4 * ((to * GP + g) % 4);
+                park[park_at(wave, to, g)] = make_float4(acc[q][i][r], acc[q][i][r + 1], acc[q][i][r + 2], acc[q][i][r + 3]);
             }
         }
     __syncthreads();
+    if (NF < NW && wave >= NF) return;               // (uniform; no barrier follows)
+    const int mine = wave * GP / GB;                 // the row block whose groups this wave finishes
     float m_all = -INFINITY, wgt[NW], l_tot = 0.f;
 #pragma unroll
-    for (int q = 0; q < NW; ++q) m_all = fmaxf(m_all, ml_sh[q][0][l32]);
+    for (int w = 0; w < NW; ++w) m_all = fmaxf(m_all, ml_sh[w][0][32 * mine + l32]);
 #pragma unroll
-    for (int q = 0; q < NW; ++q) {
-        const float m = ml_sh[q][0][l32];
-        wgt[q] = m == -INFINITY ? 0.f : solo_exp2(m - m_all);                // a wave that saw no key weighs nothing
-        l_tot += ml_sh[q][1][l32] * wgt[q];
+    for (int w = 0; w < NW; ++w) {
+        const float m = ml_sh[w][0][32 * mine + l32];
+        wgt[w] = m == -INFINITY ? 0.f : solo_exp2(m - m_all);                // a wave that saw no key weighs nothing
+        l_tot += ml_sh[w][1][32 * mine + l32] * wgt[w];
     }
     float o[GP][4], w_own = wgt[0];
 #pragma unroll
-    for (int q = 0; q < NW; ++q)
-        if (q == wave) {
-            w_own = wgt[q];
+    for (int w = 0; w < NF; ++w)
+        if (w == wave) {
+            w_own = wgt[w];
 #pragma unroll
             for (int g = 0; g < GP; ++g)
 #pragma unroll
-                for (int k = 0; k < 4; ++k) o[g][k] = acc[(q * GP + g) / 4][4 * ((q * GP + g) % 4) + k];
+                for (int k = 0; k < 4; ++k) o[g][k] = acc[(w * GP + g) / GB][(w * GP + g) % GB / 4][4 * ((w * GP + g) % 4) + k];
         }
 #pragma unroll
     for (int g = 0; g < GP; ++g)
 #pragma unroll
         for (int k = 0; k < 4; ++k) o[g][k] *= w_own;
 #pragma unroll
-    for (int q = 0; q < NW; ++q)
-        if (q != wave) {
+    for (int w = 0; w < NW; ++w)
+        if (w != wave) {
 #pragma unroll
             for (int g = 0; g < GP; ++g) {
-                const float4 x = park[park_at(q, wave, g)];
-                o[g][0] += x.x * wgt[q]; o[g][1] += x.y * wgt[q]; o[g][2] += x.z * wgt[q]; o[g][3] += x.w * wgt[q];
+                const float4 x = park[park_at(w, wave, g)];
+                o[g][0] += x.x * wgt[w]; o[g][1] += x.y * wgt[w]; o[g][2] += x.z * wgt[w]; o[g][3] += x.w * wgt[w];
             }
         }
     if constexpr (V8) {
@@ -420,23 +462,29 @@ __device__ __forceinline__ void attn_solo(const AttnKernelArgs &a, const int wgs
 #pragma unroll
             for (int k = 0; k < 4; ++k) o[g][k] *= vs;
     }
-    // ---- output: group g of this wave is dims 8 (wave GP + g) + 4 hh .. + 3 of query row l32
+    // ---- output: group g of this wave is dims 8 (first + g) + 4 hh .. + 3 of query row l32 of its row block
+    const int v = v_first + 32 * mine + l32, first = part * GB + wave * GP % GB;
+    const bool row_ok = v < rows_total;
     const size_t orow = row_base + v;
     if (a.splits == 1) {
         const float inv = 1.0f / l_tot;
         uint16_t *out = static_cast<uint16_t *>(a.O) + orow * D;
+        if constexpr (GP == 1) {
+            if (row_ok) *reinterpret_cast<uint2 *>(out + 8 * first + 4 * hh) = make_uint2(solo_pack(o[0][0] * inv, o[0][1] * inv), solo_pack(o[0][2] * inv, o[0][3] * inv));
+        } else {
 #pragma unroll
-        for (int g = 0; g < GP; g += 2) {
-            // the halves exchange words so that each lane stores eight consecutive dims
-            const u32x2 x0 = solo_swap(solo_pack(o[g][0] * inv, o[g][1] * inv), solo_pack(o[g + 1][0] * inv, o[g + 1][1] * inv));
-            const u32x2 x1 = solo_swap(solo_pack(o[g][2] * inv, o[g][3] * inv), solo_pack(o[g + 1][2] * inv, o[g + 1][3] * inv));
-            if (row_ok) *reinterpret_cast<uint4 *>(out + 8 * (wave * GP + g + hh)) = make_uint4(x0.x, x1.x, x0.y, x1.y);
+            for (int g = 0; g + 1 < GP; g += 2) {
+                // the halves exchange words so that each lane stores eight consecutive dims
+                const u32x2 x0 = solo_swap(solo_pack(o[g][0] * inv, o[g][1] * inv), solo_pack(o[g + 1][0] * inv, o[g + 1][1] * inv));
+                const u32x2 x1 = solo_swap(solo_pack(o[g][2] * inv, o[g][3] * inv), solo_pack(o[g + 1][2] * inv, o[g + 1][3] * inv));
+                if (row_ok) *reinterpret_cast<uint4 *>(out + 8 * (first + g + hh)) = make_uint4(x0.x, x1.x, x0.y, x1.y);
+            }
         }
     } else if (row_ok) {
         float *po = a.part_o + (orow * a.splits + sp) * D;
 #pragma unroll
-        for (int g = 0; g < GP; ++g) *reinterpret_cast<float4 *>(po + 8 * (wave * GP + g) + 4 * hh) = make_float4(o[g][0], o[g][1], o[g][2], o[g][3]);
-        if (hh == 0 && wave == 0) {
+        for (int g = 0; g < GP; ++g) *reinterpret_cast<float4 *>(po + 8 * (first + g) + 4 * hh) = make_float4(o[g][0], o[g][1], o[g][2], o[g][3]);
+        if (hh == 0 && first == 0) {
             float *ml = a.part_ml + (orow * a.splits + sp) * 2;
             ml[0] = m_all;
             ml[1] = l_tot;
@@ -445,39 +493,54 @@ __device__ __forceinline__ void attn_solo(const AttnKernelArgs &a, const int wgs
 #endif
 }
 
-template <int D, bool FP8, bool V8>
-__global__ __launch_bounds__(64 * kSoloWaves) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_solo_kernel(const AttnKernelArgs a)
+template <int D, bool FP8, bool V8, int RB, int VP, int NW>
+__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_solo_kernel(const AttnKernelArgs a)
 {
-    attn_solo<D, FP8, V8>(a, gridDim.x);
+    attn_solo<D, FP8, V8, RB, VP, NW>(a, gridDim.x);
 }
 
 // The same launch with the block-completion copy on the workgroups past the attending ones: for a call without key splits, which has no
 // merge launch to take it along.  (A kernel of its own: the look at where the copying workgroups start costs a plain call 0.4 us.)
-template <int D, bool FP8, bool V8>
-__global__ __launch_bounds__(64 * kSoloWaves) __attribute__((amdgpu_waves_per_eu(2, 2)))
+template <int D, bool FP8, bool V8, int RB, int VP, int NW>
+__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void attn_solo_refresh_kernel(const AttnKernelArgs a, const RefreshArgs r)
 {
     if ((int)blockIdx.x >= r.first_wg) {             // uniform: these only copy
         refresh_cache_rows(r);
         return;
     }
-    attn_solo<D, FP8, V8>(a, r.first_wg);
+    attn_solo<D, FP8, V8, RB, VP, NW>(a, r.first_wg);
 }
 
-template <int D, bool FP8, bool V8> hipError_t launch_solo(const AttnArgs &a, hipStream_t stream)
+template <int D, bool FP8, bool V8, int RB, int VP, int NW> hipError_t launch_solo(const AttnArgs &a, hipStream_t stream)
 {
     AttnKernelArgs k;
-    fill_kernel_args(a, k, 32, 32);
-    const long wgs = (long)a.B * a.Hkv * k.row_tiles * k.splits;
-    const dim3 block(64 * kSoloWaves);
+    fill_kernel_args(a, k, 32 * RB, 32);
+    const long wgs = (long)a.B * a.Hkv * k.row_tiles * k.splits * VP;
+    const dim3 block(64 * NW);
     RefreshArgs r{};
     const long copy_wgs = k.splits == 1 ? fill_refresh(a, r, kCopyWgs) : 0;
     if (copy_wgs > 0) {
         r.first_wg = (int)wgs;
-        return launch(attn_solo_refresh_kernel<D, FP8, V8>, dim3((unsigned)(wgs + copy_wgs)), block, stream, k, r);
+        return launch(attn_solo_refresh_kernel<D, FP8, V8, RB, VP, NW>, dim3((unsigned)(wgs + copy_wgs)), block, stream, k, r);
     }
-    const hipError_t e = launch(attn_solo_kernel<D, FP8, V8>, dim3((unsigned)wgs), block, stream, k);
+    const hipError_t e = launch(attn_solo_kernel<D, FP8, V8, RB, VP, NW>, dim3((unsigned)wgs), block, stream, k);
     return e != hipSuccess ? e : finish_attention(a, k.splits, stream);
+}
+// `form`: row blocks, parts, waves as decimal digits.  (Each storage type has the forms that win somewhere for it: kSoloCosts.)
+template <int D, bool FP8, bool V8> hipError_t launch_form(const AttnArgs &a, int form, hipStream_t stream)
+{
+    switch (form) {
+    case 114: return launch_solo<D, FP8, V8, 1, 1, 4>(a, stream);
+    case 124: return launch_solo<D, FP8, V8, 1, 2, 4>(a, stream);
+    case 128: return launch_solo<D, FP8, V8, 1, 2, 8>(a, stream);
+    case 118: if constexpr (D == 64) return launch_solo<D, FP8, V8, 1, 1, 8>(a, stream); break;
+    case 144: if constexpr (D == 128) return launch_solo<D, FP8, V8, 1, 4, 4>(a, stream); break;
+    case 148: if constexpr (D == 128) return launch_solo<D, FP8, V8, 1, 4, 8>(a, stream); break;
+    case 224: if constexpr (D == 128 && FP8 == V8) return launch_solo<D, FP8, V8, 2, 2, 4>(a, stream); break;
+    case 228: if constexpr (FP8) return launch_solo<D, FP8, V8, 2, 2, 8>(a, stream); break;
+    }
+    return hipErrorInvalidValue;
 }
 
 }  // namespace
@@ -489,66 +552,130 @@ bool attn_solo_serves(const AttnArgs &a)
     return a.qk_dtype == 2 && a.d == 128 && (a.v_dtype == 1 || a.v_dtype == 2);
 }
 
-// Drafter calls.  Key splits: those of least cost while every workgroup has a compute unit, in hundredths of a microsecond, fitted per
-// storage type to some 35000 timings of 19500 calls at one to sixteen splits: a workgroup, its rounds of 128 keys, both again by
-// the workgroups beside it (the caches' share), a merge launch, that again by its workgroups up to 48 and by the rows of the
-// partial states.  (The split picked is 0.1 % off the best one on average.  Decoded e4m3 values cost a round more and share less, so they split earlier: 1 x 32 heads, block 8,
-// 801 keys 12.0 unsplit, 9.3 with four splits, 11.1 on the MFMA kernel; bf16 5 x 8 heads, 7 rows, 724 keys 11.3 unsplit, 9.8 with four.)
+// What a form costs, in hundredths of a microsecond: a workgroup, that again per 100 workgroups beside it, a round (every wave of the
+// workgroup one unit), and, in tenths, a megabyte of K and V, and one of those past 80 (three copies of which no longer stay in the last-level
+// cache between calls).  Fitted per storage type and form to the times of 4000 drawn drafter calls (1 - 16 x 32/32, 32/8, 28/4, 16/16, 8/8, 4/4, 40/8
+// and 12/3 heads, 1 - 64 rows per head, 20 - 4200 keys, 1 - 16 splits, some 30000 timings; rms of the fits 2 - 7 %); `pair` is the same past 256
+// workgroups, two to a compute unit (four waves only, up to 512 workgroups).  Eight waves on two blocks (fp8) and on all of 64 head dims are priced above their
+// fit up to five and four rounds, where four waves were 2 - 5 % faster (96 heads x 40 rows, 649 keys 9.3 / 9.7).
 namespace {
-struct SoloCost { long fixed, fixed_beside, round, round_beside, merge, merge_beside, krows; };     // (beside: per 100 workgroups; merge: 48)
-constexpr SoloCost kSoloBf16 = {441, 23, 80, 28, 214, 57, 4}, kSoloFp8 = {412, 20, 70, 20, 214, 43, 12}, kSoloD64 = {351, 17, 54, 16, 206, 48, 1},
-                   kSoloV8 = {388, 37, 108, 4, 202, 46, 16};
-}  // namespace
-// Against the streaming kernel (8300 calls of 1 - 16 x 32/32, 32/8, 28/4 and 16/16 heads, 8 - 64 rows, 200 - 4096 keys): with one
-// workgroup per compute unit and at most 7 rounds of 128 keys each (8 unsplit) it takes 0.83 of the time (bf16) and 0.87 (fp8), up to 3 %
-// more on one call in a hundred.  Longer streams are bound by memory bandwidth, which that kernel's larger workgroups draw better - 8 x 32, 32
-// rows, 3992 keys fp8 63.6 / 71.8 - unless they leave it a third of its compute units idle: 11 x 32/8, 1237 keys above (264 of its
-// workgroups).  Past 256 workgroups: bf16 of at most 32 rows 0.85 up to 512, the others lose (64 rows bf16 1.03, fp8 1.01).  d = 64: 0.79
-// throughout.  e4m3 values, against the MFMA kernel (746 such calls): 0.78, 9 x 32, 48 rows, 3774 keys 125 -> 85, 11 x 32/8, 16 rows, 1360 keys
-// 23.2 -> 18.3.  Slower, up to 1.13, where a kv head's rows are two workgroups, more than 512 in all, and few keys leave both launches their
-// ramps: 11 x 32, 63 rows, 90 keys 9.3 / 10.5; from a fourth round on and with one workgroup per head it is not.
-// At most 64 keys are one tile of the kernels before, and nothing for waves to stream: few rows of up to 256 heads are faster there, fp8 8
-// rows, 37 - 62 keys 4.2 against 4.9 here, bf16 4.5 - 4.8 / 4.9 - 5.3, as is anything past 512 workgroups where a head's rows are two
-// (d = 64 272 heads, 48 rows, 48 keys 5.3 / 7.6); with the cache refresh, a launch of its own there, 7.2 / 5.1, with 64 rows 6.1 / 5.1 (fp8).
-// More than 64 rows (900 calls of 32/8, 28/4, 32/16 and 16/2 heads, 16 - 64 rows per head, 300 - 4096 keys; before: the two-waves-per-SIMD,
-// the wide or the MFMA kernel): up to 256 workgroups with at most 12 rounds each 0.78 of the time (bf16), 0.75 (fp8), 0.65 (e4m3 V, these up
-// to 512), on none more than 1.00; 256 - 384 workgroups and longer streams up to 1.3.
-SoloPlan attn_solo_plan(long rows, long heads, int N, int d, bool fp8, bool v8, bool refresh, int stream_splits)
+struct SoloTerms { int fixed, beside, round, mb, cold; };
+struct SoloCost { int form; SoloTerms one, pair; };
+constexpr SoloCost kSoloBf16[] = {{114, {491, 13, 69, 44, 110}, {494, 15, 107, 91, 47}}, {124, {430, 10, 64, 31, 103}, {406, 14, 92, 66, 76}},
+                                  {128, {473, 10, 86, 60, 110}, {}},                     {144, {402, 10, 62, 24, 117}, {400, 8, 86, 50, 157}},
+                                  {148, {411, 10, 82, 60, 153}, {}},                     {224, {483, 15, 92, 16, 55}, {469, 25, 134, 63, 39}}};
+constexpr SoloCost kSoloFp8[] = {{114, {459, 10, 61, 43, 111}, {485, 14, 82, 79, 76}},   {124, {407, 5, 50, 40, 134}, {429, 10, 62, 55, 102}},
+                                 {128, {483, 5, 57, 55, 158}, {}},                       {144, {386, 3, 44, 51, 243}, {411, 7, 58, 33, 244}},
+                                 {148, {416, 8, 52, 50, 228}, {}},                       {228, {665, 11, 82, 42, 105}, {}}};
+constexpr SoloCost kSoloV8[] = {{114, {437, 11, 102, 33, 0}, {449, 18, 135, 63, 2}},     {124, {398, 6, 70, 39, 0}, {402, 11, 99, 24, 73}},
+                                {128, {457, 10, 88, 43, 0}, {}},                         {144, {380, 5, 53, 50, 0}, {390, 9, 73, 15, 267}},
+                                {148, {402, 9, 63, 51, 0}, {}},                          {224, {467, 9, 91, 22, 37}, {469, 22, 121, 34, 30}},
+                                {228, {539, 13, 111, 40, 131}, {}}};
+constexpr SoloCost kSoloD64[] = {{114, {376, 0, 51, 34, 123}, {440, 5, 61, 66, 81}}, {118, {470, 5, 70, 50, 140}, {}},
+                                 {124, {372, 0, 45, 39, 273}, {386, 9, 60, 46, 124}}, {128, {403, 0, 52, 56, 236}, {}}};
+// A merge launch of key splits, and what it adds per 1000 rows of partial states (64 dims: half the bytes).
+constexpr int kMerge = 200, kMergeRows = 27, kMergeRowsD64 = 14;
+// The streaming kernel's cost likewise (64 rows, a round = a tile of 64 keys; `more`: per tile and round of 256 workgroups past the first).
+struct StreamTerms { int fixed, beside, round, more, mb, cold; };
+constexpr StreamTerms kStreamBf16 = {429, 40, 90, 138, 36, 0}, kStreamFp8 = {394, 26, 72, 38, 21, 32};
+
+long megabytes(int mb, int cold, long kb)                                    // hundredths
 {
-    const int forced = tune("DD_TUNE_SOLO", -1);
-    if (forced == 0) return SoloPlan{false, 1};
-    if (tune("DD_TUNE_BLOCK_SPLITS", 0) >= 1) return SoloPlan{forced == 1, stream_splits};
-    const long row_tiles = (rows + 31) / 32, wgs = heads * row_tiles;
-    const SoloCost &c = d == 64 ? kSoloD64 : v8 ? kSoloV8 : fp8 ? kSoloFp8 : kSoloBf16;
-    const long most = wgs >= 256 ? 1 : 256 / wgs < stream_splits ? 256 / wgs : stream_splits;
-    long splits = 1, rounds = 0, best = 0;
-    for (long s = 1; s <= most; ++s) {
-        const long r = ((N + s - 1) / s + 127) / 128, w = wgs * s;
-        long cost = c.fixed + c.round * r + (c.fixed_beside + c.round_beside * r) * w / 100;
-        if (s > 1) cost += c.merge + c.merge_beside * (w < 48 ? w : 48) / 48 + c.krows * heads * rows * s / 1000;
-        if (best == 0 || cost < best) {
-            splits = s;
-            rounds = r;
-            best = cost;
+    return (mb * kb + cold * (kb > 80000 ? kb - 80000 : 0)) / 10000;
+}
+struct SoloPick { int form, splits; long cost; };                            // form 0: none
+template <size_t FORMS>
+SoloPick cheapest(const SoloCost (&forms)[FORMS], int only, long rows, long heads, int N, long kb, int merge_rows, int most_splits)
+{
+    SoloPick best{0, 1, 0};
+    for (const SoloCost &f : forms) {
+        const int blocks = f.form / 100, parts = f.form / 10 % 10, waves = f.form % 10;
+        if (only != 0 ? f.form != only : blocks == 2 && rows <= 32) continue;
+        const long w1 = heads * ((rows + 32 * blocks - 1) / (32 * blocks)) * parts;
+        if (w1 > (waves == 8 ? 256 : 512) && only == 0) continue;
+        int last = 0;
+        for (int s = 1; s <= most_splits && (s == 1 || w1 * s <= 256); ++s) {
+            const int keys = ((N + s - 1) / s + 31) / 32 * 32, rounds = (keys + 32 * waves - 1) / (32 * waves);
+            if (rounds == last) continue;                // more splits for nothing
+            last = rounds;
+            const SoloTerms &t = w1 * s > 256 && waves == 4 ? f.pair : f.one;
+            long cost = t.fixed + t.beside * w1 * s / 100 + (long)t.round * rounds + megabytes(t.mb, t.cold, kb);
+            if (s > 1) cost += kMerge + merge_rows * heads * rows * s / 1000;
+            if (best.form == 0 || cost < best.cost) best = SoloPick{f.form, s, cost};
         }
     }
-    if (forced == 1) return SoloPlan{true, (int)splits};
-    if (rows <= 64 && N <= 64 && (wgs > 512 ? row_tiles == 2 : !refresh && heads <= 256 && rows <= (d == 64 || fp8 ? 48 : 32)))
-        return SoloPlan{false, 1};
-    if (rows > 64) return SoloPlan{wgs <= (v8 ? 512 : 256) && rounds <= 12, (int)splits};
-    if (d == 64) return SoloPlan{true, (int)splits};
-    if (v8) return SoloPlan{wgs <= 512 || (wgs <= 768 && (row_tiles == 1 || rounds > 3)) || rounds > 4, (int)splits};
-    const long stream_wgs = heads * stream_splits, stream_slots = (stream_wgs + 255) / 256 * 256;
-    const bool fits = wgs <= 256 || (!fp8 && row_tiles == 1 && wgs <= 512);
-    const bool idle = 10 * stream_wgs < (fp8 ? 6 : 7) * stream_slots;
-    return SoloPlan{fits && (rounds <= (splits == 1 ? 8 : 7) || idle), (int)splits};
+    return best;
+}
+SoloPick solo_pick(long rows, long heads, int N, int d, bool fp8, bool v8, int most_splits)
+{
+    const int only = tune("DD_TUNE_SOLO_FORM", 0);
+    const long kb = heads * (long)N * (d == 64 || v8 ? 256 : fp8 ? 384 : 512) / 1000;
+    return d == 64 ? cheapest(kSoloD64, only, rows, heads, N, kb, kMergeRowsD64, most_splits)
+         : v8      ? cheapest(kSoloV8, only, rows, heads, N, kb, kMergeRows, most_splits)
+         : fp8     ? cheapest(kSoloFp8, only, rows, heads, N, kb, kMergeRows, most_splits)
+                   : cheapest(kSoloBf16, only, rows, heads, N, kb, kMergeRows, most_splits);
+}
+long stream_cost(const StreamTerms &t, long rows, long heads, int N, long kb, bool refresh, int splits)
+{
+    const int keys = ((N + splits - 1) / splits + 63) / 64 * 64;
+    const long s = (N + keys - 1) / keys, wgs = heads * s, tiles = keys / 64;
+    return t.fixed + t.beside * wgs / 100 + t.round * tiles + t.more * tiles * ((wgs + 255) / 256 - 1) + megabytes(t.mb, t.cold, kb) +
+           (s > 1 ? kMerge + kMergeRows * heads * rows * s / 1000 : refresh ? kMerge : 0);          // (a refresh is a launch like a merge)
+}
+}  // namespace
+
+// Drafter calls: the cheapest form and key splits (0.7 - 1.5 % off the best of all kernels, forms and splits on average over drawn calls; splits while
+// every workgroup has a compute unit), where that is cheaper than the other kernels:
+//   Up to 64 rows per kv head, the streaming kernel by its cost (bf16 and fp8; 0.91 and 0.87 of the time of the rule before, which knew one form).
+//   d = 64: throughout.  e4m3 values, against the MFMA kernel: up to 512 workgroups of 32 rows, then where a kv head's rows are
+//   one workgroup, or streams are longer than three rounds of 128 keys (up to 768) or four (11 x 32, 63 rows, 90 keys 9.3 there / 10.5).
+//   At most 64 keys are one tile of the kernels before, and nothing for waves to stream: parts still win there while they spread the call (up to 96
+//   workgroups of 32 rows, bf16 5.05 -> 4.6, fp8 and e4m3 V 4.6 -> 4.35; with 240 5.36 / 5.65 and 4.66 / 5.3 the other way), 64 head dims
+//   do not (4.05 / 4.25), nor anything past 512 workgroups where a head's rows are two (d = 64 272 heads, 48 rows, 48 keys 5.3 / 7.6); with the
+//   cache refresh, a launch of its own there, all do.
+//   More than 64 rows (some 350 drawn calls per type; before: the two-waves-per-SIMD, the wide or the MFMA kernel): up to 256 workgroups 0.46 - 0.9 of
+//   the time, 256 - 512 of more than 64 keys 0.82 - 0.97 up to 1536 keys (d = 64 up to 2560, e4m3 V any: 0.45 - 0.8); longer ones up to 1.2 (88 heads,
+//   120 rows, 3084 keys fp8 36.9 / 45.0), more than 512 1.06 - 1.3.  bf16 past twelve rounds of 128 keys: up to 3072 keys on 128 workgroups (8 heads, 256
+//   rows, 1708 keys 15.0 -> 11.1), up to 2048 on 256; 32 heads, 112 rows, 4083 keys 24.8 / 28.1, 48 x 96, 2946 keys 25.2 / 30.9.
+SoloPlan attn_solo_plan(long rows, long heads, int N, int d, bool fp8, bool v8, bool refresh, int stream_splits)
+{
+    const int forced = tune("DD_TUNE_SOLO", -1), forced_splits = tune("DD_TUNE_BLOCK_SPLITS", 0);
+    const SoloPlan no{false, 0, 1};
+    if (forced == 0) return no;
+    const long row_tiles = (rows + 31) / 32, wgs = heads * row_tiles;
+    SoloPick pick = solo_pick(rows, heads, N, d, fp8, v8, stream_splits);
+    if (pick.form == 0) pick.form = v8 && row_tiles == 2 ? 224 : 114;        // (more workgroups than the costs know)
+    const SoloPlan plan{true, pick.form, forced_splits >= 1 ? stream_splits : pick.splits};
+    if (forced == 1) return plan;
+    if (forced_splits >= 1) return no;
+    const long rounds = (N + 127) / 128;
+    if (rows <= 64 && N <= 64 && (wgs > 512 ? row_tiles == 2 : !refresh && heads <= 256 && rows <= (d == 64 || fp8 ? 48 : 32)) &&
+        (d == 64 || wgs > 96))
+        return no;
+    if (rows > 64) {
+        if (wgs > 512 || (wgs > 256 && (N <= 64 || (!v8 && N > (d == 64 ? 2560 : 1536))))) return no;
+        if (!fp8 && d == 128 && wgs <= 256 && (N / pick.splits + 127) / 128 > 12 && N >= (wgs <= 128 ? 3072 : 2048)) return no;
+        return plan;
+    }
+    if (d == 64) return plan;
+    if (v8) return wgs <= 512 || (wgs <= 768 && (row_tiles == 1 || rounds > 3)) || rounds > 4 ? plan : no;
+    const long kb = heads * (long)N * (fp8 ? 384 : 512) / 1000;
+    // (calls from memory must win by a twentieth: 128 heads, 11 rows, 2423 keys fp8 24.3 streamed / 26.4, predicted 24.8 / 23.2)
+    return pick.cost != 0 && pick.cost * (kb > 80000 ? 20 : 19) <= 19 * stream_cost(fp8 ? kStreamFp8 : kStreamBf16, rows, heads, N, kb, refresh, stream_splits) ? plan : no;
 }
 
-hipError_t launch_attention_solo(const AttnArgs &a, hipStream_t stream)
+// Verifier calls: the form alone.
+int attn_solo_form(long rows, long heads, int N, int d, bool fp8, bool v8)
 {
-    if (a.v_dtype == 2) return launch_solo<128, true, true>(a, stream);
-    if (a.qk_dtype == 2) return launch_solo<128, true, false>(a, stream);
-    return a.d == 128 ? launch_solo<128, false, false>(a, stream) : launch_solo<64, false, false>(a, stream);
+    const int form = solo_pick(rows, heads, N, d, fp8, v8, 1).form;
+    return form != 0 ? form : 114;
+}
+
+hipError_t launch_attention_solo(const AttnArgs &a, int form, hipStream_t stream)
+{
+    if (a.v_dtype == 2) return launch_form<128, true, true>(a, form, stream);
+    if (a.qk_dtype == 2) return launch_form<128, true, false>(a, form, stream);
+    return a.d == 128 ? launch_form<128, false, false>(a, form, stream) : launch_form<64, false, false>(a, form, stream);
 }
 
 }  // namespace dd

@@ -222,7 +222,7 @@ static int block_attention(const void *Qblk, const void *Kc, const void *Vc, voi
     const bool wide = dd::tune("DD_TUNE_BLOCK_WIDE", 1) != 0 && dd::attn_wide_block_fits(a);
     const long rows = (long)(H / Hkv) * block_len, heads = (long)B * Hkv;
     const int narrow_splits = dd::attn_block_splits(block_len, B, H, Hkv, N, d, qk_dtype);
-    dd::SoloPlan solo{false, 1};
+    dd::SoloPlan solo{false, 0, 1};
     if (dd::attn_solo_serves(a) && dd::tune("DD_TUNE_DUO", -1) <= 0 && !other_kernel_forced())
         solo = dd::attn_solo_plan(rows, heads, N, d, qk_dtype == DD_FP8_E4M3, v_dtype == DD_FP8_E4M3, refresh, narrow_splits);
     dd::DuoPlan duo{0, 1};
@@ -255,7 +255,7 @@ static int block_attention(const void *Qblk, const void *Kc, const void *Vc, voi
     if (duo.blocks)
         return dd::launch_attention_duo(a, duo.blocks, static_cast<hipStream_t>(stream)) == hipSuccess ? DD_OK : DD_ERR_LAUNCH;
     if (solo.take)
-        return dd::launch_attention_solo(a, static_cast<hipStream_t>(stream)) == hipSuccess ? DD_OK : DD_ERR_LAUNCH;
+        return dd::launch_attention_solo(a, solo.form, static_cast<hipStream_t>(stream)) == hipSuccess ? DD_OK : DD_ERR_LAUNCH;
     if (wide)
         return dd::launch_attention_wide_block(a, static_cast<hipStream_t>(stream)) == hipSuccess ? DD_OK : DD_ERR_LAUNCH;
     const hipError_t e = (qk_dtype == DD_F32) ? dd::launch_attention_f32(a, static_cast<hipStream_t>(stream))

@@ -38,6 +38,7 @@ inline hipError_t launch(void (*kernel)(Params...), dim3 grid, dim3 block, hipSt
 //                              hooks of the other kernels, where set, come first)
 //   DD_TUNE_SOLO=0/1           drafter and verifier calls off / on the kernel whose waves stream keys of their own
 //                              (the hooks of the other kernels, and a drafter call's of the key splits, come first)
+//   DD_TUNE_SOLO_FORM=rpw      that kernel with r row blocks and w waves per workgroup, head dims in p parts, where the type has that form
 //   DD_TUNE_SEQ_ROUNDS=n       per-sequence rules on rows that are not split: in one launch up to n load rounds per workgroup
 //   DD_TUNE_BLOCK_STREAM=0     drafter calls with few query rows off the streaming kernel
 //   DD_TUNE_BLOCK_WIDE=0       drafter calls with many query rows off the wide-wave kernel
@@ -130,9 +131,10 @@ hipError_t launch_attention_duo(const AttnArgs &a, int blocks, hipStream_t strea
 // and head dims it serves; whether it takes a drafter call with `rows` query rows in each of `heads` (batch, kv head) pairs, and with how
 // many key splits (at most the streaming kernel's, `stream_splits`, so that one workspace serves both); the launch (+ merge).
 bool attn_solo_serves(const AttnArgs &a);
-struct SoloPlan { bool take; int splits; };
+struct SoloPlan { bool take; int form, splits; };        // form: row blocks, parts of the head dims, waves as digits
 SoloPlan attn_solo_plan(long rows, long heads, int N, int d, bool fp8, bool v8, bool refresh, int stream_splits);
-hipError_t launch_attention_solo(const AttnArgs &a, hipStream_t stream);
+int attn_solo_form(long rows, long heads, int N, int d, bool fp8, bool v8);      // a verifier call's form
+hipError_t launch_attention_solo(const AttnArgs &a, int form, hipStream_t stream);
 
 // ---- cache maintenance (cache.hip) ----------------------------------------------
 // Row r of Krows/Vrows [B, Hkv, n, d] replaces cache row pos[b * n + r] of every kv head of batch b

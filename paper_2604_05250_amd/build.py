@@ -12,7 +12,9 @@ SOURCES = ["dd_api.hip", "verify.hip", "attention_mfma.hip", "attention_wide.hip
 HEADERS = ["dd_internal.h", "attention_common.h", os.path.join("..", "..", "include", "dd.h")]
 FLAGS = ["-O3", "-std=c++17", "--offload-arch=gfx950", "-fPIC", "-shared", "-Wall", "-Wno-unused-function", "-Wno-inline-asm",
          # packed-fp32 instructions are kept out of the generated code on the test machines
-         "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
+         "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+         # leading scalar kernel arguments (up to fourteen words) are in registers when a wave starts, not fetched by it
+         "-mllvm", "-amdgpu-kernarg-preload-count=16"]
 
 
 def stale() -> bool:

@@ -40,17 +40,19 @@ struct AttnKernelArgs {
     int row_tiles;             // ceil(group * Nq / rows_per_wg)
     int splits;                // key-range splits
     int keys_per_split;        // multiple of the key tile
+    int wgs;                   // attending workgroups of the launch.  (Asking for the grid's size adds 256 bytes of hidden arguments to
+                               // every launch, which the host writes, 3.9 us for one where 184 bytes take 3.4, and the kernel fetches.)
     int block_start, block_len;
     const int32_t *block_starts;   // [B] or nullptr: the block's first row per batch entry (overrides block_start)
     float scale_log2;          // log2(e) / sqrt(d)
 };
 
-__device__ __forceinline__ void refresh_cache_rows(const RefreshArgs &r)
+template <int THREADS> __device__ __forceinline__ void refresh_cache_rows(const RefreshArgs &r)
 {
     const int cw = (int)blockIdx.x - r.first_wg;
     const int bh = cw / r.wgs_per_bh;
-    const int first = (cw - bh * r.wgs_per_bh) * (int)blockDim.x + (int)threadIdx.x;
-    const int step = r.wgs_per_bh * (int)blockDim.x;
+    const int first = (cw - bh * r.wgs_per_bh) * THREADS + (int)threadIdx.x;
+    const int step = r.wgs_per_bh * THREADS;
 #pragma unroll
     for (int w = 0; w < 2; ++w) {
         const uint4 *src = r.src[w] + (long)bh * r.per_bh[w];

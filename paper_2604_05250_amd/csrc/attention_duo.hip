@@ -95,7 +95,7 @@ void attn_duo_kernel(const AttnKernelArgs a)
     // ---- which (batch, kv head, row tile, key split); same XCD for workgroups that share K/V
     int bid = blockIdx.x;
     {
-        const int total = gridDim.x, per = total >> 3, rem = total & 7;
+        const int total = a.wgs, per = total >> 3, rem = total & 7;
         const int xcd = bid & 7, slot = bid >> 3;
         bid = xcd * per + min(xcd, rem) + slot;
     }
@@ -432,7 +432,8 @@ hipError_t launch_duo(const AttnArgs &a, hipStream_t stream)
 {
     AttnKernelArgs k;
     fill_kernel_args(a, k, 32 * R, 32 * (kDuoWaves / R));
-    const dim3 grid((unsigned)((long)a.B * a.Hkv * k.row_tiles * k.splits)), block(kDuoThreads);
+    k.wgs = (int)((long)a.B * a.Hkv * k.row_tiles * k.splits);
+    const dim3 grid((unsigned)k.wgs), block(kDuoThreads);
     hipError_t e;
     if (a.qk_dtype == 2) e = launch(attn_duo_kernel<128, true, R, RING8>, grid, block, stream, k);
     else if (a.d == 128) e = launch(attn_duo_kernel<128, false, R, RING16>, grid, block, stream, k);

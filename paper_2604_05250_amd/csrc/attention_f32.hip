@@ -228,7 +228,7 @@ template <int D, int RB>
 __global__ __launch_bounds__(kThreadsF) void attn_f32_refresh_kernel(const AttnKernelArgs a, const RefreshArgs r)
 {
     if ((int)blockIdx.x >= r.first_wg) {            // uniform: these only copy
-        refresh_cache_rows(r);
+        refresh_cache_rows<kThreadsF>(r);
         return;
     }
     attn_f32<D, RB>(a);

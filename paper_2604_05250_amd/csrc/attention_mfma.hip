@@ -189,7 +189,7 @@ __global__ __launch_bounds__(kAttnThreads, 2) void attn_mfma_kernel(const AttnKe
     {
         // Workgroups are dealt round-robin to the 8 XCDs, each with its own L2.  Remap so that the
         // workgroups sharing one (batch, kv head) - hence the same K/V - run on the same XCD.
-        const int total = gridDim.x, per = total >> 3, rem = total & 7;
+        const int total = a.wgs, per = total >> 3, rem = total & 7;
         const int xcd = bid & 7, slot = bid >> 3;
         bid = xcd * per + min(xcd, rem) + slot;
     }
@@ -625,15 +625,17 @@ __global__ __launch_bounds__(kAttnThreads, 2) void attn_mfma_kernel(const AttnKe
     }
 }
 
+constexpr int kCombineThreads = 256;
 // Merge the per-split partial states of each query row: O = sum_s 2^{m_s-M} O_s / sum_s 2^{m_s-M} l_s.
 template <bool OUT_BF16>
 __device__ __forceinline__ void combine_rows(const float *__restrict__ part_o, const float *__restrict__ part_ml,
                                              void *__restrict__ O, long rows, int splits, int d)
 {
-    const int per_row = d / 4;
-    const long gid = (long)blockIdx.x * blockDim.x + threadIdx.x;
-    const long row = gid / per_row;
-    const int c4 = (int)(gid % per_row);
+    // (a row's lanes by shifts: d is 64 or 128)
+    const int log2_lanes = d == 128 ? 5 : 4;
+    const long gid = (long)blockIdx.x * kCombineThreads + threadIdx.x;
+    const long row = gid >> log2_lanes;
+    const int c4 = (int)gid & ((1 << log2_lanes) - 1);
     if (row >= rows) return;
     // every load of the row is issued before the first use (at most 16 splits): one memory round trip
     constexpr int kMaxSplits = 16;
@@ -673,7 +675,7 @@ __device__ __forceinline__ void combine_rows(const float *__restrict__ part_o, c
 }
 
 template <bool OUT_BF16>
-__global__ __launch_bounds__(256) void attn_combine_kernel(const float *__restrict__ part_o,
+__global__ __launch_bounds__(kCombineThreads) void attn_combine_kernel(const float *__restrict__ part_o,
                                                            const float *__restrict__ part_ml, void *__restrict__ O,
                                                            long rows, int splits, int d)
 {
@@ -682,13 +684,13 @@ __global__ __launch_bounds__(256) void attn_combine_kernel(const float *__restri
 
 // the same launch with the block-completion copy on the workgroups past the merging ones
 template <bool OUT_BF16>
-__global__ __launch_bounds__(256) void attn_combine_refresh_kernel(const float *__restrict__ part_o,
+__global__ __launch_bounds__(kCombineThreads) void attn_combine_refresh_kernel(const float *__restrict__ part_o,
                                                                    const float *__restrict__ part_ml,
                                                                    void *__restrict__ O, long rows, int splits, int d,
                                                                    const RefreshArgs refresh)
 {
     if ((int)blockIdx.x >= refresh.first_wg) {             // workgroup-uniform: these only copy
-        refresh_cache_rows(refresh);
+        refresh_cache_rows<kCombineThreads>(refresh);
         return;
     }
     combine_rows<OUT_BF16>(part_o, part_ml, O, rows, splits, d);
@@ -728,6 +730,7 @@ hipError_t launch_attention_mfma(const AttnArgs &a, hipStream_t stream)
     const bool blk = a.Nq != a.N || a.Kblk != nullptr || a.splits > 1;   // drafter form of the call
     fill_kernel_args(a, k, blk && a.Nq != a.N ? attn_block_rows_per_wg(a.Nq, a.B, a.H, a.Hkv) : kRowsPerWG, TK);
     const long blocks = (long)a.B * a.Hkv * k.row_tiles * k.splits;
+    k.wgs = (int)blocks;
     const dim3 grid((unsigned)blocks), block(kAttnThreads);
     hipError_t e;
     // Verifier calls: do workgroups of 64 / 128 query rows fit the chip's 256 compute units in one round?
@@ -842,12 +845,12 @@ static hipError_t launch_combine_refresh(const AttnArgs &a, bool merge, hipStrea
     const float *po = static_cast<const float *>(a.workspace);
     const float *pml = merge ? po + (size_t)rows * a.splits * a.d : nullptr;
     const long threads = rows * (a.d / 4);
-    const long merge_wgs = (threads + 255) / 256;
+    const long merge_wgs = (threads + kCombineThreads - 1) / kCombineThreads;
     RefreshArgs r{};
     r.first_wg = (int)merge_wgs;
     const long copy_wgs = fill_refresh(a, r, 2048);
     if (merge_wgs + copy_wgs == 0) return hipSuccess;
-    const dim3 grid((unsigned)(merge_wgs + copy_wgs)), block(256);
+    const dim3 grid((unsigned)(merge_wgs + copy_wgs)), block(kCombineThreads);
     if (copy_wgs == 0) {
         if (a.v_dtype != 0)                 // bf16 output (V bf16 or fp8)
             return launch(attn_combine_kernel<true>, grid, block, stream, po, pml, a.O, rows, a.splits, a.d);

@@ -56,6 +56,12 @@ __device__ __forceinline__ const uint8_t *solo_scalar(const uint8_t *p)         
     const unsigned lo = __builtin_amdgcn_readfirstlane((unsigned)v), hi = __builtin_amdgcn_readfirstlane((unsigned)(v >> 32));
     return reinterpret_cast<const uint8_t *>(((unsigned long long)hi << 32) | lo);
 }
+// A value at a uniform address that no workgroup writes, by a scalar load.  (After a statement that may write memory the compiler takes a
+// vector load instead, and waits for every load before it.)
+template <typename T> __device__ __forceinline__ T solo_uniform(const T *p)
+{
+    return *(__attribute__((address_space(4))) const T *)(unsigned long long)p;
+}
 __device__ __forceinline__ uint4 solo_decode(unsigned w0, unsigned w1)           // eight e4m3 codes to bf16, exactly
 {
     return make_uint4(__builtin_bit_cast(unsigned, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(w0, 1.0f, false)),
@@ -71,11 +77,29 @@ template <int I, int N, typename F> __device__ __forceinline__ void static_for(F
     }
 }
 
+// What a launch passes.  The first loads need the first fourteen words only, which the hardware has put in registers when a wave starts
+// (the build asks for it: kernels whose arguments are scalars); the rest arrives while those loads are on their way.
+struct SoloArgs {
+    const void *Kblk, *Vblk;
+    void *O;
+    float *part_o, *part_ml;
+    const float *q_scale, *k_scale, *v_scale;
+    const int32_t *block_starts;
+    int Hkv, Nq, group;
+    float scale_log2;
+};
+struct SoloHead {                                    // (the same, in one piece for the kernel's body)
+    const uint8_t *Q, *K, *V;
+    int rows_total, N, kv_stride, keys_per_split, wgs;
+    int row_tiles, splits;
+    int block_start, block_len;
+};
+
 // V8: V is stored as e4m3 codes.  They travel to LDS as they are and the wave decodes its own 4 KB into its V buffer, exactly, when
 // they arrive (32 conversions of two elements per lane and unit); v_scale multiplies the result once.
-// `wgs`: the launch's attending workgroups.  RB row blocks per workgroup, VP parts of the head dims, NW waves.
+// RB row blocks per workgroup, VP parts of the head dims, NW waves.
 template <int D, bool FP8, bool V8, int RB, int VP, int NW>
-__device__ __forceinline__ void attn_solo(const AttnKernelArgs &a, const int wgs)
+__device__ __forceinline__ void attn_solo(const SoloHead &h, const SoloArgs &a)
 {
     // (device pass only: the host pass needs the kernels' handles, not assembly it cannot check)
 #if defined(__HIP_DEVICE_COMPILE__)
@@ -113,37 +137,45 @@ __device__ __forceinline__ void attn_solo(const AttnKernelArgs &a, const int wgs
     // ---- which (batch, kv head, row tile, key split); same XCD for workgroups that share K/V
     int bid = blockIdx.x;
     {
-        const int total = wgs, per = total >> 3, rem = total & 7;
+        const int total = h.wgs, per = total >> 3, rem = total & 7;
         const int xcd = bid & 7, slot = bid >> 3;
         bid = xcd * per + min(xcd, rem) + slot;
     }
     const int part = bid % VP; bid /= VP;
-    const int rt = bid % a.row_tiles; bid /= a.row_tiles;
-    const int sp = bid % a.splits; bid /= a.splits;
-    const int kvh = bid % a.Hkv;
-    const int b = bid / a.Hkv;
-    const int rows_total = a.group * a.Nq;           // query rows of this (batch, kv head): contiguous in memory
+    int rt = 0, sp = 0;                              // (a division is some 150 cycles before the first load)
+    if (h.row_tiles > 1) { rt = bid % h.row_tiles; bid /= h.row_tiles; }
+    if (h.splits > 1) { sp = bid % h.splits; bid /= h.splits; }
+    const size_t kv_head = bid;                      // batch and kv head
+    const int rows_total = h.rows_total;             // query rows of this (batch, kv head): contiguous in memory
     const int v_first = rt * 32 * RB;
-    const size_t row_base = ((size_t)b * a.H + (size_t)kvh * a.group) * a.Nq;
-    const int kbeg = sp * a.keys_per_split;
-    const int kend = min(a.N, kbeg + a.keys_per_split);
-    const int bstart = a.block_starts ? a.block_starts[b] : a.block_start;   // any value is safe: rows are chosen by range test
-    const int blen = a.block_len;
+    const size_t row_base = kv_head * rows_total;
+    auto lds_addr = [&](const void *p) __attribute__((always_inline)) { return (unsigned)(size_t)(__attribute__((address_space(3))) const void *)p; };
+    const int krow0 = lane / KCH;
+    auto kchunk = [&](int i) __attribute__((always_inline)) { return (unsigned)(((lane % KCH) ^ ((i * KDMA_ROWS + krow0) & 7)) * 16); };
+
+    // ---- the query rows, shared out over the waves: first, as they need nothing that is still on its way
+    for (int i = wave; i < RB * NK; i += NW) {
+        const int r = min(v_first + i * KDMA_ROWS + krow0, rows_total - 1);
+        const uint8_t *const src = h.Q + (row_base + r) * KROWB + kchunk(i);
+        asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(lds_addr(QS) + i * 1024), "v"(src) : "memory", "m0");
+    }
+
+    const int kbeg = sp * h.keys_per_split;
+    const int kend = min(h.N, kbeg + h.keys_per_split);
+    const int bstart = a.block_starts ? solo_uniform(a.block_starts + (unsigned)kv_head / (unsigned)a.Hkv) : h.block_start;        // any value is safe: rows are chosen by range test
+    const int blen = h.block_len;
     const int nunits = (kend - kbeg + U - 1) / U;
     const int whole = (kend - kbeg) / U;             // units [0, whole) hold 32 rows of the range
 
-    const size_t kv_head = (size_t)b * a.Hkv + kvh;
-    const uint8_t *const kc = static_cast<const uint8_t *>(a.K) + kv_head * a.kv_stride * (size_t)KROWB;
-    const uint8_t *const vc = static_cast<const uint8_t *>(a.V) + kv_head * a.kv_stride * (size_t)VPITCH + part * VSROWB;
+    const uint8_t *const kc = h.K + kv_head * h.kv_stride * (size_t)KROWB;
+    const uint8_t *const vc = h.V + kv_head * h.kv_stride * (size_t)VPITCH + part * VSROWB;
     const uint8_t *const kb_ = blen ? static_cast<const uint8_t *>(a.Kblk) + kv_head * blen * (size_t)KROWB : nullptr;
     const uint8_t *const vb_ = blen ? static_cast<const uint8_t *>(a.Vblk) + kv_head * blen * (size_t)VPITCH + part * VSROWB : nullptr;
-    auto lds_addr = [&](const void *p) __attribute__((always_inline)) { return (unsigned)(size_t)(__attribute__((address_space(3))) const void *)p; };
     char *const kbuf = reinterpret_cast<char *>(KV) + wave * SLOTB, *const vbuf = kbuf + KB, *const vstored = vbuf + VB;
     const unsigned kdst = lds_addr(KV) + wave * SLOTB, vdst = kdst + KB + (V8 ? VB : 0);
     // load i of a buffer fills its rows i * DMA_ROWS ..; lane l lands at chunk position l % CH of row l / CH and fetches the
     // chunk the swizzle maps there (with 256-byte rows K's depends on whether i is odd)
-    const int vrow0 = lane / VSCH, krow0 = lane / KCH;
-    auto kchunk = [&](int i) __attribute__((always_inline)) { return (unsigned)(((lane % KCH) ^ ((i * KDMA_ROWS + krow0) & 7)) * 16); };
+    const int vrow0 = lane / VSCH;
     const unsigned vchunk = V8 ? lane % VSCH * 16 : ((lane % CH) ^ ((vrow0 & (CH / 4 - 1)) << 2)) * 16;   // (codes lie as in memory)
     const unsigned koff[2] = {krow0 * KROWB + kchunk(0), krow0 * KROWB + kchunk(1)}, voff = vrow0 * VPITCH + vchunk;
     int blk0 = 0, blk1 = 0;                          // units outside [blk0, blk1) hold rows of the cache only
@@ -192,17 +224,12 @@ __device__ __forceinline__ void attn_solo(const AttnKernelArgs &a, const int wgs
     const std::true_type of_k;
     const std::false_type of_v;
 
-    // ---- prologue: the query rows, shared out over the waves, then this wave's first unit
-    const float k_scale = a.k_scale ? a.k_scale[kv_head] : 1.0f;
+    // ---- the rest of the prologue: the query rows' scales, this wave's first unit
+    const float k_scale = a.k_scale ? solo_uniform(a.k_scale + kv_head) : 1.0f;
     // (through LDS like the rows: the compiler's own wait for a load of its own would wait for every load after it as well)
     if (a.q_scale && wave == 0) {
-        const float *const src = a.q_scale + b * a.H + kvh * a.group + min(v_first + (RB == 2 ? lane : l32), rows_total - 1) / a.Nq;
+        const float *const src = a.q_scale + kv_head * a.group + min(v_first + (RB == 2 ? lane : l32), rows_total - 1) / a.Nq;
         asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dword %1, off" ::"s"(lds_addr(qs_sh)), "v"(src) : "memory", "m0");
-    }
-    for (int i = wave; i < RB * NK; i += NW) {
-        const int r = min(v_first + i * KDMA_ROWS + krow0, rows_total - 1);
-        const uint8_t *const src = static_cast<const uint8_t *>(a.Q) + (row_base + r) * KROWB + kchunk(i);
-        asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(lds_addr(QS) + i * 1024), "v"(src) : "memory", "m0");
     }
     if (wave < nunits) {
         load_rows(of_k, wave);
@@ -456,7 +483,7 @@ __device__ __forceinline__ void attn_solo(const AttnKernelArgs &a, const int wgs
             }
         }
     if constexpr (V8) {
-        const float vs = a.v_scale[kv_head];         // the decoded values times this are the real ones
+        const float vs = solo_uniform(a.v_scale + kv_head);         // the decoded values times this are the real ones
 #pragma unroll
         for (int g = 0; g < GP; ++g)
 #pragma unroll
@@ -466,7 +493,7 @@ __device__ __forceinline__ void attn_solo(const AttnKernelArgs &a, const int wgs
     const int v = v_first + 32 * mine + l32, first = part * GB + wave * GP % GB;
     const bool row_ok = v < rows_total;
     const size_t orow = row_base + v;
-    if (a.splits == 1) {
+    if (h.splits == 1) {
         const float inv = 1.0f / l_tot;
         uint16_t *out = static_cast<uint16_t *>(a.O) + orow * D;
         if constexpr (GP == 1) {
@@ -481,11 +508,11 @@ __device__ __forceinline__ void attn_solo(const AttnKernelArgs &a, const int wgs
             }
         }
     } else if (row_ok) {
-        float *po = a.part_o + (orow * a.splits + sp) * D;
+        float *po = a.part_o + (orow * h.splits + sp) * D;
 #pragma unroll
         for (int g = 0; g < GP; ++g) *reinterpret_cast<float4 *>(po + 8 * (first + g) + 4 * hh) = make_float4(o[g][0], o[g][1], o[g][2], o[g][3]);
         if (hh == 0 && first == 0) {
-            float *ml = a.part_ml + (orow * a.splits + sp) * 2;
+            float *ml = a.part_ml + (orow * h.splits + sp) * 2;
             ml[0] = m_all;
             ml[1] = l_tot;
         }
@@ -493,38 +520,49 @@ __device__ __forceinline__ void attn_solo(const AttnKernelArgs &a, const int wgs
 #endif
 }
 
+#define DD_SOLO_HEAD const uint8_t *Q, const uint8_t *K, const uint8_t *V, int rows_total, int N, int kv_stride, int keys_per_split, int wgs, \
+                     int tiles_splits, int block_start, int block_len
 template <int D, bool FP8, bool V8, int RB, int VP, int NW>
-__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_solo_kernel(const AttnKernelArgs a)
+__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_solo_kernel(DD_SOLO_HEAD, const SoloArgs a)
 {
-    attn_solo<D, FP8, V8, RB, VP, NW>(a, gridDim.x);
+    attn_solo<D, FP8, V8, RB, VP, NW>(SoloHead{Q, K, V, rows_total, N, kv_stride, keys_per_split, wgs, tiles_splits >> 8, tiles_splits & 255, block_start,
+                                               block_len}, a);
 }
 
 // The same launch with the block-completion copy on the workgroups past the attending ones: for a call without key splits, which has no
-// merge launch to take it along.  (A kernel of its own: the look at where the copying workgroups start costs a plain call 0.4 us.)
+// merge launch to take it along.
 template <int D, bool FP8, bool V8, int RB, int VP, int NW>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2)))
-void attn_solo_refresh_kernel(const AttnKernelArgs a, const RefreshArgs r)
+void attn_solo_refresh_kernel(DD_SOLO_HEAD, const SoloArgs a, const RefreshArgs r)
 {
-    if ((int)blockIdx.x >= r.first_wg) {             // uniform: these only copy
-        refresh_cache_rows(r);
+    if ((int)blockIdx.x >= wgs) {                            // uniform: these only copy
+        refresh_cache_rows<64 * NW>(r);
         return;
     }
-    attn_solo<D, FP8, V8, RB, VP, NW>(a, r.first_wg);
+    attn_solo<D, FP8, V8, RB, VP, NW>(SoloHead{Q, K, V, rows_total, N, kv_stride, keys_per_split, wgs, tiles_splits >> 8, tiles_splits & 255, block_start,
+                                               block_len}, a);
 }
+#undef DD_SOLO_HEAD
 
 template <int D, bool FP8, bool V8, int RB, int VP, int NW> hipError_t launch_solo(const AttnArgs &a, hipStream_t stream)
 {
     AttnKernelArgs k;
     fill_kernel_args(a, k, 32 * RB, 32);
     const long wgs = (long)a.B * a.Hkv * k.row_tiles * k.splits * VP;
+    if (k.row_tiles >= 1 << 23 || k.splits > 255 || wgs > 0x7FFFFFFF) return hipErrorInvalidValue;   // (rows of a kv head: below 2^28; splits: at most 16)
     const dim3 block(64 * NW);
+    const uint8_t *const Q = static_cast<const uint8_t *>(a.Q), *const K = static_cast<const uint8_t *>(a.K), *const V = static_cast<const uint8_t *>(a.V);
+    const SoloArgs s{a.Kblk, a.Vblk, a.O, k.part_o, k.part_ml, a.q_scale, a.k_scale, a.v_scale, a.block_starts, a.Hkv, a.Nq, k.group, k.scale_log2};
+    const int rows_total = k.group * a.Nq, tiles_splits = k.row_tiles << 8 | k.splits;
     RefreshArgs r{};
     const long copy_wgs = k.splits == 1 ? fill_refresh(a, r, kCopyWgs) : 0;
     if (copy_wgs > 0) {
         r.first_wg = (int)wgs;
-        return launch(attn_solo_refresh_kernel<D, FP8, V8, RB, VP, NW>, dim3((unsigned)(wgs + copy_wgs)), block, stream, k, r);
+        return launch(attn_solo_refresh_kernel<D, FP8, V8, RB, VP, NW>, dim3((unsigned)(wgs + copy_wgs)), block, stream, Q, K, V, rows_total, k.N,
+                      k.kv_stride, k.keys_per_split, (int)wgs, tiles_splits, k.block_start, k.block_len, s, r);
     }
-    const hipError_t e = launch(attn_solo_kernel<D, FP8, V8, RB, VP, NW>, dim3((unsigned)wgs), block, stream, k);
+    const hipError_t e = launch(attn_solo_kernel<D, FP8, V8, RB, VP, NW>, dim3((unsigned)wgs), block, stream, Q, K, V, rows_total, k.N, k.kv_stride,
+                                k.keys_per_split, (int)wgs, tiles_splits, k.block_start, k.block_len, s);
     return e != hipSuccess ? e : finish_attention(a, k.splits, stream);
 }
 // `form`: row blocks, parts, waves as decimal digits.  (Each storage type has the forms that win somewhere for it: kSoloCosts.)

@@ -104,7 +104,7 @@ void attn_stream_kernel(const AttnKernelArgs a)
     // ---- which (batch, kv head, row tile, key split); same XCD for workgroups that share K/V
     int bid = blockIdx.x;
     {
-        const int total = gridDim.x, per = total >> 3, rem = total & 7;
+        const int total = a.wgs, per = total >> 3, rem = total & 7;
         const int xcd = bid & 7, slot = bid >> 3;
         bid = xcd * per + min(xcd, rem) + slot;
     }
@@ -438,7 +438,8 @@ hipError_t launch_attention_stream(const AttnArgs &a, hipStream_t stream)
 {
     AttnKernelArgs k;
     fill_kernel_args(a, k, 2 * kRowsWaveS, TKS);
-    const dim3 grid((unsigned)((long)a.B * a.Hkv * k.row_tiles * k.splits)), block(kAttnThreads);
+    k.wgs = (int)((long)a.B * a.Hkv * k.row_tiles * k.splits);
+    const dim3 grid((unsigned)k.wgs), block(kAttnThreads);
     // A model's layers take their turns, each with a cache of its own, so a large one has left the 256 MB last-level cache
     // when it is read again: above 100 MB it is streamed past it.  us per call with plain loads -> with the hint, four
     // copies in turn (two of the largest): 67 MB 20.7 -> 22.0, 101 MB 24.9 -> 23.6, 134 MB 29.2 -> 26.6, 252 MB 54.4 -> 50.8,

@@ -290,10 +290,10 @@ void attn_wide_kernel(const AttnKernelArgs a)
     // w, w + G, w + 2G ...: at any time the G workgroups are on consecutive tiles, so neighbours work on the
     // same K/V, and neighbours are placed on the same XCD (own L2 each).
     const int tiles_total = a.B * a.Hkv * a.row_tiles;
-    int t_stride = gridDim.x;
+    int t_stride = a.wgs;
     int t_cur, split = 0;
     {
-        const int G = gridDim.x, per = G >> 3, rem = G & 7;
+        const int G = a.wgs, per = G >> 3, rem = G & 7;
         const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
         t_cur = xcd * per + min(xcd, rem) + slot;
     }
@@ -1256,6 +1256,7 @@ hipError_t launch_attention_wide(const AttnArgs &a, hipStream_t stream, bool may
     long wgs = tiles < cus ? tiles : cus;                  // one persistent workgroup per compute unit
     const long cap = tune("DD_TUNE_ATTN_WIDE_GRID", 0);
     if (cap >= 1 && cap < wgs) wgs = cap;
+    k.wgs = (int)wgs;
     const dim3 grid((unsigned)wgs), block(kAttnThreads);
     if (a.qk_dtype == 2) {
         if (a.d != 128) return hipErrorInvalidValue;      // 64-byte fp8 rows are not worth a variant
@@ -1278,7 +1279,8 @@ hipError_t launch_attention_wide_narrow(const AttnArgs &a, hipStream_t stream)
     if (a.N < TKW) return hipErrorInvalidValue;            // a K/V tile is 64 whole rows
     AttnKernelArgs k;
     fill_kernel_args(a, k, kRowsWGNarrow, TKW);
-    const dim3 grid((unsigned)((long)a.B * a.Hkv * k.row_tiles)), block(kAttnThreads);
+    k.wgs = (int)((long)a.B * a.Hkv * k.row_tiles);
+    const dim3 grid((unsigned)k.wgs), block(kAttnThreads);
     if (a.qk_dtype == 2) {
         if (a.d != 128) return hipErrorInvalidValue;
         if (a.q_mx != nullptr) return launch(attn_wide_kernel<128, true, true, false, 1, kVMx>, grid, block, stream, k);
@@ -1357,7 +1359,8 @@ hipError_t launch_attention_wide_block(const AttnArgs &a, hipStream_t stream)
     k.splits = splits;
     const size_t rows = (size_t)a.B * a.H * a.Nq;
     k.part_ml = k.part_o ? k.part_o + rows * (size_t)splits * a.d : nullptr;
-    const dim3 grid((unsigned)((long)a.B * a.Hkv * k.row_tiles * splits)), block(kAttnThreads);
+    k.wgs = (int)((long)a.B * a.Hkv * k.row_tiles * splits);
+    const dim3 grid((unsigned)k.wgs), block(kAttnThreads);
     const bool fold = a.q_scale == nullptr && a.k_scale == nullptr && a.N >= kFoldMinKeys;
     hipError_t e;
     if (a.v_dtype == 2)

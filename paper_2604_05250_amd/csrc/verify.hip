@@ -472,7 +472,7 @@ __global__ __launch_bounds__(256) void verify_finalize_kernel(const VerifyPartia
                                                               int32_t *__restrict__ out_tokens,
                                                               float *__restrict__ out_scores, VerifyExtra ex)
 {
-    const int gid = blockIdx.x * blockDim.x + threadIdx.x;
+    const int gid = blockIdx.x * 256 + threadIdx.x;
     const int row = gid / kFinalizeLanes;
     merge_splits_and_finish(part, S, row, row < P, gid % kFinalizeLanes, mask, mode, threshold, seed, kl_mode, out_mask,
                             out_tokens, out_scores, ex);

@@ -9,6 +9,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "dd_internal.h"
+
 namespace dd {
 
 // Block-completion refresh of the cache (Sec. 2.3: the cache is brought up to date when a block is done):
@@ -59,6 +61,47 @@ template <int THREADS> __device__ __forceinline__ void refresh_cache_rows(const 
         uint4 *dst = r.dst[w] + (long)bh * r.bh_stride[w] + r.offset[w];
         for (int in = first; in < r.per_bh[w]; in += step) dst[in] = src[in];
     }
+}
+
+// What the kernels of short calls take instead: their first loads need the head only, fourteen words that the hardware has put in
+// registers when a wave starts (the build asks for it; it works for leading scalar arguments), and the tail arrives while those
+// loads are on their way.  us per call: 1 x 32 heads, 512 keys, 32 rows 6.6 -> 6.2, the verifier's on them 11.5 -> 11.1.
+struct AttnHead {
+    const uint8_t *Q, *K, *V;
+    int rows_total;            // query rows of a (batch, kv head): contiguous in memory
+    int N, kv_stride, keys_per_split, wgs, row_tiles, splits, block_start, block_len;
+};
+struct AttnTail {
+    const void *Kblk, *Vblk;
+    void *O;
+    float *part_o, *part_ml;
+    const float *q_scale, *k_scale, *v_scale;
+    const int32_t *block_starts;
+    int Hkv, Nq, group;
+    float scale_log2;
+};
+#define DD_ATTN_HEAD const uint8_t *Q, const uint8_t *K, const uint8_t *V, int rows_total, int N, int kv_stride, int keys_per_split, int wgs, \
+                     unsigned tiles_splits, int block_start, int block_len
+#define DD_ATTN_HEAD_ARGS ::dd::AttnHead{Q, K, V, rows_total, N, kv_stride, keys_per_split, wgs, (int)(tiles_splits >> 4), (int)(tiles_splits & 15) + 1, block_start, block_len}
+template <typename... Params, typename... Rest>
+hipError_t launch_headed(void (*kernel)(Params...), dim3 grid, dim3 block, hipStream_t stream, const AttnKernelArgs &k, Rest... rest)
+{
+    return launch(kernel, grid, block, stream, static_cast<const uint8_t *>(k.Q), static_cast<const uint8_t *>(k.K), static_cast<const uint8_t *>(k.V),
+                  k.group * k.Nq, k.N, k.kv_stride, k.keys_per_split, k.wgs, (unsigned)k.row_tiles << 4 | (unsigned)(k.splits - 1),   // (at most 16 splits)
+                  k.block_start, k.block_len,
+                  AttnTail{k.Kblk, k.Vblk, k.O, k.part_o, k.part_ml, k.q_scale, k.k_scale, k.v_scale, k.block_starts, k.Hkv, k.Nq, k.group, k.scale_log2}, rest...);
+}
+// This workgroup's place, from its number: of `row_tiles` and `splits` (a division is some 150 cycles before the first load).
+__device__ __forceinline__ void place_of(unsigned &bid, int count, int &at)
+{
+    at = 0;
+    if (count > 1) { at = bid % (unsigned)count; bid /= (unsigned)count; }
+}
+// A value at a uniform address that no workgroup writes, by a scalar load.  (After a statement that may write memory the compiler takes a
+// vector load instead, and waits for every load before it.)
+template <typename T> __device__ __forceinline__ T uniform_load(const T *p)
+{
+    return *(__attribute__((address_space(4))) const T *)(unsigned long long)p;
 }
 
 constexpr int kAttnThreads = 256;

@@ -58,10 +58,11 @@ constexpr int duo_waitcnt_vm(int n) { return (n & 15) | ((n >> 4) << 14) | (7 <<
 // R: row blocks per workgroup, RING: tile buffers
 template <int D, bool FP8, int R, int RING>
 __global__ __launch_bounds__(kDuoThreads) __attribute__((amdgpu_waves_per_eu(2, 2)))
-void attn_duo_kernel(const AttnKernelArgs a)
+void attn_duo_kernel(DD_ATTN_HEAD, const AttnTail a)
 {
     // (device pass only: the host pass needs the handle, not assembly it cannot check)
 #if defined(__HIP_DEVICE_COMPILE__)
+    const AttnHead h = DD_ATTN_HEAD_ARGS;
     constexpr int P = kDuoWaves / R;                 // key phases
     constexpr int TK = 32 * P;                       // keys per tile
     constexpr int CH = D / 8;                        // 16-byte chunks per V / O row
@@ -93,24 +94,23 @@ void attn_duo_kernel(const AttnKernelArgs a)
     const int rg = wave % R, ph = wave / R;          // row block, key phase
 
     // ---- which (batch, kv head, row tile, key split); same XCD for workgroups that share K/V
-    int bid = blockIdx.x;
+    unsigned bid = blockIdx.x;
     {
-        const int total = a.wgs, per = total >> 3, rem = total & 7;
-        const int xcd = bid & 7, slot = bid >> 3;
+        const unsigned total = h.wgs, per = total >> 3, rem = total & 7;
+        const unsigned xcd = bid & 7, slot = bid >> 3;
         bid = xcd * per + min(xcd, rem) + slot;
     }
-    const int sp = bid % a.splits; bid /= a.splits;
-    const int rt = bid % a.row_tiles; bid /= a.row_tiles;
-    const int kvh = bid % a.Hkv;
-    const int b = bid / a.Hkv;
-    const int rows_total = a.group * a.Nq;           // query rows of this (batch, kv head): contiguous in memory
+    int sp, rt;
+    place_of(bid, h.splits, sp);
+    place_of(bid, h.row_tiles, rt);
+    const size_t kv_head = bid;                      // batch and kv head; its query rows are contiguous in memory
     const int v_tile = rt * (32 * R), v_first = v_tile + rg * 32;
     const bool wave_active = v_first < rows_total;   // uniform
-    const size_t row_base = ((size_t)b * a.H + (size_t)kvh * a.group) * a.Nq;
-    const int kbeg = sp * a.keys_per_split;
-    const int kend = min(a.N, kbeg + a.keys_per_split);
-    const int bstart = a.block_starts ? a.block_starts[b] : a.block_start;   // any value is safe: rows are chosen by range test
-    const int blen = a.block_len;
+    const size_t row_base = kv_head * rows_total;
+    const int kbeg = sp * h.keys_per_split;
+    const int kend = min(h.N, kbeg + h.keys_per_split);
+    const int bstart = a.block_starts ? uniform_load(a.block_starts + (unsigned)kv_head / (unsigned)a.Hkv) : h.block_start;   // any value is safe: rows are chosen by range test
+    const int blen = h.block_len;
     const int ntiles = (kend - kbeg + TK - 1) / TK;
 
     // ---- staging by LDS DMA: load i of this wave moves rows (8 i + wave) * DMA_ROWS .. of a tile; lane l lands at chunk
@@ -119,9 +119,8 @@ void attn_duo_kernel(const AttnKernelArgs a)
     const unsigned vchunk = ((lane % CH) ^ ((vrow0 & (CH / 4 - 1)) << 2)) * 16;
     const unsigned kchunk = ((lane % KCH) ^ (krow0 & 7)) * 16;
     const unsigned voff = vrow0 * ROWB + vchunk, koff = krow0 * KROWB + kchunk;
-    const size_t kv_head = (size_t)b * a.Hkv + kvh;
-    const uint8_t *const kc = static_cast<const uint8_t *>(a.K) + kv_head * a.kv_stride * (size_t)KROWB;
-    const uint8_t *const vc = static_cast<const uint8_t *>(a.V) + kv_head * a.kv_stride * (size_t)ROWB;
+    const uint8_t *const kc = h.K + kv_head * h.kv_stride * (size_t)KROWB;
+    const uint8_t *const vc = h.V + kv_head * h.kv_stride * (size_t)ROWB;
     const uint8_t *const kb_ = blen ? static_cast<const uint8_t *>(a.Kblk) + kv_head * blen * (size_t)KROWB : nullptr;
     const uint8_t *const vb_ = blen ? static_cast<const uint8_t *>(a.Vblk) + kv_head * blen * (size_t)ROWB : nullptr;
     const unsigned lds0 = (unsigned)(size_t)(__attribute__((address_space(3))) void *)KV;
@@ -180,11 +179,11 @@ void attn_duo_kernel(const AttnKernelArgs a)
     const bool row_ok = v < rows_total;
     // ---- prologue: this wave's scales and the workgroup's Q rows (these pass through the last ring slot), then RING - 1 tiles
     if (a.q_scale)
-        load4_at((unsigned)(size_t)(__attribute__((address_space(3))) void *)qs_sh + wave * 256, a.q_scale + b * a.H + kvh * a.group + min(v, rows_total - 1) / a.Nq);
+        load4_at((unsigned)(size_t)(__attribute__((address_space(3))) void *)qs_sh + wave * 256, a.q_scale + kv_head * a.group + min(v, rows_total - 1) / a.Nq);
 #pragma unroll
     for (int i = 0; i < NQ; ++i) {
         const int r = min(v_tile + i * kDuoWaves * KDMA_ROWS + krow0, rows_total - 1);
-        load_at(lds0 + (RING - 1) * SLOTB + (i * kDuoWaves + wave) * 1024, static_cast<const uint8_t *>(a.Q) + (row_base + r) * KROWB + kchunk);
+        load_at(lds0 + (RING - 1) * SLOTB + (i * kDuoWaves + wave) * 1024, h.Q + (row_base + r) * KROWB + kchunk);
     }
 #pragma unroll
     for (int t = 0; t < RING - 1; ++t) {
@@ -403,7 +402,7 @@ void attn_duo_kernel(const AttnKernelArgs a)
         }
     // ---- output: group g of this wave is dims 8 (ph GP + g) + 4 hh .. + 3 of query row l32
     const size_t orow = row_base + v;
-    if (a.splits == 1) {
+    if (h.splits == 1) {
         const float inv = 1.0f / l_tot;
         uint16_t *out = static_cast<uint16_t *>(a.O) + orow * D;
         static_assert(GP % 2 == 0, "groups are stored in pairs");
@@ -415,11 +414,11 @@ void attn_duo_kernel(const AttnKernelArgs a)
             if (row_ok) *reinterpret_cast<uint4 *>(out + 8 * (ph * GP + g + hh)) = make_uint4(x0.x, x1.x, x0.y, x1.y);
         }
     } else if (row_ok) {
-        float *po = a.part_o + (orow * a.splits + sp) * D;
+        float *po = a.part_o + (orow * h.splits + sp) * D;
 #pragma unroll
         for (int g = 0; g < GP; ++g) *reinterpret_cast<float4 *>(po + 8 * (ph * GP + g) + 4 * hh) = make_float4(o[g][0], o[g][1], o[g][2], o[g][3]);
         if (hh == 0 && ph == 0) {
-            float *ml = a.part_ml + (orow * a.splits + sp) * 2;
+            float *ml = a.part_ml + (orow * h.splits + sp) * 2;
             ml[0] = m_all;
             ml[1] = l_tot;
         }
@@ -435,9 +434,9 @@ hipError_t launch_duo(const AttnArgs &a, hipStream_t stream)
     k.wgs = (int)((long)a.B * a.Hkv * k.row_tiles * k.splits);
     const dim3 grid((unsigned)k.wgs), block(kDuoThreads);
     hipError_t e;
-    if (a.qk_dtype == 2) e = launch(attn_duo_kernel<128, true, R, RING8>, grid, block, stream, k);
-    else if (a.d == 128) e = launch(attn_duo_kernel<128, false, R, RING16>, grid, block, stream, k);
-    else                 e = launch(attn_duo_kernel<64, false, R, 4>, grid, block, stream, k);
+    if (a.qk_dtype == 2) e = launch_headed(attn_duo_kernel<128, true, R, RING8>, grid, block, stream, k);
+    else if (a.d == 128) e = launch_headed(attn_duo_kernel<128, false, R, RING16>, grid, block, stream, k);
+    else                 e = launch_headed(attn_duo_kernel<64, false, R, 4>, grid, block, stream, k);
     return e != hipSuccess ? e : finish_attention(a, k.splits, stream);
 }
 

@@ -35,7 +35,7 @@ __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_ex
 
 // RB: 16-row query blocks per workgroup
 template <int D, int RB>
-__device__ __forceinline__ void attn_f32(const AttnKernelArgs &a)
+__device__ __forceinline__ void attn_f32(const AttnHead &h, const AttnTail &a)
 {
     constexpr int NJ = D / 16;                      // 16-byte fragments of a Q / K row per lane
     constexpr int NH = D / 64;                      // ... of a V row
@@ -50,22 +50,21 @@ __device__ __forceinline__ void attn_f32(const AttnKernelArgs &a)
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l16 = lane & 15, g = lane >> 4;
-    int bid = blockIdx.x;
-    const int sp = bid % a.splits; bid /= a.splits;
-    const int rt = bid % a.row_tiles; bid /= a.row_tiles;
-    const int kvh = bid % a.Hkv;
-    const int b = bid / a.Hkv;
-    const int rows_total = a.group * a.Nq;          // query rows of this (batch, kv head): contiguous in memory
-    const size_t row_base = ((size_t)b * a.H + (size_t)kvh * a.group) * a.Nq;
+    unsigned bid = blockIdx.x;
+    int sp, rt;
+    place_of(bid, h.splits, sp);
+    place_of(bid, h.row_tiles, rt);
+    const size_t kv_head = bid;                     // batch and kv head; its query rows are contiguous in memory
+    const int rows_total = h.rows_total;
+    const size_t row_base = kv_head * rows_total;
 
-    const int k_begin = sp * a.keys_per_split;
-    const int k_end = min(a.N, k_begin + a.keys_per_split);
-    const size_t kv_head = (size_t)b * a.Hkv + kvh;
-    const int bstart = a.block_starts ? a.block_starts[b] : a.block_start;   // any value is safe: rows are chosen by range test
-    const float *const kc = static_cast<const float *>(a.K) + kv_head * a.kv_stride * D;
-    const float *const vc = static_cast<const float *>(a.V) + kv_head * a.kv_stride * D;
-    const float *const kb = a.Kblk ? static_cast<const float *>(a.Kblk) + kv_head * a.block_len * D : nullptr;
-    const float *const vb = a.Kblk ? static_cast<const float *>(a.Vblk) + kv_head * a.block_len * D : nullptr;
+    const int k_begin = sp * h.keys_per_split;
+    const int k_end = min(h.N, k_begin + h.keys_per_split);
+    const int bstart = a.block_starts ? uniform_load(a.block_starts + (unsigned)kv_head / (unsigned)a.Hkv) : h.block_start;   // any value is safe: rows are chosen by range test
+    const float *const kc = reinterpret_cast<const float *>(h.K) + kv_head * h.kv_stride * D;
+    const float *const vc = reinterpret_cast<const float *>(h.V) + kv_head * h.kv_stride * D;
+    const float *const kb = h.block_len ? static_cast<const float *>(a.Kblk) + kv_head * h.block_len * D : nullptr;       // (length 0: no block)
+    const float *const vb = h.block_len ? static_cast<const float *>(a.Vblk) + kv_head * h.block_len * D : nullptr;
 
     floatx4 qf[RB][NJ], acc[RB][NO], kf[2][NJ], vf[2][4][NH];
     float c[RB], m_run[RB], l_run[RB];
@@ -74,7 +73,7 @@ __device__ __forceinline__ void attn_f32(const AttnKernelArgs &a)
         const int j0 = k_begin + u * kUnitF;
         {
             const int j = min(j0 + l16, k_end - 1);
-            const bool in_blk = kb != nullptr && (unsigned)j - (unsigned)bstart < (unsigned)a.block_len;
+            const bool in_blk = (unsigned)j - (unsigned)bstart < (unsigned)h.block_len;
             const float *p = (in_blk ? kb + (size_t)(j - bstart) * D : kc + (size_t)j * D) + 4 * g;
 #pragma unroll
             for (int i = 0; i < NJ; ++i) k[i] = *reinterpret_cast<const floatx4 *>(p + 16 * i);
@@ -82,7 +81,7 @@ __device__ __forceinline__ void attn_f32(const AttnKernelArgs &a)
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             const int j = min(j0 + 4 * g + r, k_end - 1);
-            const bool in_blk = kb != nullptr && (unsigned)j - (unsigned)bstart < (unsigned)a.block_len;
+            const bool in_blk = (unsigned)j - (unsigned)bstart < (unsigned)h.block_len;
             const float *p = (in_blk ? vb + (size_t)(j - bstart) * D : vc + (size_t)j * D) + 4 * l16;
 #pragma unroll
             for (int h = 0; h < NH; ++h) v[r][h] = *reinterpret_cast<const floatx4 *>(p + 64 * h);
@@ -93,11 +92,11 @@ __device__ __forceinline__ void attn_f32(const AttnKernelArgs &a)
 #pragma unroll
     for (int q = 0; q < RB; ++q) {
         const int v = min((rt * RB + q) * 16 + l16, rows_total - 1);
-        const float *p = static_cast<const float *>(a.Q) + (row_base + v) * D + 4 * g;
+        const float *p = reinterpret_cast<const float *>(h.Q) + (row_base + v) * D + 4 * g;
 #pragma unroll
         for (int i = 0; i < NJ; ++i) qf[q][i] = *reinterpret_cast<const floatx4 *>(p + 16 * i);
         c[q] = a.scale_log2;
-        if (a.q_scale) c[q] *= a.q_scale[b * a.H + kvh * a.group + v / a.Nq];
+        if (a.q_scale) c[q] *= a.q_scale[kv_head * a.group + v / a.Nq];
         if (a.k_scale) c[q] *= a.k_scale[kv_head];
         m_run[q] = -INFINITY;
         l_run[q] = 0.f;
@@ -201,37 +200,37 @@ __device__ __forceinline__ void attn_f32(const AttnKernelArgs &a)
         }
         const size_t orow = row_base + row;
         const int dim = (piece / 4) * 64 + (ln >> 4) * 16 + (piece & 3) * 4;
-        if (a.splits == 1) {
+        if (h.splits == 1) {
             const float inv = 1.0f / l;
 #pragma unroll
             for (int r = 0; r < 4; ++r) o[r] *= inv;
             *reinterpret_cast<floatx4 *>(static_cast<float *>(a.O) + orow * D + dim) = o;
         } else {
-            *reinterpret_cast<floatx4 *>(a.part_o + (orow * a.splits + sp) * D + dim) = o;
+            *reinterpret_cast<floatx4 *>(a.part_o + (orow * h.splits + sp) * D + dim) = o;
             if (dim == 0) {
-                a.part_ml[(orow * a.splits + sp) * 2] = m;
-                a.part_ml[(orow * a.splits + sp) * 2 + 1] = l;
+                a.part_ml[(orow * h.splits + sp) * 2] = m;
+                a.part_ml[(orow * h.splits + sp) * 2 + 1] = l;
             }
         }
     }
 }
 
 template <int D, int RB>
-__global__ __launch_bounds__(kThreadsF) void attn_f32_kernel(const AttnKernelArgs a)
+__global__ __launch_bounds__(kThreadsF) void attn_f32_kernel(DD_ATTN_HEAD, const AttnTail a)
 {
-    attn_f32<D, RB>(a);
+    attn_f32<D, RB>(DD_ATTN_HEAD_ARGS, a);
 }
 
 // The same launch with the block-completion copy on the workgroups past the attending ones: for a call without key splits, which has no
 // merge launch to take it along (a launch of its own for it: 61.8 us per cycle of 4 heads and 128 keys, here 58.5).
 template <int D, int RB>
-__global__ __launch_bounds__(kThreadsF) void attn_f32_refresh_kernel(const AttnKernelArgs a, const RefreshArgs r)
+__global__ __launch_bounds__(kThreadsF) void attn_f32_refresh_kernel(DD_ATTN_HEAD, const AttnTail a, const RefreshArgs r)
 {
-    if ((int)blockIdx.x >= r.first_wg) {            // uniform: these only copy
+    if ((int)blockIdx.x >= wgs) {            // uniform: these only copy
         refresh_cache_rows<kThreadsF>(r);
         return;
     }
-    attn_f32<D, RB>(a);
+    attn_f32<D, RB>(DD_ATTN_HEAD_ARGS, a);
 }
 
 }  // namespace
@@ -251,19 +250,19 @@ hipError_t launch_attention_f32(const AttnArgs &a, hipStream_t stream)
     const long most = a.N / kSplitKeys < 256 / wgs ? a.N / kSplitKeys : 256 / wgs;
     if (s.splits > most) s.splits = most > 1 ? (int)most : 1;
     fill_kernel_args(s, k, rows_per_wg, kUnitF);
-    const long attending = heads * k.row_tiles * k.splits;
+    k.wgs = (int)(heads * k.row_tiles * k.splits);
     const dim3 block(kThreadsF);
     RefreshArgs r{};
     const long copy_wgs = k.splits == 1 ? fill_refresh(s, r, kCopyWgs) : 0;
     if (copy_wgs > 0) {
-        r.first_wg = (int)attending;
-        const dim3 grid((unsigned)(attending + copy_wgs));
-        return a.d == 128 ? launch(attn_f32_refresh_kernel<128, 1>, grid, block, stream, k, r)
-             : two ? launch(attn_f32_refresh_kernel<64, 2>, grid, block, stream, k, r) : launch(attn_f32_refresh_kernel<64, 1>, grid, block, stream, k, r);
+        r.first_wg = k.wgs;
+        const dim3 grid((unsigned)(k.wgs + copy_wgs));
+        return a.d == 128 ? launch_headed(attn_f32_refresh_kernel<128, 1>, grid, block, stream, k, r)
+             : two ? launch_headed(attn_f32_refresh_kernel<64, 2>, grid, block, stream, k, r) : launch_headed(attn_f32_refresh_kernel<64, 1>, grid, block, stream, k, r);
     }
-    const dim3 grid((unsigned)attending);
-    const hipError_t e = a.d == 128 ? launch(attn_f32_kernel<128, 1>, grid, block, stream, k)
-                       : two ? launch(attn_f32_kernel<64, 2>, grid, block, stream, k) : launch(attn_f32_kernel<64, 1>, grid, block, stream, k);
+    const dim3 grid((unsigned)k.wgs);
+    const hipError_t e = a.d == 128 ? launch_headed(attn_f32_kernel<128, 1>, grid, block, stream, k)
+                       : two ? launch_headed(attn_f32_kernel<64, 2>, grid, block, stream, k) : launch_headed(attn_f32_kernel<64, 1>, grid, block, stream, k);
     return e != hipSuccess ? e : finish_attention(s, k.splits, stream);
 }
 

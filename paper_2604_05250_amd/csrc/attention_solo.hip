@@ -56,12 +56,6 @@ __device__ __forceinline__ const uint8_t *solo_scalar(const uint8_t *p)         
     const unsigned lo = __builtin_amdgcn_readfirstlane((unsigned)v), hi = __builtin_amdgcn_readfirstlane((unsigned)(v >> 32));
     return reinterpret_cast<const uint8_t *>(((unsigned long long)hi << 32) | lo);
 }
-// A value at a uniform address that no workgroup writes, by a scalar load.  (After a statement that may write memory the compiler takes a
-// vector load instead, and waits for every load before it.)
-template <typename T> __device__ __forceinline__ T solo_uniform(const T *p)
-{
-    return *(__attribute__((address_space(4))) const T *)(unsigned long long)p;
-}
 __device__ __forceinline__ uint4 solo_decode(unsigned w0, unsigned w1)           // eight e4m3 codes to bf16, exactly
 {
     return make_uint4(__builtin_bit_cast(unsigned, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(w0, 1.0f, false)),
@@ -77,29 +71,11 @@ template <int I, int N, typename F> __device__ __forceinline__ void static_for(F
     }
 }
 
-// What a launch passes.  The first loads need the first fourteen words only, which the hardware has put in registers when a wave starts
-// (the build asks for it: kernels whose arguments are scalars); the rest arrives while those loads are on their way.
-struct SoloArgs {
-    const void *Kblk, *Vblk;
-    void *O;
-    float *part_o, *part_ml;
-    const float *q_scale, *k_scale, *v_scale;
-    const int32_t *block_starts;
-    int Hkv, Nq, group;
-    float scale_log2;
-};
-struct SoloHead {                                    // (the same, in one piece for the kernel's body)
-    const uint8_t *Q, *K, *V;
-    int rows_total, N, kv_stride, keys_per_split, wgs;
-    int row_tiles, splits;
-    int block_start, block_len;
-};
-
 // V8: V is stored as e4m3 codes.  They travel to LDS as they are and the wave decodes its own 4 KB into its V buffer, exactly, when
 // they arrive (32 conversions of two elements per lane and unit); v_scale multiplies the result once.
 // RB row blocks per workgroup, VP parts of the head dims, NW waves.
 template <int D, bool FP8, bool V8, int RB, int VP, int NW>
-__device__ __forceinline__ void attn_solo(const SoloHead &h, const SoloArgs &a)
+__device__ __forceinline__ void attn_solo(const AttnHead &h, const AttnTail &a)
 {
     // (device pass only: the host pass needs the kernels' handles, not assembly it cannot check)
 #if defined(__HIP_DEVICE_COMPILE__)
@@ -135,16 +111,16 @@ __device__ __forceinline__ void attn_solo(const SoloHead &h, const SoloArgs &a)
     const int l32 = lane & 31, hh = lane >> 5;
 
     // ---- which (batch, kv head, row tile, key split); same XCD for workgroups that share K/V
-    int bid = blockIdx.x;
+    unsigned bid = blockIdx.x;
     {
-        const int total = h.wgs, per = total >> 3, rem = total & 7;
-        const int xcd = bid & 7, slot = bid >> 3;
+        const unsigned total = h.wgs, per = total >> 3, rem = total & 7;
+        const unsigned xcd = bid & 7, slot = bid >> 3;
         bid = xcd * per + min(xcd, rem) + slot;
     }
     const int part = bid % VP; bid /= VP;
-    int rt = 0, sp = 0;                              // (a division is some 150 cycles before the first load)
-    if (h.row_tiles > 1) { rt = bid % h.row_tiles; bid /= h.row_tiles; }
-    if (h.splits > 1) { sp = bid % h.splits; bid /= h.splits; }
+    int rt, sp;
+    place_of(bid, h.row_tiles, rt);
+    place_of(bid, h.splits, sp);
     const size_t kv_head = bid;                      // batch and kv head
     const int rows_total = h.rows_total;             // query rows of this (batch, kv head): contiguous in memory
     const int v_first = rt * 32 * RB;
@@ -162,7 +138,7 @@ __device__ __forceinline__ void attn_solo(const SoloHead &h, const SoloArgs &a)
 
     const int kbeg = sp * h.keys_per_split;
     const int kend = min(h.N, kbeg + h.keys_per_split);
-    const int bstart = a.block_starts ? solo_uniform(a.block_starts + (unsigned)kv_head / (unsigned)a.Hkv) : h.block_start;        // any value is safe: rows are chosen by range test
+    const int bstart = a.block_starts ? uniform_load(a.block_starts + (unsigned)kv_head / (unsigned)a.Hkv) : h.block_start;        // any value is safe: rows are chosen by range test
     const int blen = h.block_len;
     const int nunits = (kend - kbeg + U - 1) / U;
     const int whole = (kend - kbeg) / U;             // units [0, whole) hold 32 rows of the range
@@ -225,7 +201,7 @@ __device__ __forceinline__ void attn_solo(const SoloHead &h, const SoloArgs &a)
     const std::false_type of_v;
 
     // ---- the rest of the prologue: the query rows' scales, this wave's first unit
-    const float k_scale = a.k_scale ? solo_uniform(a.k_scale + kv_head) : 1.0f;
+    const float k_scale = a.k_scale ? uniform_load(a.k_scale + kv_head) : 1.0f;
     // (through LDS like the rows: the compiler's own wait for a load of its own would wait for every load after it as well)
     if (a.q_scale && wave == 0) {
         const float *const src = a.q_scale + kv_head * a.group + min(v_first + (RB == 2 ? lane : l32), rows_total - 1) / a.Nq;
@@ -483,7 +459,7 @@ __device__ __forceinline__ void attn_solo(const SoloHead &h, const SoloArgs &a)
             }
         }
     if constexpr (V8) {
-        const float vs = solo_uniform(a.v_scale + kv_head);         // the decoded values times this are the real ones
+        const float vs = uniform_load(a.v_scale + kv_head);         // the decoded values times this are the real ones
 #pragma unroll
         for (int g = 0; g < GP; ++g)
 #pragma unroll
@@ -520,49 +496,38 @@ __device__ __forceinline__ void attn_solo(const SoloHead &h, const SoloArgs &a)
 #endif
 }
 
-#define DD_SOLO_HEAD const uint8_t *Q, const uint8_t *K, const uint8_t *V, int rows_total, int N, int kv_stride, int keys_per_split, int wgs, \
-                     int tiles_splits, int block_start, int block_len
 template <int D, bool FP8, bool V8, int RB, int VP, int NW>
-__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_solo_kernel(DD_SOLO_HEAD, const SoloArgs a)
+__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_solo_kernel(DD_ATTN_HEAD, const AttnTail a)
 {
-    attn_solo<D, FP8, V8, RB, VP, NW>(SoloHead{Q, K, V, rows_total, N, kv_stride, keys_per_split, wgs, tiles_splits >> 8, tiles_splits & 255, block_start,
-                                               block_len}, a);
+    attn_solo<D, FP8, V8, RB, VP, NW>(DD_ATTN_HEAD_ARGS, a);
 }
 
 // The same launch with the block-completion copy on the workgroups past the attending ones: for a call without key splits, which has no
 // merge launch to take it along.
 template <int D, bool FP8, bool V8, int RB, int VP, int NW>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2)))
-void attn_solo_refresh_kernel(DD_SOLO_HEAD, const SoloArgs a, const RefreshArgs r)
+void attn_solo_refresh_kernel(DD_ATTN_HEAD, const AttnTail a, const RefreshArgs r)
 {
     if ((int)blockIdx.x >= wgs) {                            // uniform: these only copy
         refresh_cache_rows<64 * NW>(r);
         return;
     }
-    attn_solo<D, FP8, V8, RB, VP, NW>(SoloHead{Q, K, V, rows_total, N, kv_stride, keys_per_split, wgs, tiles_splits >> 8, tiles_splits & 255, block_start,
-                                               block_len}, a);
+    attn_solo<D, FP8, V8, RB, VP, NW>(DD_ATTN_HEAD_ARGS, a);
 }
-#undef DD_SOLO_HEAD
 
 template <int D, bool FP8, bool V8, int RB, int VP, int NW> hipError_t launch_solo(const AttnArgs &a, hipStream_t stream)
 {
     AttnKernelArgs k;
     fill_kernel_args(a, k, 32 * RB, 32);
-    const long wgs = (long)a.B * a.Hkv * k.row_tiles * k.splits * VP;
-    if (k.row_tiles >= 1 << 23 || k.splits > 255 || wgs > 0x7FFFFFFF) return hipErrorInvalidValue;   // (rows of a kv head: below 2^28; splits: at most 16)
+    k.wgs = (int)((long)a.B * a.Hkv * k.row_tiles * k.splits * VP);
     const dim3 block(64 * NW);
-    const uint8_t *const Q = static_cast<const uint8_t *>(a.Q), *const K = static_cast<const uint8_t *>(a.K), *const V = static_cast<const uint8_t *>(a.V);
-    const SoloArgs s{a.Kblk, a.Vblk, a.O, k.part_o, k.part_ml, a.q_scale, a.k_scale, a.v_scale, a.block_starts, a.Hkv, a.Nq, k.group, k.scale_log2};
-    const int rows_total = k.group * a.Nq, tiles_splits = k.row_tiles << 8 | k.splits;
     RefreshArgs r{};
     const long copy_wgs = k.splits == 1 ? fill_refresh(a, r, kCopyWgs) : 0;
     if (copy_wgs > 0) {
-        r.first_wg = (int)wgs;
-        return launch(attn_solo_refresh_kernel<D, FP8, V8, RB, VP, NW>, dim3((unsigned)(wgs + copy_wgs)), block, stream, Q, K, V, rows_total, k.N,
-                      k.kv_stride, k.keys_per_split, (int)wgs, tiles_splits, k.block_start, k.block_len, s, r);
+        r.first_wg = k.wgs;
+        return launch_headed(attn_solo_refresh_kernel<D, FP8, V8, RB, VP, NW>, dim3((unsigned)(k.wgs + copy_wgs)), block, stream, k, r);
     }
-    const hipError_t e = launch(attn_solo_kernel<D, FP8, V8, RB, VP, NW>, dim3((unsigned)wgs), block, stream, Q, K, V, rows_total, k.N, k.kv_stride,
-                                k.keys_per_split, (int)wgs, tiles_splits, k.block_start, k.block_len, s);
+    const hipError_t e = launch_headed(attn_solo_kernel<D, FP8, V8, RB, VP, NW>, dim3((unsigned)k.wgs), block, stream, k);
     return e != hipSuccess ? e : finish_attention(a, k.splits, stream);
 }
 // `form`: row blocks, parts, waves as decimal digits.  (Each storage type has the forms that win somewhere for it: kSoloCosts.)

@@ -73,8 +73,9 @@ constexpr int waitcnt_vm(int n) { return (n & 15) | ((n >> 4) << 14) | (7 << 4) 
 // -> 21.6 (4.9 TB/s); 16 x 32, 64 rows, 4096 keys 164.9 -> 149.7 (5.4 TB/s).
 template <int D, bool NT, bool FP8>
 __global__ __launch_bounds__(kAttnThreads) __attribute__((amdgpu_waves_per_eu(FP8 ? 2 : 1, FP8 ? 2 : 1)))
-void attn_stream_kernel(const AttnKernelArgs a)
+void attn_stream_kernel(DD_ATTN_HEAD, const AttnTail a)
 {
+    const AttnHead h = DD_ATTN_HEAD_ARGS;
     constexpr int CH = D / 8;                        // 16-byte chunks (8 bf16) per row
     constexpr int KS = D / 16;                       // MFMA k-steps over the head dim
     constexpr int DC = D / 32;                       // 32-wide chunks of the head dim
@@ -102,23 +103,22 @@ void attn_stream_kernel(const AttnKernelArgs a)
     const int rg = wave & 1, ph = wave >> 1;         // row block, key phase
 
     // ---- which (batch, kv head, row tile, key split); same XCD for workgroups that share K/V
-    int bid = blockIdx.x;
+    unsigned bid = blockIdx.x;
     {
-        const int total = a.wgs, per = total >> 3, rem = total & 7;
-        const int xcd = bid & 7, slot = bid >> 3;
+        const unsigned total = h.wgs, per = total >> 3, rem = total & 7;
+        const unsigned xcd = bid & 7, slot = bid >> 3;
         bid = xcd * per + min(xcd, rem) + slot;
     }
-    const int sp = bid % a.splits; bid /= a.splits;
-    const int rt = bid % a.row_tiles; bid /= a.row_tiles;
-    const int kvh = bid % a.Hkv;
-    const int b = bid / a.Hkv;
-    const int rows_total = a.group * a.Nq;           // query rows of this (batch, kv head): contiguous in memory
-    const int v_first = rt * a.rows_per_wg + rg * kRowsWaveS;   // rows_per_wg = 64
+    int sp, rt;
+    place_of(bid, h.splits, sp);
+    place_of(bid, h.row_tiles, rt);
+    const size_t kv_head = bid;                      // batch and kv head; its query rows are contiguous in memory
+    const int v_first = rt * 2 * kRowsWaveS + rg * kRowsWaveS;
     const bool wave_active = v_first < rows_total;
-    const size_t row_base = ((size_t)b * a.H + (size_t)kvh * a.group) * a.Nq;
-    const int kbeg = sp * a.keys_per_split;
-    const int kend = min(a.N, kbeg + a.keys_per_split);
-    const int bstart = a.block_starts ? a.block_starts[b] : a.block_start;   // any value is safe: rows are chosen by range test
+    const size_t row_base = kv_head * rows_total;
+    const int kbeg = sp * h.keys_per_split;
+    const int kend = min(h.N, kbeg + h.keys_per_split);
+    const int bstart = a.block_starts ? uniform_load(a.block_starts + (unsigned)kv_head / (unsigned)a.Hkv) : h.block_start;   // any value is safe: rows are chosen by range test
     const int ntiles = (kend - kbeg + TKS - 1) / TKS;
 
     // ---- staging by LDS DMA: load i of this wave moves rows (4i + wave) * DMA_ROWS .. of a tile; lane l
@@ -128,11 +128,10 @@ void attn_stream_kernel(const AttnKernelArgs a)
     const int kdma_row0 = wave * KDMA_ROWS + lane / KCH;
     const unsigned dma_koff = (lane % KCH ^ (kdma_row0 & 7)) * 16;
     const unsigned dma_voff = (dma_pos ^ ((dma_row0 & (CH / 4 - 1)) << 2)) * 16;
-    const size_t kv_head = (size_t)b * a.Hkv + kvh;
-    const uint8_t *const kc = static_cast<const uint8_t *>(a.K) + kv_head * a.kv_stride * (size_t)KROWB;
-    const uint8_t *const vc = static_cast<const uint8_t *>(a.V) + kv_head * a.kv_stride * (size_t)ROWB;
-    const uint8_t *const kb_ = a.block_len ? static_cast<const uint8_t *>(a.Kblk) + kv_head * a.block_len * (size_t)KROWB : nullptr;
-    const uint8_t *const vb_ = a.block_len ? static_cast<const uint8_t *>(a.Vblk) + kv_head * a.block_len * (size_t)ROWB : nullptr;
+    const uint8_t *const kc = h.K + kv_head * h.kv_stride * (size_t)KROWB;
+    const uint8_t *const vc = h.V + kv_head * h.kv_stride * (size_t)ROWB;
+    const uint8_t *const kb_ = h.block_len ? static_cast<const uint8_t *>(a.Kblk) + kv_head * h.block_len * (size_t)KROWB : nullptr;
+    const uint8_t *const vb_ = h.block_len ? static_cast<const uint8_t *>(a.Vblk) + kv_head * h.block_len * (size_t)ROWB : nullptr;
     // rows of the last tile at or past the end of the key range repeat its last row (finite stand-ins, masked later)
     auto dma_tile = [&](int tile) __attribute__((always_inline)) {
         uint4 *kd = KV + (tile % kRing) * (TKS * KCH), *vd = KV + kRing * TKS * KCH + (tile % kRing) * (TKS * CH);
@@ -140,13 +139,13 @@ void attn_stream_kernel(const AttnKernelArgs a)
         for (int i = 0; i < NDMA; ++i) {
             if (i < KDMA) {
                 const int j = min(kbeg + tile * TKS + i * 4 * KDMA_ROWS + kdma_row0, kend - 1);
-                const bool in_blk = (unsigned)j - (unsigned)bstart < (unsigned)a.block_len;
+                const bool in_blk = (unsigned)j - (unsigned)bstart < (unsigned)h.block_len;
                 const uint8_t *ks = (in_blk ? kb_ : kc) + (size_t)(in_blk ? j - bstart : j) * KROWB + dma_koff;
                 __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)ks,
                                                  (__attribute__((address_space(3))) void *)(kd + (i * 4 + wave) * 64), 16, 0, NT ? 2 : 0);
             }
             const int j = min(kbeg + tile * TKS + i * 4 * DMA_ROWS + dma_row0, kend - 1);
-            const bool in_blk = (unsigned)j - (unsigned)bstart < (unsigned)a.block_len;
+            const bool in_blk = (unsigned)j - (unsigned)bstart < (unsigned)h.block_len;
             const uint8_t *vs = (in_blk ? vb_ : vc) + (size_t)(in_blk ? j - bstart : j) * ROWB + dma_voff;
             __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)vs,
                                              (__attribute__((address_space(3))) void *)(vd + (i * 4 + wave) * 64), 16, 0, NT ? 2 : 0);
@@ -164,7 +163,7 @@ void attn_stream_kernel(const AttnKernelArgs a)
         row_ok[q] = v < rows_total;
         const int vv = row_ok[q] ? v : rows_total - 1;
         if constexpr (FP8) {
-            const uint8_t *qrow = static_cast<const uint8_t *>(a.Q) + (row_base + vv) * D + 16 * hh;
+            const uint8_t *qrow = h.Q + (row_base + vv) * D + 16 * hh;
 #pragma unroll
             for (int j = 0; j < D / 64; ++j) {
                 const uint4 lo = *reinterpret_cast<const uint4 *>(qrow + 64 * j), hi = *reinterpret_cast<const uint4 *>(qrow + 64 * j + 32);
@@ -174,13 +173,13 @@ void attn_stream_kernel(const AttnKernelArgs a)
 #pragma unroll
             for (int ks = 0; ks < KS; ++ks)
                 qf[q][ks] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4 *>(
-                                static_cast<const uint16_t *>(a.Q) + (row_base + vv) * D + ks * 16 + hh * 8));
+                                reinterpret_cast<const uint16_t *>(h.Q) + (row_base + vv) * D + ks * 16 + hh * 8));
         }
         c[q] = 1.0f;
-        if (a.q_scale) c[q] = a.q_scale[b * a.H + kvh * a.group + vv / a.Nq];
+        if (a.q_scale) c[q] = a.q_scale[kv_head * a.group + vv / a.Nq];
     }
     float k_scale = 1.0f;
-    if (a.k_scale) k_scale = a.k_scale[b * a.Hkv + kvh];
+    if (a.k_scale) k_scale = uniform_load(a.k_scale + kv_head);
     __builtin_amdgcn_sched_barrier(0);               // these loads are requested before the first tiles ...
     // (a tile past the range repeats its last row)
 #pragma unroll
@@ -399,7 +398,7 @@ void attn_stream_kernel(const AttnKernelArgs a)
     for (int q = 0; q < QBS; ++q) {
         if (!row_ok[q]) continue;
         const size_t orow = row_base + v_first + q * 32 + l32;
-        if (a.splits == 1) {
+        if (h.splits == 1) {
             const float inv = 1.0f / l_tot[q];
             uint16_t *o = static_cast<uint16_t *>(a.O) + orow * D;
 #pragma unroll
@@ -411,7 +410,7 @@ void attn_stream_kernel(const AttnKernelArgs a)
                     *reinterpret_cast<uint2 *>(o + i * 32 + q4 * 8 + hh * 4) = w;
                 }
         } else {
-            float *po = a.part_o + (orow * a.splits + sp) * D;
+            float *po = a.part_o + (orow * h.splits + sp) * D;
 #pragma unroll
             for (int i = 0; i < DC; ++i)
 #pragma unroll
@@ -419,7 +418,7 @@ void attn_stream_kernel(const AttnKernelArgs a)
                     *reinterpret_cast<float4 *>(po + i * 32 + q4 * 8 + hh * 4) =
                         make_float4(acc[q][i][4 * q4], acc[q][i][4 * q4 + 1], acc[q][i][4 * q4 + 2], acc[q][i][4 * q4 + 3]);
             if (hh == 0) {
-                float *ml = a.part_ml + (orow * a.splits + sp) * 2;
+                float *ml = a.part_ml + (orow * h.splits + sp) * 2;
                 ml[0] = mc[q];
                 ml[1] = l_tot[q];
             }
@@ -449,9 +448,9 @@ hipError_t launch_attention_stream(const AttnArgs &a, hipStream_t stream)
     const bool fp8 = a.qk_dtype == 2;
     const bool nt = tune("DD_TUNE_STREAM_NT", a.Nq != a.N && (fp8 ? 3.0 : 4.0) * a.B * a.Hkv * a.N * a.d > kStreamPastCacheBytes) != 0;
     hipError_t e;
-    if (fp8)             e = nt ? launch(attn_stream_kernel<128, true, true>, grid, block, stream, k) : launch(attn_stream_kernel<128, false, true>, grid, block, stream, k);
-    else if (a.d == 128) e = nt ? launch(attn_stream_kernel<128, true, false>, grid, block, stream, k) : launch(attn_stream_kernel<128, false, false>, grid, block, stream, k);
-    else                 e = nt ? launch(attn_stream_kernel<64, true, false>, grid, block, stream, k) : launch(attn_stream_kernel<64, false, false>, grid, block, stream, k);
+    if (fp8)             e = nt ? launch_headed(attn_stream_kernel<128, true, true>, grid, block, stream, k) : launch_headed(attn_stream_kernel<128, false, true>, grid, block, stream, k);
+    else if (a.d == 128) e = nt ? launch_headed(attn_stream_kernel<128, true, false>, grid, block, stream, k) : launch_headed(attn_stream_kernel<128, false, false>, grid, block, stream, k);
+    else                 e = nt ? launch_headed(attn_stream_kernel<64, true, false>, grid, block, stream, k) : launch_headed(attn_stream_kernel<64, false, false>, grid, block, stream, k);
     return e != hipSuccess ? e : finish_attention(a, k.splits, stream);
 }
 

@@ -58,7 +58,7 @@ def build_binding(verbose: bool = False) -> str:
     cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
            f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}"]
     cmd += [x for d in inc for x in ("-isystem", d)] + ["-o", BINDING, BINDING_SOURCE, "-L" + _HERE, "-l:" + os.path.basename(LIB)]
-    cmd += ["-L" + lib, "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python", "-lamdhip64", "-Wl,-rpath,$ORIGIN"]
+    cmd += ["-L" + lib, "-lc10", "-lc10_hip", "-ltorch_hip", "-ltorch_cpu", "-ltorch_python", "-lamdhip64", "-Wl,-rpath,$ORIGIN"]
     if verbose:
         print(" ".join(cmd), flush=True)
     res = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)

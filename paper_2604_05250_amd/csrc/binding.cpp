@@ -15,6 +15,7 @@
 #include <Python.h>
 
 #include <ATen/ATen.h>
+#include <ATen/hip/EmptyTensor.h>
 #include <c10/hip/HIPGraphsC10Utils.h>
 #include <c10/hip/HIPStream.h>
 #include <torch/csrc/Exceptions.h>
@@ -247,7 +248,7 @@ template <typename F> int unlocked(F &&f)                     // the library cal
 
 at::Tensor empty_like_type(at::IntArrayRef shape, at::ScalarType type, const at::Tensor &on)
 {
-    return at::empty(shape, at::TensorOptions().dtype(type).device(on.device()));
+    return at::detail::empty_cuda(shape, type, on.device(), std::nullopt);
 }
 
 void want(Py_ssize_t got, Py_ssize_t n)

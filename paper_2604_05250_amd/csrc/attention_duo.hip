@@ -213,7 +213,7 @@ void attn_duo_kernel(DD_ATTN_HEAD, const AttnTail a)
         qf[f] = *reinterpret_cast<const intx4 *>(lds + (RING - 1) * SLOTB + rg * 32 * KROWB + k_off[f]);
     float c = a.scale_log2;                          // scores are exponentiated as 2^(s*c)
     if (a.q_scale) c *= qs_sh[wave][lane];
-    if (a.k_scale) c *= a.k_scale[kv_head];
+    if (a.k_scale) c *= uniform_load(a.k_scale + kv_head);
 
     floatx16 acc[DC];                                // O^T, unnormalised
 #pragma unroll

@@ -281,6 +281,7 @@ void attn_wide_kernel(const AttnKernelArgs a)
     __shared__ uint4 QO[4 * QOW / 16];
     __shared__ uint4 R0[VDEC ? TKW * VSCH : 1], R1[VDEC ? TKW * VSCH : 1];          // stored V tiles [key][chunk]
     __shared__ unsigned KX0[MX ? TKW : 1], KX1[MX ? TKW : 1], VX0[MX ? TKW : 1], VX1[MX ? TKW : 1];   // a tile's scale words
+    __shared__ unsigned QX[MX ? 256 : 1];            // per wave: the scale words of the next tile's query rows
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -445,6 +446,10 @@ void attn_wide_kernel(const AttnKernelArgs a)
         int ln = lane;
         asm volatile("" : "+v"(ln));
         const int drow = ln / KCH, dpos = ln % KCH;
+        if constexpr (MX) {
+            const uint8_t *src = a.q_mx + (t.row_base + min(t.v0 + wave * kRowsWave + (ln & (kRowsWave - 1)), rows_total - 1)) * 4;
+            asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dword %1, off" : : "s"(lds_addr(QX) + wave * 256), "v"(src) : "memory", "m0");
+        }
         if (__builtin_expect(t.v0 + kRowsWG <= rows_total, 1)) {
             // whole tile: 1 KB per load, contiguous on both sides - scalar bases 8 KB apart and immediates;
             // the chunk a lane fetches depends on the row modulo 8, hence on the parity of a 4-row load
@@ -665,6 +670,21 @@ void attn_wide_kernel(const AttnKernelArgs a)
         int ln = lane;
         asm volatile("" : "+v"(ln));
         intx4 q_half = {0, 0, 0, 0};
+        // The scores' factor (it takes effect with the tile's first score block).  A wave's rows are of one query head unless a head ends
+        // among them: one division and scalar loads then, on their way while the fragments are read, where 64 divisions and a vector
+        // load made a wave wait for memory once more per row tile (us: 8 x 32/8 heads, 777 keys fp8 91.0 -> 90.5, 4 x 28/4, 1500 keys e4m3 V 109.3 -> 108.8; block-scaled rows have their scale words in LDS with the
+        // rows: 16 x 32/8, 2048 keys 760 -> 751).
+        float c_tile = a.scale_log2, ks_tile = 1.0f;
+        bool one_head = true;
+        if constexpr (!MX) {
+            if (a.q_scale) {
+                const int w0 = min(t.v0 + wave * kRowsWave, rows_total - 1), w1 = min(t.v0 + wave * kRowsWave + kRowsWave, rows_total) - 1;
+                const int head = __builtin_amdgcn_readfirstlane(w0 / a.Nq);
+                one_head = w1 - head * a.Nq < a.Nq;
+                c_tile *= uniform_load(a.q_scale + t.bh0 + head);
+            }
+            if (a.k_scale) ks_tile = uniform_load(a.k_scale + t.kvs);
+        }
 #pragma unroll
         for (int q = 0; q < QB; ++q) {
 #pragma unroll
@@ -696,12 +716,15 @@ void attn_wide_kernel(const AttnKernelArgs a)
                     asm volatile("" : "+a"(qf[q][f]));
                 }
             }
-            const int v = min(t.v0 + wave * kRowsWave + q * 32 + (ln & 31), rows_total - 1);
-            c_next[q] = a.scale_log2;                        // takes effect with the tile's first score block
-            if (a.q_scale) c_next[q] *= a.q_scale[t.bh0 + v / a.Nq];
-            if (a.k_scale) c_next[q] *= a.k_scale[t.kvs];
-            if constexpr (MX)
-                qsw[q] = *reinterpret_cast<const unsigned *>(a.q_mx + (t.row_base + v) * 4) >> (8 * (ln >> 5));
+            c_next[q] = c_tile;
+            if constexpr (!MX) {
+                if (__builtin_expect(!one_head, 0)) {        // uniform
+                    const int v = min(t.v0 + wave * kRowsWave + q * 32 + (ln & 31), rows_total - 1);
+                    c_next[q] = a.scale_log2 * a.q_scale[t.bh0 + v / a.Nq];
+                }
+                c_next[q] *= ks_tile;
+            }
+            if constexpr (MX) qsw[q] = QX[wave * 64 + q * 32 + (ln & 31)] >> (8 * (ln >> 5));
         }
         // the matrix instructions written as assembly are invisible to the compiler's hazard padding:
         // keep them clear of the register writes above
@@ -1123,7 +1146,7 @@ void attn_wide_kernel(const AttnKernelArgs a)
         auto masked = [&]() __attribute__((always_inline)) {
             if constexpr (!last && (BLOCK || decltype(maskable)::value)) zero_masked_rows(vbuf(I_<1 - PAR>{}), cur, sp + 1);
         };
-        if (!BLOCK && KIND == 1 && has_next) wait_loads_and_sync(I_<NQDMA>{}, masked);
+        if (!BLOCK && KIND == 1 && has_next) wait_loads_and_sync(I_<NQDMA + (MX ? 1 : 0)>{}, masked);
         else if (last && cur.v0 + kRowsWG <= rows_total) {
             wait_loads_and_sync(I_<NST>{}, nothing);
         }

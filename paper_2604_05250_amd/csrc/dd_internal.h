@@ -40,6 +40,7 @@ inline hipError_t launch(void (*kernel)(Params...), dim3 grid, dim3 block, hipSt
 //                              (the hooks of the other kernels, and a drafter call's of the key splits, come first)
 //   DD_TUNE_SOLO_FORM=rpw      that kernel with r row blocks and w waves per workgroup, head dims in p parts, where the type has that form
 //   DD_TUNE_SEQ_ROUNDS=n       per-sequence rules on rows that are not split: in one launch up to n load rounds per workgroup
+//   DD_TUNE_VERIFY_FINE=n      verification: shortest row splits up to n workgroups (0: splits of whole load rounds)
 //   DD_TUNE_BLOCK_STREAM=0     drafter calls with few query rows off the streaming kernel
 //   DD_TUNE_BLOCK_WIDE=0       drafter calls with many query rows off the wide-wave kernel
 //   DD_TUNE_BLOCK_SPLITS=n     key splits of a drafter call on the streaming / MFMA kernels (still at least 128 keys each)

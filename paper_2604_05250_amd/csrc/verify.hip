@@ -286,24 +286,24 @@ __device__ __forceinline__ bool reduce_range(const uint4 *__restrict__ pv, const
         for (int u = 0; u < kUnroll; ++u)
             consume<BF16, KL, TRACKD>(rv[u], rd[u], true, (base + u * THREADS + tid) * E, st);
     }
-    // ragged remainder of the range
+    // Ragged remainder of the range: every load is issued (past the end, of the last vector) and the vectors that no lane of the wave
+    // has are not folded.  With loads under a lane's own condition the round was four round trips: 512 x 32000 KL 17.8 us, now 17.2;
+    // 128 x 32000 11.0 / 10.5; 1024 x 50264 confidence 21.9 / 21.1; 64 x 1024 fp32 KL 4.15 / 4.02.
     if (base < vend) {
         uint4 rv[kUnroll], rd[kUnroll];
-        bool ok[kUnroll];
 #pragma unroll
         for (int u = 0; u < kUnroll; ++u) {
-            const int idx = base + u * THREADS + tid;
-            ok[u] = idx < vend;
-            rv[u] = make_uint4(0, 0, 0, 0);
-            rd[u] = make_uint4(0, 0, 0, 0);
-            if (ok[u]) {
-                rv[u] = stream_load16(pv + idx);
-                if (KL) rd[u] = stream_load16(pd + idx);
-            }
+            const int at = min(base + u * THREADS + tid, vend - 1);
+            rv[u] = stream_load16(pv + at);
+            if (KL) rd[u] = stream_load16(pd + at);
         }
+        const int wave_base = base + (__builtin_amdgcn_readfirstlane(tid) & ~63);
 #pragma unroll
-        for (int u = 0; u < kUnroll; ++u)
-            consume<BF16, KL, TRACKD>(rv[u], rd[u], ok[u], (base + u * THREADS + tid) * E, st);
+        for (int u = 0; u < kUnroll; ++u) {
+            if (wave_base + u * THREADS >= vend) break;
+            const int idx = base + u * THREADS + tid;
+            consume<BF16, KL, TRACKD>(rv[u], rd[u], idx < vend, idx * E, st);
+        }
     }
 
     // lanes -> wave (references are already wave-uniform), waves -> workgroup
@@ -901,25 +901,30 @@ int verify_fused_threads(int P)
 
 // Vectors per split: a whole number of full iterations (kThreads * kUnroll vectors), so that only the last
 // split of a row has a ragged remainder - every load round of a workgroup is a dependent memory round trip,
-// and with few rows those round trips are the call.
+// and with few rows those round trips are the call.  A row of one such iteration is not split.
+// Where sixteen splits of every row still leave each workgroup a compute unit of its own, a split is as short as kThreads allows:
+// what a workgroup folds is then the call.  us per call, KL: 4 x 32000 7.1 -> 5.7, 16 x 16384 7.9 -> 6.5, 20 x 20000 7.9 -> 6.7;
+// unmasking 4 x 32000 6.4 -> 5.6.  Past a workgroup per unit it turns: KL 20 x 152064 (300 workgroups for 200) 9.8 -> 10.6,
+// 32 x 65536 (512 for 256) 8.6 -> 8.8.
+constexpr int kMaxRowSplits = 16, kFineWorkgroups = 256;
+static long splits_of_chunk(long nvec, long chunk) { return (nvec + chunk - 1) / chunk; }
 static int verify_split_chunk(int P, int V, int elem_bytes)
 {
-    const long nvec = (long)V * elem_bytes / 16;
+    const long nvec = (long)V * elem_bytes / 16, iter = (long)kThreads * kUnroll;
+    if (nvec <= iter) return (int)iter;
     long s = (2048 + P - 1) / P;         // about 2048 workgroups in all
-    if (s > 16) s = 16;
+    if (s > kMaxRowSplits) s = kMaxRowSplits;
     if (s < 1) s = 1;
-    const long iter = (long)kThreads * kUnroll;
-    long chunk = (nvec + s - 1) / s;
-    chunk = (chunk + iter - 1) / iter * iter;
-    return (int)chunk;
+    const long chunk = (nvec + s - 1) / s;
+    const long fine = (chunk + kThreads - 1) / kThreads * kThreads;
+    if (P * splits_of_chunk(nvec, fine) <= tune("DD_TUNE_VERIFY_FINE", kFineWorkgroups)) return (int)fine;
+    return (int)((chunk + iter - 1) / iter * iter);
 }
 
 int verify_splits(int P, int V, int elem_bytes)
 {
     if (P <= 0 || verify_fused_threads(P) != 0) return 1;
-    const long nvec = (long)V * elem_bytes / 16;
-    const long chunk = verify_split_chunk(P, V, elem_bytes);
-    const long s = (nvec + chunk - 1) / chunk;
+    const long s = splits_of_chunk((long)V * elem_bytes / 16, verify_split_chunk(P, V, elem_bytes));
     return (int)(s < 1 ? 1 : s);
 }
 
@@ -943,7 +948,11 @@ static bool seq_in_one_launch(int G, int nvec, bool bf16, bool kl)
 size_t verify_workspace_bytes(int P, int V, int elem_bytes)
 {
     if (P <= 0 || verify_fused_threads(P) != 0) return 0;
-    return (size_t)P * (size_t)verify_splits(P, V, elem_bytes) * sizeof(VerifyPartial);
+    // A workspace for P rows serves any smaller count of split rows too, also one that is split further than these.
+    const int S = verify_splits(P, V, elem_bytes);
+    const size_t states = (size_t)P * (size_t)S;
+    const size_t fewer = S == 1 ? 0 : P * kMaxRowSplits < kFineWorkgroups ? P * kMaxRowSplits : kFineWorkgroups;
+    return (states > fewer ? states : fewer) * sizeof(VerifyPartial);
 }
 
 template <bool BF16, bool KL, bool TRACKD = false>

@@ -17,6 +17,8 @@
 // block and all dims -> the form the rule picks: 1 x 32 heads, 512 keys, 32 rows bf16 8.0 -> 6.8 (4 parts); 1 x 32, 1024 keys bf16 11.4 ->
 // 8.7, fp8 9.5 -> 7.0, e4m3 V 10.1 -> 7.4 (4 parts, 8 waves); 4 x 32/8, 16 rows, 2048 keys fp8 12.2 -> 9.7; 11 x 32/8, 16 rows, 1237 keys fp8
 // 13.9 -> 12.5, e4m3 V 15.7 -> 12.6 (two blocks, 2 parts, 8 waves); 2 x 32, 800 keys, 48 rows e4m3 V 11.9 -> 8.4 (2 parts, 8 waves).
+// What the first loads need arrives in registers, as leading scalar arguments, and no hidden argument is asked for (the grid's size
+// costs a launch 256 bytes more): with the arguments in a struct the first of those calls takes 6.8, now 6.2 us, 11 x 32/8 fp8 11.6 -> 11.2.
 // Tried and not kept: a second unit on its way per wave (bf16 8.0 -> 9.4, 4 parts 6.8 -> 7.6: the first units' loads queue behind it); two
 // blocks with all dims (12.3, one wave's registers); eight waves on all dims for bf16 (8.6).
 #include "attention_common.h"

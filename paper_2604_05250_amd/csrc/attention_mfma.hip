@@ -741,13 +741,20 @@ hipError_t launch_attention_mfma(const AttnArgs &a, hipStream_t stream)
         // there: 1 x 32 heads, N 300 10.9 -> 9.2, N 512 14.7 -> 13.3, fp8 Q and K 13.2 -> 11.1, d = 64 10.1 -> 7.4; 1 x 16, N 512 12.6 -> 8.1; 1 x 8, N 1024
         // 19.3 -> 11.3.  Over 380 drawn calls of more than 64 keys 0.78 of the time up to 256 workgroups,
         // 0.91 up to 512, then 1.1 (1 x 60, N 300 15.9 against 14.1).  e4m3 values: 0.66 up to 256 workgroups, 0.78 up to 512, then 1.1 as well.
-        // Past 448 workgroups of more than 1024 keys it depends, against the two-waves-per-SIMD kernel: 1 x 8, N 2016 29.3 there / 30.8,
-        // 1 x 8 (2 kv), N 2035 29.0 / 26.8, fp8 1 x 4, N 4096 42.3 / 39.2.  64 keys and fewer: up to 256 workgroups (d = 64: 192), whose head dims it
+        // Past 448 workgroups of more than 1024 keys, against the kernels below: e4m3 values 0.66 - 0.78 and d = 64 0.82 - 0.87 at any length (8 heads,
+        // N 2046 47.6 -> 35.6; 13, N 1290 17.1 -> 14.3), fp8 0.90 - 0.95 up to 2048 keys, 0.985 at 3081, then up to 1.03, bf16 0.97 - 0.99 up to 1349,
+        // then up to 1.06 (6 heads, N 2590 32.5 / 34.6); any type where the two-waves-per-SIMD kernel does not hold the call in one round 0.61 - 0.80
+        // (bf16 10 heads, N 1613 30.0 -> 24.0).  d = 64 from 512 keys on also up to three workgroups per compute unit, 0.86 - 1.0 (8 heads,
+        // N 2674 33.3 -> 29.2), then 1.0 - 1.1 (26 heads, N 1015 17.4 / 18.5); shorter up to 1.09.
+        // 64 keys and fewer: up to 256 workgroups (d = 64: 192), whose head dims it
         // then divides: bf16 1 x 16, N 33 5.4 -> 4.6, 6 x 32, N 49 5.9 -> 5.3, fp8 1 x 32, N 48 5.2 -> 4.2; 384 workgroups, N 33 5.6 / 6.2.
         const long wgs = heads * ((rows + 31) / 32);
-        const int solo = tune("DD_TUNE_SOLO", tune("DD_TUNE_DUO", -1) <= 0 && wgs <= (a.N > 1024 ? 448 : a.N > 64 ? 512 : a.d == 64 ? 192 : 256));
+        const bool v8 = a.v_dtype == 2;
+        const int longest = v8 || a.d == 64 || !one_round64 ? a.N : fp8 ? 3072 : 1344;
+        const long most = a.N <= 64 ? (a.d == 64 ? 192 : 256) : a.N > longest ? 448 : a.d == 64 && a.N >= 512 ? 768 : 512;
+        const int solo = tune("DD_TUNE_SOLO", tune("DD_TUNE_DUO", -1) <= 0 && wgs <= most);
         if (solo != 0 && attn_solo_serves(a))
-            return launch_attention_solo(a, attn_solo_form(rows, heads, a.N, a.d, fp8, a.v_dtype == 2), stream);
+            return launch_attention_solo(a, attn_solo_form(rows, heads, a.N, a.d, fp8, v8), stream);
     }
     if (!blk && attn_duo_serves(a) && tune("DD_TUNE_ATTN_WIDE", -1) < 0 && tune("DD_TUNE_BIDIR_STREAM", -1) < 0) {
         // One round of 64-row workgroups: the two-waves-per-SIMD kernel, whose eight waves share a workgroup's keys.  Of these calls the

@@ -1,5 +1,5 @@
 // Attention with two waves per SIMD on the same query rows: the drafter's call with more than 64 rows per kv head, which
-// grouped heads make compute bound (Sec. 2.3), and verifier calls of 449 to 512 workgroups of 32 rows and more than 1024 keys (Sec. 2.2).
+// grouped heads make compute bound (Sec. 2.3), and long verifier calls of 449 to 512 workgroups of 32 rows (bf16 past 1344 keys, fp8 past 3072; Sec. 2.2).
 //     O = softmax(Q K^T / sqrt(d_k)) V   (Eq. 3)
 // One workgroup = 8 waves = R blocks of 32 query rows x P = 8 / R key phases: wave w owns row block w % R and takes every
 // P-th 32-key unit of the key stream, with a state (reference, sum, O) of its own; the P states of a row block are merged

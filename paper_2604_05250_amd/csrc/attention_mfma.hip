@@ -742,7 +742,7 @@ hipError_t launch_attention_mfma(const AttnArgs &a, hipStream_t stream)
         // 19.3 -> 11.3.  Over 380 drawn calls of more than 64 keys 0.78 of the time up to 256 workgroups,
         // 0.91 up to 512, then 1.1 (1 x 60, N 300 15.9 against 14.1).  e4m3 values: 0.66 up to 256 workgroups, 0.78 up to 512, then 1.1 as well.
         // Past 448 workgroups of more than 1024 keys, against the kernels below: e4m3 values 0.66 - 0.78 and d = 64 0.82 - 0.87 at any length (8 heads,
-        // N 2046 47.6 -> 35.6; 13, N 1290 17.1 -> 14.3), fp8 0.90 - 0.95 up to 2048 keys, 0.985 at 3081, then up to 1.03, bf16 0.97 - 0.99 up to 1349,
+        // N 2046 35.6 -> 26.6; 11, N 1289 14.3 -> 11.9), fp8 0.90 - 0.95 up to 2048 keys, 0.985 at 3081, then up to 1.03, bf16 0.97 - 0.99 up to 1349,
         // then up to 1.06 (6 heads, N 2590 32.5 / 34.6); any type where the two-waves-per-SIMD kernel does not hold the call in one round 0.61 - 0.80
         // (bf16 10 heads, N 1613 30.0 -> 24.0).  d = 64 from 512 keys on also up to three workgroups per compute unit, 0.86 - 1.0 (8 heads,
         // N 2674 33.3 -> 29.2), then 1.0 - 1.1 (26 heads, N 1015 17.4 / 18.5); shorter up to 1.09.

@@ -203,13 +203,14 @@ Scratch &scratch()
     static Scratch *s = new Scratch;
     return *s;
 }
-at::Tensor workspace(size_t nbytes, const at::Device &device, hipStream_t stream)
+// (`or_less`: the library itself says whether a fixed workspace of fewer bytes serves the call)
+at::Tensor workspace(size_t nbytes, const at::Device &device, hipStream_t stream, bool or_less)
 {
     if (nbytes == 0) return at::Tensor();
     Scratch &s = scratch();
     if (nbytes > s.peak) s.peak = nbytes;
     if (s.fixed.defined()) {
-        if ((size_t)s.fixed.numel() < nbytes || s.fixed.device() != device) {
+        if (((size_t)s.fixed.numel() < nbytes && !or_less) || s.fixed.device() != device) {
             PyErr_Format(PyExc_RuntimeError, "the fixed workspace holds %lld bytes on %s; this call needs %zu on %s",
                          (long long)s.fixed.numel(), s.fixed.device().str().c_str(), nbytes, device.str().c_str());
             throw Raised{};
@@ -233,7 +234,7 @@ at::Tensor workspace(size_t nbytes, const at::Device &device, hipStream_t stream
 struct Call {                                                // one library call: stream, scratch
     hipStream_t stream;
     at::Tensor ws;
-    Call(size_t need, const at::Tensor &on) : stream(current_stream()), ws(workspace(need, on.device(), stream)) {}
+    Call(size_t need, const at::Tensor &on, bool or_less = false) : stream(current_stream()), ws(workspace(need, on.device(), stream, or_less)) {}
     void *ptr() const { return ws.defined() ? ws.data_ptr() : nullptr; }
     size_t bytes() const { return ws.defined() ? (size_t)ws.numel() : 0; }
 };
@@ -483,7 +484,7 @@ PyObject *verify_remask(PyObject *const *a, Py_ssize_t n)
         check(unlocked([&] { return dd_verify_remask_static(ld, lv, (const uint8_t *)mk, (dd_mode)mode, threshold, seed, pm, pt, ps, B, G, V, dt, stream); }),
               "dd_verify_remask_static");
     } else {
-        const Call c(dd_verify_remask_workspace_bytes(B, G, V, dt), L);
+        const Call c(dd_verify_remask_workspace_bytes(B, G, V, dt), L, true);
         check(unlocked([&] { return dd_verify_remask(ld, lv, (const uint8_t *)mk, (dd_mode)mode, threshold, seed, pm, pt, ps, B, G, V, dt, c.ptr(),
                                                      c.bytes(), c.stream); }), "dd_verify_remask");
     }
@@ -518,7 +519,7 @@ PyObject *unmask(PyObject *const *a, Py_ssize_t n)
     uint8_t *const pm = (uint8_t *)dev(rm, "out_mask");
     int32_t *const pt = (int32_t *)dev(rt, "out_tokens");
     float *const pc = (float *)dev(rc, "out_conf");
-    const Call c(dd_unmask_workspace_bytes(B, G, V, dt), L);
+    const Call c(dd_unmask_workspace_bytes(B, G, V, dt), L, true);
     check(unlocked([&] { return dd_unmask(ld, (const uint8_t *)mk, (dd_unmask_mode)mode, threshold, px, pm, pt, pc, B, G, V, dt, c.ptr(), c.bytes(),
                                           c.stream); }), "dd_unmask");
     return triple(rm, rt, rc);
@@ -541,7 +542,7 @@ PyObject *verify_scores(PyObject *const *a, Py_ssize_t n)
     void *const ld = dev(D, "logits_d"), *const lv = dev(L, "logits_v");
     const at::Tensor kl = empty_like_type({P}, at::kFloat, L), cv = empty_like_type({P}, at::kFloat, L), tv = empty_like_type({P}, at::kInt, L);
     const at::Tensor cd = drafter ? empty_like_type({P}, at::kFloat, L) : at::Tensor(), td = drafter ? empty_like_type({P}, at::kInt, L) : at::Tensor();
-    const Call c(dd_verify_scores_workspace_bytes(P, V, dt), L);
+    const Call c(dd_verify_scores_workspace_bytes(P, V, dt), L, true);
     float *const pk = (float *)kl.data_ptr(), *const pcv = (float *)cv.data_ptr(), *const pcd = drafter ? (float *)cd.data_ptr() : nullptr;
     int32_t *const ptv = (int32_t *)tv.data_ptr(), *const ptd = drafter ? (int32_t *)td.data_ptr() : nullptr;
     check(unlocked([&] { return dd_verify_scores(ld, lv, pk, pcv, ptv, pcd, ptd, P, V, dt, c.ptr(), c.bytes(), c.stream); }), "dd_verify_scores");

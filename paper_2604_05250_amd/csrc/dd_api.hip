@@ -453,19 +453,19 @@ static int verify_remask(const void *logits_d, const void *logits_v, const uint8
                                  logit_dtype, &empty);
     if (rc != DD_OK || empty) return rc;
     const int eb = logit_dtype == DD_BF16 ? 2 : 4;
-    const size_t need = dd::verify_workspace_bytes(B * G, V, eb);
     if (static_scratch) {
+        const size_t need = dd::verify_workspace_bytes(B * G, V, eb);
         if (need > kStaticScratchBytes) return DD_ERR_WORKSPACE;  // more partial states than the static array holds
         workspace = nullptr;
         workspace_bytes = need;
         if (need > 0 && (rc = scratch_of_current_device(&workspace)) != DD_OK) return rc;
     }
-    rc = check_workspace(workspace, workspace_bytes, need);
+    rc = check_workspace(workspace, workspace_bytes, dd::verify_least_workspace_bytes(B * G, V, eb));
     if (rc != DD_OK) return rc;
     const bool kl = (mode == DD_KL_THRESH || mode == DD_KL_PROB || mode == DD_KL_TOPK);
     const hipError_t e = dd::launch_verify(kl ? logits_d : nullptr, logits_v, mask, mode, threshold, seed,
                                            out_mask, out_tokens, out_scores, B, G, V, logit_dtype == DD_BF16,
-                                           workspace, static_cast<hipStream_t>(stream));
+                                           workspace, workspace_bytes, static_cast<hipStream_t>(stream));
     return e == hipSuccess ? DD_OK : DD_ERR_LAUNCH;
 }
 
@@ -518,12 +518,12 @@ int dd_unmask(const void *logits_d, const uint8_t *mask, dd_unmask_mode mode, fl
         if (m0 < o0 + n && o0 < m0 + n) return DD_ERR_SHAPE;
     }
     if (misaligned16(logits_d)) return DD_ERR_ALIGN;
-    const int rc = check_workspace(workspace, workspace_bytes, dd::verify_workspace_bytes(B * G, V, eb));
+    const int rc = check_workspace(workspace, workspace_bytes, dd::verify_least_workspace_bytes(B * G, V, eb));
     if (rc != DD_OK) return rc;
     const hipError_t e = dd::launch_verify(nullptr, logits_d, mask,
                                            mode == DD_UNMASK_TOPK ? dd::kModeUnmaskTopk : dd::kModeUnmaskThresh,
                                            threshold, 0, out_mask, out_tokens, out_conf, B, G, V,
-                                           logit_dtype == DD_BF16, workspace, static_cast<hipStream_t>(stream), x_tokens);
+                                           logit_dtype == DD_BF16, workspace, workspace_bytes, static_cast<hipStream_t>(stream), x_tokens);
     return e == hipSuccess ? DD_OK : DD_ERR_LAUNCH;
 }
 
@@ -543,14 +543,14 @@ int dd_verify_scores(const void *logits_d, const void *logits_v,
     if (P == 0) return DD_OK;
     if (!logits_d || !logits_v || !out_kl || !out_conf_v || !out_tok_v) return DD_ERR_NULL;
     if (misaligned16(logits_v) || misaligned16(logits_d)) return DD_ERR_ALIGN;
-    const int rc = check_workspace(workspace, workspace_bytes, dd::verify_workspace_bytes(P, V, eb));
+    const int rc = check_workspace(workspace, workspace_bytes, dd::verify_least_workspace_bytes(P, V, eb));
     if (rc != DD_OK) return rc;
     dd::VerifyExtra ex;
     ex.conf_v = out_conf_v;
     ex.conf_d = out_conf_d;
     ex.tok_d = out_tok_d;
     const hipError_t e = dd::launch_verify(logits_d, logits_v, nullptr, dd::kModeScores, 0.0f, 0, nullptr, out_tok_v,
-                                           out_kl, 1, P, V, logit_dtype == DD_BF16, workspace,
+                                           out_kl, 1, P, V, logit_dtype == DD_BF16, workspace, workspace_bytes,
                                            static_cast<hipStream_t>(stream), nullptr, &ex);
     return e == hipSuccess ? DD_OK : DD_ERR_LAUNCH;
 }

@@ -50,9 +50,9 @@ inline hipError_t launch(void (*kernel)(Params...), dim3 grid, dim3 block, hipSt
 int tune(const char *name, int dflt);
 
 // ---- verification (verify.hip) -------------------------------------------------
-// Number of workgroups one logit row is split over, and workspace size.
-int verify_splits(int P, int V, int elem_bytes);
+// What the workspace query answers, and the least that a call accepts: in a workspace between the two its rows are split less.
 size_t verify_workspace_bytes(int P, int V, int elem_bytes);
+size_t verify_least_workspace_bytes(int P, int V, int elem_bytes);
 // `mode`: a dd_mode value, or one of the two below for the drafter's unmasking step (logits_v then holds the
 // drafter's logits, logits_d is unused, and x_tokens - optional - receives the tokens of the selected rows).
 constexpr int kModeUnmaskThresh = 100, kModeUnmaskTopk = 101;
@@ -67,7 +67,7 @@ struct VerifyExtra {
 hipError_t launch_verify(const void *logits_d, const void *logits_v, const uint8_t *mask,
                          int mode, float threshold, uint64_t seed,
                          uint8_t *out_mask, int32_t *out_tokens, float *out_scores,
-                         int B, int G, int V, int logit_is_bf16, void *workspace, hipStream_t stream,
+                         int B, int G, int V, int logit_is_bf16, void *workspace, size_t workspace_bytes, hipStream_t stream,
                          int32_t *x_tokens = nullptr, const VerifyExtra *extra = nullptr);
 
 // ---- attention (attention_mfma.hip, attention_f32.hip) -------------------------

@@ -899,33 +899,30 @@ int verify_fused_threads(int P)
     return P >= 2048 ? 256 : 512;        // measured: 512 lanes per row stream best for 256..1024 rows
 }
 
-// Vectors per split: a whole number of full iterations (kThreads * kUnroll vectors), so that only the last
-// split of a row has a ragged remainder - every load round of a workgroup is a dependent memory round trip,
-// and with few rows those round trips are the call.  A row of one such iteration is not split.
-// Where sixteen splits of every row still leave each workgroup a compute unit of its own, a split is as short as kThreads allows:
-// what a workgroup folds is then the call.  us per call, KL: 4 x 32000 7.1 -> 5.7, 16 x 16384 7.9 -> 6.5, 20 x 20000 7.9 -> 6.7;
-// unmasking 4 x 32000 6.4 -> 5.6.  Past a workgroup per unit it turns: KL 20 x 152064 (300 workgroups for 200) 9.8 -> 10.6,
-// 32 x 65536 (512 for 256) 8.6 -> 8.8.
+// A row's splits.  Where sixteen splits of every row still leave each workgroup a compute unit of its own, a split is as short as kThreads
+// vectors allow: what a workgroup folds (a ragged load round, or full ones and a ragged one) is then the call.  us per call, KL: 4 x 32000
+// 7.1 -> 5.7, 16 x 16384 7.9 -> 6.5, 20 x 20000 7.9 -> 6.7; unmasking 4 x 32000 6.4 -> 5.6.  Past a workgroup per unit it turns: KL
+// 20 x 152064 (300 workgroups for 200) 9.8 -> 10.6, 32 x 65536 (512 for 256) 8.6 -> 8.8.
+// Otherwise a split is a whole number of full load rounds (kThreads * kUnroll vectors), so that only the last of a row is ragged: every
+// round of a workgroup is a dependent memory round trip, and with few rows those round trips are the call.  These are also what a call
+// takes whose workspace does not hold the states of shorter ones.  A row of one such round is not split.
 constexpr int kMaxRowSplits = 16, kFineWorkgroups = 256;
-static long splits_of_chunk(long nvec, long chunk) { return (nvec + chunk - 1) / chunk; }
-static int verify_split_chunk(int P, int V, int elem_bytes)
+struct RowSplits { int count, chunk; };              // of a row; vectors in each
+static RowSplits row_splits(int P, int V, int elem_bytes, size_t workspace_bytes)
 {
     const long nvec = (long)V * elem_bytes / 16, iter = (long)kThreads * kUnroll;
-    if (nvec <= iter) return (int)iter;
+    if (nvec <= iter) return RowSplits{1, (int)iter};
     long s = (2048 + P - 1) / P;         // about 2048 workgroups in all
     if (s > kMaxRowSplits) s = kMaxRowSplits;
     if (s < 1) s = 1;
-    const long chunk = (nvec + s - 1) / s;
-    const long fine = (chunk + kThreads - 1) / kThreads * kThreads;
-    if (P * splits_of_chunk(nvec, fine) <= tune("DD_TUNE_VERIFY_FINE", kFineWorkgroups)) return (int)fine;
-    return (int)((chunk + iter - 1) / iter * iter);
-}
-
-int verify_splits(int P, int V, int elem_bytes)
-{
-    if (P <= 0 || verify_fused_threads(P) != 0) return 1;
-    const long s = splits_of_chunk((long)V * elem_bytes / 16, verify_split_chunk(P, V, elem_bytes));
-    return (int)(s < 1 ? 1 : s);
+    const long shortest = (nvec + s - 1) / s;
+    auto of = [&](long multiple) {
+        const long chunk = (shortest + multiple - 1) / multiple * multiple;
+        return RowSplits{(int)((nvec + chunk - 1) / chunk), (int)chunk};
+    };
+    const RowSplits fine = of(kThreads);
+    const long states = (long)P * fine.count;
+    return states <= tune("DD_TUNE_VERIFY_FINE", kFineWorkgroups) && states * sizeof(VerifyPartial) <= workspace_bytes ? fine : of(iter);
 }
 
 // Dependent load rounds of verify_seq_kernel (sixteen rows of kThreads vectors each), and up to how many it is taken: a round costs
@@ -949,10 +946,16 @@ size_t verify_workspace_bytes(int P, int V, int elem_bytes)
 {
     if (P <= 0 || verify_fused_threads(P) != 0) return 0;
     // A workspace for P rows serves any smaller count of split rows too, also one that is split further than these.
-    const int S = verify_splits(P, V, elem_bytes);
+    const int S = row_splits(P, V, elem_bytes, SIZE_MAX).count;
     const size_t states = (size_t)P * (size_t)S;
     const size_t fewer = S == 1 ? 0 : P * kMaxRowSplits < kFineWorkgroups ? P * kMaxRowSplits : kFineWorkgroups;
     return (states > fewer ? states : fewer) * sizeof(VerifyPartial);
+}
+
+size_t verify_least_workspace_bytes(int P, int V, int elem_bytes)
+{
+    if (P <= 0 || verify_fused_threads(P) != 0) return 0;
+    return (size_t)P * (size_t)row_splits(P, V, elem_bytes, 0).count * sizeof(VerifyPartial);
 }
 
 template <bool BF16, bool KL, bool TRACKD = false>
@@ -970,7 +973,7 @@ static hipError_t launch_row_kernel(int threads, dim3 grid, hipStream_t stream, 
 hipError_t launch_verify(const void *logits_d, const void *logits_v, const uint8_t *mask,
                          int mode, float threshold, uint64_t seed,
                          uint8_t *out_mask, int32_t *out_tokens, float *out_scores,
-                         int B, int G, int V, int logit_is_bf16, void *workspace, hipStream_t stream,
+                         int B, int G, int V, int logit_is_bf16, void *workspace, size_t workspace_bytes, hipStream_t stream,
                          int32_t *x_tokens, const VerifyExtra *extra)
 {
     const int P = B * G;
@@ -997,8 +1000,8 @@ hipError_t launch_verify(const void *logits_d, const void *logits_v, const uint8
             e = kl ? launch_row_kernel<false, true>(fused, grid, stream, ld, lv, nvec, mask, mode, threshold, seed, out_mask, out_tokens, out_scores, ex)
                    : launch_row_kernel<false, false>(fused, grid, stream, ld, lv, nvec, mask, mode, threshold, seed, out_mask, out_tokens, out_scores, ex);
     } else {
-        const int S = verify_splits(P, V, eb);
-        const int chunk = verify_split_chunk(P, V, eb);
+        const RowSplits split = row_splits(P, V, eb, workspace_bytes);
+        const int S = split.count, chunk = split.chunk;
         VerifyPartial *part = static_cast<VerifyPartial *>(workspace);
         const dim3 grid((unsigned)((long)P * S)), block(kThreads);
         const bool per_sequence = mode == 3 || mode == 5 || mode == 6 || mode == kModeUnmaskThresh || mode == kModeUnmaskTopk;

@@ -16,6 +16,8 @@
 
 #include <ATen/ATen.h>
 #include <ATen/hip/EmptyTensor.h>
+#include <ATen/record_function.h>
+#include <c10/core/impl/LocalDispatchKeySet.h>
 #include <c10/hip/HIPGraphsC10Utils.h>
 #include <c10/hip/HIPStream.h>
 #include <torch/csrc/Exceptions.h>
@@ -247,8 +249,15 @@ template <typename F> int unlocked(F &&f)                     // the library cal
     return rc;
 }
 
+// An output.  The allocator is asked directly, past the dispatcher (a cycle of ten calls in fp32 51.1 -> 47.5 us on the host's side, 59.5 -> 56.1
+// where it is slower), unless something may be listening there: a dispatch mode, tracer or transform (each adds keys to this thread's
+// set), a profiler or another observer of calls, or the fill of uninitialised memory in deterministic mode.  Device, stream, capture pool
+// and inference mode are the same either way.
 at::Tensor empty_like_type(at::IntArrayRef shape, at::ScalarType type, const at::Tensor &on)
 {
+    const bool heard = !(c10::impl::tls_local_dispatch_key_set().included_ - c10::default_included_set).empty() || at::hasCallbacks() ||
+                       at::globalContext().deterministicAlgorithms();
+    if (heard) return at::empty(shape, at::TensorOptions().dtype(type).device(on.device()));
     return at::detail::empty_cuda(shape, type, on.device(), std::nullopt);
 }
 

@@ -100,3 +100,37 @@ def test_static_entry_point_without_outputs():
     assert e.value.status == -1
     none = ld[:0], lv[:0], mask[:0]
     assert dd.dd_verify_remask_static(*none, dd.TRUST, 0.0, 0, 0, 8, None, None, None) == (None, None, None)
+
+
+def test_output_allocations_are_seen():
+    # a dispatch mode and the profiler see every output that a call allocates, as they see torch's own; what is computed is the same
+    import torch
+    from torch.utils._python_dispatch import TorchDispatchMode
+    ld, lv, mask = _verify_args()
+    x = torch.randn(1, 2, 64, 64, device="cuda:0").bfloat16()
+    calls = {"bidir": (1, lambda: [dd.dd_bidir_attention(x, x, x)]), "block": (1, lambda: [dd.dd_block_attention_cached(x, x, x, 0)]),
+             "unmask": (3, lambda: dd.dd_unmask(ld, mask, dd.UNMASK_THRESH, 0.5, 2, 8)), "scores": (5, lambda: dd.dd_verify_scores(ld, lv)),
+             "verify": (3, lambda: dd.dd_verify_remask(ld, lv, mask, dd.TRUST, 0.0, 0, 2, 8))}
+    seen = []
+
+    class Listen(TorchDispatchMode):
+        def __torch_dispatch__(self, func, types, args=(), kwargs=None):
+            seen.append(func)
+            return func(*args, **(kwargs or {}))
+    for name, (outputs, call) in calls.items():
+        want = call()                                        # (and the stream's scratch tensor is there)
+        seen.clear()
+        with Listen():
+            got = call()
+        assert seen.count(torch.ops.aten.empty.memory_format) == outputs, (name, seen)
+        with torch.profiler.profile(activities=[torch.profiler.ProfilerActivity.CPU]) as prof:
+            call()
+        assert sum(e.count for e in prof.key_averages() if e.key == "aten::empty") == outputs, name
+        was = torch.are_deterministic_algorithms_enabled()
+        torch.use_deterministic_algorithms(True)
+        try:
+            again = call()
+        finally:
+            torch.use_deterministic_algorithms(was)
+        torch.cuda.synchronize()
+        assert all(torch.equal(a, b) and torch.equal(a, c) for a, b, c in zip(want, got, again)), name

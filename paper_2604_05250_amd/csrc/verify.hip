@@ -942,14 +942,14 @@ static bool seq_in_one_launch(int G, int nvec, bool bf16, bool kl)
     return rounds <= (kl ? kSeqMaxRoundsKl : kSeqMaxRounds) && (!bf16 || (long)G * nvec <= (kl ? 2560 : 5120));
 }
 
+// Room for the most splits that any count of rows up to P has (a row has at most sixteen, of kThreads vectors or more), so that a size
+// queried for P rows, up to 191, serves fewer: P rows' own splits can be half of what P - 1 have (126464 bf16 logits, 136 rows: 16, 137: 8).
 size_t verify_workspace_bytes(int P, int V, int elem_bytes)
 {
     if (P <= 0 || verify_fused_threads(P) != 0) return 0;
-    // A workspace for P rows serves any smaller count of split rows too, also one that is split further than these.
-    const int S = row_splits(P, V, elem_bytes, SIZE_MAX).count;
-    const size_t states = (size_t)P * (size_t)S;
-    const size_t fewer = S == 1 ? 0 : P * kMaxRowSplits < kFineWorkgroups ? P * kMaxRowSplits : kFineWorkgroups;
-    return (states > fewer ? states : fewer) * sizeof(VerifyPartial);
+    const long nvec = (long)V * elem_bytes / 16, parts = (nvec + kThreads - 1) / kThreads;
+    const long most = nvec <= (long)kThreads * kUnroll ? 1 : parts < kMaxRowSplits ? parts : kMaxRowSplits;
+    return (size_t)P * (size_t)most * sizeof(VerifyPartial);
 }
 
 size_t verify_least_workspace_bytes(int P, int V, int elem_bytes)

@@ -8,6 +8,14 @@ OFF_WIDE = {"DD_TUNE_BLOCK_WIDE": "0"}                # ... the MFMA kernel
 SOLO = {"DD_TUNE_SOLO": "1"}                          # waves that stream keys of their own
 DUO2, DUO4 = {"DD_TUNE_DUO": "2"}, {"DD_TUNE_DUO": "4"}      # two waves per SIMD, 64 / 128 rows per workgroup
 
+# that kernel's forms (row blocks, parts of the head dims, waves as digits) by storage: (q and k, v, head dims) as dtype tags, 1 bf16, 2 e4m3
+SOLO_FORMS = {(1, 1, 128): (114, 124, 128, 144, 148, 224), (2, 1, 128): (114, 124, 128, 144, 148, 228),
+              (2, 2, 128): (114, 124, 128, 144, 148, 224, 228), (1, 1, 64): (114, 118, 124, 128)}
+
+
+def solo_form(form, splits=1):
+    return {"DD_TUNE_SOLO": "1", "DD_TUNE_SOLO_FORM": str(form), "DD_TUNE_BLOCK_SPLITS": str(splits)}
+
 
 def with_splits(env, n):
     return dict(env, DD_TUNE_BLOCK_SPLITS=str(n))

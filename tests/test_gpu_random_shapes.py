@@ -12,7 +12,7 @@ from _util import out_to_f64, to_dev
 
 pytestmark = pytest.mark.gpu
 HOOKS = ("DD_TUNE_ATTN_WIDE", "DD_TUNE_ATTN_WIDE_GRID", "DD_TUNE_BIDIR_STREAM", "DD_TUNE_BLOCK_WIDE", "DD_TUNE_BLOCK_STREAM",
-         "DD_TUNE_BLOCK_WIDE_ROWS", "DD_TUNE_SOLO", "DD_TUNE_DUO")
+         "DD_TUNE_BLOCK_WIDE_ROWS", "DD_TUNE_SOLO", "DD_TUNE_SOLO_FORM", "DD_TUNE_BLOCK_SPLITS", "DD_TUNE_DUO")
 FORCED = [SOLO, DUO2, DUO4]                                  # beside the kernels that a call's own draw picks
 TOL = {wl.BF16: (2e-2, 5e-3), wl.FP8_E4M3: (6e-2, 5e-3), wl.F32: (1e-4, 1e-5)}
 

@@ -16,6 +16,9 @@ BF16, FP8 = wl.BF16, wl.FP8_E4M3
     (BF16, BF16, 64, 38, 38, 511), (BF16, BF16, 64, 38, 38, 512),                                     # 608, shorter and just long enough
     (BF16, BF16, 64, 12, 3, 1345),                                                                    # grouped heads, 507
     (FP8, FP8, 128, 16, 16, 1024), (FP8, FP8, 128, 14, 14, 1057), (FP8, BF16, 128, 14, 14, 1121),     # 512, 476 and 504
+    (BF16, BF16, 128, 128, 128, 64), (BF16, BF16, 128, 129, 129, 33), (FP8, BF16, 128, 128, 32, 33), (FP8, BF16, 128, 129, 129, 64),      # 64 keys and
+    (FP8, FP8, 128, 128, 128, 64), (FP8, FP8, 128, 129, 129, 33), (BF16, BF16, 64, 96, 96, 64), (BF16, BF16, 64, 97, 97, 33),             # fewer: 256, 192
+    (BF16, BF16, 128, 86, 86, 65),                                                                                                       # ... 258 of more
     (BF16, BF16, 128, 11, 11, 1344), (BF16, BF16, 128, 11, 11, 1345), (BF16, BF16, 128, 13, 13, 1231)])      # 462, 473, 507 (not one round of 64 rows)
 def test_verifier_calls_at_the_line(qk, v, d, H, Hkv, N):
     import torch

@@ -555,26 +555,30 @@ bool attn_solo_serves(const AttnArgs &a)
 }
 
 // What a form costs, in hundredths of a microsecond: a workgroup, that again per 100 workgroups beside it, a round (every wave of the
-// workgroup one unit), and, in tenths, a megabyte of K and V, and one of those past 80 (three copies of which no longer stay in the last-level
-// cache between calls).  Fitted per storage type and form to the times of 4000 drawn drafter calls (1 - 16 x 32/32, 32/8, 28/4, 16/16, 8/8, 4/4, 40/8
-// and 12/3 heads, 1 - 64 rows per head, 20 - 4200 keys, 1 - 16 splits, some 30000 timings; rms of the fits 2 - 7 %); `pair` is the same past 256
-// workgroups, two to a compute unit (four waves only, up to 512 workgroups).  Eight waves on two blocks (fp8) and on all of 64 head dims are priced above their
-// fit up to five and four rounds, where four waves were 2 - 5 % faster (96 heads x 40 rows, 649 keys 9.3 / 9.7).
+// workgroup one unit), a round past the fourth on top, and, in tenths, a megabyte of K and V, and one of those past 80; `pair` is the same
+// past 256 workgroups, two to a compute unit (four waves only, up to 512 workgroups).
+// Fitted per storage type and form to the times of 4000 drawn drafter calls on three sets of inputs in turn, which the last-level cache
+// holds up to 80 MB (1 - 16 x 8 head counts, 1 - 64 rows per head, 20 - 4200 keys, 1 - 16 splits, some 30000 timings; rms of the fits 2 - 7 %).  `late`
+// and the constants of 118 were then searched over 7700 drawn calls timed on such inputs and on 650 MB of them in turn, from memory, as a
+// model's layers find them: eight waves that stream many units each are fast from the cache alone (fp8 32 heads, 64 rows, 3643 keys on 148
+// 13.6 us, from memory 20.5; on 114 in four key splits 13.2 and 16.2).  The mean of the two counts, and a loss of 2 % or more against the
+// kernels that served a call before these forms weighs six times.  Over 8500 other drawn calls the picks take 0.79 - 0.90 of those kernels' time
+// by type, from the cache and from memory; half a percent takes more than 1.06 from memory (up to 1.15), most of it 0.8 - 0.9 from the cache.
 namespace {
-struct SoloTerms { int fixed, beside, round, mb, cold; };
+struct SoloTerms { int fixed, beside, round, late, mb, cold; };
 struct SoloCost { int form; SoloTerms one, pair; };
-constexpr SoloCost kSoloBf16[] = {{114, {491, 13, 69, 44, 110}, {494, 15, 107, 91, 47}}, {124, {430, 10, 64, 31, 103}, {406, 14, 92, 66, 76}},
-                                  {128, {473, 10, 86, 60, 110}, {}},                     {144, {402, 10, 62, 24, 117}, {400, 8, 86, 50, 157}},
-                                  {148, {411, 10, 82, 60, 153}, {}},                     {224, {483, 15, 92, 16, 55}, {469, 25, 134, 63, 39}}};
-constexpr SoloCost kSoloFp8[] = {{114, {459, 10, 61, 43, 111}, {485, 14, 82, 79, 76}},   {124, {407, 5, 50, 40, 134}, {429, 10, 62, 55, 102}},
-                                 {128, {483, 5, 57, 55, 158}, {}},                       {144, {386, 3, 44, 51, 243}, {411, 7, 58, 33, 244}},
-                                 {148, {416, 8, 52, 50, 228}, {}},                       {228, {665, 11, 82, 42, 105}, {}}};
-constexpr SoloCost kSoloV8[] = {{114, {437, 11, 102, 33, 0}, {449, 18, 135, 63, 2}},     {124, {398, 6, 70, 39, 0}, {402, 11, 99, 24, 73}},
-                                {128, {457, 10, 88, 43, 0}, {}},                         {144, {380, 5, 53, 50, 0}, {390, 9, 73, 15, 267}},
-                                {148, {402, 9, 63, 51, 0}, {}},                          {224, {467, 9, 91, 22, 37}, {469, 22, 121, 34, 30}},
-                                {228, {539, 13, 111, 40, 131}, {}}};
-constexpr SoloCost kSoloD64[] = {{114, {376, 0, 51, 34, 123}, {440, 5, 61, 66, 81}}, {118, {470, 5, 70, 50, 140}, {}},
-                                 {124, {372, 0, 45, 39, 273}, {386, 9, 60, 46, 124}}, {128, {403, 0, 52, 56, 236}, {}}};
+constexpr SoloCost kSoloBf16[] = {{114, {491, 13, 69, 0, 44, 110}, {494, 15, 107, 0, 91, 47}}, {124, {430, 10, 64, 0, 31, 103}, {406, 14, 92, 0, 66, 76}},
+                                  {128, {473, 10, 86, 11, 60, 110}, {}}, {144, {402, 10, 62, 0, 24, 117}, {400, 8, 86, 0, 50, 157}},
+                                  {148, {411, 10, 82, 26, 60, 153}, {}}, {224, {483, 15, 92, 0, 16, 55}, {469, 25, 134, 0, 63, 39}}};
+constexpr SoloCost kSoloFp8[] = {{114, {459, 10, 61, 0, 43, 111}, {485, 14, 82, 0, 79, 76}}, {124, {407, 5, 50, 0, 40, 134}, {429, 10, 62, 0, 55, 102}},
+                                 {128, {483, 5, 57, 0, 55, 158}, {}}, {144, {386, 3, 44, 0, 51, 243}, {411, 7, 58, 0, 33, 244}},
+                                 {148, {416, 8, 52, 15, 50, 228}, {}}, {228, {665, 11, 82, 0, 42, 105}, {}}};
+constexpr SoloCost kSoloV8[] = {{114, {437, 11, 102, 0, 33, 0}, {449, 18, 135, 0, 63, 2}}, {124, {398, 6, 70, 0, 39, 0}, {402, 11, 99, 15, 24, 73}},
+                                {128, {457, 10, 88, 1, 43, 0}, {}}, {144, {380, 5, 53, 0, 50, 0}, {390, 9, 73, 0, 15, 267}},
+                                {148, {402, 9, 63, 14, 51, 0}, {}}, {224, {467, 9, 91, 0, 22, 37}, {469, 22, 121, 0, 34, 30}},
+                                {228, {539, 13, 111, 0, 40, 131}, {}}};
+constexpr SoloCost kSoloD64[] = {{114, {376, 0, 51, 0, 34, 123}, {440, 5, 61, 0, 66, 81}}, {118, {440, 1, 70, 2, 51, 140}, {}},
+                                 {124, {372, 0, 45, 0, 39, 273}, {386, 9, 60, 0, 46, 124}}, {128, {403, 0, 52, 0, 56, 236}, {}}};
 // A merge launch of key splits, and what it adds per 1000 rows of partial states (64 dims: half the bytes).
 constexpr int kMerge = 200, kMergeRows = 27, kMergeRowsD64 = 14;
 // The streaming kernel's cost likewise (64 rows, a round = a tile of 64 keys; `more`: per tile and round of 256 workgroups past the first).
@@ -601,7 +605,7 @@ SoloPick cheapest(const SoloCost (&forms)[FORMS], int only, long rows, long head
             if (rounds == last) continue;                // more splits for nothing
             last = rounds;
             const SoloTerms &t = w1 * s > 256 && waves == 4 ? f.pair : f.one;
-            long cost = t.fixed + t.beside * w1 * s / 100 + (long)t.round * rounds + megabytes(t.mb, t.cold, kb);
+            long cost = t.fixed + t.beside * w1 * s / 100 + (long)t.round * rounds + (long)t.late * (rounds > 4 ? rounds - 4 : 0) + megabytes(t.mb, t.cold, kb);
             if (s > 1) cost += kMerge + merge_rows * heads * rows * s / 1000;
             if (best.form == 0 || cost < best.cost) best = SoloPick{f.form, s, cost};
         }
@@ -626,19 +630,28 @@ long stream_cost(const StreamTerms &t, long rows, long heads, int N, long kb, bo
 }
 }  // namespace
 
-// Drafter calls: the cheapest form and key splits (0.7 - 1.5 % off the best of all kernels, forms and splits on average over drawn calls; splits while
-// every workgroup has a compute unit), where that is cheaper than the other kernels:
-//   Up to 64 rows per kv head, the streaming kernel by its cost (bf16 and fp8; 0.91 and 0.87 of the time of the rule before, which knew one form).
-//   d = 64: throughout.  e4m3 values, against the MFMA kernel: up to 512 workgroups of 32 rows, then where a kv head's rows are
-//   one workgroup, or streams are longer than three rounds of 128 keys (up to 768) or four (11 x 32, 63 rows, 90 keys 9.3 there / 10.5).
-//   At most 64 keys are one tile of the kernels before, and nothing for waves to stream: parts still win there while they spread the call (up to 96
-//   workgroups of 32 rows, bf16 5.05 -> 4.6, fp8 and e4m3 V 4.6 -> 4.35; with 240 5.36 / 5.65 and 4.66 / 5.3 the other way), 64 head dims
-//   do not (4.05 / 4.25), nor anything past 512 workgroups where a head's rows are two (d = 64 272 heads, 48 rows, 48 keys 5.3 / 7.6); with the
-//   cache refresh, a launch of its own there, all do.
-//   More than 64 rows (some 350 drawn calls per type; before: the two-waves-per-SIMD, the wide or the MFMA kernel): up to 256 workgroups 0.46 - 0.9 of
-//   the time, 256 - 512 of more than 64 keys 0.82 - 0.97 up to 1536 keys (d = 64 up to 2560, e4m3 V any: 0.45 - 0.8); longer ones up to 1.2 (88 heads,
-//   120 rows, 3084 keys fp8 36.9 / 45.0), more than 512 1.06 - 1.3.  bf16 past twelve rounds of 128 keys: up to 3072 keys on 128 workgroups (8 heads, 256
-//   rows, 1708 keys 15.0 -> 11.1), up to 2048 on 256; 32 heads, 112 rows, 4083 keys 24.8 / 28.1, 48 x 96, 2946 keys 25.2 / 30.9.
+// Drafter calls: the cheapest form and key splits (as many as leave every workgroup a compute unit), where that beats the other kernels.
+//
+// At most 64 keys are one tile of the other kernels, and nothing for waves to stream.  Few rows stay off this kernel there, unless
+//   - its parts spread the call, up to 96 workgroups of 32 rows (bf16 5.05 -> 4.6, fp8 and e4m3 V 4.6 -> 4.35; with 240 5.36 / 5.65 and
+//     4.66 / 5.3 the other way; 64 head dims never: 4.05 / 4.25), or
+//   - the call has the cache refresh, a launch of its own on the others.
+// So do more than 512 workgroups where a head's rows are two (d = 64, 272 heads, 48 rows, 48 keys 5.3 / 7.6).
+//
+// More than 64 rows (against the two-waves-per-SIMD, the wide and the MFMA kernel; some 350 drawn calls per type):
+//   - up to 256 workgroups 0.46 - 0.9 of the time.  bf16 past twelve rounds of 128 keys loses from 2048 keys on, on at most 128 workgroups from
+//     3072 on (8 heads, 256 rows, 1708 keys 15.0 -> 11.1; 32 x 112, 4083 keys 24.8 / 28.1; 48 x 96, 2946 keys 25.2 / 30.9).
+//   - up to 512, bf16 and fp8: 0.82 - 0.97 from 65 to 1536 keys (d = 64 to 2560), longer ones up to 1.2 (88 heads, 120 rows, 3084 keys
+//     fp8 36.9 / 45.0).  These figures are from the cache; from memory the last third of that range is up to 1.1 the other way.
+//   - up to 512, e4m3 V: 0.45 - 0.93 from 65 keys on.
+//   - past 512 1.06 - 1.3.
+//
+// Up to 64 rows:
+//   - d = 64: throughout.
+//   - e4m3 V, against the MFMA kernel: up to 512 workgroups of 32 rows; then where a head's rows are one workgroup, or streams are longer
+//     than three rounds of 128 keys (up to 768) or four (11 x 32, 63 rows, 90 keys 9.3 there / 10.5).
+//   - bf16 and fp8, against the streaming kernel: by its cost (0.91 and 0.87 of the time of one form by rule).  Calls from memory must win by a
+//     twentieth (128 heads, 11 rows, 2423 keys fp8 24.3 streamed / 26.4, predicted 24.8 / 23.2).
 SoloPlan attn_solo_plan(long rows, long heads, int N, int d, bool fp8, bool v8, bool refresh, int stream_splits)
 {
     const int forced = tune("DD_TUNE_SOLO", -1), forced_splits = tune("DD_TUNE_BLOCK_SPLITS", 0);
@@ -651,19 +664,22 @@ SoloPlan attn_solo_plan(long rows, long heads, int N, int d, bool fp8, bool v8, 
     if (forced == 1) return plan;
     if (forced_splits >= 1) return no;
     const long rounds = (N + 127) / 128;
-    if (rows <= 64 && N <= 64 && (wgs > 512 ? row_tiles == 2 : !refresh && heads <= 256 && rows <= (d == 64 || fp8 ? 48 : 32)) &&
-        (d == 64 || wgs > 96))
-        return no;
+    if (rows <= 64 && N <= 64) {
+        if (wgs > 512 && row_tiles == 2) return no;
+        const bool few = wgs <= 512 && !refresh && heads <= 256 && rows <= (d == 64 || fp8 ? 48 : 32);
+        if (few && (d == 64 || wgs > 96)) return no;
+    }
     if (rows > 64) {
-        if (wgs > 512 || (wgs > 256 && (N <= 64 || (!v8 && N > (d == 64 ? 2560 : 1536))))) return no;
+        if (wgs > 512) return no;
+        if (wgs > 256 && (N <= 64 || (!v8 && N > (d == 64 ? 2560 : 1536)))) return no;
         if (!fp8 && d == 128 && wgs <= 256 && (N / pick.splits + 127) / 128 > 12 && N >= (wgs <= 128 ? 3072 : 2048)) return no;
         return plan;
     }
     if (d == 64) return plan;
     if (v8) return wgs <= 512 || (wgs <= 768 && (row_tiles == 1 || rounds > 3)) || rounds > 4 ? plan : no;
     const long kb = heads * (long)N * (fp8 ? 384 : 512) / 1000;
-    // (calls from memory must win by a twentieth: 128 heads, 11 rows, 2423 keys fp8 24.3 streamed / 26.4, predicted 24.8 / 23.2)
-    return pick.cost != 0 && pick.cost * (kb > 80000 ? 20 : 19) <= 19 * stream_cost(fp8 ? kStreamFp8 : kStreamBf16, rows, heads, N, kb, refresh, stream_splits) ? plan : no;
+    const long streamed = stream_cost(fp8 ? kStreamFp8 : kStreamBf16, rows, heads, N, kb, refresh, stream_splits);
+    return pick.cost != 0 && pick.cost * (kb > 80000 ? 20 : 19) <= 19 * streamed ? plan : no;
 }
 
 // Verifier calls: the form alone.

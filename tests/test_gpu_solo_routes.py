@@ -1,0 +1,53 @@
+"""Which kernel, form and key splits the library's rules pick, told by the bits of the result: a call by rule gives those of the same call
+forced there by hook, and not those of the route that its neighbours across a line of the rule take."""
+import pytest
+
+import paper_2604_05250_amd as dd
+from paper_2604_05250_amd import workloads as wl
+from _kernels import solo_form
+
+pytestmark = pytest.mark.gpu
+BF16, FP8 = wl.BF16, wl.FP8_E4M3
+ELSEWHERE = {"DD_TUNE_SOLO": "0"}
+HOOKS = ("DD_TUNE_SOLO", "DD_TUNE_SOLO_FORM", "DD_TUNE_BLOCK_SPLITS")
+# (q and k, v, head dims), (B, H, Hkv, N, block_len, fresh), the rule's route, another one
+DRAFTS = [
+    # long streams of few workgroups: in key splits, not eight waves with every one of them (from the cache alone that is faster)
+    ((FP8, BF16, 128), (4, 32, 8, 3643, 16, True), solo_form(128, 2), solo_form(148)),
+    ((BF16, BF16, 128), (4, 32, 8, 2250, 16, True), solo_form(114, 4), solo_form(148)),
+    ((FP8, FP8, 128), (3, 16, 16, 3773, 32, True), solo_form(114, 5), solo_form(148)),
+    ((FP8, FP8, 128), (6, 32, 32, 1598, 32, True), solo_form(114), solo_form(124)),
+    ((FP8, BF16, 128), (1, 32, 32, 1024, 32, True), solo_form(148), solo_form(114, 4)),       # (a short one stays)
+]
+
+
+def by(monkeypatch, env, call):
+    import torch
+    for k in HOOKS:
+        monkeypatch.delenv(k, raising=False)
+    for k, v in env.items():
+        monkeypatch.setenv(k, v)
+    O = call()
+    torch.cuda.synchronize()
+    return O
+
+
+@pytest.mark.parametrize("store,shape,here,there", DRAFTS)
+def test_drafter_routes(monkeypatch, store, shape, here, there):
+    import torch
+    (qk, v, d), (B, H, Hkv, N, bl, fresh) = store, shape
+    g = torch.Generator(device="cuda:0").manual_seed(N)
+    normal = lambda *s: torch.randn(s, generator=g, device="cuda:0")
+    of = lambda x, t: (x * 90).clamp(-448, 448).to(torch.float8_e4m3fn) if t == FP8 else x.bfloat16()
+    Q, K, V = of(normal(B, H, bl, d), qk), of(normal(B, Hkv, N, d), qk), of(normal(B, Hkv, N, d), v)
+    Kb, Vb = (of(normal(B, Hkv, bl, d), qk), of(normal(B, Hkv, bl, d), v)) if fresh else (None, None)
+    scale = lambda heads: torch.full((B, heads), 1 / 90, device="cuda:0")
+    s = {"q_scale": scale(H), "k_scale": scale(Hkv)} if qk == FP8 else {}
+
+    def call():
+        if v == FP8:
+            return dd.dd_block_attention_cached_fp8v(Q, K, V, 0, scale(H), scale(Hkv), scale(Hkv), Kblk=Kb, Vblk=Vb)
+        return dd.dd_block_attention_cached(Q, K, V, 0, Kblk=Kb, Vblk=Vb, **s)
+    got, want, other = by(monkeypatch, {}, call), by(monkeypatch, here, call), by(monkeypatch, there, call)
+    assert not torch.equal(want, other), "the bits do not tell the two routes apart"
+    assert torch.equal(got, want)

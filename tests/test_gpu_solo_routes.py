@@ -18,6 +18,9 @@ DRAFTS = [
     ((FP8, FP8, 128), (3, 16, 16, 3773, 32, True), solo_form(114, 5), solo_form(148)),
     ((FP8, FP8, 128), (6, 32, 32, 1598, 32, True), solo_form(114), solo_form(124)),
     ((FP8, BF16, 128), (1, 32, 32, 1024, 32, True), solo_form(148), solo_form(114, 4)),       # (a short one stays)
+    # e4m3 V, more than 64 rows, 257 to 512 workgroups: at 64 keys and fewer too
+    ((FP8, FP8, 128), (6, 32, 8, 64, 64, True), solo_form(114), ELSEWHERE),
+    ((FP8, FP8, 128), (12, 28, 4, 40, 24, True), solo_form(114), ELSEWHERE),
 ]
 
 

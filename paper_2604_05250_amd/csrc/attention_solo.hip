@@ -643,7 +643,9 @@ long stream_cost(const StreamTerms &t, long rows, long heads, int N, long kb, bo
 //     3072 on (8 heads, 256 rows, 1708 keys 15.0 -> 11.1; 32 x 112, 4083 keys 24.8 / 28.1; 48 x 96, 2946 keys 25.2 / 30.9).
 //   - up to 512, bf16 and fp8: 0.82 - 0.97 from 65 to 1536 keys (d = 64 to 2560), longer ones up to 1.2 (88 heads, 120 rows, 3084 keys
 //     fp8 36.9 / 45.0).  These figures are from the cache; from memory the last third of that range is up to 1.1 the other way.
-//   - up to 512, e4m3 V: 0.45 - 0.93 at any length, 64 keys and fewer included (48 heads x 256 rows, 64 keys 10.8 -> 6.1).
+//   - up to 512, e4m3 V: 0.45 - 0.93 at any length, 64 keys and fewer included (48 heads x 256 rows, 64 keys 10.8 -> 6.1), except where rows fill
+//     the wide kernel's 256-row tiles and the stream is long: 40 x 256, 4096 keys 39.7 / 47.9, 20 x 448, 3800 keys 33.4 / 39.8,
+//     48 x 256, 3700 keys 37.2 / 42.0; with 512 workgroups 64 x 256, 4050 keys 47.3 / 54.9.  Tiles a quarter empty: 32 x 384, 3495 keys 51 -> 40.
 //   - past 512 1.06 - 1.3.
 //
 // Up to 64 rows:
@@ -672,6 +674,8 @@ SoloPlan attn_solo_plan(long rows, long heads, int N, int d, bool fp8, bool v8, 
     if (rows > 64) {
         if (wgs > 512) return no;
         if (wgs > 256 && !v8 && (N <= 64 || N > (d == 64 ? 2560 : 1536))) return no;
+        if (wgs > 384 && v8 && N > 3840 && rows % 256 == 0) return no;
+        if (wgs > 256 && wgs <= 384 && v8 && N > 3328 && 8 * rows >= 7 * ((rows + 255) / 256 * 256)) return no;
         if (!fp8 && d == 128 && wgs <= 256 && (N / pick.splits + 127) / 128 > 12 && N >= (wgs <= 128 ? 3072 : 2048)) return no;
         return plan;
     }

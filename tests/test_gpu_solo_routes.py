@@ -18,9 +18,15 @@ DRAFTS = [
     ((FP8, FP8, 128), (3, 16, 16, 3773, 32, True), solo_form(114, 5), solo_form(148)),
     ((FP8, FP8, 128), (6, 32, 32, 1598, 32, True), solo_form(114), solo_form(124)),
     ((FP8, BF16, 128), (1, 32, 32, 1024, 32, True), solo_form(148), solo_form(114, 4)),       # (a short one stays)
-    # e4m3 V, more than 64 rows, 257 to 512 workgroups: at 64 keys and fewer too
+    # e4m3 V, more than 64 rows, 257 to 512 workgroups: at 64 keys and fewer too ...
     ((FP8, FP8, 128), (6, 32, 8, 64, 64, True), solo_form(114), ELSEWHERE),
     ((FP8, FP8, 128), (12, 28, 4, 40, 24, True), solo_form(114), ELSEWHERE),
+    # ... but not long streams whose rows fill the wide kernel's tiles
+    ((FP8, FP8, 128), (5, 32, 8, 3328, 64, True), solo_form(224), ELSEWHERE),
+    ((FP8, FP8, 128), (5, 32, 8, 3329, 64, True), ELSEWHERE, solo_form(224)),
+    ((FP8, FP8, 128), (4, 32, 8, 3500, 96, True), solo_form(224), ELSEWHERE),                 # 384 rows: a tile is half empty
+    ((FP8, FP8, 128), (8, 32, 8, 3840, 64, True), solo_form(224), ELSEWHERE),
+    ((FP8, FP8, 128), (8, 32, 8, 3841, 64, True), ELSEWHERE, solo_form(224)),
 ]
 
 

@@ -653,7 +653,8 @@ long stream_cost(const StreamTerms &t, long rows, long heads, int N, long kb, bo
 //   - e4m3 V, against the MFMA kernel: up to 512 workgroups of 32 rows; then where a head's rows are one workgroup, or streams are longer
 //     than three rounds of 128 keys (up to 768) or four (11 x 32, 63 rows, 90 keys 9.3 there / 10.5).
 //   - bf16 and fp8, against the streaming kernel: by its cost (0.91 and 0.87 of the time of one form by rule).  Calls from memory must win by a
-//     twentieth (128 heads, 11 rows, 2423 keys fp8 24.3 streamed / 26.4, predicted 24.8 / 23.2).
+//     twentieth (128 heads, 11 rows, 2423 keys fp8 24.3 streamed / 26.4, predicted 24.8 / 23.2), and fp8 rows of one workgroup, two workgroups
+//     to a compute unit, stay streamed past 100 MB (288 heads, 32 rows, 1500 keys 39.5 / 41.8, 320 x 32, 892 keys 24.5 / 26.0).
 SoloPlan attn_solo_plan(long rows, long heads, int N, int d, bool fp8, bool v8, bool refresh, int stream_splits)
 {
     const int forced = tune("DD_TUNE_SOLO", -1), forced_splits = tune("DD_TUNE_BLOCK_SPLITS", 0);
@@ -682,6 +683,7 @@ SoloPlan attn_solo_plan(long rows, long heads, int N, int d, bool fp8, bool v8, 
     if (d == 64) return plan;
     if (v8) return wgs <= 512 || (wgs <= 768 && (row_tiles == 1 || rounds > 3)) || rounds > 4 ? plan : no;
     const long kb = heads * (long)N * (fp8 ? 384 : 512) / 1000;
+    if (fp8 && wgs > 256 && row_tiles == 1 && kb > 100000) return no;
     const long streamed = stream_cost(fp8 ? kStreamFp8 : kStreamBf16, rows, heads, N, kb, refresh, stream_splits);
     return pick.cost != 0 && pick.cost * (kb > 80000 ? 20 : 19) <= 19 * streamed ? plan : no;
 }

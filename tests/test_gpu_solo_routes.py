@@ -30,6 +30,10 @@ DRAFTS = [
     # fp8, one workgroup of rows per head, two to a compute unit: streamed past 100 MB
     ((FP8, BF16, 128), (9, 32, 32, 904, 32, True), solo_form(114), ELSEWHERE),
     ((FP8, BF16, 128), (9, 32, 32, 905, 32, True), ELSEWHERE, solo_form(114)),
+    # a block that is the whole sequence
+    ((BF16, BF16, 128), (5, 16, 16, 24, 24, True), ELSEWHERE, solo_form(124)),
+    ((BF16, BF16, 128), (5, 16, 16, 24, 24, False), solo_form(124), ELSEWHERE),
+    ((BF16, BF16, 128), (5, 16, 16, 25, 24, True), solo_form(124), ELSEWHERE),
 ]
 
 

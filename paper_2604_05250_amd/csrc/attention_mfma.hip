@@ -737,30 +737,32 @@ hipError_t launch_attention_mfma(const AttnArgs &a, hipStream_t stream)
     const long heads = (long)a.B * a.Hkv, rows = (long)(a.H / a.Hkv) * a.Nq;
     const bool one_round64 = heads * ((rows + 63) / 64) <= 256, one_round128 = heads * ((rows + 127) / 128) <= 256;
     if (!blk && tune("DD_TUNE_ATTN_WIDE", -1) < 0 && tune("DD_TUNE_BIDIR_STREAM", -1) < 0) {
-        // Up to two workgroups of 32 rows per compute unit: the kernel whose waves stream keys of their own.  us, on the kernels below ->
-        // there: 1 x 32 heads, N 300 10.9 -> 9.2, N 512 14.7 -> 13.3, fp8 Q and K 13.2 -> 11.1, d = 64 10.1 -> 7.4; 1 x 16, N 512 12.6 -> 8.1; 1 x 8, N 1024
-        // 19.3 -> 11.3.  Over 380 drawn calls of more than 64 keys 0.78 of the time up to 256 workgroups,
-        // 0.91 up to 512, then 1.1 (1 x 60, N 300 15.9 against 14.1).  e4m3 values: 0.66 up to 256 workgroups, 0.78 up to 512, then 1.1 as well.
-        // Past 448 workgroups of more than 1024 keys, against the kernels below: e4m3 values 0.66 - 0.78 and d = 64 0.82 - 0.87 at any length (8 heads,
-        // N 2046 35.6 -> 26.6; 11, N 1289 14.3 -> 11.9), fp8 0.90 - 0.95 up to 2048 keys, 0.985 at 3081, then up to 1.03, bf16 0.97 - 0.99 up to 1349,
-        // then up to 1.06 (6 heads, N 2590 32.5 / 34.6); any type where the two-waves-per-SIMD kernel does not hold the call in one round 0.61 - 0.80
-        // (bf16 10 heads, N 1613 30.0 -> 24.0).  d = 64 from 512 keys on also up to three workgroups per compute unit, 0.86 - 1.0 (8 heads,
-        // N 2674 33.3 -> 29.2), then 1.0 - 1.1 (26 heads, N 1015 17.4 / 18.5); shorter up to 1.09.
-        // 64 keys and fewer: up to 256 workgroups (d = 64: 192), whose head dims it
-        // then divides: bf16 1 x 16, N 33 5.4 -> 4.6, 6 x 32, N 49 5.9 -> 5.3, fp8 1 x 32, N 48 5.2 -> 4.2; 384 workgroups, N 33 5.6 / 6.2.
+        // The kernel whose waves stream keys of their own, up to two workgroups of 32 rows per compute unit.  us, on the kernels below -> there:
+        // 1 x 32 heads, N 300 10.9 -> 9.2, N 512 14.7 -> 13.3, fp8 Q and K 13.2 -> 11.1, d = 64 10.1 -> 7.4; 1 x 16, N 512 12.6 -> 8.1; 1 x 8, N 1024
+        // 19.3 -> 11.3.  Over 380 drawn calls of more than 64 keys 0.78 of the time up to 256 workgroups, 0.91 up to 512, then 1.1 (1 x 60,
+        // N 300 15.9 against 14.1); e4m3 values 0.66, 0.78 and 1.1.  Other limits:
+        //   - 449 to 512 workgroups that the two-waves-per-SIMD kernel holds in one round: bf16 to 1344 keys (0.97 - 0.99, then up to 1.06: 6 heads,
+        //     N 2590 32.5 / 34.6), fp8 to 3072 (0.90 - 0.985, then up to 1.03).  e4m3 values 0.66 - 0.78 and d = 64 0.82 - 0.87 at any length (8 heads,
+        //     N 2046 35.6 -> 26.6; 11, N 1289 14.3 -> 11.9), and any type that it does not hold in one round 0.61 - 0.80 (bf16 10 heads, N 1613 30.0 -> 24.0).
+        //   - d = 64 from 512 keys on: three workgroups per compute unit, 0.86 - 1.0 (8 heads, N 2674 33.3 -> 29.2), then 1.0 - 1.1 (26 heads,
+        //     N 1015 17.4 / 18.5); shorter up to 1.09.
+        //   - 64 keys and fewer: 256 workgroups (d = 64: 192), whose head dims it then divides: bf16 1 x 16, N 33 5.4 -> 4.6, 6 x 32, N 49 5.9 -> 5.3,
+        //     fp8 1 x 32, N 48 5.2 -> 4.2; 384 workgroups, N 33 5.6 / 6.2.
+        //   - twelve keys and fewer: 128 (but bf16 with 128 head dims), where parts no longer pay: fp8 192 heads, N 6 4.1 / 4.4; d = 64 160, N 9 3.85 / 3.95.
         const long wgs = heads * ((rows + 31) / 32);
         const bool v8 = a.v_dtype == 2;
         const int longest = v8 || a.d == 64 || !one_round64 ? a.N : fp8 ? 3072 : 1344;
-        const long most = a.N <= 64 ? (a.d == 64 ? 192 : 256) : a.N > longest ? 448 : a.d == 64 && a.N >= 512 ? 768 : 512;
+        long most = a.N > longest ? 448 : a.d == 64 && a.N >= 512 ? 768 : 512;
+        if (a.N <= 64) most = a.N <= 12 && (fp8 || a.d == 64) ? 128 : a.d == 64 ? 192 : 256;
         const int solo = tune("DD_TUNE_SOLO", tune("DD_TUNE_DUO", -1) <= 0 && wgs <= most);
         if (solo != 0 && attn_solo_serves(a))
             return launch_attention_solo(a, attn_solo_form(rows, heads, a.N, a.d, fp8, v8), stream);
     }
     if (!blk && attn_duo_serves(a) && tune("DD_TUNE_ATTN_WIDE", -1) < 0 && tune("DD_TUNE_BIDIR_STREAM", -1) < 0) {
         // One round of 64-row workgroups: the two-waves-per-SIMD kernel, whose eight waves share a workgroup's keys.  Of these calls the
-        // one above leaves it those of 449 to 512 workgroups of 32 rows and more than 1024 keys.  us, on the wide kernel -> there (bf16 / fp8 Q
-        // and K): 1 x 8 heads, N 2048 37.6 -> 32.0 / 34.2 -> 23.3; 1 x 4, N 4096 67.3 -> 56.8 / 60.1 -> 39.2.  On its 128-row workgroups, one
-        // round of them: 32 x N 1024 23.5 -> 24.4, 16 x N 2048 40.2 -> 40.2, fp8 32.6 -> 33.4: no.
+        // one above leaves it those of 449 to 512 workgroups of 32 rows past its limits of keys (bf16 1344, fp8 with bf16 V 3072).  us, on the
+        // wide kernel -> there: bf16 1 x 8 heads, N 2048 37.6 -> 32.0, 1 x 4, N 4096 67.3 -> 56.8, fp8 60.1 -> 39.2.  On its 128-row workgroups,
+        // one round of them: 32 x N 1024 23.5 -> 24.4, 16 x N 2048 40.2 -> 40.2, fp8 32.6 -> 33.4: no.
         const int forced = tune("DD_TUNE_DUO", -1);
         const int blocks = forced >= 0 ? forced : one_round64 && a.N > 1024 ? 2 : 0;
         if (blocks == 2 || blocks == 4) return launch_attention_duo(a, blocks, stream);

@@ -122,8 +122,9 @@ int attn_wide_block_rows(int block_len, int B, int H, int Hkv, int N);      // 2
 hipError_t launch_attention_wide_block(const AttnArgs &a, hipStream_t stream);
 bool attn_stream_fits(const AttnArgs &a);
 // Two waves per SIMD: drafter calls with more than 64 query rows per kv head that fit one round of its workgroups and are not served by the
-// next kernel, verifier calls of 449 to 512 workgroups of 32 rows and more than 1024 keys.  Which storage types and head dims it serves; how it takes a drafter call with `rows` query rows in each of
-// `heads` (batch, kv head) pairs: 32-row blocks per workgroup (2 or 4; 0: not at all) and key splits; the launch (+ merge).
+// next kernel, and verifier calls of 449 to 512 workgroups of 32 rows that are too long for it (bf16 past 1344 keys, fp8 with bf16 V past 3072).
+// Which storage types and head dims it serves; how it takes a drafter call with `rows` query rows in each of `heads` (batch, kv head)
+// pairs: 32-row blocks per workgroup (2 or 4; 0: not at all) and key splits; the launch (+ merge).
 struct DuoPlan { int blocks, splits; };
 bool attn_duo_serves(const AttnArgs &a);
 DuoPlan attn_duo_plan(long rows, long heads, int N, bool light);   // light: fp8 keys or 64 head dims

@@ -5,6 +5,7 @@ import pytest
 import paper_2604_05250_amd as dd
 from paper_2604_05250_amd import workloads as wl
 from _kernels import solo_form
+from _util import to_dev
 
 pytestmark = pytest.mark.gpu
 BF16, FP8 = wl.BF16, wl.FP8_E4M3
@@ -67,3 +68,16 @@ def test_drafter_routes(monkeypatch, store, shape, here, there):
     got, want, other = by(monkeypatch, {}, call), by(monkeypatch, here, call), by(monkeypatch, there, call)
     assert not torch.equal(want, other), "the bits do not tell the two routes apart"
     assert torch.equal(got, want)
+
+
+@pytest.mark.parametrize("qk,v,d,H,N,here", [(FP8, BF16, 128, 128, 12, True), (FP8, BF16, 128, 129, 12, False), (FP8, BF16, 128, 129, 13, True),
+                                             (FP8, FP8, 128, 129, 12, False), (BF16, BF16, 64, 129, 12, False), (BF16, BF16, 128, 129, 12, True)])
+def test_verifier_routes_of_few_keys(monkeypatch, qk, v, d, H, N, here):
+    import torch
+    cfg = wl.custom_config(B=1, H=H, Hkv=H, N=N, d=d, qk_dtype=qk, v_dtype=v, prompt=0, G=N, bl=N)
+    inp = wl.attention_inputs(cfg, seed=N + d)
+    Q, K, V, qs, ks, vs = (to_dev(inp.get(k)) if inp.get(k) is not None else None for k in ("Q", "K", "V", "q_scale", "k_scale", "v_scale"))
+    call = lambda: dd.dd_bidir_attention_fp8v(Q, K, V, qs, ks, vs) if v == FP8 else dd.dd_bidir_attention(Q, K, V, q_scale=qs, k_scale=ks, qk_dtype=qk, v_dtype=v)
+    got, solo, other = by(monkeypatch, {}, call), by(monkeypatch, {"DD_TUNE_SOLO": "1"}, call), by(monkeypatch, ELSEWHERE, call)
+    assert not torch.equal(solo, other), "the bits do not tell the two routes apart"
+    assert torch.equal(got, solo if here else other)

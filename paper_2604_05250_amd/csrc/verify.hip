@@ -14,6 +14,7 @@
 // identical; the last merge and the log / divide are done in fp64.
 #include "dd_internal.h"
 
+#include <algorithm>
 #include <limits.h>
 #include <math.h>
 
@@ -906,13 +907,13 @@ int verify_fused_threads(int P)
 // Otherwise a split is a whole number of full load rounds (kThreads * kUnroll vectors), so that only the last of a row is ragged: every
 // round of a workgroup is a dependent memory round trip, and with few rows those round trips are the call.  These are also what a call
 // takes whose workspace does not hold the states of shorter ones.  A row of one such round is not split.
-constexpr int kMaxRowSplits = 16, kFineWorkgroups = 256;
+constexpr int kRowWorkgroups = 2048, kMaxRowSplits = 16, kFineWorkgroups = 256;      // (about 2048 workgroups in all)
 struct RowSplits { int count, chunk; };              // of a row; vectors in each
 static RowSplits row_splits(int P, int V, int elem_bytes, size_t workspace_bytes)
 {
     const long nvec = (long)V * elem_bytes / 16, iter = (long)kThreads * kUnroll;
     if (nvec <= iter) return RowSplits{1, (int)iter};
-    long s = (2048 + P - 1) / P;         // about 2048 workgroups in all
+    long s = (kRowWorkgroups + P - 1) / P;
     if (s > kMaxRowSplits) s = kMaxRowSplits;
     if (s < 1) s = 1;
     const long shortest = (nvec + s - 1) / s;
@@ -942,14 +943,23 @@ static bool seq_in_one_launch(int G, int nvec, bool bf16, bool kl)
     return rounds <= (kl ? kSeqMaxRoundsKl : kSeqMaxRounds) && (!bf16 || (long)G * nvec <= (kl ? 2560 : 5120));
 }
 
-// Room for the most splits that any count of rows up to P has (a row has at most sixteen, of kThreads vectors or more), so that a size
-// queried for P rows, up to 191, serves fewer: P rows' own splits can be half of what P - 1 have (126464 bf16 logits, 136 rows: 16, 137: 8).
+// The most states that any count of rows up to P has, so that a size queried for P rows, up to 191, serves fewer: where one more row lowers
+// the splits, its states can be half of what one row less has (126464 bf16 logits, 136 rows 16 splits, 137 rows 8).
 size_t verify_workspace_bytes(int P, int V, int elem_bytes)
 {
     if (P <= 0 || verify_fused_threads(P) != 0) return 0;
-    const long nvec = (long)V * elem_bytes / 16, parts = (nvec + kThreads - 1) / kThreads;
-    const long most = nvec <= (long)kThreads * kUnroll ? 1 : parts < kMaxRowSplits ? parts : kMaxRowSplits;
-    return (size_t)P * (size_t)most * sizeof(VerifyPartial);
+    const long nvec = (long)V * elem_bytes / 16;
+    long most = (long)P * row_splits(P, V, elem_bytes, SIZE_MAX).count;
+    if (nvec > (long)kThreads * kUnroll) {
+        const long fine = P * row_splits(1, V, elem_bytes, SIZE_MAX).count;
+        most = std::max(most, std::min(fine, (long)kFineWorkgroups));
+        for (int s = kMaxRowSplits; s > 1; --s) {
+            const int last = (kRowWorkgroups + s - 2) / (s - 1) - 1;             // the most rows that are split s times
+            if (last >= P) break;
+            most = std::max(most, (long)last * row_splits(last, V, elem_bytes, 0).count);
+        }
+    }
+    return (size_t)most * sizeof(VerifyPartial);
 }
 
 size_t verify_least_workspace_bytes(int P, int V, int elem_bytes)

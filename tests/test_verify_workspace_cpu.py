@@ -13,3 +13,13 @@ def test_a_workspace_serves_fewer_rows(dtype, V):
     assert dd.dd_verify_remask_workspace_bytes(1, 192, V, dtype) == 0
     for call in (dd.dd_unmask_workspace_bytes, lambda B, G, V, t: dd.dd_verify_scores_workspace_bytes(B * G, V, t)):
         assert [call(1, P, V, dtype) for P in range(1, 192)] == need
+
+
+@pytest.mark.parametrize("V", [8200, 32000, 90184, 126464, 152064])
+def test_the_query_holds_what_a_call_splits_into(V):
+    # splits of whole load rounds (1024 vectors), about 2048 workgroups in all; of 256 vectors where that is at most 256 workgroups
+    nvec = V // 8
+    for P in range(1, 192):
+        shortest = -(-nvec // max(1, min(16, -(-2048 // P))))
+        fine, rounds = (P * -(-nvec // (-(-shortest // m) * m)) for m in (256, 1024))
+        assert dd.dd_verify_remask_workspace_bytes(1, P, V, dd.BF16) >= 32 * (fine if fine <= 256 else rounds), P

@@ -287,18 +287,20 @@ __device__ __forceinline__ bool reduce_range(const uint4 *__restrict__ pv, const
         for (int u = 0; u < kUnroll; ++u)
             consume<BF16, KL, TRACKD>(rv[u], rd[u], true, (base + u * THREADS + tid) * E, st);
     }
-    // Ragged remainder of the range: every load is issued (past the end, of the last vector) and the vectors that no lane of the wave
-    // has are not folded.  With loads under a lane's own condition the round was four round trips: 512 x 32000 KL 17.8 us, now 17.2;
-    // 128 x 32000 11.0 / 10.5; 1024 x 50264 confidence 21.9 / 21.1; 64 x 1024 fp32 KL 4.15 / 4.02.
+    // Ragged remainder of the range: the vectors that some lane of the wave has are asked for together (past the end the last vector), and
+    // folded after that.  With loads under a lane's own condition the round was four round trips: 512 x 32000 KL 17.8 us, now 17.2;
+    // 128 x 32000 11.0 / 10.5; 1024 x 50264 confidence 21.9 / 21.1; 64 x 1024 fp32 KL 4.15 / 4.02.  With every load issued, also of vectors
+    // that no lane of the wave has, short rows were slower (fp32 KL 1122 x 816 8.5 / 9.1, 910 x 1424 8.6 / 9.1).
     if (base < vend) {
         uint4 rv[kUnroll], rd[kUnroll];
+        const int wave_base = base + (__builtin_amdgcn_readfirstlane(tid) & ~63);
 #pragma unroll
         for (int u = 0; u < kUnroll; ++u) {
+            if (wave_base + u * THREADS >= vend) break;
             const int at = min(base + u * THREADS + tid, vend - 1);
             rv[u] = stream_load16(pv + at);
             if (KL) rd[u] = stream_load16(pd + at);
         }
-        const int wave_base = base + (__builtin_amdgcn_readfirstlane(tid) & ~63);
 #pragma unroll
         for (int u = 0; u < kUnroll; ++u) {
             if (wave_base + u * THREADS >= vend) break;

@@ -70,11 +70,13 @@ def test_drafter_routes(monkeypatch, store, shape, here, there):
     assert torch.equal(got, want)
 
 
-@pytest.mark.parametrize("qk,v,d,H,N,here", [(FP8, BF16, 128, 128, 12, True), (FP8, BF16, 128, 129, 12, False), (FP8, BF16, 128, 129, 13, True),
-                                             (FP8, FP8, 128, 129, 12, False), (BF16, BF16, 64, 129, 12, False), (BF16, BF16, 128, 129, 12, True)])
-def test_verifier_routes_of_few_keys(monkeypatch, qk, v, d, H, N, here):
+@pytest.mark.parametrize("qk,v,d,H,Hkv,N,here", [
+    (FP8, BF16, 128, 128, 128, 12, True), (FP8, BF16, 128, 129, 129, 12, False), (FP8, BF16, 128, 129, 129, 31, False), (FP8, BF16, 128, 129, 129, 32, True),
+    (FP8, FP8, 128, 129, 129, 31, False), (BF16, BF16, 64, 129, 129, 31, False), (BF16, BF16, 128, 129, 129, 12, True),
+    (FP8, BF16, 128, 325, 65, 9, False), (FP8, BF16, 128, 390, 65, 8, True)])                 # 45 and 48 rows per kv head, 130 workgroups
+def test_verifier_routes_of_few_keys(monkeypatch, qk, v, d, H, Hkv, N, here):
     import torch
-    cfg = wl.custom_config(B=1, H=H, Hkv=H, N=N, d=d, qk_dtype=qk, v_dtype=v, prompt=0, G=N, bl=N)
+    cfg = wl.custom_config(B=1, H=H, Hkv=Hkv, N=N, d=d, qk_dtype=qk, v_dtype=v, prompt=0, G=N, bl=N)
     inp = wl.attention_inputs(cfg, seed=N + d)
     Q, K, V, qs, ks, vs = (to_dev(inp.get(k)) if inp.get(k) is not None else None for k in ("Q", "K", "V", "q_scale", "k_scale", "v_scale"))
     call = lambda: dd.dd_bidir_attention_fp8v(Q, K, V, qs, ks, vs) if v == FP8 else dd.dd_bidir_attention(Q, K, V, q_scale=qs, k_scale=ks, qk_dtype=qk, v_dtype=v)

@@ -556,7 +556,8 @@ bool attn_solo_serves(const AttnArgs &a)
 
 // What a form costs, in hundredths of a microsecond: a workgroup, that again per 100 workgroups beside it, a round (every wave of the
 // workgroup one unit), a round past the fourth on top, and, in tenths, a megabyte of K and V, and one of those past 80; `pair` is the same
-// past 256 workgroups, two to a compute unit (four waves only, up to 512 workgroups).
+// past 256 workgroups, two to a compute unit (four waves only, up to 512 workgroups; divided head dims with the cache refresh, whose workgroups
+// then come on top, to 480: 256 heads, 32 rows, 33 keys 7.4 on 124, 6.1 on 114).
 // Fitted per storage type and form to the times of 4000 drawn drafter calls on three sets of inputs in turn, which the last-level cache
 // holds up to 80 MB (1 - 16 x 8 head counts, 1 - 64 rows per head, 20 - 4200 keys, 1 - 16 splits, some 30000 timings; rms of the fits 2 - 7 %).  `late`
 // and the constants of 118 were then searched over 7700 drawn calls timed on such inputs and on 650 MB of them in turn, from memory, as a
@@ -591,14 +592,14 @@ long megabytes(int mb, int cold, long kb)                                    // 
 }
 struct SoloPick { int form, splits; long cost; };                            // form 0: none
 template <size_t FORMS>
-SoloPick cheapest(const SoloCost (&forms)[FORMS], int only, long rows, long heads, int N, long kb, int merge_rows, int most_splits)
+SoloPick cheapest(const SoloCost (&forms)[FORMS], int only, long rows, long heads, int N, long kb, int merge_rows, int most_splits, bool refresh)
 {
     SoloPick best{0, 1, 0};
     for (const SoloCost &f : forms) {
         const int blocks = f.form / 100, parts = f.form / 10 % 10, waves = f.form % 10;
         if (only != 0 ? f.form != only : blocks == 2 && rows <= 32) continue;
         const long w1 = heads * ((rows + 32 * blocks - 1) / (32 * blocks)) * parts;
-        if (w1 > (waves == 8 ? 256 : 512) && only == 0) continue;
+        if (w1 > (waves == 8 ? 256 : refresh && parts > 1 ? 480 : 512) && only == 0) continue;
         int last = 0;
         for (int s = 1; s <= most_splits && (s == 1 || w1 * s <= 256); ++s) {
             const int keys = ((N + s - 1) / s + 31) / 32 * 32, rounds = (keys + 32 * waves - 1) / (32 * waves);
@@ -612,14 +613,14 @@ SoloPick cheapest(const SoloCost (&forms)[FORMS], int only, long rows, long head
     }
     return best;
 }
-SoloPick solo_pick(long rows, long heads, int N, int d, bool fp8, bool v8, int most_splits)
+SoloPick solo_pick(long rows, long heads, int N, int d, bool fp8, bool v8, int most_splits, bool refresh)
 {
     const int only = tune("DD_TUNE_SOLO_FORM", 0);
     const long kb = heads * (long)N * (d == 64 || v8 ? 256 : fp8 ? 384 : 512) / 1000;
-    return d == 64 ? cheapest(kSoloD64, only, rows, heads, N, kb, kMergeRowsD64, most_splits)
-         : v8      ? cheapest(kSoloV8, only, rows, heads, N, kb, kMergeRows, most_splits)
-         : fp8     ? cheapest(kSoloFp8, only, rows, heads, N, kb, kMergeRows, most_splits)
-                   : cheapest(kSoloBf16, only, rows, heads, N, kb, kMergeRows, most_splits);
+    return d == 64 ? cheapest(kSoloD64, only, rows, heads, N, kb, kMergeRowsD64, most_splits, refresh)
+         : v8      ? cheapest(kSoloV8, only, rows, heads, N, kb, kMergeRows, most_splits, refresh)
+         : fp8     ? cheapest(kSoloFp8, only, rows, heads, N, kb, kMergeRows, most_splits, refresh)
+                   : cheapest(kSoloBf16, only, rows, heads, N, kb, kMergeRows, most_splits, refresh);
 }
 long stream_cost(const StreamTerms &t, long rows, long heads, int N, long kb, bool refresh, int splits)
 {
@@ -663,7 +664,7 @@ SoloPlan attn_solo_plan(long rows, long heads, int N, int d, bool fp8, bool v8, 
     const SoloPlan no{false, 0, 1};
     if (forced == 0) return no;
     const long row_tiles = (rows + 31) / 32, wgs = heads * row_tiles;
-    SoloPick pick = solo_pick(rows, heads, N, d, fp8, v8, stream_splits);
+    SoloPick pick = solo_pick(rows, heads, N, d, fp8, v8, stream_splits, refresh);
     if (pick.form == 0) pick.form = v8 && row_tiles == 2 ? 224 : 114;        // (more workgroups than the costs know)
     const SoloPlan plan{true, pick.form, forced_splits >= 1 ? stream_splits : pick.splits};
     if (forced == 1) return plan;
@@ -693,7 +694,7 @@ SoloPlan attn_solo_plan(long rows, long heads, int N, int d, bool fp8, bool v8, 
 // Verifier calls: the form alone.
 int attn_solo_form(long rows, long heads, int N, int d, bool fp8, bool v8)
 {
-    const int form = solo_pick(rows, heads, N, d, fp8, v8, 1).form;
+    const int form = solo_pick(rows, heads, N, d, fp8, v8, 1, false).form;
     return form != 0 ? form : 114;
 }
 

@@ -632,14 +632,16 @@ long stream_cost(const StreamTerms &t, long rows, long heads, int N, long kb, bo
 }  // namespace
 
 // Drafter calls: the cheapest form and key splits (as many as leave every workgroup a compute unit), where that beats the other kernels.
-// `all_fresh`: the block is the whole sequence, so nothing is read from the cache.
+// `fresh`: keys that come from the block's own rows (N: all of them, nothing is read from the cache).
 //
 // At most 64 keys are one tile of the other kernels, and nothing for waves to stream.  Few rows stay off this kernel there, unless
 //   - its parts spread the call, up to 96 workgroups of 32 rows (bf16 5.05 -> 4.6, fp8 and e4m3 V 4.6 -> 4.35; with 240 5.36 / 5.65 and
 //     4.66 / 5.3 the other way; 64 head dims never: 4.05 / 4.25), and bf16 reads some row from the cache (80 heads, 8 keys, all of them the
 //     block's 3.98 / 4.42), or
 //   - the call has the cache refresh, a launch of its own on the others.
-// So do more than 512 workgroups where a head's rows are two (d = 64, 272 heads, 48 rows, 48 keys 5.3 / 7.6).
+// So do more than 512 workgroups where a head's rows are two (d = 64, 272 heads, 48 rows, 48 keys 5.3 / 7.6).  Up to 256 workgroups of more rows
+// run here (bf16 120 heads, 64 rows, 48 keys 5.95 -> 5.1, 64 keys 5.85 -> 4.7, fp8 64 keys 4.95 -> 4.45), but where keys of both kinds meet
+// in a unit that is not full: bf16 of fewer than 56 rows (40 rows, 33 keys 5.3 / 5.5) and fp8 (56 rows, 33 keys 4.92 / 5.17) by their cost.
 //
 // More than 64 rows (against the two-waves-per-SIMD, the wide and the MFMA kernel; some 350 drawn calls per type):
 //   - up to 256 workgroups 0.46 - 0.9 of the time.  bf16 past twelve rounds of 128 keys loses from 2048 keys on, on at most 128 workgroups from
@@ -658,7 +660,7 @@ long stream_cost(const StreamTerms &t, long rows, long heads, int N, long kb, bo
 //   - bf16 and fp8, against the streaming kernel: by its cost (0.91 and 0.87 of the time of one form by rule).  Calls from memory must win by a
 //     twentieth (128 heads, 11 rows, 2423 keys fp8 24.3 streamed / 26.4, predicted 24.8 / 23.2), and fp8 rows of one workgroup, two workgroups
 //     to a compute unit, stay streamed past 100 MB (288 heads, 32 rows, 1500 keys 39.5 / 41.8, 320 x 32, 892 keys 24.5 / 26.0).
-SoloPlan attn_solo_plan(long rows, long heads, int N, int d, bool fp8, bool v8, bool refresh, bool all_fresh, int stream_splits)
+SoloPlan attn_solo_plan(long rows, long heads, int N, int d, bool fp8, bool v8, bool refresh, int fresh, int stream_splits)
 {
     const int forced = tune("DD_TUNE_SOLO", -1), forced_splits = tune("DD_TUNE_BLOCK_SPLITS", 0);
     const SoloPlan no{false, 0, 1};
@@ -673,7 +675,9 @@ SoloPlan attn_solo_plan(long rows, long heads, int N, int d, bool fp8, bool v8, 
     if (rows <= 64 && N <= 64) {
         if (wgs > 512 && row_tiles == 2) return no;
         const bool few = wgs <= 512 && !refresh && heads <= 256 && rows <= (d == 64 || fp8 ? 48 : 32);
-        if (few && (d == 64 || wgs > 96 || (!fp8 && all_fresh))) return no;
+        if (few && (d == 64 || wgs > 96 || (!fp8 && fresh == N))) return no;
+        const bool mixed = fresh > 0 && fresh < N && N % 32 != 0;
+        if (!few && row_tiles == 2 && wgs <= 256 && (!mixed || (!fp8 && rows >= 56))) return plan;
     }
     if (rows > 64) {
         if (wgs > 512) return no;

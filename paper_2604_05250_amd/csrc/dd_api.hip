@@ -224,7 +224,7 @@ static int block_attention(const void *Qblk, const void *Kc, const void *Vc, voi
     const int narrow_splits = dd::attn_block_splits(block_len, B, H, Hkv, N, d, qk_dtype);
     dd::SoloPlan solo{false, 0, 1};
     if (dd::attn_solo_serves(a) && dd::tune("DD_TUNE_DUO", -1) <= 0 && !other_kernel_forced())
-        solo = dd::attn_solo_plan(rows, heads, N, d, qk_dtype == DD_FP8_E4M3, v_dtype == DD_FP8_E4M3, refresh, Kblk && block_len == N, narrow_splits);
+        solo = dd::attn_solo_plan(rows, heads, N, d, qk_dtype == DD_FP8_E4M3, v_dtype == DD_FP8_E4M3, refresh, Kblk ? block_len : 0, narrow_splits);
     dd::DuoPlan duo{0, 1};
     if (!solo.take && dd::attn_duo_serves(a) && (rows > 64 || dd::tune("DD_TUNE_DUO", 0) > 0) && !other_kernel_forced()) {
         duo = dd::attn_duo_plan(rows, heads, N, qk_dtype == DD_FP8_E4M3 || d == 64);

@@ -28,6 +28,13 @@ DRAFTS = [
     ((FP8, FP8, 128), (4, 32, 8, 3500, 96, True), solo_form(224), ELSEWHERE),                 # 384 rows: a tile is half empty
     ((FP8, FP8, 128), (8, 32, 8, 3840, 64, True), solo_form(224), ELSEWHERE),
     ((FP8, FP8, 128), (8, 32, 8, 3841, 64, True), ELSEWHERE, solo_form(224)),
+    # 33 to 64 rows, 64 keys and fewer: here, but where keys of both kinds meet in a unit that is not full
+    ((BF16, BF16, 128), (15, 32, 8, 48, 16, False), solo_form(124), ELSEWHERE),
+    ((BF16, BF16, 128), (15, 32, 8, 48, 14, True), solo_form(124), ELSEWHERE),
+    ((BF16, BF16, 128), (15, 32, 8, 48, 13, True), ELSEWHERE, solo_form(124)),
+    ((BF16, BF16, 128), (15, 32, 8, 64, 13, True), solo_form(124), ELSEWHERE),
+    ((FP8, BF16, 128), (15, 32, 8, 64, 16, True), solo_form(124), ELSEWHERE),
+    ((FP8, BF16, 128), (15, 32, 8, 48, 16, True), ELSEWHERE, solo_form(124)),
     # fp8, one workgroup of rows per head, two to a compute unit: streamed past 100 MB
     ((FP8, BF16, 128), (9, 32, 32, 904, 32, True), solo_form(114), ELSEWHERE),
     ((FP8, BF16, 128), (9, 32, 32, 905, 32, True), ELSEWHERE, solo_form(114)),

@@ -632,7 +632,8 @@ long stream_cost(const StreamTerms &t, long rows, long heads, int N, long kb, bo
 }  // namespace
 
 // Drafter calls: the cheapest form and key splits (as many as leave every workgroup a compute unit), where that beats the other kernels.
-// `fresh`: keys that come from the block's own rows (N: all of them, nothing is read from the cache).
+// `fresh`: keys that come from the block's own rows (N: all of them, nothing is read from the cache); `wide_wgs`, `wide_rows`: the wide
+// kernel's workgroups, 0 where it cannot serve, and the rows of one.
 //
 // At most 64 keys are one tile of the other kernels, and nothing for waves to stream.  Few rows stay off this kernel there, unless
 //   - its parts spread the call, up to 96 workgroups of 32 rows (bf16 5.05 -> 4.6, fp8 and e4m3 V 4.6 -> 4.35; with 240 5.36 / 5.65 and
@@ -648,9 +649,12 @@ long stream_cost(const StreamTerms &t, long rows, long heads, int N, long kb, bo
 //     3072 on (8 heads, 256 rows, 1708 keys 15.0 -> 11.1; 32 x 112, 4083 keys 24.8 / 28.1; 48 x 96, 2946 keys 25.2 / 30.9).
 //   - up to 512, bf16 and fp8: 0.82 - 0.97 from 65 to 1536 keys (d = 64 to 2560), longer ones up to 1.2 (88 heads, 120 rows, 3084 keys
 //     fp8 36.9 / 45.0).  These figures are from the cache; from memory the last third of that range is up to 1.1 the other way.
-//   - up to 512, e4m3 V: 0.45 - 0.93 at any length, 64 keys and fewer included (48 heads x 256 rows, 64 keys 10.8 -> 6.1), except where rows fill
-//     the wide kernel's 256-row tiles and the stream is long: 40 x 256, 4096 keys 39.7 / 47.9, 20 x 448, 3800 keys 33.4 / 39.8,
-//     48 x 256, 3700 keys 37.2 / 42.0; with 512 workgroups 64 x 256, 4050 keys 47.3 / 54.9.  Tiles a quarter empty: 32 x 384, 3495 keys 51 -> 40.
+//   - up to 512, e4m3 V: 0.45 - 0.93 at any length, 64 keys and fewer included (48 heads x 256 rows, 64 keys 10.8 -> 6.1), except long streams
+//     that the wide kernel can serve, in four waves here: up to 320 workgroups where it fills four fifths of the compute units, past 2600 keys (80 x
+//     80, 2900 keys 26.5 / 29.4; 64 x 96, eight waves, 25.4 / 20.1 the other way) or, with its 128-row tiles nearly full, 2200 (72 x 112, 2600 keys
+//     27.0 / 30.3); up to 512 past 3328 where full tiles are 180 compute units' worth or more (20 x 448, 3800 keys 33.4 / 39.8, 64 x 256, 4050 keys
+//     47.3 / 54.9; 72 x 160, 3900 keys, 135 of them, 67.8 / 45.0 the other way).  Where it cannot serve: 72 x 128, 4200 keys 48 -> 46, 80 x 168, 3500 keys
+//     69 -> 43.
 //   - past 512 1.06 - 1.3.
 //
 // Up to 64 rows:
@@ -660,13 +664,15 @@ long stream_cost(const StreamTerms &t, long rows, long heads, int N, long kb, bo
 //   - bf16 and fp8, against the streaming kernel: by its cost (0.91 and 0.87 of the time of one form by rule).  Calls from memory must win by a
 //     twentieth (128 heads, 11 rows, 2423 keys fp8 24.3 streamed / 26.4, predicted 24.8 / 23.2), and fp8 rows of one workgroup, two workgroups
 //     to a compute unit, stay streamed past 100 MB (288 heads, 32 rows, 1500 keys 39.5 / 41.8, 320 x 32, 892 keys 24.5 / 26.0).
-SoloPlan attn_solo_plan(long rows, long heads, int N, int d, bool fp8, bool v8, bool refresh, int fresh, int stream_splits)
+SoloPlan attn_solo_plan(long rows, long heads, int N, int d, bool fp8, bool v8, bool refresh, int fresh, long wide_wgs, int wide_rows,
+                        int stream_splits)
 {
     const int forced = tune("DD_TUNE_SOLO", -1), forced_splits = tune("DD_TUNE_BLOCK_SPLITS", 0);
     const SoloPlan no{false, 0, 1};
     if (forced == 0) return no;
     const long row_tiles = (rows + 31) / 32, wgs = heads * row_tiles;
     SoloPick pick = solo_pick(rows, heads, N, d, fp8, v8, stream_splits, refresh);
+    const bool four_waves = pick.form % 10 != 8;
     if (pick.form == 0) pick.form = v8 && row_tiles == 2 ? 224 : 114;        // (more workgroups than the costs know)
     const SoloPlan plan{true, pick.form, forced_splits >= 1 ? stream_splits : pick.splits};
     if (forced == 1) return plan;
@@ -682,8 +688,11 @@ SoloPlan attn_solo_plan(long rows, long heads, int N, int d, bool fp8, bool v8, 
     if (rows > 64) {
         if (wgs > 512) return no;
         if (wgs > 256 && !v8 && (N <= 64 || N > (d == 64 ? 2560 : 1536))) return no;
-        if (wgs > 384 && v8 && N > 3840 && rows % 256 == 0) return no;
-        if (wgs > 256 && wgs <= 384 && v8 && N > 3328 && 8 * rows >= 7 * ((rows + 255) / 256 * 256)) return no;
+        if (v8 && wide_wgs > 0 && wgs > 192 && four_waves) {
+            const long tile_rows = (rows + wide_rows - 1) / wide_rows * wide_rows;
+            if (wgs <= 320 && 5 * wide_wgs > 4 * 256 && N > (wgs > 256 && wide_rows == 128 && rows >= 112 ? 2200 : 2600)) return no;
+            if (wgs > 256 && 8 * rows >= 7 * tile_rows && rows * wide_wgs > 180 * tile_rows && N > 3328) return no;
+        }
         if (!fp8 && d == 128 && wgs <= 256 && (N / pick.splits + 127) / 128 > 12 && N >= (wgs <= 128 ? 3072 : 2048)) return no;
         return plan;
     }

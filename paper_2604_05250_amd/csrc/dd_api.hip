@@ -222,9 +222,12 @@ static int block_attention(const void *Qblk, const void *Kc, const void *Vc, voi
     const bool wide = dd::tune("DD_TUNE_BLOCK_WIDE", 1) != 0 && dd::attn_wide_block_fits(a);
     const long rows = (long)(H / Hkv) * block_len, heads = (long)B * Hkv;
     const int narrow_splits = dd::attn_block_splits(block_len, B, H, Hkv, N, d, qk_dtype);
+    const int wide_rows = dd::attn_wide_block_rows(block_len, B, H, Hkv, N);
+    const long wide_wgs = wide ? heads * ((rows + wide_rows - 1) / wide_rows) * dd::attn_wide_block_splits(block_len, B, H, Hkv, N) : 0;
     dd::SoloPlan solo{false, 0, 1};
     if (dd::attn_solo_serves(a) && dd::tune("DD_TUNE_DUO", -1) <= 0 && !other_kernel_forced())
-        solo = dd::attn_solo_plan(rows, heads, N, d, qk_dtype == DD_FP8_E4M3, v_dtype == DD_FP8_E4M3, refresh, Kblk ? block_len : 0, narrow_splits);
+        solo = dd::attn_solo_plan(rows, heads, N, d, qk_dtype == DD_FP8_E4M3, v_dtype == DD_FP8_E4M3, refresh, Kblk ? block_len : 0, wide_wgs, wide_rows,
+                                  narrow_splits);
     dd::DuoPlan duo{0, 1};
     if (!solo.take && dd::attn_duo_serves(a) && (rows > 64 || dd::tune("DD_TUNE_DUO", 0) > 0) && !other_kernel_forced()) {
         duo = dd::attn_duo_plan(rows, heads, N, qk_dtype == DD_FP8_E4M3 || d == 64);
@@ -241,10 +244,8 @@ static int block_attention(const void *Qblk, const void *Kc, const void *Vc, voi
     // Long bf16 streams that the splits here leave a fifth of the compute units without: the wide kernel's larger tiles split finer (48 heads x 192
     // rows, 3709 keys: 39.2 on 240 workgroups against 43.3 on 192; 24 x 512, 3857 keys 43.1 / 46.3; at 2600 keys still 0.96).
     if (duo.splits > 1 && wide && qk_dtype == DD_BF16 && d == 128 && N >= 3072 && dd::tune("DD_TUNE_DUO", -1) < 0) {
-        const int per_wg = dd::attn_wide_block_rows(block_len, B, H, Hkv, N);
         const long here = heads * ((rows + 32 * duo.blocks - 1) / (32 * duo.blocks)) * duo.splits;
-        const long there = heads * ((rows + per_wg - 1) / per_wg) * dd::attn_wide_block_splits(block_len, B, H, Hkv, N);
-        if (5 * here <= 4 * there) duo.blocks = 0;
+        if (5 * here <= 4 * wide_wgs) duo.blocks = 0;
     }
     const int general = wide ? dd::attn_wide_block_splits(block_len, B, H, Hkv, N) : narrow_splits;
     const int splits = duo.blocks ? duo.splits : solo.take ? solo.splits : general;

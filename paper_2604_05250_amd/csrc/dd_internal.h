@@ -134,7 +134,8 @@ hipError_t launch_attention_duo(const AttnArgs &a, int blocks, hipStream_t strea
 // many key splits (at most the streaming kernel's, `stream_splits`, so that one workspace serves both); the launch (+ merge).
 bool attn_solo_serves(const AttnArgs &a);
 struct SoloPlan { bool take; int form, splits; };        // form: row blocks, parts of the head dims, waves as digits
-SoloPlan attn_solo_plan(long rows, long heads, int N, int d, bool fp8, bool v8, bool refresh, int fresh, int stream_splits);
+SoloPlan attn_solo_plan(long rows, long heads, int N, int d, bool fp8, bool v8, bool refresh, int fresh, long wide_wgs, int wide_rows,
+                        int stream_splits);
 int attn_solo_form(long rows, long heads, int N, int d, bool fp8, bool v8);      // a verifier call's form
 hipError_t launch_attention_solo(const AttnArgs &a, int form, hipStream_t stream);
 

@@ -22,12 +22,20 @@ DRAFTS = [
     # e4m3 V, more than 64 rows, 257 to 512 workgroups: at 64 keys and fewer too ...
     ((FP8, FP8, 128), (6, 32, 8, 64, 64, True), solo_form(114), ELSEWHERE),
     ((FP8, FP8, 128), (12, 28, 4, 40, 24, True), solo_form(114), ELSEWHERE),
-    # ... but not long streams whose rows fill the wide kernel's tiles
-    ((FP8, FP8, 128), (5, 32, 8, 3328, 64, True), solo_form(224), ELSEWHERE),
-    ((FP8, FP8, 128), (5, 32, 8, 3329, 64, True), ELSEWHERE, solo_form(224)),
+    # ... but not long streams that the wide kernel can serve
+    ((FP8, FP8, 128), (10, 40, 8, 2600, 16, False), solo_form(114), ELSEWHERE),
+    ((FP8, FP8, 128), (10, 40, 8, 2601, 16, False), ELSEWHERE, solo_form(114)),
+    ((FP8, FP8, 128), (10, 40, 8, 2601, 16, True), solo_form(114), ELSEWHERE),                # its own rows: shorter than a tile there
+    ((FP8, FP8, 128), (5, 32, 8, 2600, 64, True), solo_form(224), ELSEWHERE),
+    ((FP8, FP8, 128), (5, 32, 8, 2601, 64, True), ELSEWHERE, solo_form(224)),
+    ((FP8, FP8, 128), (11, 16, 4, 3328, 64, True), solo_form(224), ELSEWHERE),
+    ((FP8, FP8, 128), (11, 16, 4, 3329, 64, True), ELSEWHERE, solo_form(224)),
+    ((FP8, FP8, 128), (11, 32, 4, 3329, 32, True), solo_form(224), ELSEWHERE),
     ((FP8, FP8, 128), (4, 32, 8, 3500, 96, True), solo_form(224), ELSEWHERE),                 # 384 rows: a tile is half empty
-    ((FP8, FP8, 128), (8, 32, 8, 3840, 64, True), solo_form(224), ELSEWHERE),
-    ((FP8, FP8, 128), (8, 32, 8, 3841, 64, True), ELSEWHERE, solo_form(224)),
+    ((FP8, FP8, 128), (8, 32, 8, 3328, 64, True), solo_form(224), ELSEWHERE),
+    ((FP8, FP8, 128), (8, 32, 8, 3329, 64, True), ELSEWHERE, solo_form(224)),
+    ((FP8, FP8, 128), (9, 32, 8, 2200, 28, False), solo_form(224), ELSEWHERE),                # 128-row tiles nearly full
+    ((FP8, FP8, 128), (9, 32, 8, 2201, 28, False), ELSEWHERE, solo_form(224)),
     # 33 to 64 rows, 64 keys and fewer: here, but where keys of both kinds meet in a unit that is not full
     ((BF16, BF16, 128), (15, 32, 8, 48, 16, False), solo_form(124), ELSEWHERE),
     ((BF16, BF16, 128), (15, 32, 8, 48, 14, True), solo_form(124), ELSEWHERE),

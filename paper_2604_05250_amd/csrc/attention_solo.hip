@@ -644,11 +644,14 @@ long stream_cost(const StreamTerms &t, long rows, long heads, int N, long kb, bo
 // run here (bf16 120 heads, 64 rows, 48 keys 5.95 -> 5.1, 64 keys 5.85 -> 4.7, fp8 64 keys 4.95 -> 4.45), but where keys of both kinds meet
 // in a unit that is not full: bf16 of fewer than 56 rows (40 rows, 33 keys 5.3 / 5.5) and fp8 (56 rows, 33 keys 4.92 / 5.17) by their cost.
 //
-// More than 64 rows (against the two-waves-per-SIMD, the wide and the MFMA kernel; some 350 drawn calls per type):
+// More than 64 rows (against the two-waves-per-SIMD, the wide and the MFMA kernel; thousands of drawn calls, from the cache and from memory):
 //   - up to 256 workgroups 0.46 - 0.9 of the time.  bf16 past twelve rounds of 128 keys loses from 2048 keys on, on at most 128 workgroups from
-//     3072 on (8 heads, 256 rows, 1708 keys 15.0 -> 11.1; 32 x 112, 4083 keys 24.8 / 28.1; 48 x 96, 2946 keys 25.2 / 30.9).
-//   - up to 512, bf16 and fp8: 0.82 - 0.97 from 65 to 1536 keys (d = 64 to 2560), longer ones up to 1.2 (88 heads, 120 rows, 3084 keys
-//     fp8 36.9 / 45.0).  These figures are from the cache; from memory the last third of that range is up to 1.1 the other way.
+//     3072 on (8 heads, 256 rows, 1708 keys 15.0 -> 11.1; 32 x 112, 4083 keys 24.8 / 28.1; 48 x 96, 2946 keys 25.2 / 30.9), fp8 past 95 MB where
+//     no eight-wave form fits (80 x 96, 3600 keys 31.0 / 36.9, 4200 34.2 / 41.4; 3000 even).
+//   - up to 512, bf16 and fp8: 0.75 - 0.97 from 65 to 1536 keys (d = 64 to 2560), longer ones up to 1.2 (88 heads, 120 rows, 3084 keys
+//     fp8 36.9 / 45.0).  bf16 past 70 MB loses too, where the two-waves-per-SIMD kernel takes 64-row workgroups (120 x 80, 1536 keys 26.5 / 29.6;
+//     128 x 128, 1000 keys, 66 MB, 16.9 / 16.1 the other way), past 95 MB where it does not (168 x 96, 1200 keys 26.3 / 28.3).  From memory the
+//     last third of the range is up to 1.1 the other way, fp8 to 1.15.
 //   - up to 512, e4m3 V: 0.45 - 0.93 at any length, 64 keys and fewer included (48 heads x 256 rows, 64 keys 10.8 -> 6.1), except long streams
 //     that the wide kernel can serve, in four waves here: up to 320 workgroups where it fills four fifths of the compute units, past 2600 keys (80 x
 //     80, 2900 keys 26.5 / 29.4; 64 x 96, eight waves, 25.4 / 20.1 the other way) or, with its 128-row tiles nearly full, 2200 (72 x 112, 2600 keys
@@ -677,7 +680,7 @@ SoloPlan attn_solo_plan(long rows, long heads, int N, int d, bool fp8, bool v8, 
     const SoloPlan plan{true, pick.form, forced_splits >= 1 ? stream_splits : pick.splits};
     if (forced == 1) return plan;
     if (forced_splits >= 1) return no;
-    const long rounds = (N + 127) / 128;
+    const long rounds = (N + 127) / 128, kb = heads * (long)N * (d == 64 || v8 ? 256 : fp8 ? 384 : 512) / 1000;
     if (rows <= 64 && N <= 64) {
         if (wgs > 512 && row_tiles == 2) return no;
         const bool few = wgs <= 512 && !refresh && heads <= 256 && rows <= (d == 64 || fp8 ? 48 : 32);
@@ -687,18 +690,21 @@ SoloPlan attn_solo_plan(long rows, long heads, int N, int d, bool fp8, bool v8, 
     }
     if (rows > 64) {
         if (wgs > 512) return no;
-        if (wgs > 256 && !v8 && (N <= 64 || N > (d == 64 ? 2560 : 1536))) return no;
         if (v8 && wide_wgs > 0 && wgs > 192 && four_waves) {
             const long tile_rows = (rows + wide_rows - 1) / wide_rows * wide_rows;
             if (wgs <= 320 && 5 * wide_wgs > 4 * 256 && N > (wgs > 256 && wide_rows == 128 && rows >= 112 ? 2200 : 2600)) return no;
             if (wgs > 256 && 8 * rows >= 7 * tile_rows && rows * wide_wgs > 180 * tile_rows && N > 3328) return no;
         }
-        if (!fp8 && d == 128 && wgs <= 256 && (N / pick.splits + 127) / 128 > 12 && N >= (wgs <= 128 ? 3072 : 2048)) return no;
+        if (v8) return plan;
+        if (wgs > 256 && (N <= 64 || N > (d == 64 ? 2560 : 1536))) return no;
+        if (d == 64) return plan;
+        if (fp8 && wgs > 192 && wgs <= 256 && four_waves && kb > 95000) return no;
+        if (!fp8 && wgs > 256 && kb > (heads * ((rows + 63) / 64) <= 256 ? 70000 : 95000)) return no;
+        if (!fp8 && wgs <= 256 && (N / pick.splits + 127) / 128 > 12 && N >= (wgs <= 128 ? 3072 : 2048)) return no;
         return plan;
     }
     if (d == 64) return plan;
     if (v8) return wgs <= 512 || (wgs <= 768 && (row_tiles == 1 || rounds > 3)) || rounds > 4 ? plan : no;
-    const long kb = heads * (long)N * (fp8 ? 384 : 512) / 1000;
     if (fp8 && wgs > 256 && row_tiles == 1 && kb > 100000) return no;
     const long streamed = stream_cost(fp8 ? kStreamFp8 : kStreamBf16, rows, heads, N, kb, refresh, stream_splits);
     return pick.cost != 0 && pick.cost * (kb > 80000 ? 20 : 19) <= 19 * streamed ? plan : no;

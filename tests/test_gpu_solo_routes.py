@@ -36,6 +36,11 @@ DRAFTS = [
     ((FP8, FP8, 128), (8, 32, 8, 3329, 64, True), ELSEWHERE, solo_form(224)),
     ((FP8, FP8, 128), (9, 32, 8, 2200, 28, False), solo_form(224), ELSEWHERE),                # 128-row tiles nearly full
     ((FP8, FP8, 128), (9, 32, 8, 2201, 28, False), ELSEWHERE, solo_form(224)),
+    # more than 64 rows: bf16 past 95 MB (two workgroups per compute unit), fp8 likewise (one, four waves)
+    ((BF16, BF16, 128), (21, 32, 8, 1104, 24, True), solo_form(114), ELSEWHERE),
+    ((BF16, BF16, 128), (21, 32, 8, 1105, 24, True), ELSEWHERE, solo_form(114)),
+    ((FP8, BF16, 128), (10, 32, 8, 3092, 24, True), solo_form(114), ELSEWHERE),
+    ((FP8, BF16, 128), (10, 32, 8, 3093, 24, True), ELSEWHERE, solo_form(114)),
     # 33 to 64 rows, 64 keys and fewer: here, but where keys of both kinds meet in a unit that is not full
     ((BF16, BF16, 128), (15, 32, 8, 48, 16, False), solo_form(124), ELSEWHERE),
     ((BF16, BF16, 128), (15, 32, 8, 48, 14, True), solo_form(124), ELSEWHERE),

@@ -439,8 +439,12 @@ def run_config(args, config_id):
         fold = not fp8 and c.N >= 1024 and heads * -(-rows // 256) >= 192
         tf = {False: "false", True: "true"}
         if (not fp8 or c.d == 128) and stored_v != 2:
-            if c.N > 64 and heads * -(-rows // 32) <= (448 if c.N > 1024 else 512):
-                return f"attn_solo_kernel<{c.d}, {tf[fp8]}, {tf[stored_v == 1]}>"
+            longest = c.N if stored_v == 1 or c.d == 64 or not one_round[64] else 3072 if fp8 else 1344
+            most = 448 if c.N > longest else 768 if c.d == 64 and c.N >= 512 else 512
+            if c.N <= 64:
+                most = 128 if rows < 48 and c.N % 32 and (fp8 or c.d == 64) else 192 if c.d == 64 else 256
+            if heads * -(-rows // 32) <= most:
+                return f"attn_solo_kernel<{c.d}, {tf[fp8]}, {tf[stored_v == 1]}, ...>"
             if stored_v == 0 and one_round[64] and c.N > 1024:
                 return f"attn_duo_kernel<{c.d}, {tf[fp8]}, 2, {3 if fp8 else 2 if c.d == 128 else 4}>"
         if not fp8 or c.d == 128:

@@ -13,12 +13,12 @@
 // What bounds it: some 4 us of launch, first loads and merge, then per unit a chain (K fragments, S, weights, V fragments, O) of
 // 0.45 - 0.75 us that nothing else on the SIMD covers while a workgroup is four waves, and the 64 B/clk of a compute unit's path to LDS (100
 // GB/s at most, measured).  Parts shorten a unit and the merge; a second wave per SIMD (eight waves) fills the chain's gaps where streams
-// are long, for 0.3 - 0.8 us more of launch and merge; two row blocks share a unit's loads.  us per call in a stream of them, four waves on one
-// block and all dims -> the form the rule picks: 1 x 32 heads, 512 keys, 32 rows bf16 8.0 -> 6.8 (4 parts); 1 x 32, 1024 keys bf16 11.4 ->
-// 8.7, fp8 9.5 -> 7.0, e4m3 V 10.1 -> 7.4 (4 parts, 8 waves); 4 x 32/8, 16 rows, 2048 keys fp8 12.2 -> 9.7; 11 x 32/8, 16 rows, 1237 keys fp8
-// 13.9 -> 12.5, e4m3 V 15.7 -> 12.6 (two blocks, 2 parts, 8 waves); 2 x 32, 800 keys, 48 rows e4m3 V 11.9 -> 8.4 (2 parts, 8 waves).
+// are long, for 0.3 - 0.8 us more of launch and merge; two row blocks share a unit's loads.  A form is named by its digits (row blocks, parts,
+// waves).  us per call in a stream of them, 114 -> the form that the rule picks: 1 x 32 heads, 32 rows, 512 keys bf16 7.5 -> 5.9 (148), 1024
+// keys bf16 9.6 -> 8.0, fp8 8.8 -> 6.7, e4m3 V 9.3 -> 6.9 (148); 4 x 32/8, 16 rows, 2048 keys fp8 10.4 -> 9.4 (124); 2 x 32, 48 rows, 800 keys
+// e4m3 V 11.8 -> 8.1 (128); 11 x 32/8, 64 rows, 1237 keys e4m3 V 15.1 -> 12.3 (228), fp8 114 itself (11.45, 228 11.54).
 // What the first loads need arrives in registers, as leading scalar arguments, and no hidden argument is asked for (the grid's size
-// costs a launch 256 bytes more): with the arguments in a struct the first of those calls takes 6.8, now 6.2 us, 11 x 32/8 fp8 11.6 -> 11.2.
+// costs a launch 256 bytes more): with the arguments in a struct 1 x 32, 512 keys on 144 takes 6.8, so 6.2 us, 11 x 32/8 fp8 11.6 -> 11.2.
 // Tried and not kept: a second unit on its way per wave (bf16 8.0 -> 9.4, 4 parts 6.8 -> 7.6: the first units' loads queue behind it); two
 // blocks with all dims (12.3, one wave's registers); eight waves on all dims for bf16 (8.6).
 #include "attention_common.h"

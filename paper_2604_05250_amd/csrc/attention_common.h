@@ -89,7 +89,8 @@ hipError_t launch_headed(void (*kernel)(Params...), dim3 grid, dim3 block, hipSt
     return launch(kernel, grid, block, stream, static_cast<const uint8_t *>(k.Q), static_cast<const uint8_t *>(k.K), static_cast<const uint8_t *>(k.V),
                   k.group * k.Nq, k.N, k.kv_stride, k.keys_per_split, k.wgs, (unsigned)k.row_tiles << 4 | (unsigned)(k.splits - 1),   // (at most 16 splits)
                   k.block_start, k.block_len,
-                  AttnTail{k.Kblk, k.Vblk, k.O, k.part_o, k.part_ml, k.q_scale, k.k_scale, k.v_scale, k.block_starts, k.Hkv, k.Nq, k.group, k.scale_log2}, rest...);
+                  AttnTail{k.Kblk, k.Vblk, k.O, k.part_o, k.part_ml, k.q_scale, k.k_scale, k.v_scale, k.block_starts, k.Hkv, k.Nq, k.group,
+                           k.scale_log2}, rest...);
 }
 // This workgroup's place, from its number: of `row_tiles` and `splits` (a division is some 150 cycles before the first load).
 __device__ __forceinline__ void place_of(unsigned &bid, int count, int &at)

@@ -109,7 +109,8 @@ void attn_duo_kernel(DD_ATTN_HEAD, const AttnTail a)
     const size_t row_base = kv_head * rows_total;
     const int kbeg = sp * h.keys_per_split;
     const int kend = min(h.N, kbeg + h.keys_per_split);
-    const int bstart = a.block_starts ? uniform_load(a.block_starts + (unsigned)kv_head / (unsigned)a.Hkv) : h.block_start;   // any value is safe: rows are chosen by range test
+    // (any value is safe: rows are chosen by range test)
+    const int bstart = a.block_starts ? uniform_load(a.block_starts + (unsigned)kv_head / (unsigned)a.Hkv) : h.block_start;
     const int blen = h.block_len;
     const int ntiles = (kend - kbeg + TK - 1) / TK;
 

@@ -60,7 +60,8 @@ __device__ __forceinline__ void attn_f32(const AttnHead &h, const AttnTail &a)
 
     const int k_begin = sp * h.keys_per_split;
     const int k_end = min(h.N, k_begin + h.keys_per_split);
-    const int bstart = a.block_starts ? uniform_load(a.block_starts + (unsigned)kv_head / (unsigned)a.Hkv) : h.block_start;   // any value is safe: rows are chosen by range test
+    // (any value is safe: rows are chosen by range test)
+    const int bstart = a.block_starts ? uniform_load(a.block_starts + (unsigned)kv_head / (unsigned)a.Hkv) : h.block_start;
     const float *const kc = reinterpret_cast<const float *>(h.K) + kv_head * h.kv_stride * D;
     const float *const vc = reinterpret_cast<const float *>(h.V) + kv_head * h.kv_stride * D;
     const float *const kb = h.block_len ? static_cast<const float *>(a.Kblk) + kv_head * h.block_len * D : nullptr;       // (length 0: no block)

@@ -140,7 +140,8 @@ __device__ __forceinline__ void attn_solo(const AttnHead &h, const AttnTail &a)
 
     const int kbeg = sp * h.keys_per_split;
     const int kend = min(h.N, kbeg + h.keys_per_split);
-    const int bstart = a.block_starts ? uniform_load(a.block_starts + (unsigned)kv_head / (unsigned)a.Hkv) : h.block_start;        // any value is safe: rows are chosen by range test
+    // (any value is safe: rows are chosen by range test)
+    const int bstart = a.block_starts ? uniform_load(a.block_starts + (unsigned)kv_head / (unsigned)a.Hkv) : h.block_start;
     const int blen = h.block_len;
     const int nunits = (kend - kbeg + U - 1) / U;
     const int whole = (kend - kbeg) / U;             // units [0, whole) hold 32 rows of the range
@@ -193,7 +194,8 @@ __device__ __forceinline__ void attn_solo(const AttnHead &h, const AttnTail &a)
                 constexpr int I = decltype(i)::value;
                 const int j = min(k0 + I * (K ? KDMA_ROWS : VDMA_ROWS) + (K ? krow0 : vrow0), kend - 1);
                 const bool in_blk = (unsigned)j - (unsigned)bstart < (unsigned)blen;
-                const uint8_t *const src = (K ? (in_blk ? kb_ : kc) : (in_blk ? vb_ : vc)) + (size_t)(in_blk ? j - bstart : j) * PITCH + (K ? kchunk(I) : vchunk);
+                const uint8_t *const src = (K ? (in_blk ? kb_ : kc) : (in_blk ? vb_ : vc)) +
+                                           (size_t)(in_blk ? j - bstart : j) * PITCH + (K ? kchunk(I) : vchunk);
                 const unsigned d = dst - BIAS + I * 1024;
                 asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(d), "v"(src) : "memory", "m0");
             });
@@ -472,7 +474,9 @@ __device__ __forceinline__ void attn_solo(const AttnHead &h, const AttnTail &a)
         const float inv = 1.0f / l_tot;
         uint16_t *out = static_cast<uint16_t *>(a.O) + orow * D;
         if constexpr (GP == 1) {
-            if (row_ok) *reinterpret_cast<uint2 *>(out + 8 * first + 4 * hh) = make_uint2(solo_pack(o[0][0] * inv, o[0][1] * inv), solo_pack(o[0][2] * inv, o[0][3] * inv));
+            if (row_ok)
+                *reinterpret_cast<uint2 *>(out + 8 * first + 4 * hh) =
+                    make_uint2(solo_pack(o[0][0] * inv, o[0][1] * inv), solo_pack(o[0][2] * inv, o[0][3] * inv));
         } else {
 #pragma unroll
             for (int g = 0; g + 1 < GP; g += 2) {

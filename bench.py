@@ -442,7 +442,8 @@ def run_config(args, config_id):
             longest = c.N if stored_v == 1 or c.d == 64 or not one_round[64] else 3072 if fp8 else 1344
             most = 448 if c.N > longest else 768 if c.d == 64 and c.N >= 512 else 512
             if c.N <= 64:
-                most = 128 if rows < 48 and c.N % 32 and (fp8 or c.d == 64) else 192 if c.d == 64 else 256
+                short = c.N < 32 if fp8 else c.d == 64 and c.N % 32 != 0
+                most = 128 if rows < 48 and short else 192 if c.d == 64 else 256
             if heads * -(-rows // 32) <= most:
                 return f"attn_solo_kernel<{c.d}, {tf[fp8]}, {tf[stored_v == 1]}, ...>"
             if stored_v == 0 and one_round[64] and c.N > 1024:

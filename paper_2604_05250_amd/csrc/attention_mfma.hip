@@ -748,14 +748,14 @@ hipError_t launch_attention_mfma(const AttnArgs &a, hipStream_t stream)
         //     N 1015 17.4 / 18.5); shorter up to 1.09.
         //   - 64 keys and fewer: 256 workgroups (d = 64: 192), whose head dims it then divides: bf16 1 x 16, N 33 5.4 -> 4.6, 6 x 32, N 49 5.9 -> 5.3,
         //     fp8 1 x 32, N 48 5.2 -> 4.2; 384 workgroups, N 33 5.6 / 6.2.
-        //   - fewer than 48 rows per kv head on units of 32 keys that are not full: 128 (but bf16 with 128 head dims), where parts no longer pay: fp8
-        //     192 heads, N 6 4.1 / 4.4, N 18 4.2 / 4.4, 128 x 36 rows, N 9 4.55 / 4.75; d = 64 160, N 9 3.85 / 3.95, 192, N 18 3.85 / 4.0; full, fp8 192, N 32
-        //     4.36 -> 4.07; 64 x 77, N 11 5.2 -> 4.7.
+        //   - fewer than 48 rows per kv head and 32 keys (fp8) or a unit of 32 that is not full (d = 64): 128, where parts no longer pay: fp8 192 heads, N 6
+        //     4.1 / 4.4, N 18 4.2 / 4.4, 128 x 36 rows, N 9 4.55 / 4.75; d = 64 160, N 9 3.85 / 3.95, 192, N 18 3.85 / 4.0, 80, N 36 3.95 / 4.1.  Fp8 192,
+        //     N 32 4.36 -> 4.07, 80 x 40 rows, N 40 5.05 -> 4.4, 64 x 77, N 11 5.2 -> 4.7.
         const long wgs = heads * ((rows + 31) / 32);
         const bool v8 = a.v_dtype == 2;
         const int longest = v8 || a.d == 64 || !one_round64 ? a.N : fp8 ? 3072 : 1344;
         long most = a.N > longest ? 448 : a.d == 64 && a.N >= 512 ? 768 : 512;
-        if (a.N <= 64) most = rows < 48 && a.N % 32 != 0 && (fp8 || a.d == 64) ? 128 : a.d == 64 ? 192 : 256;
+        if (a.N <= 64) most = rows < 48 && (fp8 ? a.N < 32 : a.d == 64 && a.N % 32 != 0) ? 128 : a.d == 64 ? 192 : 256;
         const int solo = tune("DD_TUNE_SOLO", tune("DD_TUNE_DUO", -1) <= 0 && wgs <= most);
         if (solo != 0 && attn_solo_serves(a))
             return launch_attention_solo(a, attn_solo_form(rows, heads, a.N, a.d, fp8, v8), stream);

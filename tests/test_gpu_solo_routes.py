@@ -92,7 +92,8 @@ def test_drafter_routes(monkeypatch, store, shape, here, there):
 
 @pytest.mark.parametrize("qk,v,d,H,Hkv,N,here", [
     (FP8, BF16, 128, 128, 128, 12, True), (FP8, BF16, 128, 129, 129, 12, False), (FP8, BF16, 128, 129, 129, 31, False), (FP8, BF16, 128, 129, 129, 32, True),
-    (FP8, FP8, 128, 129, 129, 31, False), (BF16, BF16, 64, 129, 129, 31, False), (BF16, BF16, 128, 129, 129, 12, True),
+    (FP8, FP8, 128, 129, 129, 31, False), (FP8, BF16, 128, 80, 80, 40, True),
+    (BF16, BF16, 64, 129, 129, 31, False), (BF16, BF16, 64, 80, 80, 40, False), (BF16, BF16, 128, 129, 129, 12, True),
     (FP8, BF16, 128, 325, 65, 9, False), (FP8, BF16, 128, 390, 65, 8, True)])                 # 45 and 48 rows per kv head, 130 workgroups
 def test_verifier_routes_of_few_keys(monkeypatch, qk, v, d, H, Hkv, N, here):
     import torch

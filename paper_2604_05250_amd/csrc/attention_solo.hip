@@ -645,8 +645,9 @@ long stream_cost(const StreamTerms &t, long rows, long heads, int N, long kb, bo
 //     block's 3.98 / 4.42), or
 //   - the call has the cache refresh, a launch of its own on the others.
 // So do more than 512 workgroups where a head's rows are two (d = 64, 272 heads, 48 rows, 48 keys 5.3 / 7.6).  Up to 256 workgroups of more rows
-// run here (bf16 120 heads, 64 rows, 48 keys 5.95 -> 5.1, 64 keys 5.85 -> 4.7, fp8 64 keys 4.95 -> 4.45), but where keys of both kinds meet
-// in a unit that is not full: bf16 of fewer than 56 rows (40 rows, 33 keys 5.3 / 5.5) and fp8 (56 rows, 33 keys 4.92 / 5.17) by their cost.
+// run here (bf16 120 heads, 64 rows, 48 keys 5.95 -> 5.1, 64 keys 5.85 -> 4.7, fp8 64 keys 4.95 -> 4.45), but by their cost where the last unit is
+// not full and holds the block's keys: bf16 of fewer than 56 rows (40 rows, 33 keys 5.3 / 5.5) or of the block's keys alone (60 rows, 15 keys 4.96 /
+// 5.4), fp8 where keys of both kinds meet (56 rows, 33 keys 4.92 / 5.17).
 //
 // More than 64 rows (against the two-waves-per-SIMD, the wide and the MFMA kernel; thousands of drawn calls, from the cache and from memory):
 //   - up to 256 workgroups 0.46 - 0.9 of the time.  bf16 past twelve rounds of 128 keys loses from 2048 keys on, on at most 128 workgroups from
@@ -689,8 +690,8 @@ SoloPlan attn_solo_plan(long rows, long heads, int N, int d, bool fp8, bool v8, 
         if (wgs > 512 && row_tiles == 2) return no;
         const bool few = wgs <= 512 && !refresh && heads <= 256 && rows <= (d == 64 || fp8 ? 48 : 32);
         if (few && (d == 64 || wgs > 96 || (!fp8 && fresh == N))) return no;
-        const bool mixed = fresh > 0 && fresh < N && N % 32 != 0;
-        if (!few && row_tiles == 2 && wgs <= 256 && (!mixed || (!fp8 && rows >= 56))) return plan;
+        const bool plain = N % 32 == 0 || fresh == 0 || (fp8 ? fresh == N : fresh < N && rows >= 56);
+        if (!few && row_tiles == 2 && wgs <= 256 && plain) return plan;
     }
     if (rows > 64) {
         if (wgs > 512) return no;

@@ -45,6 +45,8 @@ DRAFTS = [
     ((BF16, BF16, 128), (15, 32, 8, 48, 16, False), solo_form(124), ELSEWHERE),
     ((BF16, BF16, 128), (15, 32, 8, 48, 14, True), solo_form(124), ELSEWHERE),
     ((BF16, BF16, 128), (15, 32, 8, 48, 13, True), ELSEWHERE, solo_form(124)),
+    ((BF16, BF16, 128), (15, 32, 8, 15, 15, True), ELSEWHERE, solo_form(124)),                # the block's keys alone
+    ((FP8, BF16, 128), (15, 32, 8, 15, 15, True), solo_form(124), ELSEWHERE),
     ((BF16, BF16, 128), (15, 32, 8, 64, 13, True), solo_form(124), ELSEWHERE),
     ((FP8, BF16, 128), (15, 32, 8, 64, 16, True), solo_form(124), ELSEWHERE),
     ((FP8, BF16, 128), (15, 32, 8, 48, 16, True), ELSEWHERE, solo_form(124)),

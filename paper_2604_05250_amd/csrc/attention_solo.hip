@@ -657,7 +657,8 @@ long stream_cost(const StreamTerms &t, long rows, long heads, int N, long kb, bo
 //     fp8 36.9 / 45.0).  bf16 past 70 MB loses too, where the two-waves-per-SIMD kernel takes 64-row workgroups (120 x 80, 1536 keys 26.5 / 29.6;
 //     128 x 128, 1000 keys, 66 MB, 16.9 / 16.1 the other way), past 95 MB where it does not (168 x 96, 1200 keys 26.3 / 28.3).  From memory the
 //     last third of the range is up to 1.1 the other way, fp8 to 1.15.
-//   - up to 512, e4m3 V: 0.45 - 0.93 at any length, 64 keys and fewer included (48 heads x 256 rows, 64 keys 10.8 -> 6.1), except long streams
+//   - up to 512, e4m3 V: 0.45 - 0.93 at any length, 64 keys and fewer included (48 heads x 256 rows, 64 keys 10.8 -> 6.1) down to 25 with two workgroups
+//     per compute unit (96 x 72, 33 keys 6.05 -> 5.7, 24 keys 5.4 / 5.7), except long streams
 //     that the wide kernel can serve, in four waves here: up to 320 workgroups where it fills four fifths of the compute units, past 2600 keys (80 x
 //     80, 2900 keys 26.5 / 29.4; 64 x 96, eight waves, 25.4 / 20.1 the other way) or, with its 128-row tiles nearly full, 2200 (72 x 112, 2600 keys
 //     27.0 / 30.3); up to 512 past 3328 where full tiles are 180 compute units' worth or more (20 x 448, 3800 keys 33.4 / 39.8, 64 x 256, 4050 keys
@@ -700,7 +701,7 @@ SoloPlan attn_solo_plan(long rows, long heads, int N, int d, bool fp8, bool v8, 
             if (wgs <= 320 && 5 * wide_wgs > 4 * 256 && N > (wgs > 256 && wide_rows == 128 && rows >= 112 ? 2200 : 2600)) return no;
             if (wgs > 256 && 8 * rows >= 7 * tile_rows && rows * wide_wgs > 180 * tile_rows && N > 3328) return no;
         }
-        if (v8) return plan;
+        if (v8) return wgs > 256 && N <= 24 ? no : plan;
         if (wgs > 256 && (N <= 64 || N > (d == 64 ? 2560 : 1536))) return no;
         if (d == 64) return plan;
         if (fp8 && wgs > 192 && wgs <= 256 && four_waves && kb > 95000) return no;

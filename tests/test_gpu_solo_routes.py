@@ -22,6 +22,8 @@ DRAFTS = [
     # e4m3 V, more than 64 rows, 257 to 512 workgroups: at 64 keys and fewer too ...
     ((FP8, FP8, 128), (6, 32, 8, 64, 64, True), solo_form(114), ELSEWHERE),
     ((FP8, FP8, 128), (12, 28, 4, 40, 24, True), solo_form(114), ELSEWHERE),
+    ((FP8, FP8, 128), (12, 32, 8, 25, 18, True), solo_form(114), ELSEWHERE),
+    ((FP8, FP8, 128), (12, 32, 8, 24, 18, True), ELSEWHERE, solo_form(114)),
     # ... but not long streams that the wide kernel can serve
     ((FP8, FP8, 128), (10, 40, 8, 2600, 16, False), solo_form(114), ELSEWHERE),
     ((FP8, FP8, 128), (10, 40, 8, 2601, 16, False), ELSEWHERE, solo_form(114)),
